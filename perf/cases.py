@@ -270,8 +270,8 @@ def _directions(c, seed):
     return (u / u.norm(dim=1, keepdim=True)).to(BF16)
 
 
-POLICY = dict(c=5, t_forgive=100, window=100, k0=1.5, alpha=0.01, grow=1.1, shrink=0.9, n_max=10, min_dist_mult=0.35, eps=1e-4)
-BETA_H, BETA_G, WARM = 0.9, 0.8, 3
+POLICY = dict(c=5, t_forgive=100, k0=1.5, alpha=0.01, grow=1.1, shrink=0.9, n_max=10, min_dist_mult=0.35, eps=1e-4)
+BETA_H, BETA_G, WARM = 0.9, 0.8, 12                         # warm-up: the averages come near enough to stay inside the fences
 
 
 class _DeviceArray:
@@ -319,7 +319,8 @@ def prepare(case, seed):
         s["h"] = [_signals(c, seed, 16 + i)[1] for i in range(c["stages"])]
         s["g"] = [_signals(c, seed, 32 + i, 1e-3)[1] for i in range(c["stages"])]
         s["dirs"] = _directions(c, seed)
-        s["loop"] = sv.Sentinel(s["ver"], c["stages"], c["workers"], c["tokens"], c["d"], ALL_METRICS + ("sw",), s["dirs"], BETA_H, BETA_G, POLICY, POLICY)
+        policy = dict(POLICY, window=6 * c["workers"])          # the last six iterations
+        s["loop"] = sv.Sentinel(s["ver"], c["stages"], c["workers"], c["tokens"], c["d"], ALL_METRICS + ("sw",), s["dirs"], BETA_H, BETA_G, policy, policy)
         for _ in range(WARM):
             _iterate(s, True)
         s["ema"] = [_ema(s["loop"], i, k, (c["tokens"], c["d"])) for k in ("h", "g") for i in range(c["stages"])]
