@@ -449,6 +449,19 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
   };
 
   const double Td = T, attn_flop = (d.causal ? 2.0 : 4.0) * B * d.n_heads * (double)S * S * c->hd;
+  // Before a router the sums keep their cut (mfma_settled_runs), as one product where the widths allow it (whole) or as one per
+  // matrix, rotated from bf16 there.
+  const bool routed = c->moe && dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && D % 64 == 0;
+  bool whole = true;
+  auto settle_qkv = [&](GemmArgs& f) {
+    if (!routed || c->Dq % 128 || c->Dkv % 128) return;
+    const int64_t ws = (int64_t)c->split_ws_floats, big = (int64_t)((T + 255) / 256) * (c->Dqkv / 256);
+    const int r = mfma_settled_runs(T, c->Dqkv, D, ws);
+    whole = c->Dq % 256 == 0 && c->Dkv % 256 == 0 && (big >= 192 || r >= 2);
+    f.runs[0] = whole ? r : mfma_settled_runs(T, c->Dq, D, ws);
+    f.runs[1] = f.runs[2] = whole ? r : mfma_settled_runs(T, c->Dkv, D, ws);
+    f.rope_bf16 = !whole;
+  };
   bool fused1 = false;
   if (fuse) {
     GemmArgs f = nt(T, c->Dqkv, D, x, D, wf.wq, qkv, c->Dqkv, d.rope ? EPI_ROPE : EPI_STORE);
@@ -456,7 +469,8 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
     f.rope_cs = c->rope_cs; f.rope_S = S; f.rope_hd = c->hd; f.rope_cols = c->Dq + c->Dkv;
     f.rscale = c->rstd;
     f.split_ws = c->split_ws; f.split_ws_floats = (int64_t)c->split_ws_floats;   // few tokens: runs of k slices per tile
-    if (mfma_gemm_supported(f)) {                      // the one-launch q | k | v product: the large tile (whole, or over runs of k slices)
+    settle_qkv(f);
+    if (whole && mfma_gemm_supported(f)) {             // the one-launch q | k | v product
       sv_status s = row_rstd(x);
       if (s != SV_OK) return s;
       SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dqkv * D, st, mfma_gemm(f, st));
@@ -470,6 +484,7 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
     f.nbcol = 3; f.Bcol[0] = w.wq; f.Bcol[1] = w.wk; f.Bcol[2] = w.wv; f.ncol[0] = c->Dq; f.ncol[1] = c->Dkv; f.ncol[2] = c->Dkv;
     f.rope_cs = c->rope_cs; f.rope_S = S; f.rope_hd = c->hd; f.rope_cols = c->Dq + c->Dkv;
     f.split_ws = c->split_ws; f.split_ws_floats = (int64_t)c->split_ws_floats;
+    settle_qkv(f);
     if (dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && mfma_gemm_supported(f)) {
       SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dqkv * D, st, mfma_gemm(f, st));
     } else {
@@ -492,6 +507,7 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
   {
     GemmArgs g = nt(T, D, c->Dq, o, c->Dq, w.wo, x1, D, EPI_RESID);
     g.R = x; g.ldr = D;
+    if (routed && D % 128 == 0 && c->Dq % 64 == 0) g.runs[0] = mfma_settled_runs(T, D, c->Dq, (int64_t)c->split_ws_floats);
     if (fused2) leave_rowsq(g); else c->rowsq_of = nullptr;
     SV_OP(c, SV_OP_GEMM_O, 2.0 * Td * D * c->Dq, st, gemm(c, g, st));
   }
@@ -1106,7 +1122,7 @@ sv_status sv_gemm_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, i
   GemmArgs g; memset(&g, 0, sizeof(g));
   g.M = M; g.N = N; g.nseg = 1; g.seg[0] = GemmSeg{A, lda, B, ldb, K};
   g.b_is_kn = b_is_kn ? 1 : 0; g.epi = EPI_STORE; g.C = Cout; g.ldc = ldc;
-  if (!mfma_gemm_supported(g) || ((tile == 1 || tile == 3) && N % 256) || (tile == 4 && b_is_kn)) return SV_EUNSUPPORTED;
+  if (N % 128 || !mfma_gemm_supported(g) || ((tile == 1 || tile == 3) && N % 256) || (tile == 4 && b_is_kn)) return SV_EUNSUPPORTED;
   return mfma_gemm(g, (hipStream_t)stream, tile) == hipSuccess ? SV_OK : SV_EHIP;
 }
 

@@ -165,6 +165,10 @@ struct GemmArgs {
   int nbcol; const void* Bcol[3]; int ncol[3];
   // EPI_ROPE: (cos, sin) table [rope_S][rope_hd / 2][2] of floats
   const float* rope_cs; int rope_S, rope_hd, rope_cols;
+  // optional: how the sum over k is cut, for products a router's decision hangs on (0 = as is cheapest).  runs[j] >= 1: the
+  // columns of Bcol[j] (of the whole product without a column map: j = 0) are the fp32 sum, in order, of that many contiguous
+  // runs of k slices, whatever tile makes them; rope_bf16: the rotation takes the product rounded to bf16
+  int runs[3]; int rope_bf16;
   // optional grouped form (mixture of experts): rows [256 i, 256 i + 256) of the product use the weight matrices of
   // group tile_group[i], found group_stride elements apart behind every seg[].B and B2; with m_dev the row count is
   // read from device memory (*m_dev <= M, a multiple of 256) and M only bounds the launch
@@ -238,7 +242,8 @@ hipError_t launch_moe_combine_bwd(const void* dy, const void* yp, const void* dx
 // gemm_mfma.hip: bf16 only; returns hipErrorInvalidValue if the shape is outside its limits
 bool mfma_gemm_supported(const GemmArgs& a);
 bool mfma_gemm_emits_rowsq(const GemmArgs& a);          // would mfma_gemm(a, st) fill a.rowsq?
-hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile = 0);   // tile: 0 auto, 1 = 256x256, 2 = 128x128
+int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats);   // the GemmArgs::runs of an [N,K] product before a router
+hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile = 0);   // tile: 0 auto, 1 = 256x256, 2 = 128x128, 3 = 256x128, 4 = 64x128
 
 // attn_mfma.hip: bf16, head_dim 64 | 128.  scale_hd (0 = hd): the head dimension the softmax scale 1/sqrt(.) is taken from,
 // for inputs whose heads were zero-padded from scale_hd to hd columns

@@ -5,13 +5,15 @@
 // op(B) = B^T with B stored [N,K] (forward: activations times [out,in] weights) or B stored
 // [K,N] (backward: gradients times the same [out,in] weights, contraction over "out").
 //
-// Kernel shape: a BM x BN output tile per workgroup, K walked in slices of 64.  Both operand
+// Three kernels.  [N,K] operands take the persistent 256x256 direct-to-LDS kernel or, where its tiles would not fill the
+// chip or the columns are no multiple of 256, the direct-to-LDS kernel on smaller tiles, whole or over runs of k slices
+// (plan_gemm prices them).  [K,N] operands go through registers, transposed on the way (8x8 blocks, v_perm).
+//
+// Common shape: a BM x BN output tile per workgroup, K walked in slices of 64.  Both operand
 // slices are staged in LDS as rows of 64 bf16 (128 bytes) whose eight 16-byte chunks are
 // XOR-swizzled by the row index, so that the 16-byte fragment reads of v_mfma_f32_32x32x16_bf16
 // (a lane reads 8 consecutive k of one row) and the 16-byte staging writes are bank-conflict
-// free.  LDS is double buffered: the global loads of slice k+1 are in flight while slice k is
-// multiplied.  A [K,N] operand is transposed in registers (8x8 blocks, v_perm) on its way into
-// LDS, so both layouts feed the same multiply loop.
+// free.
 //
 // The weight tile takes the MFMA "A" slot and the activation tile the "B" slot: each lane then
 // owns one token row and groups of 4 consecutive output features, which makes every epilogue
@@ -36,7 +38,7 @@ __device__ __forceinline__ int lds_off(int row, int chunk) { return row * 128 + 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool KN, bool DUAL>
+template <int BM, int BN, int WAVES_M, int WAVES_N>
 struct Cfg {
   static constexpr int NT = 64 * WAVES_M * WAVES_N;
   static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
@@ -45,9 +47,7 @@ struct Cfg {
   static constexpr int WCH = BN * 8 / NT;      // weight tile
   static constexpr int STAGE = (BM + BN) * 128;
   static constexpr int LDS = 2 * STAGE;
-  static constexpr int NOUT = DUAL ? BN / 2 : BN;   // output columns per tile
-  static_assert(!DUAL || !KN, "the dual product is forward only");
-  static_assert(!KN || WCH % 8 == 0, "a [K,N] operand is staged in whole 8x8 blocks per thread");
+  static_assert(WCH % 8 == 0, "a [K,N] operand is staged in whole 8x8 blocks per thread");
 };
 
 // x of the lane N places further on in its row of 16 lanes (cyclic)
@@ -117,6 +117,10 @@ __device__ __forceinline__ float epilogue_math4(const GemmArgs& a, bool roped, c
     case EPI_ROPE: {
       if (roped) {
         const f32x4 cs = in.cs;
+        if (a.rope_bf16) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = (float)(bf16)v[i];
+        }
         o[0] = v[0] * cs[0] - v[1] * cs[1];
         o[1] = v[0] * cs[1] + v[1] * cs[0];
         o[2] = v[2] * cs[2] - v[3] * cs[3];
@@ -156,15 +160,12 @@ template <int EPI> constexpr int kEpiAhead = EPI == EPI_ROPE ? 2 : EPI == EPI_SW
 // does this kind of epilogue take GemmArgs::rscale?
 template <int EPI> constexpr bool kEpiScaled = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_ROPE;
 
-// The accumulators of one 32-row block of a wave tile: NIO feature blocks of 32 (the second half of the
-// accumulator blocks is the `up` product of a dual launch).  Per feature block: its four loads first,
-// then compute and store.
-template <int EPI, int NIO, int NI, int MI>
+// The accumulators of one 32-row block of a wave tile.  Per feature block: its four loads first, then compute and store.
+template <int EPI, int NI, int MI>
 __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, int M, const f32x16 (&acc)[NI][MI], int mi, int m, int nbase) {
   if (m >= M) return;
-  const float rs = kEpiScaled<EPI> && a.rscale ? a.rscale[m] : 1.0f;
 #pragma unroll
-  for (int ni = 0; ni < NIO; ++ni) {
+  for (int ni = 0; ni < NI; ++ni) {
     EpiIn in[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) epilogue_load4<EPI>(a, m, nbase + ni * 32 + q * 8, in[q]);
@@ -172,27 +173,19 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, int M, const f3
     for (int q = 0; q < 4; ++q) {
       float v[4], u[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = acc[ni][mi][q * 4 + i];
-        u[i] = (EPI == EPI_SWIGLU) ? acc[ni + (NIO < NI ? NIO : 0)][mi][q * 4 + i] : 0.0f;
-      }
-      epilogue_apply4<EPI>(a, m, nbase + ni * 32 + q * 8, v, u, in[q], rs);
+      for (int i = 0; i < 4; ++i) { v[i] = acc[ni][mi][q * 4 + i]; u[i] = 0.0f; }
+      epilogue_apply4<EPI>(a, m, nbase + ni * 32 + q * 8, v, u, in[q]);
     }
   }
 }
 
-// SPLIT: blockIdx.y takes one of gridDim.y contiguous runs of k slices and leaves its fp32 partial product in
-// a.split_ws[blockIdx.y][M][N]; splitk_reduce_kernel adds the runs in a fixed order and applies the epilogue.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool KN, int EPI, bool SPLIT = false>
+// B stored [K,N]: both operands staged through registers, the weights transposed on the way.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmArgs a, int tiles_m, int tiles_n) {
-  constexpr bool DUAL = EPI == EPI_SWIGLU;
-  static_assert(!SPLIT || (!DUAL && !KN && BM * BN <= 128 * 128), "split-k serves the small [N,K] tiles");
-  using C = Cfg<BM, BN, WAVES_M, WAVES_N, KN, DUAL>;
+  using C = Cfg<BM, BN, WAVES_M, WAVES_N>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  // grouped form: the row count lives in device memory and the launch covers its bound
-  const int M = a.m_dev ? *a.m_dev : a.M;
-  if (a.m_dev) tiles_m = (M + BM - 1) / BM;
+  const int M = a.M;
   // ---- tile assignment (XCD-contiguous, grouped raster)
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = (nblk + 7) >> 3;
@@ -203,8 +196,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
   const int gsz = min(tiles_m - first_m, kGroupM);
   const int tile_m = first_m + (pid % in_group) % gsz;
   const int tile_n = (pid % in_group) / gsz;
-  const int m0 = tile_m * BM, n0 = tile_n * C::NOUT;
-  const int64_t goff = a.tile_group ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;   // this row block's weight matrices
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WAVES_M, wn = wave / WAVES_M;
@@ -227,20 +219,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
       const int m = min(m0 + r, M - 1);
       xreg[i] = *reinterpret_cast<const bf16x8*>(A + (int64_t)m * lda + kin + c * 8);
     }
-    if (!KN) {
-#pragma unroll
-      for (int i = 0; i < C::WCH; ++i) {
-        const int e = tid + i * C::NT, r = e >> 3, c = e & 7;
-        const bf16* B;
-        int n;
-        if (DUAL && r >= BN / 2) { B = (const bf16*)a.B2 + goff; n = n0 + r - BN / 2; }
-        else { B = (const bf16*)a.seg[seg].B + goff; n = n0 + r; }
-        const int64_t ld = (DUAL && r >= BN / 2) ? a.ldb2 : ldb;
-        wreg[i] = *reinterpret_cast<const bf16x8*>(B + (int64_t)n * ld + kin + c * 8);
-      }
-    } else {
+    {
       // thread owns 8x8 blocks: 8 consecutive k rows x 8 consecutive n columns
-      const bf16* B = (const bf16*)a.seg[seg].B + goff;
+      const bf16* B = (const bf16*)a.seg[seg].B;
 #pragma unroll
       for (int b = 0; b < C::WCH / 8; ++b) {
         const int blk = tid + b * C::NT, ng = blk % (BN / 8), kg = blk / (BN / 8);
@@ -267,13 +248,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
       const int e = tid + i * C::NT, r = e >> 3, c = e & 7;
       *reinterpret_cast<bf16x8*>(xs + lds_off(r, c)) = xreg[i];
     }
-    if (!KN) {
-#pragma unroll
-      for (int i = 0; i < C::WCH; ++i) {
-        const int e = tid + i * C::NT, r = e >> 3, c = e & 7;
-        *reinterpret_cast<bf16x8*>(ws + lds_off(r, c)) = wreg[i];
-      }
-    } else {
+    {
 #pragma unroll
       for (int b = 0; b < C::WCH / 8; ++b) {
         const int blk = tid + b * C::NT, ng = blk % (BN / 8), kg = blk / (BN / 8);
@@ -297,13 +272,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
 
   int nslices = 0;
   for (int s = 0; s < a.nseg; ++s) nslices += a.seg[s].K / BK;
-  if (SPLIT) {                                       // this workgroup's run of slices; the loads start at its first
-    const int first = (int)((int64_t)nslices * blockIdx.y / gridDim.y);
-    nslices = (int)((int64_t)nslices * (blockIdx.y + 1) / gridDim.y) - first;
-    int skip = first;
-    while (skip >= a.seg[seg].K / BK) { skip -= a.seg[seg].K / BK; ++seg; }
-    kin = skip * BK;
-  }
 
   f32x16 acc[C::NI][C::MI];
 #pragma unroll
@@ -317,10 +285,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
   const int l31 = lane & 31, lhi = lane >> 5;
   int wrow[C::NI];
 #pragma unroll
-  for (int ni = 0; ni < C::NI; ++ni) {
-    if (DUAL) wrow[ni] = (ni < C::NI / 2 ? wn * (C::WTN / 2) + ni * 32 : BN / 2 + wn * (C::WTN / 2) + (ni - C::NI / 2) * 32) + l31;
-    else wrow[ni] = wn * C::WTN + ni * 32 + l31;
-  }
+  for (int ni = 0; ni < C::NI; ++ni) wrow[ni] = wn * C::WTN + ni * 32 + l31;
 
   auto multiply = [&](int stage) {
     const char* xs = smem + stage * C::STAGE;
@@ -383,28 +348,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(GemmA
 
   // ---- epilogue: lane owns token row (lane & 31) of each 32-row block and, per register
   // quad q, output features 8q + 4*(lane>>5) .. +3 of each 32-feature block.
-  constexpr int NIO = DUAL ? C::NI / 2 : C::NI;
-  if constexpr (SPLIT) {
-    float* part = a.split_ws + (int64_t)blockIdx.y * M * a.N;
 #pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi) {
-      const int m = m0 + wm * C::WTM + mi * 32 + l31;
-      if (m >= M) continue;
-#pragma unroll
-      for (int ni = 0; ni < C::NI; ++ni)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 v;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = acc[ni][mi][q * 4 + i];
-          *reinterpret_cast<f32x4*>(part + (int64_t)m * a.N + n0 + wn * C::WTN + ni * 32 + q * 8 + lhi * 4) = v;
-        }
-    }
-  } else {
-#pragma unroll
-    for (int mi = 0; mi < C::MI; ++mi)
-      epilogue_rows<EPI, NIO, C::NI, C::MI>(a, M, acc, mi, m0 + wm * C::WTM + mi * 32 + l31, n0 + wn * (DUAL ? C::WTN / 2 : C::WTN) + lhi * 4);
-  }
+  for (int mi = 0; mi < C::MI; ++mi)
+    epilogue_rows<EPI, C::NI, C::MI>(a, M, acc, mi, m0 + wm * C::WTM + mi * 32 + l31, n0 + wn * C::WTN + lhi * 4);
 }
 
 // Sum of the split-k partial products, in the order of the splits, then the epilogue: one thread per 4 consecutive
@@ -452,12 +398,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int nspl
 //
 // NF: the forms that stand at the two ends of an RMSNorm run inside the products (their own instantiations, for the same
 // reason): the kinds that can follow a norm multiply every row by GemmArgs::rscale, EPI_RESID also writes GemmArgs::rowsq.
-// SPLIT: a tile's k slices are dealt to nsplit workgroups in contiguous runs (virtual block = (run, tile), the tiles of one run
-// next to each other so that an XCD's workgroups share operand panels); each leaves its fp32 partial product in
-// a.split_ws[run][M][N] and splitk_reduce_kernel adds the runs in a fixed order and applies the epilogue.
-template <int EPI, bool GROUPED, bool NF = false, bool SPLIT = false>
-__global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tiles_m, int tiles_n, int nsplit) {
-  static_assert(!SPLIT || (EPI == EPI_STORE && !GROUPED && !NF), "a split run stores bare partial products");
+template <int EPI, bool GROUPED, bool NF = false>
+__global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tiles_m, int tiles_n) {
   constexpr bool DUAL = EPI == EPI_SWIGLU;
   constexpr bool RS = NF && kEpiScaled<EPI>, SQ = NF && EPI == EPI_RESID;
   constexpr int BM = 256, BN = 256, STAGE = (BM + BN) * 128, MI = 4, NI = 4;
@@ -470,14 +412,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   // Persistent workgroups: workgroup b works on the virtual block ids b, b + gridDim.x, ...; a virtual id
   // maps to a tile so that ids congruent mod 8 (one XCD) walk a contiguous run of tiles in groups of
   // kGroupM row tiles.  gridDim.x is a multiple of 8, so a workgroup stays on its XCD's run.
-  const int nblk = tiles_m * tiles_n, nvb = SPLIT ? nblk * nsplit : nblk;
-  const int per_xcd = (nvb + 7) >> 3;
-  auto tile_of = [&](int vb, int& m0, int& n0, int& run) -> bool {
+  const int nblk = tiles_m * tiles_n;
+  const int per_xcd = (nblk + 7) >> 3;
+  auto tile_of = [&](int vb, int& m0, int& n0) -> bool {
     if (vb >= per_xcd * 8) return false;
-    int pid = (vb & 7) * per_xcd + (vb >> 3);
-    if (pid >= nvb) return false;
-    run = 0;
-    if (SPLIT) { run = pid / nblk; pid -= run * nblk; }
+    const int pid = (vb & 7) * per_xcd + (vb >> 3);
+    if (pid >= nblk) return false;
     const int in_group = kGroupM * tiles_n;
     const int first_m = (pid / in_group) * kGroupM;
     const int gsz = min(tiles_m - first_m, kGroupM);
@@ -491,21 +431,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 
   // ---- DMA side: one continuous stream of slices across this workgroup's tiles, always one slice
   // ahead of the multiply.  State: virtual block d_vb (tile d_m0, d_n0), segment dseg, offset dk.
-  int d_vb = blockIdx.x, d_m0 = 0, d_n0 = 0, d_run = 0, d_left = 0, dseg = 0, dk = 0, d_K = 0;   // d_K: length of segment dseg, kept in a register
+  int d_vb = blockIdx.x, d_m0 = 0, d_n0 = 0, dseg = 0, dk = 0, d_K = 0;   // d_K: length of segment dseg, kept in a register
                                                                            // (a per-slice kernel-argument load would share
                                                                            // its wait counter with the LDS reads)
-  bool d_valid = tile_of(d_vb, d_m0, d_n0, d_run);
+  bool d_valid = tile_of(d_vb, d_m0, d_n0);
   int nslices = 0;
   for (int s = 0; s < a.nseg; ++s) nslices += a.seg[s].K / BK;
-  // SPLIT: run r of a tile takes the slices [r * nslices / nsplit, (r + 1) * nslices / nsplit) of its segments laid end to end
-  auto start_run = [&]() {                                    // the stream's position at the first slice of run d_run
-    const int ks = d_run * nslices / nsplit;
-    d_left = (d_run + 1) * nslices / nsplit - ks;
-    dseg = 0;
-    int k = ks * BK;
-    while (k >= a.seg[dseg].K) { k -= a.seg[dseg].K; ++dseg; }
-    dk = k;
-  };
   const char *gA, *gB, *gB2;
   __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the stream reads: base = first row, no bound
   unsigned voffA[8], voffB[8];
@@ -544,24 +475,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   };
   auto advance = [&]() {                                      // to the next slice of the stream
     dk += BK;
-    if (SPLIT) {
-      if (--d_left == 0) {                                    // the run is through: on to the next virtual block
-        d_vb += gridDim.x;
-        d_valid = tile_of(d_vb, d_m0, d_n0, d_run);
-        if (d_valid) { start_run(); set_segment(); }
-        else dk -= BK;                                        // a finished stream re-reads its last slice
-        return;
-      }
-      if (dk < d_K) return;
-      dk = 0; ++dseg; set_segment();
-      return;
-    }
     if (dk < d_K) return;
     dk = 0;
     if (dseg + 1 < a.nseg) { ++dseg; set_segment(); return; }
     dseg = 0;
     d_vb += gridDim.x;
-    d_valid = tile_of(d_vb, d_m0, d_n0, d_run);
+    d_valid = tile_of(d_vb, d_m0, d_n0);
     if (d_valid) set_segment();
   };
 
@@ -608,16 +527,14 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 
   if (!d_valid) return;
   bf16x8 xf0[MI], wf0[NI], xf1[MI], wf1[NI];
-  if (SPLIT) start_run();
   set_segment();
 #pragma unroll
   for (int j = 0; j < 16; ++j) dma(0, j);                     // slice 0 of the first tile
   advance();
   int par = 0;                                                // LDS stage of the current tile's slice 0
 
-  int m0, n0, run;
-  for (int vb = blockIdx.x; tile_of(vb, m0, n0, run); vb += gridDim.x) {
-    const int nsl = SPLIT ? (run + 1) * nslices / nsplit - run * nslices / nsplit : nslices;   // slices of this virtual block
+  int m0, n0;
+  for (int vb = blockIdx.x; tile_of(vb, m0, n0); vb += gridDim.x) {
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
@@ -639,10 +556,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     const __amdgpu_buffer_rsrc_t bC = desc(a.C, a.ldc), bC2 = desc(a.C2, a.ldc), bC3 = desc(a.C3, a.ldc);
     const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr), bR2 = desc(a.R2, a.ldr);
     const int vC = ((wm * 128 + er) * a.ldc + ec4 * 4) * 2, vR = ((wm * 128 + er) * a.ldr + ec4 * 4) * 2;
-    // SPLIT: the run's partial product, fp32 [M][N]
-    const __amdgpu_buffer_rsrc_t bW = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.split_ws + ((int64_t)run * M + m0) * a.N + ncol0), (short)0, -1, 0x00020000);
-    const int vW = ((wm * 128 + er) * a.N + ec4 * 4) * 4;
     // offsets of row block rb (rows rb .. rb + 3 of the wave's 128): per lane (vo) and scalar (so).  A ragged tile
     // re-reads its last row for the rows past the end, which takes the row into the lane's part.
     auto place = [&](auto check_tag, int rb, int ld, int vlane, int& vo, int& so) {
@@ -699,7 +612,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       rs_pre0 = a.rscale[min(m0 + wm * 128 + lane, M - 1)];
       rs_pre1 = a.rscale[min(m0 + wm * 128 + 64 + lane, M - 1)];
     }
-    if (nsl == 1) first_inputs();
+    if (nslices == 1) first_inputs();
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       xf0[g] = *reinterpret_cast<const bf16x8*>(smem + par * STAGE + lds_off(xrow[g], lhi));
@@ -709,12 +622,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     step(xf1, wf1, xf0, wf0, true, par, 2, true, par ^ 1, 8);
     if (d_valid) advance();
     step(xf0, wf0, xf1, wf1, true, par, 3, false, 0, 0);
-    for (int kt = 1; kt < nsl; ++kt) {
+    for (int kt = 1; kt < nslices; ++kt) {
       const int st = (par + kt) & 1;
       __builtin_amdgcn_s_waitcnt(0);   // my DMAs of slice kt have landed, my fragment reads of slice kt-1 are done
       __syncthreads();                 // ... and so have everybody's: stage st is complete, stage st^1 is free
       SV_SB;
-      if (kt == nsl - 1) first_inputs();     // their round trip hides behind the last slice's products
+      if (kt == nslices - 1) first_inputs();     // their round trip hides behind the last slice's products
       SV_SB;
       step(xf1, wf1, xf0, wf0, true, st, 0, true, st ^ 1, 0);     // MFMAs of (kt-1, k step 3)
       step(xf0, wf0, xf1, wf1, true, st, 1, true, st ^ 1, 8);
@@ -731,8 +644,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     // stage that was just consumed (16-byte chunks XOR-swizzled by the row: conflict-free both ways)
     // and reads it back so that 16 consecutive lanes cover 128 contiguous bytes of an output row;
     // every global access of the epilogue (result, residual, gate / up) becomes a full-line run.
-    const int sl = (par + nsl - 1) & 1;
-    par = (par + nsl) & 1;
+    const int sl = (par + nslices - 1) & 1;
+    par = (par + nslices) & 1;
     __syncthreads();                                   // everybody is done reading stage sl
     char* patch = smem + sl * STAGE + wave * 16384;
     // per wave, behind the two stages: the row factors of its 128 rows (each lane of the read-back needs those of the
@@ -836,15 +749,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 #pragma unroll
           for (int i = 0; i < 4; ++i) { lo[i] = a_lo[i]; hi[i] = a_hi[i]; }
           const bool ok = !CHECK || wm * 128 + rb + er < M - m0;
-          if constexpr (SPLIT) {                       // the bare accumulators: 16 lanes x 16 bytes = 256 contiguous bytes of a row, twice
-            int vo = vW, so = rb * a.N * 4;
-            if (CHECK) { vo = (min(wm * 128 + rb + er, M - 1 - m0) * a.N + ec4 * 4) * 4; so = 0; }
-            if (ok) {
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a_lo), bW, vo, so, 0);
-              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, a_hi), bW, vo + 256, so, 0);
-            }
-            continue;
-          }
           int vo, so;
           place(check_tag, rb, a.ldc, vC, vo, so);
           auto put_lo = [&](int w, bf16x4 pk) {
@@ -887,6 +791,370 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 #undef SV_SB
 }
 
+// ------------------------------------------------------------------------------------------
+// Direct-to-LDS kernel on smaller tiles: (WM * 32 * MI) x (WN * 32 * NI) outputs per workgroup of WM x WN waves, NST LDS
+// stages of one 64-deep slice each.  It serves what the 256x256 kernel cannot fill the chip with (fewer than about one
+// tile per CU) and widths that are no multiple of 256: any multiple of 8 columns -- weight rows past the end re-read the
+// last group of 8, outputs past the end (rows and columns) are dropped by the bounds check of the buffer stores.
+//
+// What bounds it: LDS.  A 128x128 tile moves 32 KB into LDS (64 B/clk) and 64 KB out of it (about 200 B/clk) per slice
+// of 512 matrix cycles, so a CU is busy with LDS about 1.5 x as long as with MFMAs; the 256x256 tile (0.75 x) stays the
+// better one wherever it fills the chip.  NST: the loads of slice k + NST - 1 are issued when slice k is multiplied.
+// With two workgroups on a CU (2 stages each) they cover each other's wait for memory; where there is at most about one
+// tile per CU, one workgroup runs alone and 4 stages keep three slices in flight instead.
+//
+// The one wait + barrier per slice stands before the last of its four 16-wide k steps, whose fragments are in registers
+// by then: behind it the first fragments of the next slice are asked for, and the step's MFMAs hide their latency.
+template <int WM, int WN, int MI, int NI, int NST, bool DUAL>
+struct MidCfg {
+  static constexpr int NW = WM * WN, NT = 64 * NW, BM = WM * 32 * MI, BN = WN * 32 * NI, NOUT = DUAL ? BN / 2 : BN;
+  static constexpr int STAGE = (BM + BN) * 128, LDS = NST * STAGE;
+  static constexpr int NA = BM / 8 / NW, NB = BN / 8 / NW, ND = NA + NB;      // 1 KB loads per wave and slice
+  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && (!DUAL || NI % 2 == 0), "tile shape");
+  static_assert(NW * 32 * NI * 32 * 4 <= LDS, "the epilogue's patches fit the stages");
+  static_assert(ND * (NST - 2) < 64, "the wait count has 6 bits");
+};
+
+//
+// SPLIT: a tile's k slices are dealt to nsplit workgroups in contiguous runs, each leaves its fp32 partial product in
+// a.split_ws[run][M][N] and splitk_reduce_kernel adds the runs in order.  SUMMED: the same sum of runs (GemmArgs::runs) in one
+// workgroup, the running total beside the accumulators: bit for bit what the partial products and their reduction give.
+template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT, bool SUMMED>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, int tiles_m, int tiles_n, int nsplit) {
+  constexpr bool DUAL = EPI == EPI_SWIGLU;
+  static_assert(!SPLIT || (EPI == EPI_STORE && !GROUPED), "a split run stores bare partial products");
+  static_assert(!SUMMED || (!DUAL && !GROUPED && !SPLIT), "one sum of runs per output");
+  using C = MidCfg<WM, WN, MI, NI, NST, DUAL>;
+  constexpr int BM = C::BM, BN = C::BN, STAGE = C::STAGE, NW = C::NW, NA = C::NA, NB = C::NB;
+  constexpr int kGroup = 1024 / BM;                       // row tiles per raster group: 1024 rows, as on the large tile
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+
+  const int M = GROUPED ? *a.m_dev : a.M;
+  if (GROUPED) tiles_m = (M + BM - 1) / BM;
+  // tile assignment as in the 256x256 kernel: ids congruent mod 8 (one XCD) walk a contiguous run of tiles
+  const int nblk = tiles_m * tiles_n, nvb = SPLIT ? nblk * nsplit : nblk;
+  const int per_xcd = (nvb + 7) >> 3;
+  int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || pid >= nvb) return;
+  int run = 0;
+  if (SPLIT) { run = pid / nblk; pid -= run * nblk; }
+  const int in_group = kGroup * tiles_n;
+  const int first_m = (pid / in_group) * kGroup;
+  const int gsz = min(tiles_m - first_m, kGroup);
+  const int m0 = (first_m + (pid % in_group) % gsz) * BM;
+  const int n0 = ((pid % in_group) / gsz) * C::NOUT;
+
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lhi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % WM, wn = wave / WM;
+
+  // ---- the stream of slices: segment dseg, offset dk
+  int dseg = 0, dk = 0, d_K = 0, left;
+  int nsl = 0;
+  for (int s = 0; s < a.nseg; ++s) nsl += a.seg[s].K / BK;
+  left = nsl;
+  if (SPLIT) {                                            // run r takes the slices [r * nsl / nsplit, (r + 1) * nsl / nsplit)
+    const int ks = (int)((int64_t)run * nsl / nsplit);
+    nsl = (int)((int64_t)(run + 1) * nsl / nsplit) - ks;
+    left = nsl;
+    int k = ks * BK;
+    while (k >= a.seg[dseg].K) { k -= a.seg[dseg].K; ++dseg; }
+    dk = k;
+  }
+  const bf16* pA;
+  const bf16* pB[NB];                                     // first row of the panel; of each group of 8 weight rows
+  unsigned voffA[NA], voffB[NB];
+  auto set_segment = [&]() {
+    const GemmSeg& sg = a.seg[dseg];
+    d_K = sg.K;
+    pA = (const bf16*)sg.A + (int64_t)m0 * sg.lda;
+    const int64_t goff = GROUPED ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int r = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ swz(r);
+      voffA[i] = (unsigned)((int64_t)min(r, M - 1 - m0) * sg.lda + c * 8) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int g = (wave + NW * i) * 8, r = g + (lane >> 3), c = (lane & 7) ^ swz(r);
+      const bf16* B = (const bf16*)sg.B + goff;
+      int64_t ldb = sg.ldb;
+      int row;                                            // the group's first weight row
+      if (DUAL) {
+        const bool up = g >= BN / 2;
+        if (up) { B = (const bf16*)a.B2 + goff; ldb = a.ldb2; }
+        row = min(n0 + (up ? g - BN / 2 : g), a.N - 8);
+      } else {
+        row = min(n0 + g, a.N - 8);
+        if ((EPI == EPI_STORE || EPI == EPI_ROPE) && a.nbcol > 0) {
+          const int o1 = a.ncol[0], o2 = o1 + a.ncol[1];
+          if (a.nbcol > 2 && row >= o2) { B = (const bf16*)a.Bcol[2]; row -= o2; }
+          else if (a.nbcol > 1 && row >= o1) { B = (const bf16*)a.Bcol[1]; row -= o1; }
+          else B = (const bf16*)a.Bcol[0];
+        }
+      }
+      pB[i] = B + (int64_t)row * ldb;
+      voffB[i] = (unsigned)((int64_t)(lane >> 3) * ldb + c * 8) * 2u;
+    }
+  };
+  auto dma = [&](int stage, int j) {                      // j: the wave's NA activation groups, then its NB weight groups
+    const int i = j < NA ? j : j - NA;
+    char* dst = smem + stage * STAGE + (j < NA ? 0 : BM * 128) + (wave + NW * i) * 1024;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(j < NA ? pA : pB[j < NA ? 0 : i]), (short)0, -1, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16,
+                                             (int)(j < NA ? voffA[j < NA ? i : 0] : voffB[j < NA ? 0 : i]), dk * 2, 0, 0);
+  };
+  auto advance = [&]() {                                  // to the next slice; past the last one the stream re-reads it
+    if (--left <= 0) return;
+    dk += BK;
+    if (dk < d_K) return;
+    dk = 0; ++dseg; set_segment();
+  };
+
+  // ---- the epilogue's places.  Each wave turns its accumulators over 32 rows at a time through an LDS patch of its own and
+  // reads them back so that LPR consecutive lanes hold one row's outputs (4 per lane), RPI rows per instruction.
+  constexpr bool kHasInputs = EPI == EPI_RESID || EPI == EPI_SWIGLU_BWD || EPI == EPI_GELU_BWD || EPI == EPI_ROPE;
+  constexpr int LPR = DUAL ? NI * 4 : NI * 8, RPI = 64 / LPR, TR = 32 / RPI;
+  const int er = lane / LPR, ec = lane % LPR;
+  const int mw = wm * 32 * MI, n = n0 + wn * (DUAL ? NI * 16 : NI * 32) + ec * 4;    // the lane's first row (+ er) and columns n .. n + 3
+  const int rows = min(M - m0, BM);
+  // rows past M lie past the descriptor's end, columns past N are sent there
+  auto desc = [&](const void* base, int64_t ld, int es) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (int64_t)m0 * ld * es), (short)0, (int)(rows * ld * es), 0x00020000);
+  };
+  const unsigned vcol = n < a.N ? (unsigned)n : SPLIT ? 0x20000000u : 0x40000000u;     // byte offset 2^31: past every descriptor's end
+  const bool rscaled = kEpiScaled<EPI> && !GROUPED && !SPLIT && a.rscale;
+  EpiIn in[2][TR];
+  float rs[2][TR];
+  int rope_p0 = 0, rope_i0 = 0;
+  if (EPI == EPI_ROPE) { rope_p0 = (m0 + mw) % a.rope_S; rope_i0 = (n % a.rope_hd) >> 1; }
+  auto load_inputs = [&](int mi, EpiIn (&e)[TR], float (&f)[TR]) {
+    if (kHasInputs) {
+      const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr, 2), bR2 = desc(a.R2, a.ldr, 2);
+#pragma unroll
+      for (int t = 0; t < TR; ++t) {
+        const int r = mw + mi * 32 + t * RPI + er;
+        if (EPI == EPI_ROPE) {
+          int p = rope_p0 + mi * 32 + t * RPI + er;
+          if (a.rope_S >= BM) p -= p >= a.rope_S ? a.rope_S : 0; else p %= a.rope_S;
+          e[t].cs = *reinterpret_cast<const f32x4*>(a.rope_cs + ((int64_t)p * (a.rope_hd >> 1) + rope_i0) * 2);
+        } else {
+          const unsigned vo = ((unsigned)(r * (int)a.ldr) + vcol) * 2u;
+          e[t].r = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(bR, (int)vo, 0, 0));
+          if (EPI == EPI_SWIGLU_BWD) e[t].r2 = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(bR2, (int)vo, 0, 0));
+        }
+      }
+    }
+    if (kEpiScaled<EPI>) {
+#pragma unroll
+      for (int t = 0; t < TR; ++t) f[t] = 1.0f;
+      if (rscaled) {
+#pragma unroll
+        for (int t = 0; t < TR; ++t) f[t] = a.rscale[min(m0 + mw + mi * 32 + t * RPI + er, M - 1)];
+      }
+    }
+  };
+
+  f32x16 acc[NI][MI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < MI; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  // ---- fragment addresses: row 32 b + (lane & 31) of a tile, chunk 2 kk + lhi.  The swizzle sees a 32-row block only by
+  // its parity, which turns chunk 2 kk into 2 (kk ^ 2): one base per k step and operand, block offsets are immediates.
+  const int bx = wm * MI, bw = wn * (DUAL ? NI / 2 : NI);
+  unsigned offX[4], offW[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    offX[kk] = (unsigned)(bx * 4096 + lds_off(l31, (kk * 2 + lhi) ^ ((bx & 1) << 2)));
+    offW[kk] = (unsigned)(BM * 128 + bw * 4096 + lds_off(l31, (kk * 2 + lhi) ^ ((bw & 1) << 2)));
+  }
+  constexpr int kUp = DUAL ? BN / 64 - NI / 2 : 0;         // from the block after the last gate block to the first up block
+  auto read = [&](const char* base, int kk, bf16x8 (&x)[MI], bf16x8 (&w)[NI]) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+      const int b = DUAL && ni >= NI / 2 ? ni + kUp : ni;
+      w[ni] = *reinterpret_cast<const bf16x8*>(base + offW[kk ^ ((b & 1) << 1)] + b * 4096);
+    }
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) x[mi] = *reinterpret_cast<const bf16x8*>(base + offX[kk ^ ((mi & 1) << 1)] + mi * 4096);
+  };
+#define SV_SB __builtin_amdgcn_sched_barrier(0)
+  constexpr int kLgkm0 = 0xc07f;                           // lgkmcnt(0), nothing else
+  constexpr int kLandedCnt = C::ND * (NST - 2);            // loads that may still be in flight when the next slice has landed
+  constexpr int kLanded = 0x0070 | (kLandedCnt & 15) | ((kLandedCnt >> 4) << 14);      // vmcnt(kLandedCnt) lgkmcnt(0)
+  // this wave's wait, then the workgroup's barrier
+#define SV_MEET(imm) do { SV_SB; __builtin_amdgcn_s_waitcnt(imm); asm volatile("s_barrier" ::: "memory"); SV_SB; } while (0)
+  auto mul = [&](bf16x8 (&x)[MI], bf16x8 (&w)[NI]) {
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ni], x[mi], acc[ni][mi], 0, 0, 0);
+  };
+
+  if (!SPLIT) load_inputs(0, in[0], rs[0]);                // older than every slice: in order, so landed when the first has
+  SV_SB;
+  set_segment();
+#pragma unroll
+  for (int s = 0; s + 1 < NST; ++s) {
+#pragma unroll
+    for (int j = 0; j < C::ND; ++j) dma(s, j);
+    advance();
+  }
+  bf16x8 x0[MI], w0[NI], x1[MI], w1[NI];
+  f32x16 tot[SUMMED ? NI : 1][SUMMED ? MI : 1];
+  int run_end = nsl, runs = 1, run_i = 0;                  // SUMMED: the run being summed ends before slice run_end
+  if (SUMMED) {
+    int j = 0, c = n0;
+    while (j + 1 < a.nbcol && c >= a.ncol[j]) { c -= a.ncol[j]; ++j; }
+    runs = a.runs[j];
+    run_end = nsl / runs;
+  }
+  SV_MEET(kLanded);
+  read(smem, 0, x0, w0);
+  int st = 0;
+  for (int kt = 0; kt < nsl; ++kt) {
+    const char* base = smem + st * STAGE;
+    const int fill = st == 0 ? NST - 1 : st - 1;           // the stage slice kt - 1 has left
+    st = st + 1 == NST ? 0 : st + 1;
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    SV_SB;
+    read(base, 1, x1, w1);
+    SV_SB;
+#pragma unroll
+    for (int j = 0; j < C::ND; ++j) {                      // the next loads, one behind each MFMA
+      if (j < MI * NI) acc[j / MI][j % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[j / MI], x0[j % MI], acc[j / MI][j % MI], 0, 0, 0);
+      SV_SB;
+      dma(fill, j);
+      SV_SB;
+      if (j + 1 == MI * NI) {
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        SV_SB;
+        read(base, 2, x0, w0);
+        SV_SB;
+      }
+      if (j >= MI * NI && j < 2 * MI * NI) {
+        const int i = j - MI * NI;
+        acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[i / MI], x1[i % MI], acc[i / MI][i % MI], 0, 0, 0);
+        SV_SB;
+      }
+    }
+#pragma unroll
+    for (int i = C::ND; i < MI * NI; ++i) acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[i / MI], x0[i % MI], acc[i / MI][i % MI], 0, 0, 0);
+    if (C::ND < MI * NI) {
+      __builtin_amdgcn_s_waitcnt(kLgkm0);
+      SV_SB;
+      read(base, 2, x0, w0);
+      SV_SB;
+    }
+#pragma unroll
+    for (int i = C::ND > MI * NI ? C::ND - MI * NI : 0; i < MI * NI; ++i)
+      acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[i / MI], x1[i % MI], acc[i / MI][i % MI], 0, 0, 0);
+    advance();
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    SV_SB;
+    read(base, 3, x1, w1);
+    SV_SB;
+    mul(x0, w0);
+    SV_SB;
+    SV_MEET(kLanded);                                         // everybody's loads of slice kt + 1 have landed, their reads of slice kt are done
+    read(smem + st * STAGE, 0, x0, w0);                    // past the last slice: a stage nobody needs
+    SV_SB;
+    mul(x1, w1);
+    SV_SB;
+    if constexpr (SUMMED) {
+      if (kt + 1 == run_end) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+          for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              tot[ni][mi][r] = run_i == 0 ? acc[ni][mi][r] : tot[ni][mi][r] + acc[ni][mi][r];
+              acc[ni][mi][r] = 0.0f;
+            }
+        ++run_i;
+        run_end = (int)((int64_t)(run_i + 1) * nsl / runs);
+      }
+    }
+  }
+  SV_MEET(0);                                                 // the re-read slices too: the stages become the patches
+
+  // ---- epilogue
+  char* patch = smem + wave * (32 * NI * 128);
+  const __amdgpu_buffer_rsrc_t bC = SPLIT ? desc(a.split_ws + (int64_t)run * M * a.N, a.N, 4) : desc(a.C, a.ldc, 2);
+  const __amdgpu_buffer_rsrc_t bC2 = desc(a.C2, a.ldc, 2), bC3 = desc(a.C3, a.ldc, 2);
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    constexpr int kMask = NI * 8 - 1;
+    if (!SPLIT && mi + 1 < MI) load_inputs(mi + 1, in[(mi + 1) & 1], rs[(mi + 1) & 1]);
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = SUMMED ? tot[SUMMED ? ni : 0][SUMMED ? mi : 0][q * 4 + i] : acc[ni][mi][q * 4 + i];
+        *reinterpret_cast<f32x4*>(patch + l31 * (NI * 128) + (((ni * 8 + q * 2 + lhi) ^ (l31 & kMask)) << 4)) = v;
+      }
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    __builtin_amdgcn_wave_barrier();
+    f32x4 va[TR], vu[TR];
+#pragma unroll
+    for (int t = 0; t < TR; ++t) {
+      const int row = t * RPI + er;
+      va[t] = *reinterpret_cast<const f32x4*>(patch + row * (NI * 128) + ((ec ^ (row & kMask)) << 4));
+      if (DUAL) vu[t] = *reinterpret_cast<const f32x4*>(patch + row * (NI * 128) + (((ec + NI * 4) ^ (row & kMask)) << 4));
+    }
+#pragma unroll
+    for (int t = 0; t < TR; ++t) {
+      const int r = mw + mi * 32 + t * RPI + er;
+      if (SPLIT) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, va[t]), bC, (int)(((unsigned)(r * a.N) + vcol) * 4u), 0, 0);
+        continue;
+      }
+      float v[4], u[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { v[i] = va[t][i]; u[i] = DUAL ? vu[t][i] : 0.0f; }
+      const unsigned vo = ((unsigned)(r * (int)a.ldc) + vcol) * 2u;
+      epilogue_math4<EPI>(a, EPI == EPI_ROPE && n < a.rope_cols, v, u, in[mi & 1][t], kEpiScaled<EPI> ? rs[mi & 1][t] : 1.0f, [&](int w, bf16x4 p) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, p), w == 0 ? bC : w == 1 ? bC2 : bC3, (int)vo, 0, 0);
+      });
+    }
+    __builtin_amdgcn_wave_barrier();                       // the reads of this block are issued before the next block's writes
+  }
+#undef SV_MEET
+#undef SV_SB
+}
+
+// compute units of the current device: the persistent kernel's grid and the tile rule count with it
+int cu_count() {
+  static const int n = [] {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8) return 256;
+    return v;
+  }();
+  return n;
+}
+
+template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false>
+hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st) {
+  using C = MidCfg<WM, WN, MI, NI, NST, EPI == EPI_SWIGLU>;
+  auto kern = gemm_mid_kernel<WM, WN, MI, NI, NST, EPI, GROUPED, SPLIT, SUMMED>;
+  static bool configured = false;   // per process; the attribute is per function
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  const int tiles_m = (a.M + C::BM - 1) / C::BM, tiles_n = (a.N + C::NOUT - 1) / C::NOUT;
+  const int64_t per_xcd = ((int64_t)tiles_m * tiles_n * nsplit + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(C::NT), C::LDS, st, a, tiles_m, tiles_n, nsplit);
+  return hipGetLastError();
+}
+
 template <int EPI, bool GROUPED, bool NF = false>
 hipError_t launch_dma(const GemmArgs& a, hipStream_t st) {
   auto kern = gemm_mfma_dma_kernel<EPI, GROUPED, NF>;
@@ -899,120 +1167,159 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t st) {
   }
   const int tiles_m = (a.M + 255) / 256, tiles_n = a.N / (EPI == EPI_SWIGLU ? 128 : 256);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  static int n_cu = 0;                                   // one persistent workgroup per CU (128 KB of LDS each)
-  if (n_cu == 0) {
-    int dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return hipErrorUnknown;
-    n_cu = (prop.multiProcessorCount / 8) * 8;
-    if (n_cu < 8) n_cu = 8;
-  }
+  const int n_cu = std::max(8, cu_count() / 8 * 8);       // one persistent workgroup per CU (128 KB of LDS each)
   const int grid = per_xcd * 8 < n_cu ? per_xcd * 8 : n_cu;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a, tiles_m, tiles_n, 1);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
-// the 256 x 256 kernel over nsplit runs of k slices per tile, then the reduction with the epilogue
-template <int EPI>
-hipError_t launch_dma_split(const GemmArgs& a, int nsplit, hipStream_t st) {
-  auto kern = gemm_mfma_dma_kernel<EPI_STORE, false, false, true>;
-  constexpr int lds = 2 * 512 * 128 + 4 * 1024;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
-  const int tiles_m = (a.M + 255) / 256, tiles_n = a.N / 256;
-  const int per_xcd = (tiles_m * tiles_n * nsplit + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256), lds, st, a, tiles_m, tiles_n, nsplit);   // at most one workgroup per CU
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t threads = (int64_t)a.M * (a.N / 4);
-  hipLaunchKernelGGL(splitk_reduce_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, nsplit);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool KN, int EPI>
-hipError_t launch_cfg(const GemmArgs& a, hipStream_t st) {
-  using C = Cfg<BM, BN, WAVES_M, WAVES_N, KN, EPI == EPI_SWIGLU>;
-  auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, KN, EPI>;
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
+hipError_t launch_kn(const GemmArgs& a, hipStream_t st) {
+  using C = Cfg<BM, BN, WAVES_M, WAVES_N>;
+  auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, EPI>;
   static bool configured = false;   // per process; the attribute is per function
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / C::NOUT;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN;
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(C::NT), C::LDS, st, a, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
-// 128 x 64 tiles, nsplit runs of k slices each, then the reduction with the epilogue
-template <int EPI>
-hipError_t launch_split(const GemmArgs& a, int nsplit, hipStream_t st) {
-  using C = Cfg<128, 64, 2, 2, false, false>;
-  auto kern = gemm_mfma_kernel<128, 64, 2, 2, false, EPI_STORE, true>;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-    if (e != hipSuccess) return e;
-    configured = true;
+inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// ---- which kernel and tile serves a product.  Every choice is priced as rounds of workgroups over the CUs times (a fixed part
+// + slices x time per slice), plus for runs of k slices the reduction launch and the traffic of the partial products; the
+// cheapest is taken.  The figures are microseconds fitted to a sweep over 64 .. 8192 rows, 320 .. 14336 columns and K =
+// 512 .. 14336 with every tile forced (within 15 % of the measured times there).  Where the lines come out, with both
+// sides as measured on that sweep: 4096 x 1024, K = 1024 (256 tiles of 128 x 128) 13.4 us against 19 on 256 x 128 and 33 on
+// 256 x 256 over runs; 8192 x 1024, K = 8192 (256 tiles of 256 x 128) 113 us against 121 and 124; 8192 x 2048, K = 2048
+// (256 tiles of 256 x 256) 59 us against 64 on 256 x 128; 512 x 4096, K = 14336 (256 x 128 over 4 runs) 63 us against 85 whole;
+// 1024^3 (256 tiles of 64 x 64) 7.0 us against 8.1 on 64 x 128 and 9.6 on 128 x 128.
+enum TileKind { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTile64, kTileKinds };
+struct TileCost { int bm, bn; double fixed, slice; };
+constexpr TileCost kTileCost[kTileKinds] = {{256, 256, 4.0, 1.55}, {256, 128, 6.5, 0.86}, {128, 128, 5.0, 0.52}, {64, 128, 4.0, 0.36}, {64, 64, 3.5, 0.21}};
+struct Plan { int kind, runs; };
+
+bool panels_fit(const GemmArgs& a) {      // 32-bit byte offsets inside a panel of 256 rows, and inside a tile's outputs
+  for (int s = 0; s < a.nseg; ++s)
+    if (!(256 * a.seg[s].lda * 2 < (int64_t)1 << 32 && 256 * a.seg[s].ldb * 2 < (int64_t)1 << 32)) return false;
+  return !(a.epi == EPI_SWIGLU && 256 * a.ldb2 * 2 >= (int64_t)1 << 32);
+}
+
+bool fits_256(const GemmArgs& a) {        // the persistent 256x256 kernel has whole tiles of columns
+  if (a.N % (a.epi == EPI_SWIGLU ? 128 : 256)) return false;
+  for (int j = 0; j < a.nbcol; ++j)
+    if (a.ncol[j] % 256) return false;
+  return !(a.epi == EPI_SWIGLU && a.ldc % 8);            // its epilogue stores 16 bytes per lane
+}
+
+bool fits_mid(const GemmArgs& a) {        // buffer descriptors over a tile's rows keep below 2^31 bytes
+  return 256 * a.ldc * 2 < (int64_t)1 << 31 && 256 * a.ldr * 2 < (int64_t)1 << 31 && (int64_t)256 * a.N * 4 < (int64_t)1 << 31;
+}
+
+bool summed_runs(const GemmArgs& a) { return a.runs[0] > 1 || a.runs[1] > 1 || a.runs[2] > 1; }
+
+Plan plan_gemm(const GemmArgs& a) {
+  if (summed_runs(a)) return Plan{kTile128, 1};
+  const bool dual = a.epi == EPI_SWIGLU;
+  int slices = 0;
+  for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
+  const double cus = cu_count();
+  Plan best{-1, 1};
+  double best_cost = 0.0;
+  for (int k = 0; k < kTileKinds; ++k) {
+    if (k == kTile256 ? !fits_256(a) : !fits_mid(a)) continue;
+    if (k == kTile64 && dual) continue;                  // a wave of it holds one block of 32 columns: no gate / up pair
+    const TileCost& t = kTileCost[k];
+    const int nout = dual ? t.bn / 2 : t.bn;
+    const int64_t tiles = (int64_t)((a.M + t.bm - 1) / t.bm) * ((a.N + nout - 1) / nout);
+    const bool splits = a.split_ws && !a.runs[0] && k != kTile256 && !dual && !a.tile_group;
+    for (int runs = 1; runs <= (splits ? 8 : 1); ++runs) {
+      if (runs > 1 && (slices < 4 * runs || (int64_t)runs * a.M * a.N > a.split_ws_floats)) break;
+      const double rounds = (double)((tiles * runs + (int64_t)cus - 1) / (int64_t)cus);
+      double cost = rounds * (t.fixed + t.slice * ((slices + runs - 1) / runs));
+      if (k == kTile256) cost += 4.0;
+      if (runs > 1) cost += 4.0 + (4.0 * runs + 4.0) * a.M * (double)a.N / 4.5e6;
+      if (best.kind < 0 || cost < best_cost) { best = Plan{k, runs}; best_cost = cost; }
+    }
   }
-  const int tiles_m = (a.M + 127) / 128, tiles_n = a.N / 64;
-  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8, nsplit), dim3(C::NT), C::LDS, st, a, tiles_m, tiles_n);
-  hipError_t e = hipGetLastError();
+  return best;
+}
+
+template <int EPI, bool GROUPED>
+hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
+  switch (kind) {
+    case kTile256:
+      if constexpr (!GROUPED && EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD)
+        if (a.rscale || a.rowsq) return launch_dma<EPI, false, true>(a, st);   // the ends of a norm that runs inside the products
+      return launch_dma<EPI, GROUPED>(a, st);
+    case kTile256x128: return launch_mid<4, 2, 2, 2, 3, EPI, GROUPED>(a, 1, st);
+    case kTile128: return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED>(a, 1, st);
+    case kTile64x128: return launch_mid<2, 2, 1, 2, 3, EPI, GROUPED>(a, 1, st);
+    default:
+      if constexpr (EPI != EPI_SWIGLU) return launch_mid<2, 2, 1, 1, 8, EPI, GROUPED>(a, 1, st);
+      return hipErrorInvalidValue;
+  }
+}
+
+// runs of k slices into a.split_ws, then the reduction with the epilogue
+template <int EPI>
+hipError_t launch_runs(const GemmArgs& a, const Plan& p, hipStream_t st) {
+  hipError_t e;
+  switch (p.kind) {
+    case kTile256x128: e = launch_mid<4, 2, 2, 2, 3, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile128: e = launch_mid<4, 2, 1, 2, 4, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile64x128: e = launch_mid<2, 2, 1, 2, 3, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile64: e = launch_mid<2, 2, 1, 1, 8, EPI_STORE, false, true>(a, p.runs, st); break;
+    default: return hipErrorInvalidValue;
+  }
   if (e != hipSuccess) return e;
   const int64_t threads = (int64_t)a.M * (a.N / 4);
-  hipLaunchKernelGGL(splitk_reduce_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, nsplit);
+  hipLaunchKernelGGL(splitk_reduce_kernel<EPI>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, p.runs);
   return hipGetLastError();
 }
 
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-// Tile choice: the 256x256 tile has the best LDS-traffic-to-MFMA ratio; fall back to 128x128
-// when the large tile would leave most of the 256 CUs without work.
-bool use_big_tile(const GemmArgs& a) {
-  const int nout = a.epi == EPI_SWIGLU ? 128 : 256;
-  if (a.N % nout) return false;
-  const int64_t tiles = (int64_t)((a.M + 255) / 256) * (a.N / nout);
-  return tiles >= 192;
-}
-
-
-// Few tiles of 256 x 256 (few tokens against a wide projection): how many runs of k slices per tile bring the direct-to-LDS
-// kernel to about one workgroup per CU, or 0 where that form does not apply (no scratch for the partial products, the
-// dual or grouped product, fewer than 4 slices per run).  A 256-CU part is assumed: the rule only shapes the launch.
-int dma_split_runs(const GemmArgs& a) {
-  if (!a.split_ws || a.b_is_kn || a.tile_group || a.epi == EPI_SWIGLU || a.rowsq || a.N % 256) return 0;
-  const int64_t tiles = (int64_t)((a.M + 255) / 256) * (a.N / 256);
-  if (tiles >= 192) return 0;
-  int slices = 0;
-  for (int s = 0; s < a.nseg; ++s) {
-    slices += a.seg[s].K / BK;
-    if (!(256 * a.seg[s].lda * 2 < (int64_t)1 << 32 && 256 * a.seg[s].ldb * 2 < (int64_t)1 << 32)) return 0;
+template <int EPI>
+hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
+  if (summed_runs(a)) {
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE) return launch_mid<4, 2, 1, 2, 4, EPI, false, false, true>(a, 1, st);
+    return hipErrorInvalidValue;
   }
-  int64_t n = std::min<int64_t>(std::min<int64_t>(8, 256 / tiles), slices / 4);
-  n = std::min<int64_t>(n, a.split_ws_floats / ((int64_t)a.M * a.N));
-  return n >= 2 ? (int)n : 0;
+  if constexpr (EPI != EPI_SWIGLU)
+    if (p.runs > 1) return launch_runs<EPI>(a, p, st);
+  return launch_tile<EPI, false>(a, p.kind, st);
 }
 
 }  // namespace
 
-namespace {
-// the 256 x 256 direct-to-LDS kernel serves this product (the DMA offsets are 32-bit byte offsets within a 256-row panel)
-bool takes_dma_kernel(const GemmArgs& a) {
-  if (a.b_is_kn || !use_big_tile(a)) return false;
-  for (int s = 0; s < a.nseg; ++s)
-    if (!(256 * a.seg[s].lda * 2 < (int64_t)1 << 32 && 256 * a.seg[s].ldb * 2 < (int64_t)1 << 32)) return false;
-  return !(a.epi == EPI_SWIGLU && a.ldc % 8);            // its epilogue stores 16 bytes per lane
+// Which expert a token takes is decided by sums that start here, and a near-tie follows their last bits: the products that lead to
+// a router keep their sums cut the way verifiers of this library have cut them (a second verifier, or the same one after an
+// update, then routes every token alike), while tile and launch are free.  The cut: runs that once brought 256x256 tiles to one
+// workgroup per CU, or 128x64 tiles to three.
+int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats) {
+  const int slices = K / BK;
+  const int64_t fit = ws_floats / std::max<int64_t>(1, M * N);
+  if (N % 256 == 0) {
+    const int64_t tiles = ((M + 255) / 256) * (N / 256);
+    if (tiles >= 192) return 1;
+    const int64_t n = std::min<int64_t>(std::min<int64_t>(std::min<int64_t>(8, 256 / tiles), slices / 4), fit);
+    if (n >= 2) return (int)n;
+  }
+  const int64_t rows = (M + 127) / 128;
+  if (N % 128 == 0 && rows * (N / 128) < 160) {
+    const int64_t wgs = rows * (N / 64);
+    const int64_t n = std::min<int64_t>(std::min<int64_t>(std::min<int64_t>(8, slices / 8), (768 + wgs - 1) / wgs), fit);
+    if (n >= 2) return (int)n;
+  }
+  return 1;
 }
-}  // namespace
 
 bool mfma_gemm_emits_rowsq(const GemmArgs& a) {
-  return a.rowsq && a.epi == EPI_RESID && !a.tile_group && mfma_gemm_supported(a) && takes_dma_kernel(a);
+  return a.rowsq && a.epi == EPI_RESID && !a.tile_group && mfma_gemm_supported(a) && plan_gemm(a).kind == kTile256;
 }
 
 bool mfma_gemm_supported(const GemmArgs& a) {
@@ -1022,21 +1329,25 @@ bool mfma_gemm_supported(const GemmArgs& a) {
   const bool dual = a.epi == EPI_SWIGLU;
   if (dual && (a.b_is_kn || a.nseg != 1 || !a.B2 || a.ldb2 % 8 || !aligned16(a.B2))) return false;
   if (a.epi < EPI_STORE || a.epi > EPI_ROPE) return false;
-  if (a.nbcol > 0 || a.epi == EPI_ROPE) {
-    // fused QKV form: served by the 256x256 direct-to-LDS kernel only (whole tiles, or runs of k slices for few tiles)
-    if (a.b_is_kn || a.nseg != 1 || a.nbcol > 3 || a.N % 256 || !(use_big_tile(a) || dma_split_runs(a))) return false;
+  if (a.nbcol > 0 || a.epi == EPI_ROPE) {                // the fused q | k | v form; a group of 8 weight rows belongs to one matrix
+    if (a.b_is_kn || a.nseg != 1 || a.nbcol > 3) return false;
     int tot = 0;
-    for (int j = 0; j < a.nbcol; ++j) { if (a.ncol[j] % 256 || !aligned16(a.Bcol[j])) return false; tot += a.ncol[j]; }
-    if (a.nbcol > 0 && tot != a.N) return false;
+    for (int j = 0; j < a.nbcol; ++j) { if (a.ncol[j] % 8 || !aligned16(a.Bcol[j])) return false; tot += a.ncol[j]; }
+    if (a.nbcol > 0 && (tot != a.N || a.epi == EPI_SWIGLU)) return false;
     if (a.epi == EPI_ROPE && (!a.rope_cs || a.rope_hd % 4 || a.rope_cols % 4 || a.rope_S < 1)) return false;
   }
   if ((a.tile_group != nullptr) != (a.m_dev != nullptr)) return false;      // the grouped form needs both
-  if (a.tile_group && (a.nbcol > 0 || a.group_stride % 8 || a.M % 256)) return false;
+  if (a.tile_group && (a.b_is_kn || a.nbcol > 0 || a.group_stride % 8 || a.M % 256)) return false;
   if (a.tile_group && a.epi != EPI_STORE && a.epi != EPI_SWIGLU && a.epi != EPI_SWIGLU_BWD) return false;
+  if (summed_runs(a)) {                                  // served by the 128x128 tile, whose columns lie in one matrix
+    if (a.b_is_kn || a.tile_group || a.nseg != 1 || a.rowsq || !fits_mid(a) || (a.epi != EPI_STORE && a.epi != EPI_RESID && a.epi != EPI_ROPE)) return false;
+    for (int j = 0; j < std::max(1, a.nbcol); ++j)
+      if (a.runs[j] < 1 || a.runs[j] > a.seg[0].K / BK || (a.nbcol > 0 && a.ncol[j] % 128)) return false;
+  }
   if (a.b_is_kn && (a.epi == EPI_RESID || a.epi == EPI_GELU || a.epi == EPI_SWIGLU)) return false;
   if ((a.epi == EPI_RESID || a.epi == EPI_SWIGLU_BWD || a.epi == EPI_GELU_BWD) && !a.R) return false;
   if (a.epi == EPI_SWIGLU_BWD && (!a.R2 || !a.C2)) return false;
-  if (a.N % (dual ? 64 : 128)) return false;
+  if (a.N < 8 || a.N % (a.b_is_kn ? 128 : 8)) return false;
   if (a.ldc % 4 || !aligned16(a.C)) return false;
   if ((a.C2 && !aligned16(a.C2)) || (a.C3 && !aligned16(a.C3))) return false;
   if ((a.R || a.R2) && (a.ldr % 4 || !aligned16(a.R) || (a.R2 && !aligned16(a.R2)))) return false;
@@ -1044,110 +1355,40 @@ bool mfma_gemm_supported(const GemmArgs& a) {
     const GemmSeg& g = a.seg[s];
     if (g.K < BK || g.K % BK || g.lda % 8 || g.ldb % 8 || !aligned16(g.A) || !aligned16(g.B)) return false;
   }
-  return true;
+  return a.b_is_kn || (panels_fit(a) && (fits_256(a) || fits_mid(a)));
 }
 
 hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile) {
   if (!mfma_gemm_supported(a)) return hipErrorInvalidValue;
   if ((tile == 1 || tile == 3) && a.N % (a.epi == EPI_SWIGLU ? 128 : 256)) return hipErrorInvalidValue;
-  const bool big = tile == 1 || tile == 3 || (tile == 0 && use_big_tile(a));
-  if (!a.b_is_kn && big && tile != 3) {
-    bool fits = true;                                      // as in takes_dma_kernel, for a forced tile too
-    for (int s = 0; s < a.nseg; ++s) fits = fits && 256 * a.seg[s].lda * 2 < (int64_t)1 << 32 && 256 * a.seg[s].ldb * 2 < (int64_t)1 << 32;
-    if (a.epi == EPI_SWIGLU && a.ldc % 8) fits = false;       // its epilogue stores 16 bytes per lane
-    if (fits) {
-      if (a.tile_group) {
-        switch (a.epi) {                                   // the epilogues the mixture-of-experts products use
-          case EPI_STORE: return launch_dma<EPI_STORE, true>(a, st);
-          case EPI_SWIGLU: return launch_dma<EPI_SWIGLU, true>(a, st);
-          case EPI_SWIGLU_BWD: return launch_dma<EPI_SWIGLU_BWD, true>(a, st);
-          default: return hipErrorInvalidValue;
-        }
-      }
-      if (a.rscale || a.rowsq) {
-        switch (a.epi) {                                   // the ends of a norm that runs inside the products
-          case EPI_STORE: return launch_dma<EPI_STORE, false, true>(a, st);
-          case EPI_RESID: return launch_dma<EPI_RESID, false, true>(a, st);
-          case EPI_GELU: return launch_dma<EPI_GELU, false, true>(a, st);
-          case EPI_SWIGLU: return launch_dma<EPI_SWIGLU, false, true>(a, st);
-          case EPI_ROPE: return launch_dma<EPI_ROPE, false, true>(a, st);
-          default: return hipErrorInvalidValue;
-        }
-      }
-      switch (a.epi) {
-        case EPI_STORE: return launch_dma<EPI_STORE, false>(a, st);
-        case EPI_RESID: return launch_dma<EPI_RESID, false>(a, st);
-        case EPI_GELU: return launch_dma<EPI_GELU, false>(a, st);
-        case EPI_SWIGLU: return launch_dma<EPI_SWIGLU, false>(a, st);
-        case EPI_SWIGLU_BWD: return launch_dma<EPI_SWIGLU_BWD, false>(a, st);
-        case EPI_GELU_BWD: return launch_dma<EPI_GELU_BWD, false>(a, st);
-        case EPI_ROPE: return launch_dma<EPI_ROPE, false>(a, st);
-        default: return hipErrorInvalidValue;
-      }
-    }
-  }
-  if (tile == 0) {
-    // few tokens: the large tile over runs of k slices, about one workgroup per CU, instead of small tiles
-    const int runs = dma_split_runs(a);
-    if (runs) {
-      switch (a.epi) {
-        case EPI_STORE: return launch_dma_split<EPI_STORE>(a, runs, st);
-        case EPI_RESID: return launch_dma_split<EPI_RESID>(a, runs, st);
-        case EPI_GELU: return launch_dma_split<EPI_GELU>(a, runs, st);
-        case EPI_SWIGLU_BWD: return launch_dma_split<EPI_SWIGLU_BWD>(a, runs, st);
-        case EPI_GELU_BWD: return launch_dma_split<EPI_GELU_BWD>(a, runs, st);
-        case EPI_ROPE: return launch_dma_split<EPI_ROPE>(a, runs, st);
-        default: return hipErrorInvalidValue;
-      }
-    }
-  }
-  if (a.nbcol > 0 || a.epi == EPI_ROPE) return hipErrorInvalidValue;   // only the direct-to-LDS kernel implements these
-  if (!a.b_is_kn) {
-    // Few rows (a 512-token micro-batch against a 4096-wide projection is 128 tiles of 128 x 128 for 256 CUs):
-    // 128 x 64 tiles double the workgroups.
-    const bool narrow = !big && !a.tile_group && a.epi != EPI_SWIGLU &&
-                        (tile == 4 || (tile == 0 && (int64_t)((a.M + 127) / 128) * (a.N / 128) < 160));
-    if (narrow) {
-      // Long k with few workgroups (the down-projection of a 512-token micro-batch: 256 workgroups x 224 slices):
-      // split k so that about three workgroups share a CU and cover each other's load-to-multiply latency.
-      int slices = 0;
-      for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
-      const int64_t wgs = (int64_t)((a.M + 127) / 128) * (a.N / 64);
-      int nsplit = (int)std::min<int64_t>(std::min<int64_t>(8, slices / 8), (768 + wgs - 1) / wgs);
-      if (a.split_ws) nsplit = (int)std::min<int64_t>(nsplit, a.split_ws_floats / ((int64_t)a.M * a.N));
-      if (a.split_ws && tile == 0 && nsplit >= 2) {
-        switch (a.epi) {
-          case EPI_STORE: return launch_split<EPI_STORE>(a, nsplit, st);
-          case EPI_RESID: return launch_split<EPI_RESID>(a, nsplit, st);
-          case EPI_GELU: return launch_split<EPI_GELU>(a, nsplit, st);
-          case EPI_SWIGLU_BWD: return launch_split<EPI_SWIGLU_BWD>(a, nsplit, st);
-          case EPI_GELU_BWD: return launch_split<EPI_GELU_BWD>(a, nsplit, st);
-          default: return hipErrorInvalidValue;
-        }
-      }
-      switch (a.epi) {
-        case EPI_STORE: return launch_cfg<128, 64, 2, 2, false, EPI_STORE>(a, st);
-        case EPI_RESID: return launch_cfg<128, 64, 2, 2, false, EPI_RESID>(a, st);
-        case EPI_GELU: return launch_cfg<128, 64, 2, 2, false, EPI_GELU>(a, st);
-        case EPI_SWIGLU_BWD: return launch_cfg<128, 64, 2, 2, false, EPI_SWIGLU_BWD>(a, st);
-        case EPI_GELU_BWD: return launch_cfg<128, 64, 2, 2, false, EPI_GELU_BWD>(a, st);
-        default: return hipErrorInvalidValue;
-      }
-    }
+  if (a.b_is_kn) {
+    const bool big = tile == 1 || tile == 3 || (tile == 0 && a.N % 256 == 0 && (int64_t)((a.M + 255) / 256) * (a.N / 256) >= 192);
     switch (a.epi) {
-      case EPI_STORE: return big ? launch_cfg<256, 256, 2, 2, false, EPI_STORE>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_STORE>(a, st);
-      case EPI_RESID: return big ? launch_cfg<256, 256, 2, 2, false, EPI_RESID>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_RESID>(a, st);
-      case EPI_GELU: return big ? launch_cfg<256, 256, 2, 2, false, EPI_GELU>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_GELU>(a, st);
-      case EPI_SWIGLU: return big ? launch_cfg<256, 256, 2, 2, false, EPI_SWIGLU>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_SWIGLU>(a, st);
-      case EPI_SWIGLU_BWD: return big ? launch_cfg<256, 256, 2, 2, false, EPI_SWIGLU_BWD>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_SWIGLU_BWD>(a, st);
-      case EPI_GELU_BWD: return big ? launch_cfg<256, 256, 2, 2, false, EPI_GELU_BWD>(a, st) : launch_cfg<128, 128, 2, 2, false, EPI_GELU_BWD>(a, st);
+      case EPI_STORE: return big ? launch_kn<256, 256, 2, 2, EPI_STORE>(a, st) : launch_kn<128, 128, 2, 1, EPI_STORE>(a, st);
+      case EPI_SWIGLU_BWD: return big ? launch_kn<256, 256, 2, 2, EPI_SWIGLU_BWD>(a, st) : launch_kn<128, 128, 2, 1, EPI_SWIGLU_BWD>(a, st);
+      case EPI_GELU_BWD: return big ? launch_kn<256, 256, 2, 2, EPI_GELU_BWD>(a, st) : launch_kn<128, 128, 2, 1, EPI_GELU_BWD>(a, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  Plan p{tile == 1 ? kTile256 : tile == 2 ? kTile128 : tile == 3 ? kTile256x128 : kTile64x128, 1};
+  if (tile == 0) p = plan_gemm(a);
+  else if (p.kind == kTile256 ? !fits_256(a) : !fits_mid(a)) return hipErrorInvalidValue;
+  if (a.tile_group) {
+    switch (a.epi) {                                       // the epilogues the mixture-of-experts products use
+      case EPI_STORE: return launch_tile<EPI_STORE, true>(a, p.kind, st);
+      case EPI_SWIGLU: return launch_tile<EPI_SWIGLU, true>(a, p.kind, st);
+      case EPI_SWIGLU_BWD: return launch_tile<EPI_SWIGLU_BWD, true>(a, p.kind, st);
       default: return hipErrorInvalidValue;
     }
   }
   switch (a.epi) {
-    case EPI_STORE: return big ? launch_cfg<256, 256, 2, 2, true, EPI_STORE>(a, st) : launch_cfg<128, 128, 2, 1, true, EPI_STORE>(a, st);
-    case EPI_SWIGLU_BWD: return big ? launch_cfg<256, 256, 2, 2, true, EPI_SWIGLU_BWD>(a, st) : launch_cfg<128, 128, 2, 1, true, EPI_SWIGLU_BWD>(a, st);
-    case EPI_GELU_BWD: return big ? launch_cfg<256, 256, 2, 2, true, EPI_GELU_BWD>(a, st) : launch_cfg<128, 128, 2, 1, true, EPI_GELU_BWD>(a, st);
+    case EPI_STORE: return launch_plan<EPI_STORE>(a, p, st);
+    case EPI_RESID: return launch_plan<EPI_RESID>(a, p, st);
+    case EPI_GELU: return launch_plan<EPI_GELU>(a, p, st);
+    case EPI_SWIGLU: return launch_plan<EPI_SWIGLU>(a, p, st);
+    case EPI_SWIGLU_BWD: return launch_plan<EPI_SWIGLU_BWD>(a, p, st);
+    case EPI_GELU_BWD: return launch_plan<EPI_GELU_BWD>(a, p, st);
+    case EPI_ROPE: return launch_plan<EPI_ROPE>(a, p, st);
     default: return hipErrorInvalidValue;
   }
 }

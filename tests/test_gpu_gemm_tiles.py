@@ -1,0 +1,66 @@
+"""The direct-to-LDS products on smaller tiles: each tile alone at its edges (one row, one slice fewer and more than the stages it
+keeps in flight, ragged rows), and through stages whose widths are multiples of 8 only or sit on either side of a choice of tile."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+import stage_inputs as si
+from gpu_util import assert_close, dev, host, rel_l2
+from test_gpu_moe import run_constructed
+from test_gpu_stage import run_stage
+
+
+@pytest.mark.parametrize("tile", [0, 2, 3, 4], ids=["auto", "128x128", "256x128", "64x128"])
+@pytest.mark.parametrize("M,N,K", [(1, 128, 64), (63, 256, 128), (64, 256, 192), (129, 512, 256), (255, 256, 320), (257, 768, 576), (520, 256, 2304)])
+def test_product_at_the_edges_of_the_tiles(tile, M, N, K):
+    import paper_2603_03592_amd as sv
+    if tile == 3 and N % 256:
+        z = dev(np.zeros((128, 128), np.float32), "bf16")
+        with pytest.raises(sv.SVError):
+            sv.sv_gemm_bf16(z, z, tile=3)
+        return
+    g = np.random.default_rng(M * 7 + K)
+    a = si.round_to_bf16(g.standard_normal((M, K)).astype(np.float32))
+    b = si.round_to_bf16(g.standard_normal((N, K)).astype(np.float32))
+    got = host(sv.sv_gemm_bf16(dev(a, "bf16"), dev(b, "bf16"), tile=tile))
+    want = a.astype(np.float64) @ b.astype(np.float64).T
+    # one bf16 rounding (2^-9) of a sum whose fp32 error stays below K 2^-24 sum |a b| < 2^-2 of that rounding at these K
+    np.testing.assert_allclose(got, want, rtol=2 ** -8, atol=2 ** -20 * K * np.abs(want).max())
+    assert rel_l2(got, want) < 3e-3
+
+
+def test_product_refuses_what_it_refused():
+    import paper_2603_03592_amd as sv
+    for n, k in ((64, 128), (192, 128), (128, 96), (128, 32)):
+        with pytest.raises(sv.SVError):
+            sv.sv_gemm_bf16(dev(np.zeros((130, k), np.float32), "bf16"), dev(np.zeros((n, k), np.float32), "bf16"))
+
+
+# widths that are multiples of 64 (or 8, for the MLP) but not of 128; one kv head of 64 columns; fewer rows than a tile and ragged
+# row tiles; a sequence shorter than a tile (RoPE positions wrap several times inside it)
+EDGES = {
+    "swiglu_192_kv64": (si.StageDesc(2, 192, 3, 1, 320), 3, 43),
+    "gelu_ln_320": (si.StageDesc(1, 320, 5, 5, 832, mlp="gelu", norm="ln", rope=False), 2, 77),
+    "odd_mlp_width": (si.StageDesc(1, 192, 3, 3, 200), 2, 65),
+    "one_token": (si.StageDesc(1, 192, 3, 1, 320), 1, 1),
+    "mqa_128_bidir": (si.StageDesc(1, 384, 3, 1, 960, causal=False), 5, 61),
+    "ragged_960": (si.StageDesc(1, 960, 15, 5, 1088), 1, 301),
+    "gelu_rms_runs": (si.StageDesc(1, 448, 7, 1, 3200, mlp="gelu"), 1, 130),
+}
+
+
+@pytest.mark.parametrize("case", list(EDGES))
+@pytest.mark.parametrize("fuse", [False, True], ids=["norm_pass", "norm_inside"])
+def test_stage_at_widths_that_are_no_multiple_of_a_tile(case, fuse):
+    desc, B, S = EDGES[case]
+    (gh, gg), (wh, wg), _ = run_stage(desc, B, S, seed=21, backward=True, weight_scale=2.0, fuse=fuse)
+    assert_close(gh, wh, 2e-2, "h")
+    assert_close(gg, wg, 2e-2, "g")
+
+
+@pytest.mark.parametrize("desc,B,S", [(si.StageDesc(1, 192, 3, 1, 192, n_experts=4, top_k=1, n_shared=1), 8, 25),
+                                      (si.StageDesc(1, 320, 5, 5, 448, n_experts=8, top_k=2, router_norm=True), 16, 16)])
+def test_grouped_products_on_small_tiles(desc, B, S):
+    """Rows of one expert start on multiples of 256 and the row count comes from device memory; expert widths are multiples of 64."""
+    run_constructed(desc, B, S, 5, backward=True)
