@@ -338,6 +338,7 @@ hipError_t gemm(sv_ctx* c, const GemmArgs& a, hipStream_t st) {
     g.split_ws = c->split_ws; g.split_ws_floats = (int64_t)c->split_ws_floats;
     return mfma_gemm(g, st);
   }
+  if (c->d.dtype == SV_F32 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && f32_gemm_supported(a)) return f32_gemm(a, st);
   return plain_gemm(a, c->d.dtype, st);
 }
 
@@ -360,6 +361,8 @@ hipError_t attn_fwd(sv_ctx* c, const void* qkv, void* o, float* lse, int B, int 
     if (e == hipSuccess) e = plain_pad_heads(c->o_pad, ldo, o, c->Dq, T, d.n_heads, c->hd, c->pad_hd, 0, st);
     return e;
   }
+  if (d.dtype == SV_F32 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && f32_attn_supported(qkv, c->Dqkv, B, d.n_heads, c->hd))
+    return f32_attn_fwd((const float*)qkv, c->Dqkv, (float*)o, lse, B, S, d.n_heads, d.n_kv_heads, c->hd, d.causal, st);
   return plain_attn_fwd(qkv, c->Dqkv, o, lse, B, S, d.n_heads, d.n_kv_heads, c->hd, d.causal, d.dtype, st);
 }
 
@@ -487,6 +490,8 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
     settle_qkv(f);
     if (dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && mfma_gemm_supported(f)) {
       SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dqkv * D, st, mfma_gemm(f, st));
+    } else if (dt == SV_F32 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && f32_gemm_supported(f)) {
+      SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dqkv * D, st, f32_gemm(f, st));
     } else {
       SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dq * D, st, gemm(c, nt(T, c->Dq, D, c->n, D, w.wq, qkv, c->Dqkv, EPI_STORE), st));
       SV_OP(c, SV_OP_GEMM_QKV, 2.0 * Td * c->Dkv * D, st, gemm(c, nt(T, c->Dkv, D, c->n, D, w.wk, at(qkv, c->Dq, es), c->Dqkv, EPI_STORE), st));

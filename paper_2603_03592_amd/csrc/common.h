@@ -245,6 +245,12 @@ bool mfma_gemm_emits_rowsq(const GemmArgs& a);          // would mfma_gemm(a, st
 int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats);   // the GemmArgs::runs of an [N,K] product before a router
 hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile = 0);   // tile: 0 auto, 1 = 256x256, 2 = 128x128, 3 = 256x128, 4 = 64x128
 
+// f32_mfma.hip: fp32 products (with the column map and EPI_ROPE; no rscale / rowsq) and attention forward on the matrix cores
+bool f32_gemm_supported(const GemmArgs& a);
+hipError_t f32_gemm(const GemmArgs& a, hipStream_t st);
+bool f32_attn_supported(const void* qkv, int64_t ld, int B, int H, int hd);
+hipError_t f32_attn_fwd(const float* qkv, int64_t ld, float* o, float* lse, int B, int S, int H, int Hkv, int hd, int causal, hipStream_t st);
+
 // attn_mfma.hip: bf16, head_dim 64 | 128.  scale_hd (0 = hd): the head dimension the softmax scale 1/sqrt(.) is taken from,
 // for inputs whose heads were zero-padded from scale_hd to hd columns
 bool mfma_attn_supported(int S, int H, int Hkv, int hd, int64_t ld);

@@ -1,7 +1,7 @@
 // Plain kernels: every step of the block forward / input-gradient backward for any shape and
-// for E = float or bf16 storage, all arithmetic in fp32 on the vector ALUs.  They are the
-// product path for fp32 stages (the fp32 benchmark stage is tiny) and for the element-wise /
-// row-wise steps of bf16 stages; bf16 contractions normally run on the MFMA kernels instead.
+// for E = float or bf16 storage, all arithmetic in fp32 on the vector ALUs.  They serve what the
+// matrix-core kernels do not take (products whose k or alignment does not fit, fp32 attention backward, head_dim 8 in
+// fp32) and the element-wise / row-wise steps of every stage.
 #include "common.h"
 
 namespace sv {
