@@ -85,6 +85,27 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * __expf(-0.5f * z * z) * 0.39894228040143268f;
 }
 
+// GELU for the epilogues of the bf16 products.  With a = |z| the normal tail 1/2 erfc(a / sqrt 2) = exp(-a^2 / 2) t P(t), t = 1 / (1 +
+// 0.3 a): P of degree 7 fitted here for least relative error over a in [0, 13] (1.1e-7), so 9 multiply-adds, one reciprocal and
+// one exponential where erff takes both sides of a branch; the derivative's exp(-z^2 / 2) is the same one.  Over |z| <= 9 its
+// largest error is 3.8e-7 against 4.5e-7 through erff, relative to the result 4e-6 (erff: all of it in the negative tail).
+__device__ __forceinline__ float normal_cdf_f(float z, float& ez) {
+  const float a = fabsf(z), t = __builtin_amdgcn_rcpf(fmaf(0.3f, a, 1.0f));
+  ez = __builtin_amdgcn_exp2f(-0.72134752044448170f * (a * a));            // exp(-z^2 / 2)
+  float q = 0.03619647434818525f;
+  q = fmaf(q, t, -0.15938469609299546f);
+  q = fmaf(q, t, 0.21012874640472984f);
+  q = fmaf(q, t, -0.05717627819721227f);
+  q = fmaf(q, t, 0.13042084038660928f);
+  q = fmaf(q, t, 0.0993458926848985f);
+  q = fmaf(q, t, 0.12084571258937257f);
+  q = fmaf(q, t, 0.11962325166055274f);
+  const float h = q * t * ez;
+  return z < 0.0f ? h : 1.0f - h;
+}
+__device__ __forceinline__ float gelu_epi_f(float z) { float ez; return z * normal_cdf_f(z, ez); }
+__device__ __forceinline__ float gelu_grad_epi_f(float z) { float ez; const float p = normal_cdf_f(z, ez); return fmaf(z * 0.39894228040143268f, ez, p); }
+
 }  // namespace sv
 
 // ----------------------------------------------------------------------------------------

@@ -96,7 +96,7 @@ __device__ __forceinline__ float epilogue_math4(const GemmArgs& a, bool roped, c
     case EPI_GELU: {
       if (a.C2) { bf16x4 p; for (int i = 0; i < 4; ++i) p[i] = (bf16)v[i]; put(1, p); }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = gelu_f(v[i]);
+      for (int i = 0; i < 4; ++i) o[i] = gelu_epi_f(v[i]);
     } break;
     case EPI_SWIGLU: {
       if (a.C2) { bf16x4 p; for (int i = 0; i < 4; ++i) p[i] = (bf16)v[i]; put(1, p); }
@@ -132,7 +132,7 @@ __device__ __forceinline__ float epilogue_math4(const GemmArgs& a, bool roped, c
     } break;
     default:  // EPI_GELU_BWD
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = v[i] * gelu_grad_f((float)r[i]);
+      for (int i = 0; i < 4; ++i) o[i] = v[i] * gelu_grad_epi_f((float)r[i]);
       break;
   }
   bf16x4 p;
