@@ -10,6 +10,7 @@
 //                         is flagged when any enabled metric exceeds its threshold).
 //   ema_update_kernel   : Eq. momentum_def over the un-flagged submissions.
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -18,115 +19,6 @@ namespace sv {
 namespace {
 
 constexpr int kTPW = kScoreTokensPerWG / 4;  // tokens per wave
-
-// NEED_L1 / NEED_Z / NEED_SFR prune the sums a launch does not need (the statistic family is
-// requested by mask): with only the relative L2 enabled a token costs two FMAs per element and the
-// pass is bound by HBM; with all eight sums it is bound by the vector ALUs (about 18 ops/element).
-template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR>
-__global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
-                                                           const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
-                                                           int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
-                                                           ScorePartial* __restrict__ partials) {
-  // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): ids congruent mod 8 get a contiguous run of
-  // token tiles, and within a run the claim index varies fastest, so the submissions that share a tile of the
-  // reference run together on one XCD and fetch it from memory once instead of once per XCD.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int claim = slot % n_claims;
-  const int tile = xcd * ((tiles_per_claim + 7) >> 3) + slot / n_claims;
-  if (tile >= tiles_per_claim) return;               // the last XCD's run may be short (whole workgroup leaves)
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const EC* cbase = claims + (int64_t)claim * claim_stride;
-  const ER* rbase = ref + (int64_t)claim * ref_stride;
-
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float best = -1.0f;
-  int best_t = 0, bad = 0;
-
-  for (int i = 0; i < kTPW; ++i) {
-    const int64_t t = (int64_t)tile * kScoreTokensPerWG + i * 4 + wave;
-    if (t >= T) break;  // uniform per wave
-    const EC* c = cbase + t * D;
-    const ER* r = rbase + t * D;
-    float sc = 0, sr = 0, scc = 0, srr = 0, sad = 0, sdd = 0;
-    int nsi = 0;
-    auto accumulate = [&](const float (&cv)[8], const float (&rv)[8]) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float a = cv[j], b = rv[j], d = a - b;
-        srr = fmaf(b, b, srr); sdd = fmaf(d, d, sdd);
-        if (NEED_Z) { sc += a; sr += b; scc = fmaf(a, a, scc); }
-        if (NEED_L1) sad += fabsf(d);
-        // sign(a) != sign(b) with sign(0) = 0: the two signs agree iff both "positive" and both "negative" tests agree
-        if (NEED_SFR) nsi += (int)(((a > 0.0f) != (b > 0.0f)) | ((a < 0.0f) != (b < 0.0f)));
-      }
-    };
-    int k = lane * 8;
-    for (; k + 1536 < D; k += 2048) {                 // four 16-byte loads of each operand in flight per lane
-      float c0[8], c1[8], c2[8], c3[8], r0[8], r1[8], r2[8], r3[8];
-      load8(c + k, c0); load8(c + k + 512, c1); load8(c + k + 1024, c2); load8(c + k + 1536, c3);
-      load8(r + k, r0); load8(r + k + 512, r1); load8(r + k + 1024, r2); load8(r + k + 1536, r3);
-      accumulate(c0, r0); accumulate(c1, r1); accumulate(c2, r2); accumulate(c3, r3);
-    }
-    for (; k < D; k += 512) {
-      float cv[8], rv[8];
-      load8(c + k, cv);
-      load8(r + k, rv);
-      accumulate(cv, rv);
-    }
-    srr = wave_sum(srr); sdd = wave_sum(sdd);
-    if (NEED_Z) { sc = wave_sum(sc); sr = wave_sum(sr); scc = wave_sum(scc); }
-    if (NEED_L1) sad = wave_sum(sad);
-    float ns = 0.0f;
-    if (NEED_SFR) ns = wave_sum((float)nsi);      // at most D / 64 per lane: exact in fp32
-    const float rel = sqrtf(sdd) / fmaxf(sqrtf(srr), 1e-30f);
-    if (lane == 0 && token_scores) token_scores[(int64_t)claim * T + t] = rel;
-    acc[0] += sc; acc[1] += sr; acc[2] += scc; acc[3] += srr;
-    acc[4] += (double)sc - (double)sr;            // sum of differences, only used for the mean of d in the z-scored L2
-    acc[5] += sad; acc[6] += sdd; acc[7] += ns;
-    if (!(rel <= 3.0e38f)) bad = 1;           // NaN or inf
-    else if (rel > best) { best = rel; best_t = (int)t; }
-  }
-
-  __shared__ double s_acc[4][8];
-  __shared__ float s_best[4];
-  __shared__ int s_bt[4], s_bad[4];
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s_acc[wave][j] = acc[j];
-    s_best[wave] = best; s_bt[wave] = best_t; s_bad[wave] = bad;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    ScorePartial p;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) p.s[j] = s_acc[0][j] + s_acc[1][j] + s_acc[2][j] + s_acc[3][j];
-    float b = -1.0f; int bt = 0, bd = 0;
-    for (int w = 0; w < 4; ++w) {
-      bd |= s_bad[w];
-      if (s_best[w] > b || (s_best[w] == b && s_best[w] >= 0.0f && s_bt[w] < bt)) { b = s_best[w]; bt = s_bt[w]; }
-    }
-    p.max_rel = b; p.argmax = bt; p.bad = bd; p.pad = 0;
-    partials[(int64_t)claim * tiles_per_claim + tile] = p;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The same statistics for several submissions against ONE shared reference, rows of any multiple of 2 KB.  A wave
-// owns a token and takes its row in parts of NU KB (NU = 2 or 4): it loads the reference part into registers once,
-// forms the reference's own sums and -- for the sign-flip ratio -- one class mask per element, and then streams the
-// same part of every submission of its group past them, the next submission's loads in flight while the current one
-// is reduced.  Compared with score_tokens_kernel the reference is read once per group instead of once per submission,
-// and its share of the arithmetic is paid once: 7-8 vector instructions per element instead of 16, which moves the
-// all-statistics pass from the vector ALUs' bound to the memory's.
-//   sign test: sign(a) == sign(b), with sign(0) = sign(NaN) = 0, is one v_cmp_class of a against the set of classes
-//   that b's sign allows; the matches are counted on the scalar unit from the lane mask.
-// Lane c of a wave adds up submission c's sums over the parts of a token (a predicated add after each wave
-// reduction) and closes the token -- per-token relative L2, running sums -- for all submissions at once; the four
-// waves' sums are folded per submission at the end, into the same per-(submission, tile) records as above.
-// With SUM the kernel also writes, per element, the sum over the group's submissions whose bit in `skip` is clear
-// (added in index order, fp32): the mean the EMA update needs, without another pass over the submissions.  SUM needs
-// the whole set in one group.
-constexpr int kGroupMax = 32;                 // submissions per group (<= 64: one lane each)
 
 __device__ __forceinline__ float dpp_add(float v, int ctrl_sel) {
   const int x = __float_as_int(v);
@@ -148,6 +40,132 @@ __device__ __forceinline__ float wave_sum_rows(float v) {
   const float r2 = __int_as_float(__builtin_amdgcn_readlane(x, 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(x, 48));
   return (r0 + r1) + (r2 + r3);
 }
+
+// NEED_L1 / NEED_Z / NEED_SFR prune the sums a launch does not need (the statistic family is
+// requested by mask): with only the relative L2 enabled a token costs two FMAs per element and the
+// pass is bound by HBM; with all eight sums it is bound by the vector ALUs (about 18 ops/element).
+// TW: tokens per workgroup, and per record.  With few records of 16 (one submission of up to 4096 tokens) the pass is a chain of
+// memory round trips, one per token of a wave, on a part of the CUs: 4 tokens then, one per wave on four times the workgroups
+// (512 tokens of 4096, both sides bf16: 13 -> 6 us; 2331 of 960: 10 -> 5.5).
+template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, int TW>
+__global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
+                                                           const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
+                                                           int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
+                                                           ScorePartial* __restrict__ partials) {
+  // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): ids congruent mod 8 get a contiguous run of
+  // token tiles, and within a run the claim index varies fastest, so the submissions that share a tile of the
+  // reference run together on one XCD and fetch it from memory once instead of once per XCD.
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int claim = slot % n_claims;
+  const int tile = xcd * ((tiles_per_claim + 7) >> 3) + slot / n_claims;
+  if (tile >= tiles_per_claim) return;               // the last XCD's run may be short (whole workgroup leaves)
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const EC* cbase = claims + (int64_t)claim * claim_stride;
+  const ER* rbase = ref + (int64_t)claim * ref_stride;
+
+  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  float best = -1.0f;
+  int best_t = 0, bad = 0;
+
+  for (int i = 0; i < TW / 4; ++i) {
+    const int64_t t = (int64_t)tile * TW + i * 4 + wave;
+    if (t >= T) break;  // uniform per wave
+    const EC* c = cbase + t * D;
+    const ER* r = rbase + t * D;
+    float sc = 0, sr = 0, scc = 0, srr = 0, sad = 0, sdd = 0;
+    int nsi = 0;
+    auto accumulate = [&](const float (&cv)[8], const float (&rv)[8]) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float a = cv[j], b = rv[j], d = a - b;
+        srr = fmaf(b, b, srr); sdd = fmaf(d, d, sdd);
+        if (NEED_Z) { sc += a; sr += b; scc = fmaf(a, a, scc); }
+        if (NEED_L1) sad += fabsf(d);
+        // sign(a) != sign(b) with sign(0) = 0: the two signs agree iff both "positive" and both "negative" tests agree
+        if (NEED_SFR) nsi += (int)(((a > 0.0f) != (b > 0.0f)) | ((a < 0.0f) != (b < 0.0f)));
+      }
+    };
+    // N units of 512 elements from k0 on, all their loads in flight before the first is used; of the row's last unit the lanes
+    // past its end take two equal zeros, which add nothing to any sum
+    // (55 submissions of 5338 x 1856, each with its own fp32 reference: 750 -> 560 us, 5.8 TB/s, against one unit at a time)
+    auto part = [&](auto n_tag, auto last_tag, int k0) {
+      constexpr int N = decltype(n_tag)::value;
+      float cv[N][8], rv[N][8];
+#pragma unroll
+      for (int m = 0; m < N; ++m) {
+        const int k = k0 + m * 512 + lane * 8;
+        if (decltype(last_tag)::value && m == N - 1) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) cv[m][j] = rv[m][j] = 0.0f;
+          if (k < D) { load8(c + k, cv[m]); load8(r + k, rv[m]); }
+        } else {
+          load8(c + k, cv[m]);
+          load8(r + k, rv[m]);
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < N; ++m) accumulate(cv[m], rv[m]);
+    };
+    int k0 = 0;
+    for (; k0 + 2048 <= D; k0 += 2048) part(std::integral_constant<int, 4>{}, std::false_type{}, k0);
+    const int rest = D - k0;
+    if (rest > 1536) part(std::integral_constant<int, 4>{}, std::true_type{}, k0);
+    else if (rest > 1024) part(std::integral_constant<int, 3>{}, std::true_type{}, k0);
+    else if (rest > 512) part(std::integral_constant<int, 2>{}, std::true_type{}, k0);
+    else if (rest > 0) part(std::integral_constant<int, 1>{}, std::true_type{}, k0);
+    srr = wave_sum_rows(srr); sdd = wave_sum_rows(sdd);
+    if (NEED_Z) { sc = wave_sum_rows(sc); sr = wave_sum_rows(sr); scc = wave_sum_rows(scc); }
+    if (NEED_L1) sad = wave_sum_rows(sad);
+    float ns = 0.0f;
+    if (NEED_SFR) ns = wave_sum_rows((float)nsi);      // at most D / 64 per lane: exact in fp32
+    const float rel = sqrtf(sdd) / fmaxf(sqrtf(srr), 1e-30f);
+    if (lane == 0 && token_scores) token_scores[(int64_t)claim * T + t] = rel;
+    acc[0] += sc; acc[1] += sr; acc[2] += scc; acc[3] += srr;
+    acc[4] += (double)sc - (double)sr;            // sum of differences, only used for the mean of d in the z-scored L2
+    acc[5] += sad; acc[6] += sdd; acc[7] += ns;
+    if (!(rel <= 3.0e38f)) bad = 1;           // NaN or inf
+    else if (rel > best) { best = rel; best_t = (int)t; }
+  }
+
+  __shared__ double s_acc[4][8];
+  __shared__ float s_best[4];
+  __shared__ int s_bt[4], s_bad[4];
+  if (lane == 0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s_acc[wave][j] = acc[j];
+    s_best[wave] = best; s_bt[wave] = best_t; s_bad[wave] = bad;
+  }
+  __syncthreads();
+  ScorePartial* p = partials + (int64_t)claim * tiles_per_claim + tile;
+  if (threadIdx.x < 8) {                             // one sum each, the waves in order
+    p->s[threadIdx.x] = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
+  } else if (threadIdx.x == 64) {
+    float b = -1.0f; int bt = 0, bd = 0;
+    for (int w = 0; w < 4; ++w) {
+      bd |= s_bad[w];
+      if (s_best[w] > b || (s_best[w] == b && s_best[w] >= 0.0f && s_bt[w] < bt)) { b = s_best[w]; bt = s_bt[w]; }
+    }
+    p->max_rel = b; p->argmax = bt; p->bad = bd; p->pad = 0;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same statistics for several submissions against ONE shared reference, rows of any multiple of 2 KB.  A wave
+// owns a token and takes its row in parts of NU KB (NU = 2 or 4): it loads the reference part into registers once,
+// forms the reference's own sums and -- for the sign-flip ratio -- one class mask per element, and then streams the
+// same part of every submission of its group past them, the next submission's loads in flight while the current one
+// is reduced.  Compared with score_tokens_kernel the reference is read once per group instead of once per submission,
+// and its share of the arithmetic is paid once: 7-8 vector instructions per element instead of 16, which moves the
+// all-statistics pass from the vector ALUs' bound to the memory's.
+//   sign test: sign(a) == sign(b), with sign(0) = sign(NaN) = 0, is one v_cmp_class of a against the set of classes
+//   that b's sign allows; the matches are counted on the scalar unit from the lane mask.
+// Lane c of a wave adds up submission c's sums over the parts of a token (a predicated add after each wave
+// reduction) and closes the token -- per-token relative L2, running sums -- for all submissions at once; the four
+// waves' sums are folded per submission at the end, into the same per-(submission, tile) records as above.
+// With SUM the kernel also writes, per element, the sum over the group's submissions whose bit in `skip` is clear
+// (added in index order, fp32): the mean the EMA update needs, without another pass over the submissions.  SUM needs
+// the whole set in one group.
+constexpr int kGroupMax = 32;                 // submissions per group (<= 64: one lane each)
 
 template <typename E, int N> struct RawUnit;                     // N consecutive elements as they come from memory
 template <> struct RawUnit<bf16, 8> { bf16x8 v; __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const bf16x8*>(p); }
@@ -330,11 +348,11 @@ struct Tau4 { float v[4]; };
 __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial* __restrict__ partials, int tiles_per_claim,
                                                              int64_t T, int D, uint32_t mask, Tau4 tau, int reduce,
                                                              sv_result* __restrict__ results) {
-  const int claim = blockIdx.x, tid = threadIdx.x;
+  const int claim = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const ScorePartial* p = partials + (int64_t)claim * tiles_per_claim;
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   float best = -1.0f; int bt = 0, bad = 0;
-  for (int i = tid; i < tiles_per_claim; i += 256) {     // tiles visited in increasing order
+  for (int i = tid; i < tiles_per_claim; i += nt) {      // tiles visited in increasing order
     const ScorePartial q = p[i];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] += q.s[j];
@@ -348,7 +366,7 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial*
   for (int j = 0; j < 8; ++j) s_acc[tid][j] = acc[j];
   s_best[tid] = best; s_bt[tid] = bt; s_bad[tid] = bad;
   __syncthreads();
-  for (int stride = 128; stride > 0; stride >>= 1) {     // fixed tree: run-to-run identical
+  for (int stride = nt >> 1; stride > 0; stride >>= 1) { // fixed tree: run-to-run identical
     if (tid < stride) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) s_acc[tid][j] += s_acc[tid + stride][j];
@@ -497,13 +515,21 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
 #undef SV_LAUNCH_PARTS
 #undef SV_LAUNCH_PARTS3
 #undef SV_LAUNCH_PARTS5
-      hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(256), 0, st, scratch, (int)tiles, T, D, mask, tau, reduce,
+      hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(tiles <= 128 ? 64 : 256), 0, st, scratch, (int)tiles, T, D, mask, tau, reduce,
                          results + c0);
       continue;
     }
+    const int64_t tiles4 = (T + 3) / 4;                // up to one record of 16 tokens per CU: smaller ones (see the kernel)
+    const bool few = tiles * nc <= 256 && tiles4 * nc <= scratch_elems;
+    const int tpc = (int)(few ? tiles4 : tiles);
+    const dim3 gridt((unsigned)(8 * ((tpc + 7) / 8) * nc));
 #define SV_LAUNCH_SCORE3(EC, ER, L1, Z, SFR)                                                                           \
-  hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR>), grid, block, 0, st, (const EC*)cp, claim_stride,          \
-                     (const ER*)rp, ref_stride, T, D, nc, (int)tiles, ts, scratch)
+  do {                                                                                                                 \
+    if (few) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
+                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch);                          \
+    else hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, kScoreTokensPerWG>), gridt, block, 0, st, (const EC*)cp, claim_stride, \
+                            (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch);                              \
+  } while (0)
 #define SV_LAUNCH_SCORE(EC, ER)                                                                                          \
   do {                                                                                                                   \
     const bool l1 = mask & SV_M_L1, z = mask & SV_M_ZL2, sfr = mask & SV_M_SFR;                                          \
@@ -519,7 +545,7 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     else SV_LAUNCH_SCORE(float, float);
 #undef SV_LAUNCH_SCORE
 #undef SV_LAUNCH_SCORE3
-    hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(256), 0, st, scratch, (int)tiles, T, D, mask, tau, reduce,
+    hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(tpc <= 128 ? 64 : 256), 0, st, scratch, tpc, T, D, mask, tau, reduce,
                        results + c0);
   }
   return hipGetLastError();
