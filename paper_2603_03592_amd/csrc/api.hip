@@ -1064,8 +1064,7 @@ sv_status sv_sw_against_projection(sv_ctx* c, const void* claims, int64_t claim_
   const int64_t Tpad = sw_padded_len(T);
   if (Tpad > kSwSortChunkMax) { set_err(c, "rows longer than %lld are sorted in place: use sv_sliced_wasserstein", (long long)kSwSortChunkMax); return SV_EUNSUPPORTED; }
   hipStream_t st = (hipStream_t)stream;
-  SV_HIP(c, launch_sw_copy_pad(c->sw_proj, ref_proj, L, T, Tpad, st));
-  SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(c->sw_proj, L, T, Tpad, nullptr, 0, L, nullptr, 0, st));
+  SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(c->sw_proj, L, T, Tpad, nullptr, 0, L, nullptr, 0, st, ref_proj));
   SV_OP(c, SV_OP_SW_PROJECT, 2.0 * (double)T * D * L * n_claims, st,
         launch_sw_project(claims, claim_stride, n_claims, claim_dtype, directions, L, D, T, Tpad, claim_proj_out, st));
   // rows of one LDS chunk: the last sort pass adds up |a - b| against the reference and leaves the projections as they are

@@ -147,10 +147,9 @@ hipError_t launch_sw_project(const void* X, int64_t stride, int count, int dtype
 bool sw_project_with_ref_supported(int dtype, int ref_dtype);
 hipError_t launch_sw_project_with_ref(const void* X, int64_t stride, int count, int dtype, const void* ref, int ref_dtype, const void* U,
                                       int L, int D, int64_t T, int64_t Tpad, float* P, float* Pref, hipStream_t st);
-// Sort n_seg rows; with ref != nullptr also w1[first_seg + s] = sum_t |row_s[t] - ref_row[t]| (ref rows already sorted).
+// Sort n_seg rows of P (read from `src`, rows of the same pitch, if given); with ref != nullptr also w1[first_seg + s] = sum_t |row_s[t] - ref_row[t]| (ref rows already sorted).
 hipError_t launch_sw_sort(float* P, int n_seg, int64_t T, int64_t Tpad, const float* ref, int ref_shared, int L, float* w1,
-                          int first_seg, hipStream_t st);
-hipError_t launch_sw_copy_pad(float* dst, const float* src, int L, int64_t T, int64_t Tpad, hipStream_t st);
+                          int first_seg, hipStream_t st, const float* src = nullptr);
 hipError_t launch_sw_proj_ema(float* pm, const float* P, int n, uint32_t skip, int L, int64_t T, int64_t Tpad, float beta, float w,
                               hipStream_t st);
 constexpr int64_t kSwSortChunkMax = 16384;   // longest row one workgroup sorts in LDS (longer rows are sorted in place in global memory)

@@ -196,89 +196,122 @@ __global__ __launch_bounds__(256) void sw_project_kernel(const E* __restrict__ X
 }
 
 // ---------------------------------------------------------------------------------------------
-// Bitonic sorting network on rows of length Tpad (a power of two).  Element i of a row is compared
-// with i ^ j in the stage (k, j), ascending where (i & k) == 0.
+// Bitonic sorting network on rows of length Tpad (a power of two), ascending everywhere: in the first stage of level k
+// element i of a block of k meets its mirror image k - 1 - i, in the others i meets i + j.  So a comparator is a minimum and a
+// maximum and needs no direction.  It works on keys, the float's bits made to order as unsigned numbers: a total order, with
+// NaNs at the ends.  Padding is the largest key of all and never leaves the positions from T on, so whatever touches
+// padding only is skipped (27 % of the network at T = 6000).  The result is the same for every input.
 //
-// sw_sort_chunk_kernel keeps a chunk of `ch` consecutive elements in LDS and runs the stages
-// (k, j) for k = k_first, 2 k_first, ..., k_last and j = min(k / 2, ch / 2) ... 1 on it.  With
-// k_first = 2 and k_last = ch it sorts the chunk from scratch; with k_first = k_last = k > ch it
-// finishes stage k after sw_sort_global_kernel has done the strides j >= ch.
+// sw_sort_chunk_kernel keeps a chunk of `ch` consecutive elements in LDS and runs the levels
+// k = k_first, 2 k_first, ..., k_last on it.  With k_first = 2 and k_last = ch it sorts the chunk from scratch; with
+// k_first = k_last = k > ch it finishes level k after sw_sort_global_kernel has done the strides j >= ch.
 // If `ref` is non-null (only for ch == Tpad) the sorted row is not written back; instead the
 // workgroup adds up |row[i] - ref_row[i]| over the T real samples in a fixed order and stores the
 // sum in w1[first_seg + segment]; the reference row is row (segment % L) of `ref` when ref_shared,
 // else row `segment`.
 //
-// The network is LDS-bound when every stage is a round trip, so a thread takes eight float4 vectors
-// v0 + m s (m = 0..7) into registers and runs up to three stages (vector strides 4s, 2s, s) on them
-// per round trip; the last pass of a level (s = 1: 32 consecutive elements) also runs the strides
-// 2 and 1 inside the vectors, and the first pass of a sort from scratch runs all of the levels
-// k = 2 .. 32 (15 stages).  13 levels of an 8192-element row take 24 round trips instead of 91.
-// The comparator and the order of the stages are those of the plain network, so the result is the same for
-// every input.  Vectors are XOR-swizzled in LDS (bits 4, 5, 6 of the vector index folded into bits
+// A stage per round trip through LDS would be LDS-bound, so a thread takes eight vectors of four elements
+// v0 + m s (m = 0..7; of a mirrored stage's upper half the mirrored ones) into registers and runs up to three stages
+// (vector strides 4s, 2s, s) on them per round trip; the last pass of a level (s = 1: 32 consecutive elements) also runs
+// the strides 2 and 1 inside the vectors, and the first pass of a sort from scratch all of the levels
+// k = 2 .. 32 (15 stages).  13 levels of an 8192-element row take 24 round trips instead of 91.  What is left is about half
+// arithmetic (two instructions per comparator; with directions and float comparisons it was three and a scalar one) and half LDS.
+// 1024 rows of 8192 against a reference: 71 -> 56 us, 64 rows alone 39 -> 28, 2048 rows at T = 6000 139 -> 100.
+// Vectors are XOR-swizzled in LDS (bits 4, 5, 6 of the vector index folded into bits
 // 1, 2 and 0 + 3) so that 16 neighbouring lanes hit 16 different 16-byte slots at every stride.
-template <int A, int B>
-__device__ __forceinline__ void cx_in(f32x4& v, bool asc) {          // components A and B of one vector
-  const float a = v[A], b = v[B];
-  const bool swap = (a > b) == asc;
-  v[A] = swap ? b : a; v[B] = swap ? a : b;
+typedef __attribute__((ext_vector_type(4))) uint32_t key4;
+constexpr uint32_t kPadKey = 0xffffffffu;
+
+__device__ __forceinline__ uint32_t key_of(float x) {
+  const uint32_t b = __float_as_uint(x);
+  return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
 }
-__device__ __forceinline__ void cxv(f32x4& a, f32x4& b, bool asc) {
+__device__ __forceinline__ float value_of(uint32_t k) { return __uint_as_float(k ^ (~(uint32_t)((int32_t)k >> 31) | 0x80000000u)); }
+__device__ __forceinline__ key4 keys_of(const f32x4& v) { return key4{key_of(v[0]), key_of(v[1]), key_of(v[2]), key_of(v[3])}; }
+
+__device__ __forceinline__ void cx(uint32_t& a, uint32_t& b) {
+  const uint32_t lo = min(a, b), hi = max(a, b);
+  a = lo; b = hi;
+}
+template <int A, int B>
+__device__ __forceinline__ void cx_in(key4& v) {                     // components A and B of one vector
+  uint32_t a = v[A], b = v[B];
+  cx(a, b);
+  v[A] = a; v[B] = b;
+}
+template <int FLIP>
+__device__ __forceinline__ void cxv(key4& a, key4& b) {              // component i meets component i, or (FLIP) 3 - i
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const bool swap = (a[i] > b[i]) == asc;
-    const float na = swap ? b[i] : a[i], nb = swap ? a[i] : b[i];
-    a[i] = na; b[i] = nb;
+    const int j = FLIP ? 3 - i : i;
+    uint32_t x = a[i], y = b[j];
+    cx(x, y);
+    a[i] = x; b[j] = y;
   }
 }
-// vectors m and m + SM of the eight, direction of vector m
+// vectors m and m + SM of the eight
 template <int SM>
-__device__ __forceinline__ void vec_stage(f32x4 (&e)[8], const bool (&asc)[8]) {
+__device__ __forceinline__ void vec_stage(key4 (&e)[8]) {
 #pragma unroll
   for (int m = 0; m < 8; ++m)
-    if ((m & SM) == 0) cxv(e[m], e[m + SM], asc[m]);
+    if ((m & SM) == 0) cxv<0>(e[m], e[m + SM]);
+}
+// first stage of a level on blocks of N of the eight vectors: vector m meets vector N - 1 - m, last component first
+template <int N>
+__device__ __forceinline__ void mirror_stage(key4 (&e)[8]) {
+#pragma unroll
+  for (int b = 0; b < 8; b += N)
+#pragma unroll
+    for (int m = 0; m < N / 2; ++m) cxv<1>(e[b + m], e[b + N - 1 - m]);
 }
 // strides 2 and 1 inside every vector
-__device__ __forceinline__ void in_stages(f32x4 (&e)[8], const bool (&asc)[8], bool with_stride2) {
+__device__ __forceinline__ void in_stages(key4 (&e)[8]) {
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
-    if (with_stride2) { cx_in<0, 2>(e[m], asc[m]); cx_in<1, 3>(e[m], asc[m]); }
-    cx_in<0, 1>(e[m], asc[m]); cx_in<2, 3>(e[m], asc[m]);
+    cx_in<0, 2>(e[m]); cx_in<1, 3>(e[m]);
+    cx_in<0, 1>(e[m]); cx_in<2, 3>(e[m]);
   }
 }
 
-__global__ __launch_bounds__(512) void sw_sort_chunk_kernel(float* __restrict__ P, int64_t Tpad, int ch, int64_t k_first, int64_t k_last,
+__global__ __launch_bounds__(512) void sw_sort_chunk_kernel(const float* src, float* P, int64_t Tpad, int ch, int64_t k_first, int64_t k_last,
                                                             const float* __restrict__ ref, int ref_shared, int L, int64_t T,
                                                             float* __restrict__ w1, int first_seg) {
   extern __shared__ __attribute__((aligned(16))) float s[];
-  f32x4* s4 = reinterpret_cast<f32x4*>(s);
+  key4* s4 = reinterpret_cast<key4*>(s);
   const int tid = threadIdx.x, nt = blockDim.x;
   const int64_t gbase = (int64_t)blockIdx.x * ch;
+  const float* from = src + (int64_t)blockIdx.y * Tpad + gbase;   // rows to read; P itself if they are sorted in place
   float* row = P + (int64_t)blockIdx.y * Tpad + gbase;
   const int nvec = ch >> 2, ngroups = ch >> 5;
+  const int real = (int)min((int64_t)ch, max((int64_t)0, T - gbase));      // the chunk's elements from here on are padding, always
   const bool swz = nvec >= 128;                       // the swizzle permutes inside blocks of 128 vectors
   auto phys = [&](int v) { return swz ? v ^ ((((v >> 4) & 3) << 1) | (((v >> 6) & 1) * 9)) : v; };
-  for (int v = tid; v < nvec; v += nt) s4[phys(v)] = *reinterpret_cast<const f32x4*>(row + 4 * v);
+  for (int v = tid; v < nvec; v += nt) {
+    key4 e = key4{kPadKey, kPadKey, kPadKey, kPadKey};
+    if (4 * v < real) e = keys_of(*reinterpret_cast<const f32x4*>(from + 4 * v));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * v + i >= real) e[i] = kPadKey;
+    s4[phys(v)] = e;
+  }
   __syncthreads();
 
-  // one round trip: the stages `mask` (4: stride 4s, 2: stride 2s, 1: stride s, in vectors) of level k, and with
-  // in_vec (s = 1 only) the strides 2 and 1 inside the vectors
-  auto pass = [&](int64_t k, int s_log, int mask, bool in_vec) {
+  // one round trip: the stages `mask` (4: stride 4s, or with `mirror` the mirrored stage; 2: stride 2s, 1: stride s, in
+  // vectors), and with in_vec (s = 1 only) the strides 2 and 1 inside the vectors
+  auto pass = [&](bool mirror, int s_log, int mask, bool in_vec) {
     for (int g = tid; g < ngroups; g += nt) {
-      const int v0 = ((g >> s_log) << (3 + s_log)) + (g & ((1 << s_log) - 1));
-      f32x4 e[8];
-      bool asc[8];
+      const int off = g & ((1 << s_log) - 1), v0 = ((g >> s_log) << (3 + s_log)) + off;
+      if (4 * v0 >= real) continue;
+      const int up = mirror ? (1 << s_log) - 1 - 2 * off : 0;                // from an offset to its mirror image
+      key4 e[8];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const int v = v0 + (m << s_log);
-        e[m] = s4[phys(v)];
-        asc[m] = ((gbase + 4 * (int64_t)v) & k) == 0;
-      }
-      if (mask & 4) vec_stage<4>(e, asc);
-      if (mask & 2) vec_stage<2>(e, asc);
-      if (mask & 1) vec_stage<1>(e, asc);
-      if (in_vec) in_stages(e, asc, true);
+      for (int m = 0; m < 8; ++m) e[m] = s4[phys(v0 + (m << s_log) + (m >= 4 ? up : 0))];
+      if (mask & 4) { if (mirror) mirror_stage<8>(e); else vec_stage<4>(e); }
+      if (mask & 2) vec_stage<2>(e);
+      if (mask & 1) vec_stage<1>(e);
+      if (in_vec) in_stages(e);
 #pragma unroll
-      for (int m = 0; m < 8; ++m) s4[phys(v0 + (m << s_log))] = e[m];
+      for (int m = 0; m < 8; ++m) s4[phys(v0 + (m << s_log) + (m >= 4 ? up : 0))] = e[m];
     }
     __syncthreads();
   };
@@ -286,25 +319,18 @@ __global__ __launch_bounds__(512) void sw_sort_chunk_kernel(float* __restrict__ 
   int64_t k = k_first;
   if (k_first <= 2) {                                  // levels 2 .. 32 on 32 consecutive elements, one round trip
     for (int g = tid; g < ngroups; g += nt) {
-      f32x4 e[8];
-      bool asc[8];
+      if (32 * g >= real) continue;
+      key4 e[8];
 #pragma unroll
       for (int m = 0; m < 8; ++m) e[m] = s4[phys(8 * g + m)];
 #pragma unroll
-      for (int m = 0; m < 8; ++m) { cx_in<0, 1>(e[m], true); cx_in<2, 3>(e[m], false); }                // level 2
-#pragma unroll
-      for (int m = 0; m < 8; ++m) asc[m] = (m & 1) == 0;                                                  // level 4
-      in_stages(e, asc, true);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) asc[m] = (m & 2) == 0;                                                  // level 8
-      vec_stage<1>(e, asc); in_stages(e, asc, true);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) asc[m] = (m & 4) == 0;                                                  // level 16
-      vec_stage<2>(e, asc); vec_stage<1>(e, asc); in_stages(e, asc, true);
-      const bool a32 = ((gbase + 32 * (int64_t)g) & 32) == 0;                                             // level 32
-#pragma unroll
-      for (int m = 0; m < 8; ++m) asc[m] = a32;
-      vec_stage<4>(e, asc); vec_stage<2>(e, asc); vec_stage<1>(e, asc); in_stages(e, asc, true);
+      for (int m = 0; m < 8; ++m) {
+        cx_in<0, 1>(e[m]); cx_in<2, 3>(e[m]);                                                               // level 2
+        cx_in<0, 3>(e[m]); cx_in<1, 2>(e[m]); cx_in<0, 1>(e[m]); cx_in<2, 3>(e[m]);                        // level 4
+      }
+      mirror_stage<2>(e); in_stages(e);                                                                     // level 8
+      mirror_stage<4>(e); vec_stage<1>(e); in_stages(e);                                                    // level 16
+      mirror_stage<8>(e); vec_stage<2>(e); vec_stage<1>(e); in_stages(e);                                   // level 32
 #pragma unroll
       for (int m = 0; m < 8; ++m) s4[phys(8 * g + m)] = e[m];
     }
@@ -312,29 +338,36 @@ __global__ __launch_bounds__(512) void sw_sort_chunk_kernel(float* __restrict__ 
     k = 64;
   }
   for (; k <= k_last; k <<= 1) {
-    // vector-stride stages of this level inside the chunk: strides min(k, ch) / 8 ... 1
+    // vector-stride stages of this level inside the chunk: strides min(k, ch) / 8 ... 1; the first one is mirrored if the
+    // level's own first stage is inside the chunk
     int cur = 0;
     for (int64_t j = (k < ch ? k : (int64_t)ch) >> 3; j >= 1; j >>= 1) ++cur;
+    bool mirror = k <= ch;
     while (cur > 3) {                                  // leading stages: first the remainder, then threes
       const int g = (cur - 3) % 3 == 0 ? 3 : (cur - 3) % 3;
       // the eight vectors always span twice the top stride (s = top / 4); a remainder runs the upper stages only
-      pass(k, cur - 3, g == 3 ? 7 : (g == 2 ? 6 : 4), false);
+      pass(mirror, cur - 3, g == 3 ? 7 : (g == 2 ? 6 : 4), false);
       cur -= g;
+      mirror = false;
     }
-    pass(k, 0, cur == 3 ? 7 : (cur == 2 ? 3 : 1), true);
+    pass(false, 0, cur == 3 ? 7 : (cur == 2 ? 3 : 1), true);
   }
   if (ref == nullptr) {
-    for (int v = tid; v < nvec; v += nt) *reinterpret_cast<f32x4*>(row + 4 * v) = s4[phys(v)];
+    for (int v = tid; v < nvec; v += nt) {
+      const key4 e = s4[phys(v)];
+      *reinterpret_cast<f32x4*>(row + 4 * v) = f32x4{value_of(e[0]), value_of(e[1]), value_of(e[2]), value_of(e[3])};
+    }
     return;
   }
   const int seg = blockIdx.y;
   const float* rrow = ref + (int64_t)(ref_shared ? seg % L : seg) * Tpad;
   float sum = 0.0f;
-  for (int v = tid; 4 * (int64_t)v < T; v += nt) {   // the padding (+inf on both sides) is left out
-    const f32x4 a = s4[phys(v)], b = *reinterpret_cast<const f32x4*>(rrow + 4 * v);
+  for (int v = tid; 4 * (int64_t)v < T; v += nt) {   // the padding is left out
+    const key4 a = s4[phys(v)];
+    const f32x4 b = *reinterpret_cast<const f32x4*>(rrow + 4 * v);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (4 * (int64_t)v + i < T) sum += fabsf(a[i] - b[i]);
+      if (4 * (int64_t)v + i < T) sum += fabsf(value_of(a[i]) - b[i]);
   }
   sum = wave_sum(sum);
   __syncthreads();                                  // the row is no longer needed: reuse its first words
@@ -347,15 +380,14 @@ __global__ __launch_bounds__(512) void sw_sort_chunk_kernel(float* __restrict__ 
   }
 }
 
-// One stage (k, j) with j >= chunk size, straight on global memory.
+// One stage (k, j) with j >= chunk size, straight on global memory (mirrored if it is the level's first).
 __global__ __launch_bounds__(256) void sw_sort_global_kernel(float* __restrict__ P, int64_t Tpad, int64_t k, int64_t j) {
   const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (p >= (Tpad >> 1)) return;
   float* row = P + (int64_t)blockIdx.y * Tpad;
-  const int64_t i = 2 * p - (p & (j - 1));
-  const bool asc = (i & k) == 0;
-  const float a = row[i], b = row[i + j];
-  if ((a > b) == asc) { row[i] = b; row[i + j] = a; }
+  const int64_t i = 2 * p - (p & (j - 1)), o = 2 * j == k ? i ^ (k - 1) : i + j;
+  const float a = row[i], b = row[o];
+  if (key_of(a) > key_of(b)) { row[i] = b; row[o] = a; }
 }
 
 // Unfused W1 for rows longer than one chunk: one workgroup per segment, fixed order.
@@ -384,15 +416,6 @@ __global__ void sw_finalize_kernel(const float* __restrict__ w1, int n_claims, i
     results[c].metric_mask |= SV_M_SW;
     if (!(v <= tau)) results[c].flag = 1u;
   }
-}
-
-// A reference that is only known through its projections (kept up to date by sw_proj_ema_kernel): copy the L rows
-// into the slot the sort works on, with the padding behind the T samples set to +inf.
-__global__ __launch_bounds__(256) void sw_copy_pad_kernel(float* __restrict__ dst, const float* __restrict__ src, int64_t T, int64_t Tpad) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= Tpad) return;
-  const int64_t i = (int64_t)blockIdx.y * Tpad + t;
-  dst[i] = t < T ? src[i] : __builtin_huge_valf();
 }
 
 // The projection is linear, so the projections of m <- beta m + (1 - beta) mean_clean(x) are the same combination of
@@ -461,28 +484,24 @@ hipError_t launch_sw_project_with_ref(const void* X, int64_t stride, int count, 
 }
 
 hipError_t launch_sw_sort(float* P, int n_seg, int64_t T, int64_t Tpad, const float* ref, int ref_shared, int L, float* w1,
-                          int first_seg, hipStream_t st) {
+                          int first_seg, hipStream_t st, const float* src) {
   if (n_seg <= 0) return hipSuccess;
+  if (!src) src = P;
   const int ch = (int)min(Tpad, (int64_t)kSortChunkMax);
   const int nt = max(64, min(512, ch / 32));      // a thread holds 32 elements in the register passes
   const size_t lds = (size_t)ch * sizeof(float);
   const dim3 grid((unsigned)(Tpad / ch), (unsigned)n_seg);
   if (Tpad == ch) {
-    sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(P, Tpad, ch, 2, Tpad, ref, ref_shared, L, T, w1, first_seg);
+    sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(src, P, Tpad, ch, 2, Tpad, ref, ref_shared, L, T, w1, first_seg);
     return hipGetLastError();
   }
-  sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(P, Tpad, ch, 2, ch, nullptr, 0, L, T, nullptr, 0);
+  sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(src, P, Tpad, ch, 2, ch, nullptr, 0, L, T, nullptr, 0);
   for (int64_t k = 2 * (int64_t)ch; k <= Tpad; k <<= 1) {
     for (int64_t j = k >> 1; j >= ch; j >>= 1)
       sw_sort_global_kernel<<<dim3((unsigned)((Tpad / 2 + 255) / 256), (unsigned)n_seg), 256, 0, st>>>(P, Tpad, k, j);
-    sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(P, Tpad, ch, k, k, nullptr, 0, L, T, nullptr, 0);
+    sw_sort_chunk_kernel<<<grid, nt, lds, st>>>(P, P, Tpad, ch, k, k, nullptr, 0, L, T, nullptr, 0);
   }
   if (ref) sw_w1_kernel<<<n_seg, 256, 0, st>>>(P, ref, ref_shared, L, T, Tpad, w1, first_seg);
-  return hipGetLastError();
-}
-
-hipError_t launch_sw_copy_pad(float* dst, const float* src, int L, int64_t T, int64_t Tpad, hipStream_t st) {
-  sw_copy_pad_kernel<<<dim3((unsigned)((Tpad + 255) / 256), (unsigned)L), 256, 0, st>>>(dst, src, T, Tpad);
   return hipGetLastError();
 }
 

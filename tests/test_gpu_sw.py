@@ -189,3 +189,23 @@ def test_sw_against_projection_limits():
     with pytest.raises(sv.SVError):
         ver.sw_against_projection(big, torch.zeros((L, 32768), dtype=torch.float32, device="cuda"), dev(u, "bf16"), 1.0)
     ver.close()
+
+
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 127, 129, 1000, 4097, 6000, 16384, 16385, 40000])
+def test_sw_rows_of_every_kind_of_length(T):
+    """Directions that pick single features, so the projections are the features themselves and the distance is that of sorted
+    columns: rows shorter than one register block, ending inside one, of whole chunks, and longer than a chunk.  Ties and
+    values of both signs and zero included."""
+    import torch
+    import paper_2603_03592_amd as sv
+    D, L, n = 64, 32, 2
+    g = np.random.default_rng(T)
+    ref = np.round(g.standard_normal((T, D)) * 8) / 8
+    claims = np.round(g.standard_normal((n, T, D)) * 8 + 1) / 8
+    u = torch.eye(L, D, dtype=torch.bfloat16, device="cuda")
+    ver = sv.Verifier(si.StageDesc(1, 128, 4, 4, 128, mlp="gelu", norm="ln", rope=False, dtype="f32"), T, 64, sliced_w=True)
+    got = ver.sliced_wasserstein(dev(claims, "bf16"), dev(ref, "bf16"), u, 1e9).cpu().numpy()
+    ver.close()
+    a, b = np.sort(claims[:, :, :L], axis=1), np.sort(ref[:, :L], axis=0)
+    want = np.abs(a - b[None]).mean(axis=(1, 2))
+    np.testing.assert_allclose(got, want, rtol=2e-6)       # eighths below 2^4 are exact; fp32 sums of T of them in 64-way partial sums
