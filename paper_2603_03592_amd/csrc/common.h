@@ -126,6 +126,19 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
                         int claim_dtype, int ref_dtype, int64_t T, int D, uint32_t mask, const float* tau4,
                         int reduce, float* token_scores, sv_result* results, ScorePartial* scratch,
                         int64_t scratch_elems, hipStream_t st, uint32_t skip = 0, float* sum_out = nullptr);
+// the scores and the flag from the records of one score pass, `tiles` per submission
+hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
+                                 int reduce, sv_result* results, hipStream_t st);
+// signal_pass.hip: statistics, sum and projections of up to 16 bf16 submissions against one fp32 reference in one pass.  Writes
+// ceil(T / 16) records per submission, sum_out as the score pass does and P[n][L][Tpad] without its padding.
+bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, const float* m, const void* U, int L, int64_t T, int D);
+hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,
+                              uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st);
+// api.hip: what sv_score_and_sum and sv_sw_against_projection do together for the verifier loop, over one pass of the submissions;
+// SV_EUNSUPPORTED (and nothing enqueued) where they have to be called one after the other
+sv_status check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, const float* m, int64_t T, int D, uint32_t metric_mask,
+                        const float* tau4, sv_result* results, const uint8_t* skip_host, float* sum_out, const void* directions, int L,
+                        const float* ref_proj, float* claim_proj_out, float* sw_out, hipStream_t st);
 // api.hip: error text for entry points without a context (sv_last_error(NULL) returns it on the same thread)
 void set_global_error(const char* fmt, ...);
 // With sum_out the score pass also writes sum_out[t, :] = sum of the submissions whose bit in `skip` is clear (fp32, index

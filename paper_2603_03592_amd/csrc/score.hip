@@ -456,6 +456,14 @@ __global__ __launch_bounds__(256) void ema_update_kernel(float* __restrict__ m, 
 
 }  // namespace
 
+hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
+                                 int reduce, sv_result* results, hipStream_t st) {
+  Tau4 tau;
+  for (int i = 0; i < 4; ++i) tau.v[i] = tau4 ? tau4[i] : 0.0f;
+  hipLaunchKernelGGL(score_finalize_kernel, dim3(n_claims), dim3(tiles <= 128 ? 64 : 256), 0, st, partials, tiles, T, D, mask, tau, reduce, results);
+  return hipGetLastError();
+}
+
 bool score_sum_supported(int n_claims, int64_t ref_stride, int claim_dtype, int D) {
   const int64_t row_bytes = (int64_t)D * (claim_dtype == SV_BF16 ? 2 : 4);
   return n_claims >= 1 && n_claims <= kGroupMax && ref_stride == 0 && row_bytes % 2048 == 0;
@@ -479,8 +487,6 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
   int64_t per_launch = scratch_elems / tiles;
   if (per_launch < 1) return hipErrorInvalidValue;
   if (per_launch * (tiles + 7) > 0x7fffffffLL) per_launch = 0x7fffffffLL / (tiles + 7);
-  Tau4 tau;
-  for (int i = 0; i < 4; ++i) tau.v[i] = tau4 ? tau4[i] : 0.0f;
   const int64_t csz = claim_dtype == SV_BF16 ? 2 : 4, rsz = ref_dtype == SV_BF16 ? 2 : 4;
   for (int64_t c0 = 0; c0 < n_claims; c0 += per_launch) {
     const int nc = (int)((n_claims - c0 < per_launch) ? (n_claims - c0) : per_launch);
@@ -515,8 +521,8 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
 #undef SV_LAUNCH_PARTS
 #undef SV_LAUNCH_PARTS3
 #undef SV_LAUNCH_PARTS5
-      hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(tiles <= 128 ? 64 : 256), 0, st, scratch, (int)tiles, T, D, mask, tau, reduce,
-                         results + c0);
+      hipError_t e = launch_score_finalize(scratch, nc, (int)tiles, T, D, mask, tau4, reduce, results + c0, st);
+      if (e != hipSuccess) return e;
       continue;
     }
     const int64_t tiles4 = (T + 3) / 4;                // up to one record of 16 tokens per CU: smaller ones (see the kernel)
@@ -545,8 +551,8 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     else SV_LAUNCH_SCORE(float, float);
 #undef SV_LAUNCH_SCORE
 #undef SV_LAUNCH_SCORE3
-    hipLaunchKernelGGL(score_finalize_kernel, dim3(nc), dim3(tpc <= 128 ? 64 : 256), 0, st, scratch, tpc, T, D, mask, tau, reduce,
-                       results + c0);
+    hipError_t e = launch_score_finalize(scratch, nc, tpc, T, D, mask, tau4, reduce, results + c0, st);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }

@@ -1,7 +1,8 @@
 // Alg. momentum_verification end to end for the verifiers of p pipeline stages with d workers each
 // (worker r of every stage belongs to data-parallel pipe r).  The device work -- the statistics of every
 // worker's signal against the stage's EMA, the gradient replacement, the EMA update over the clean set --
-// goes through the library's own C entry points on the caller's stream; the decisions in between are the
+// goes through the library's own entry points (the checks of a call through one pass over the signals, check_signals, where
+// the shape allows it) on the caller's stream; the decisions in between are the
 // host-side policy (sv_policy_*).  Each forward / backward call therefore waits once for the stream: the
 // few scalars per worker have to reach the host before the policy can decide who enters the EMA.
 #include <stdarg.h>
@@ -13,7 +14,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "stageverify.h"
+#include "common.h"
 
 struct sv_sentinel {
   sv_ctx* ctx = nullptr;
@@ -70,7 +71,14 @@ sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, const float* 
   const int64_t stride = c.T * c.D;
   const float inf = std::numeric_limits<float>::infinity();
   const float tau[4] = {inf, inf, inf, inf};      // nothing is decided on the device here: the fences live in the policy
-  sv_status sum_st = s->sum_dev ? sv_score_and_sum(s->ctx, signals, stride, d, m, dtype, SV_F32, c.T, c.D, c.metric_mask & 15u, tau,
+  // statistics, sum and projections in one pass over the signals where the shape allows it
+  sv_status one = SV_EUNSUPPORTED;
+  if ((c.metric_mask & SV_M_SW) && pm && s->sum_dev) {
+    one = sv::check_signals(s->ctx, signals, stride, d, dtype, m, c.T, c.D, c.metric_mask & 15u, tau, s->res_dev, skip, s->sum_dev, c.directions, c.n_dirs,
+                            pm, s->cproj, s->sw_dev, st);
+    if (one != SV_OK && one != SV_EUNSUPPORTED) { set_err(s, "the loop's pass: %s", sv_last_error(s->ctx)); return one; }
+  }
+  sv_status sum_st = one == SV_OK ? SV_OK : s->sum_dev ? sv_score_and_sum(s->ctx, signals, stride, d, m, dtype, SV_F32, c.T, c.D, c.metric_mask & 15u, tau,
                                                    SV_REDUCE_GLOBAL, nullptr, s->res_dev, skip, s->sum_dev, st)
                                 : SV_EUNSUPPORTED;
   *summed = sum_st == SV_OK;
@@ -81,7 +89,8 @@ sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, const float* 
   SN_HIP(s, hipMemcpyAsync(s->res_host, s->res_dev, sizeof(sv_result) * d, hipMemcpyDeviceToHost, st));
   if (c.metric_mask & SV_M_SW) {
     if (pm) ++s->n_sw_carried;
-    if (pm)
+    if (one == SV_OK) {
+    } else if (pm)
       SN_SV(s, sv_sw_against_projection(s->ctx, signals, stride, d, dtype, c.T, c.D, c.directions, c.n_dirs, pm, s->cproj, inf, s->sw_dev,
                                         nullptr, st));
     else
