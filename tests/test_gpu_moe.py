@@ -360,3 +360,11 @@ def test_moe_descriptor_checks():
     assert sv.sv_check_desc(dataclasses.replace(ok, top_k=5))[0] == 1                 # top_k > n_experts
     assert sv.sv_check_desc(dataclasses.replace(ok, n_experts=17, top_k=2))[0] == 2   # more experts than the kernels hold
     assert sv.sv_check_desc(dataclasses.replace(ok, mlp="gelu"))[0] == 2
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("E,K", [(3, 3), (5, 2), (8, 4), (8, 5), (8, 7), (9, 1), (16, 6), (16, 8)])
+def test_every_number_of_experts_per_token(E, K, dtype):
+    """The routing and combining kernels are made per K and for up to 8 or 16 experts; widths of more and of less than one trip."""
+    run_constructed(si.StageDesc(1, 576 if E > 8 else 256, 9 if E > 8 else 4, 1, 128, n_experts=E, top_k=K, dtype=dtype), 4, 40, seed=17, backward=True,
+                    grad_std=1.0 if dtype == "f32" else 1e-3)
