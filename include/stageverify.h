@@ -433,6 +433,13 @@ sv_status sv_profile_select(sv_ctx *ctx, uint64_t op_mask);
 sv_status sv_gemm_bf16(const void *A, int64_t lda, const void *B, int64_t ldb, int32_t b_is_kn, void *C, int64_t ldc,
                        int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
 
+/* Test aid, no device call: what the residual product C[M,N] = A[M,K] * B[N,K]^T + R of a block runs on, with ws_floats
+ * floats of scratch for partial products.  row_sums: the next norm runs inside the product behind it, so the rows' sums of
+ * squares are wanted from this one.  *leaves_row_sums: will the norm rely on this product for them (else it reads the rows itself);
+ * *tile: 1 = 256x256, 2 = 128x128, 3 = 256x128, 4 = 64x128, 5 = 64x64 (0: the vector kernel); *runs: k in that many runs. */
+sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32_t row_sums, int32_t *leaves_row_sums,
+                       int32_t *tile, int32_t *runs);
+
 #ifdef __cplusplus
 }
 #endif

@@ -153,6 +153,8 @@ def _load():
     L.sv_prepare_weights.argtypes = [vp, C.POINTER(BlockWeightsC), vp]
     L.sv_gemm_bf16.restype = C.c_int
     L.sv_gemm_bf16.argtypes = [vp, i64, vp, i64, i32, vp, i64, i32, i32, i32, i32, vp]
+    L.sv_gemm_plan.restype = C.c_int
+    L.sv_gemm_plan.argtypes = [i32, i32, i32, i64, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     return L
 
 
@@ -171,6 +173,15 @@ def sv_gemm_bf16(a, b, b_is_kn: bool = False, tile: int = 0, out=None):
     if st != SV_OK:
         raise SVError(st, "sv_gemm_bf16")
     return out
+
+
+def sv_gemm_plan(M: int, N: int, K: int, ws_floats: int = 0, row_sums: bool = False):
+    """(leaves_row_sums, tile, runs) of the residual product C[M,N] = A[M,K] B[N,K]^T + R; no device call."""
+    leaves, tile, runs = C.c_int32(), C.c_int32(), C.c_int32()
+    st = lib.sv_gemm_plan(M, N, K, ws_floats, int(row_sums), C.byref(leaves), C.byref(tile), C.byref(runs))
+    if st != SV_OK:
+        raise SVError(st, "sv_gemm_plan")
+    return bool(leaves.value), tile.value, runs.value
 
 
 def _policy_cfg(c=5, t_forgive=100, window=100, k0=1.5, alpha=0.01, grow=1.1, shrink=0.9, n_max=10, min_dist_mult=0.0,

@@ -333,6 +333,14 @@ hipEvent_t take_event(sv_ctx* c) {
 inline char* at(void* p, int64_t elems, int es) { return (char*)p + elems * es; }
 inline const char* at(const void* p, int64_t elems, int es) { return (const char*)p + elems * es; }
 
+// Ask product g for its rows' sums of squares (planes of ld floats) if the kernel it runs on can leave them.
+bool want_rowsq(GemmArgs& g, float* rowsq, int ld) {
+  g.rowsq = rowsq; g.rowsq_ld = ld;
+  if (mfma_gemm_emits_rowsq(g)) return true;
+  g.rowsq = nullptr; g.rowsq_ld = 0;
+  return false;
+}
+
 hipError_t gemm(sv_ctx* c, const GemmArgs& a, hipStream_t st) {
   if (c->d.dtype == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && mfma_gemm_supported(a)) {
     GemmArgs g = a;
@@ -447,9 +455,7 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
   auto leave_rowsq = [&](GemmArgs& g) {
     c->rowsq_of = nullptr;
     if (!fuse) return;
-    g.rowsq = c->rowsq; g.rowsq_ld = T;                // planes of T floats
-    if (dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && mfma_gemm_emits_rowsq(g)) c->rowsq_of = g.C;
-    else { g.rowsq = nullptr; g.rowsq_ld = 0; }
+    if (dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && want_rowsq(g, c->rowsq, T)) c->rowsq_of = g.C;
   };
 
   const double Td = T, attn_flop = (d.causal ? 2.0 : 4.0) * B * d.n_heads * (double)S * S * c->hd;
@@ -1129,6 +1135,17 @@ sv_status sv_gemm_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, i
   g.b_is_kn = b_is_kn ? 1 : 0; g.epi = EPI_STORE; g.C = Cout; g.ldc = ldc;
   if (N % 128 || !mfma_gemm_supported(g) || ((tile == 1 || tile == 3) && N % 256) || (tile == 4 && b_is_kn)) return SV_EUNSUPPORTED;
   return mfma_gemm(g, (hipStream_t)stream, tile) == hipSuccess ? SV_OK : SV_EHIP;
+}
+
+sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32_t row_sums, int32_t* leaves_row_sums, int32_t* tile, int32_t* runs) {
+  if (M < 1 || N < 1 || K < 1 || ws_floats < 0 || !leaves_row_sums || !tile || !runs) return SV_EINVAL;
+  alignas(16) static float some[4];                      // the plan looks at alignments, not at what is there
+  GemmArgs g = nt(M, N, K, some, K, some, some, N, EPI_RESID);
+  g.R = some; g.ldr = N;
+  *leaves_row_sums = row_sums && want_rowsq(g, some, M);                        // asked and launched as in block_forward
+  g.split_ws = ws_floats ? some : nullptr; g.split_ws_floats = ws_floats;
+  mfma_gemm_plan(g, tile, runs);
+  return SV_OK;
 }
 
 }  // extern "C"

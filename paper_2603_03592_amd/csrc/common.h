@@ -275,6 +275,7 @@ hipError_t launch_moe_combine_bwd(const void* dy, const void* yp, const void* dx
 // gemm_mfma.hip: bf16 only; returns hipErrorInvalidValue if the shape is outside its limits
 bool mfma_gemm_supported(const GemmArgs& a);
 bool mfma_gemm_emits_rowsq(const GemmArgs& a);          // would mfma_gemm(a, st) fill a.rowsq?
+void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs);   // what mfma_gemm(a, st) would run on (numbers of sv_gemm_plan)
 int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats);   // the GemmArgs::runs of an [N,K] product before a router
 hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile = 0);   // tile: 0 auto, 1 = 256x256, 2 = 128x128, 3 = 256x128, 4 = 64x128
 

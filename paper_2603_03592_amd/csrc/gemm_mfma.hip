@@ -1223,6 +1223,8 @@ bool fits_mid(const GemmArgs& a) {        // buffer descriptors over a tile's ro
 
 bool summed_runs(const GemmArgs& a) { return a.runs[0] > 1 || a.runs[1] > 1 || a.runs[2] > 1; }
 
+// Asked twice for a product that may leave row sums, once to know whether it will (mfma_gemm_emits_rowsq) and once to launch it:
+// with a.rowsq set the answer does not depend on the scratch, which only runs of k use.
 Plan plan_gemm(const GemmArgs& a) {
   if (summed_runs(a)) return Plan{kTile128, 1};
   const bool dual = a.epi == EPI_SWIGLU;
@@ -1237,7 +1239,7 @@ Plan plan_gemm(const GemmArgs& a) {
     const TileCost& t = kTileCost[k];
     const int nout = dual ? t.bn / 2 : t.bn;
     const int64_t tiles = (int64_t)((a.M + t.bm - 1) / t.bm) * ((a.N + nout - 1) / nout);
-    const bool splits = a.split_ws && !a.runs[0] && k != kTile256 && !dual && !a.tile_group;
+    const bool splits = a.split_ws && !a.runs[0] && !a.rowsq && k != kTile256 && !dual && !a.tile_group;
     for (int runs = 1; runs <= (splits ? 8 : 1); ++runs) {
       if (runs > 1 && (slices < 4 * runs || (int64_t)runs * a.M * a.N > a.split_ws_floats)) break;
       const double rounds = (double)((tiles * runs + (int64_t)cus - 1) / (int64_t)cus);
@@ -1285,6 +1287,7 @@ hipError_t launch_runs(const GemmArgs& a, const Plan& p, hipStream_t st) {
 
 template <int EPI>
 hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
+  if (a.rowsq && (p.kind != kTile256 || p.runs > 1)) return hipErrorInvalidValue;    // somebody will read them: mfma_gemm_emits_rowsq first
   if (summed_runs(a)) {
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE) return launch_mid<4, 2, 1, 2, 4, EPI, false, false, true>(a, 1, st);
     return hipErrorInvalidValue;
@@ -1320,6 +1323,14 @@ int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats) {
 
 bool mfma_gemm_emits_rowsq(const GemmArgs& a) {
   return a.rowsq && a.epi == EPI_RESID && !a.tile_group && mfma_gemm_supported(a) && plan_gemm(a).kind == kTile256;
+}
+
+void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs) {
+  constexpr int number[kTileKinds] = {1, 3, 2, 4, 5};
+  *tile = 0; *runs = 1;
+  if (a.b_is_kn || !mfma_gemm_supported(a)) return;
+  const Plan p = plan_gemm(a);
+  *tile = number[p.kind]; *runs = p.runs;
 }
 
 bool mfma_gemm_supported(const GemmArgs& a) {
