@@ -459,8 +459,8 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
   };
 
   const double Td = T, attn_flop = (d.causal ? 2.0 : 4.0) * B * d.n_heads * (double)S * S * c->hd;
-  // Before a router the sums keep their cut (mfma_settled_runs), as one product where the widths allow it (whole) or as one per
-  // matrix, rotated from bf16 there.
+  // Before a router, of this block or a later one, the sums keep their cut (mfma_settled_runs): q | k | v as one product where
+  // the widths allow it (whole) or as one per matrix, rotated from bf16 there.
   const bool routed = c->moe && dt == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS) && D % 64 == 0;
   bool whole = true;
   auto settle_qkv = [&](GemmArgs& f) {
@@ -471,6 +471,9 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
     f.runs[0] = whole ? r : mfma_settled_runs(T, c->Dq, D, ws);
     f.runs[1] = f.runs[2] = whole ? r : mfma_settled_runs(T, c->Dkv, D, ws);
     f.rope_bf16 = !whole;
+  };
+  auto settle_resid = [&](GemmArgs& f) {                  // a product that writes the residual stream a router reads
+    if (routed && D % 128 == 0 && f.seg[0].K % 64 == 0) f.runs[0] = mfma_settled_runs(T, D, f.seg[0].K, (int64_t)c->split_ws_floats);
   };
   bool fused1 = false;
   if (fuse) {
@@ -519,7 +522,7 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
   {
     GemmArgs g = nt(T, D, c->Dq, o, c->Dq, w.wo, x1, D, EPI_RESID);
     g.R = x; g.ldr = D;
-    if (routed && D % 128 == 0 && c->Dq % 64 == 0) g.runs[0] = mfma_settled_runs(T, D, c->Dq, (int64_t)c->split_ws_floats);
+    settle_resid(g);
     if (fused2) leave_rowsq(g); else c->rowsq_of = nullptr;
     SV_OP(c, SV_OP_GEMM_O, 2.0 * Td * D * c->Dq, st, gemm(c, g, st));
   }
@@ -564,6 +567,7 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
       SV_OP(c, SV_OP_GEMM_GATEUP, 4.0 * Td * Fs * D, st, gemm(c, g, st));
       GemmArgs h = nt(T, D, Fs, c->act, Fs, w.ws_down, y, D, EPI_RESID);
       h.R = x1; h.ldr = D;
+      if (l + 1 < d.n_blocks) settle_resid(h);           // the next block routes by it
       SV_OP(c, SV_OP_GEMM_DOWN, 2.0 * Td * D * Fs, st, gemm(c, h, st));
       base = y;
     }
