@@ -428,6 +428,7 @@ sv_status sv_profile_select(sv_ctx *ctx, uint64_t op_mask);
  * the block recompute uses (fp32 accumulation, bf16 result).  b_is_kn = 0: B stored [N,K]
  * (C = A B^T); 1: B stored [K,N] (C = A B).  tile, as rows x columns: 0 = automatic, 1 = 256x256, 2 = 128x128,
  * 3 = 256x128 (256x256 when B is [K,N]; N % 256), 4 = 64x128 (B stored [N,K] only).
+ * Rows so far apart that 256 of them are beyond 32-bit offsets (strides of 2^23 elements, of 2^22 in C) take the vector kernel.
  * Returns SV_EUNSUPPORTED for shapes outside the kernels' limits (N % 128, K % 64, 16-byte
  * aligned rows).  No context is needed.                                                      */
 sv_status sv_gemm_bf16(const void *A, int64_t lda, const void *B, int64_t ldb, int32_t b_is_kn, void *C, int64_t ldc,

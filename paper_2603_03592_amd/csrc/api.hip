@@ -1137,7 +1137,8 @@ sv_status sv_gemm_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, i
   GemmArgs g; memset(&g, 0, sizeof(g));
   g.M = M; g.N = N; g.nseg = 1; g.seg[0] = GemmSeg{A, lda, B, ldb, K};
   g.b_is_kn = b_is_kn ? 1 : 0; g.epi = EPI_STORE; g.C = Cout; g.ldc = ldc;
-  if (N % 128 || !mfma_gemm_supported(g) || ((tile == 1 || tile == 3) && N % 256) || (tile == 4 && b_is_kn)) return SV_EUNSUPPORTED;
+  if (N % 128 || !mfma_gemm_shape(g) || ((tile == 1 || tile == 3) && N % 256) || (tile == 4 && b_is_kn)) return SV_EUNSUPPORTED;
+  if (!mfma_gemm_reaches(g, tile)) return plain_gemm(g, SV_BF16, (hipStream_t)stream) == hipSuccess ? SV_OK : SV_EHIP;
   return mfma_gemm(g, (hipStream_t)stream, tile) == hipSuccess ? SV_OK : SV_EHIP;
 }
 

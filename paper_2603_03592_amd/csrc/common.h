@@ -273,7 +273,9 @@ hipError_t launch_moe_combine_bwd(const void* dy, const void* yp, const void* dx
                                   int score_kind, int norm, const MoeRoute& r, int accumulate, void* dn, int dtype, hipStream_t st);
 
 // gemm_mfma.hip: bf16 only; returns hipErrorInvalidValue if the shape is outside its limits
-bool mfma_gemm_supported(const GemmArgs& a);
+bool mfma_gemm_shape(const GemmArgs& a);                 // sizes, alignments and epilogue are within its limits
+bool mfma_gemm_reaches(const GemmArgs& a, int tile);     // ... and the row strides too, which the direct-to-LDS kernels address with 32 bits
+bool mfma_gemm_supported(const GemmArgs& a);             // both, for the automatic choice
 bool mfma_gemm_emits_rowsq(const GemmArgs& a);          // would mfma_gemm(a, st) fill a.rowsq?
 void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs);   // what mfma_gemm(a, st) would run on (numbers of sv_gemm_plan)
 int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats);   // the GemmArgs::runs of an [N,K] product before a router

@@ -1214,6 +1214,7 @@ bool fits_256(const GemmArgs& a) {        // the persistent 256x256 kernel has w
   if (a.N % (a.epi == EPI_SWIGLU ? 128 : 256)) return false;
   for (int j = 0; j < a.nbcol; ++j)
     if (a.ncol[j] % 256) return false;
+  if (256 * a.ldc * 2 >= (int64_t)1 << 31 || 256 * a.ldr * 2 >= (int64_t)1 << 31) return false;   // a tile's outputs by 32-bit byte offsets
   return !(a.epi == EPI_SWIGLU && a.ldc % 8);            // its epilogue stores 16 bytes per lane
 }
 
@@ -1333,7 +1334,7 @@ void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs) {
   *tile = number[p.kind]; *runs = p.runs;
 }
 
-bool mfma_gemm_supported(const GemmArgs& a) {
+bool mfma_gemm_shape(const GemmArgs& a) {
   if (a.M < 1 || a.nseg < 1 || a.nseg > 3) return false;
   if (a.rscale && (a.tile_group || (a.epi != EPI_STORE && a.epi != EPI_GELU && a.epi != EPI_SWIGLU && a.epi != EPI_ROPE))) return false;
   if (a.rowsq && (a.epi != EPI_RESID || a.rowsq_ld < a.M)) return false;
@@ -1366,8 +1367,15 @@ bool mfma_gemm_supported(const GemmArgs& a) {
     const GemmSeg& g = a.seg[s];
     if (g.K < BK || g.K % BK || g.lda % 8 || g.ldb % 8 || !aligned16(g.A) || !aligned16(g.B)) return false;
   }
-  return a.b_is_kn || (panels_fit(a) && (fits_256(a) || fits_mid(a)));
+  return true;
 }
+
+bool mfma_gemm_reaches(const GemmArgs& a, int tile) {
+  if (a.b_is_kn) return true;                            // 64-bit addresses
+  return panels_fit(a) && ((tile <= 1 && fits_256(a)) || (tile != 1 && fits_mid(a)));
+}
+
+bool mfma_gemm_supported(const GemmArgs& a) { return mfma_gemm_shape(a) && mfma_gemm_reaches(a, 0); }
 
 hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile) {
   if (!mfma_gemm_supported(a)) return hipErrorInvalidValue;

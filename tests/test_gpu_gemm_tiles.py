@@ -37,6 +37,30 @@ def test_product_refuses_what_it_refused():
             sv.sv_gemm_bf16(dev(np.zeros((130, k), np.float32), "bf16"), dev(np.zeros((n, k), np.float32), "bf16"))
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("far,ld", [("a", 1 << 23), ("b", 1 << 23), ("c", 1 << 22), ("c", 1 << 23)], ids=["a", "b", "c22", "c23"])
+def test_rows_too_far_apart_for_32_bit_offsets(far, ld, tile):
+    """Operands and results that are narrow views of very wide matrices."""
+    import torch
+    import paper_2603_03592_amd as sv
+    M, N, K = 70, 256, 128
+    g = np.random.default_rng(5)
+    a = si.round_to_bf16(g.standard_normal((M, K)).astype(np.float32))
+    b = si.round_to_bf16(g.standard_normal((N, K)).astype(np.float32))
+
+    def view(x, rows, cols, is_far):
+        base = torch.zeros((rows - 1) * (ld if is_far else cols) + cols, dtype=torch.bfloat16, device="cuda")
+        v = base.as_strided((rows, cols), (ld if is_far else cols, 1))
+        if x is not None:
+            v.copy_(dev(x, "bf16"))
+        return v
+
+    got = host(sv.sv_gemm_bf16(view(a, M, K, far == "a"), view(b, N, K, far == "b"), tile=tile, out=view(None, M, N, far == "c")))
+    want = a.astype(np.float64) @ b.astype(np.float64).T
+    bound = 2.0 ** -8 * np.abs(want) + 4 * K * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T)
+    assert (np.abs(got - want) <= bound).all()
+
+
 # widths that are multiples of 64 (or 8, for the MLP) but not of 128; one kv head of 64 columns; fewer rows than a tile and ragged
 # row tiles; a sequence shorter than a tile (RoPE positions wrap several times inside it)
 EDGES = {
