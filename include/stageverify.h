@@ -434,6 +434,13 @@ sv_status sv_profile_select(sv_ctx *ctx, uint64_t op_mask);
 sv_status sv_gemm_bf16(const void *A, int64_t lda, const void *B, int64_t ldb, int32_t b_is_kn, void *C, int64_t ldc,
                        int32_t M, int32_t N, int32_t K, int32_t tile, void *stream);
 
+/* Test aid: the same product with B stored [N,K] and N any multiple of 8, on one tile (2 = 128x128, 3 = 256x128, 4 = 64x128,
+ * 5 = 64x64) and with its k slices of 64 cut into `runs` contiguous runs whose fp32 sums are added in order.  ws (runs * M * N
+ * floats): every run in workgroups of its own, partial products in ws.  ws NULL: the runs one after the other in one workgroup
+ * (tile 2 only), the same bits; with runs = 1 the whole product on any of the tiles.           */
+sv_status sv_gemm_bf16_runs(const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc, int32_t M, int32_t N,
+                            int32_t K, int32_t tile, int32_t runs, float *ws, int64_t ws_floats, void *stream);
+
 /* Test aid, no device call: what the residual product C[M,N] = A[M,K] * B[N,K]^T + R of a block runs on, with ws_floats
  * floats of scratch for partial products.  row_sums: the next norm runs inside the product behind it, so the rows' sums of
  * squares are wanted from this one.  *leaves_row_sums: will the norm rely on this product for them (else it reads the rows itself);

@@ -153,6 +153,8 @@ def _load():
     L.sv_prepare_weights.argtypes = [vp, C.POINTER(BlockWeightsC), vp]
     L.sv_gemm_bf16.restype = C.c_int
     L.sv_gemm_bf16.argtypes = [vp, i64, vp, i64, i32, vp, i64, i32, i32, i32, i32, vp]
+    L.sv_gemm_bf16_runs.restype = C.c_int
+    L.sv_gemm_bf16_runs.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp, i64, vp]
     L.sv_gemm_plan.restype = C.c_int
     L.sv_gemm_plan.argtypes = [i32, i32, i32, i64, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     return L
@@ -172,6 +174,19 @@ def sv_gemm_bf16(a, b, b_is_kn: bool = False, tile: int = 0, out=None):
                           M, N, K, tile, torch.cuda.current_stream().cuda_stream)
     if st != SV_OK:
         raise SVError(st, "sv_gemm_bf16")
+    return out
+
+
+def sv_gemm_bf16_runs(a, b, tile: int, runs: int, apart: bool):
+    """C = a @ b.T on one tile with k in `runs` runs: each in workgroups of its own (apart), else one after the other in one."""
+    import torch
+    (M, K), N = a.shape, b.shape[0]
+    out = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
+    ws = torch.empty(runs * M * N, dtype=torch.float32, device=a.device) if apart else None
+    st = lib.sv_gemm_bf16_runs(a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0), out.data_ptr(), out.stride(0), M, N, K, tile, runs,
+                               ws.data_ptr() if apart else None, runs * M * N if apart else 0, torch.cuda.current_stream().cuda_stream)
+    if st != SV_OK:
+        raise SVError(st, "sv_gemm_bf16_runs")
     return out
 
 

@@ -1142,6 +1142,16 @@ sv_status sv_gemm_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, i
   return mfma_gemm(g, (hipStream_t)stream, tile) == hipSuccess ? SV_OK : SV_EHIP;
 }
 
+sv_status sv_gemm_bf16_runs(const void* A, int64_t lda, const void* B, int64_t ldb, void* Cout, int64_t ldc, int32_t M, int32_t N, int32_t K,
+                            int32_t tile, int32_t runs, float* ws, int64_t ws_floats, void* stream) {
+  if (!A || !B || !Cout || M < 1 || N < 1 || K < 1) return SV_EINVAL;
+  GemmArgs g = nt(M, N, K, A, lda, B, Cout, ldc, EPI_STORE);
+  g.seg[0].ldb = ldb;
+  g.split_ws = ws; g.split_ws_floats = ws ? ws_floats : 0;
+  const hipError_t e = mfma_gemm_runs(g, tile, runs, (hipStream_t)stream);
+  return e == hipSuccess ? SV_OK : e == hipErrorInvalidValue ? SV_EUNSUPPORTED : SV_EHIP;
+}
+
 sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32_t row_sums, int32_t* leaves_row_sums, int32_t* tile, int32_t* runs) {
   if (M < 1 || N < 1 || K < 1 || ws_floats < 0 || !leaves_row_sums || !tile || !runs) return SV_EINVAL;
   alignas(16) static float some[4];                      // the plan looks at alignments, not at what is there

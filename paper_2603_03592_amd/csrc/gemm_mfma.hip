@@ -1412,4 +1412,17 @@ hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile) {
   }
 }
 
+hipError_t mfma_gemm_runs(const GemmArgs& a, int tile, int runs, hipStream_t st) {
+  constexpr int kind[6] = {-1, -1, kTile128, kTile256x128, kTile64x128, kTile64};
+  if (a.epi != EPI_STORE || a.b_is_kn || a.nseg != 1 || a.tile_group || a.rowsq || tile < 2 || tile > 5 || runs < 1 || runs > a.seg[0].K / BK ||
+      !mfma_gemm_supported(a) || !fits_mid(a))
+    return hipErrorInvalidValue;
+  if (a.split_ws) return (int64_t)runs * a.M * a.N <= a.split_ws_floats ? launch_runs<EPI_STORE>(a, Plan{kind[tile], runs}, st) : hipErrorInvalidValue;
+  if (runs == 1) return launch_tile<EPI_STORE, false>(a, kind[tile], st);
+  if (tile != 2) return hipErrorInvalidValue;
+  GemmArgs g = a;
+  g.runs[0] = runs;
+  return mfma_gemm(g, st);
+}
+
 }  // namespace sv

@@ -23,3 +23,18 @@ def test_row_sums_are_promised_only_by_products_that_write_them(N, K):
             promised += leaves
         assert not sv.sv_gemm_plan(M, N, K, SCRATCH)[0]
     assert promised > 0 or N % 256 or N < 2048
+
+
+def test_the_stage_tests_reach_products_whole_and_over_runs():
+    """The stages of test_gpu_gemm_tiles.py are there for the epilogues behind both kinds of launch: if another price moves them, this
+    fails and they need other sizes."""
+    def ws(T, D, F):
+        return min(SCRATCH, 8 * T * max(D, F))
+    assert sv.sv_gemm_plan(130, 448, 3200, ws(130, 448, 3200))[2] > 1              # gelu_rms_runs, down-projection
+    assert sv.sv_gemm_plan(301, 960, 1088, ws(301, 960, 1088))[2] == 1             # ragged_960
+    assert sv.sv_gemm_plan(130, 192, 200, ws(130, 192, 200)) == (False, 0, 1)      # odd_mlp_width: k is no multiple of 64
+
+
+def test_every_tile_serves_some_size():
+    seen = {sv.sv_gemm_plan(M, N, K, SCRATCH)[1] for M in (64, 512, 2331, 4096, 8192) for N in (960, 1024, 2048, 4096) for K in (512, 2048, 14336)}
+    assert seen == {1, 2, 3, 4, 5}

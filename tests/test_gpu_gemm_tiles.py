@@ -11,6 +11,17 @@ from test_gpu_moe import run_constructed
 from test_gpu_stage import run_stage
 
 
+def assert_one_rounding(got, a, b):
+    """bf16 keeps 8 significant bits (7 of them stored), so rounding moves a result by at most half of 2^-7 of itself; before it stands
+    the fp32 sum, whose K additions are each off by at most 2^-24 of a partial sum <= sum |a b|, with 1 + 2^-8 for the rounding of that
+    error."""
+    a, b = a.astype(np.float64), b.astype(np.float64)
+    want, K = a @ b.T, a.shape[1]
+    bound = 2.0 ** -8 * np.abs(want) + (1 + 2.0 ** -8) * K * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)
+    worst = np.abs(got - want) / bound
+    assert worst.max() <= 1.0, (worst.max(), np.unravel_index(worst.argmax(), worst.shape))
+
+
 @pytest.mark.parametrize("tile", [0, 2, 3, 4], ids=["auto", "128x128", "256x128", "64x128"])
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (63, 256, 128), (64, 256, 192), (129, 512, 256), (255, 256, 320), (257, 768, 576), (520, 256, 2304)])
 def test_product_at_the_edges_of_the_tiles(tile, M, N, K):
@@ -25,9 +36,42 @@ def test_product_at_the_edges_of_the_tiles(tile, M, N, K):
     b = si.round_to_bf16(g.standard_normal((N, K)).astype(np.float32))
     got = host(sv.sv_gemm_bf16(dev(a, "bf16"), dev(b, "bf16"), tile=tile))
     want = a.astype(np.float64) @ b.astype(np.float64).T
-    # one bf16 rounding (2^-9) of a sum whose fp32 error stays below K 2^-24 sum |a b| < 2^-2 of that rounding at these K
-    np.testing.assert_allclose(got, want, rtol=2 ** -8, atol=2 ** -20 * K * np.abs(want).max())
+    assert_one_rounding(got, a, b)
     assert rel_l2(got, want) < 3e-3
+
+
+RUN_SHAPES = [(1, 8, 64 * 5), (77, 136, 64 * 7), (128, 128, 64 * 8), (200, 72, 64 * 13), (257, 264, 64 * 17), (300, 520, 64 * 40)]
+
+
+@pytest.mark.parametrize("M,N,K", RUN_SHAPES)
+def test_runs_of_k_give_the_same_bits_on_every_tile(M, N, K):
+    """Whole and over runs that do not divide the slices, rows and columns that end inside a tile: the partial products of every tile,
+    added by the second launch, against the sums one workgroup makes of the same runs, and those against 64 bits."""
+    import paper_2603_03592_amd as sv
+    g = np.random.default_rng(M + N + K)
+    a = si.round_to_bf16(g.standard_normal((M, K)).astype(np.float32))
+    b = si.round_to_bf16(g.standard_normal((N, K)).astype(np.float32))
+    ad, bd = dev(a, "bf16"), dev(b, "bf16")
+    for runs in (1, 2, 3, 5, 8):
+        if runs > K // 64:
+            continue
+        want = host(sv.sv_gemm_bf16_runs(ad, bd, 2, runs, apart=False))
+        assert_one_rounding(want, a, b)
+        for tile in (2, 3, 4, 5):
+            assert np.array_equal(host(sv.sv_gemm_bf16_runs(ad, bd, tile, runs, apart=True)), want), (tile, runs)
+            if runs == 1:
+                assert np.array_equal(host(sv.sv_gemm_bf16_runs(ad, bd, tile, 1, apart=False)), want), tile
+            else:
+                assert tile == 2 or refused(sv, ad, bd, tile, runs)
+    assert refused(sv, ad, bd, 2, K // 64 + 1) and refused(sv, ad, bd, 1, 1) and refused(sv, ad, bd, 6, 1)
+
+
+def refused(sv, a, b, tile, runs):
+    try:
+        sv.sv_gemm_bf16_runs(a, b, tile, runs, apart=False)
+    except sv.SVError:
+        return True
+    return False
 
 
 def test_product_refuses_what_it_refused():
@@ -56,9 +100,7 @@ def test_rows_too_far_apart_for_32_bit_offsets(far, ld, tile):
         return v
 
     got = host(sv.sv_gemm_bf16(view(a, M, K, far == "a"), view(b, N, K, far == "b"), tile=tile, out=view(None, M, N, far == "c")))
-    want = a.astype(np.float64) @ b.astype(np.float64).T
-    bound = 2.0 ** -8 * np.abs(want) + 4 * K * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T)
-    assert (np.abs(got - want) <= bound).all()
+    assert_one_rounding(got, a, b)
 
 
 # widths that are multiples of 64 (or 8, for the MLP) but not of 128; one kv head of 64 columns; fewer rows than a tile and ragged
