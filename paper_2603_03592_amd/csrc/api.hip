@@ -1170,7 +1170,8 @@ sv_status sv::check_signals(sv_ctx* c, const void* signals, int64_t stride, int 
                             const float* ref_proj, float* claim_proj_out, float* sw_out, hipStream_t st) {
   const int64_t Tpad = sw_padded_len(T), tiles = (T + 15) / 16;
   if (!(c->flags & SV_FLAG_SLICED_W) || !sum_out || !ref_proj || !claim_proj_out || T > c->max_tokens || Tpad > kSwSortChunkMax ||
-      tiles * n > kScoreScratchElems || !signal_pass_supported(signals, stride, n, dtype, m, directions, L, T, D))
+      tiles * n > kScoreScratchElems || !signal_pass_supported(signals, stride, n, dtype, m, directions, L, T, D) ||
+      !signal_pass_pays(n, T, D, score_sum_supported(n, 0, dtype, D)))
     return SV_EUNSUPPORTED;
   uint32_t skip = 0;
   for (int i = 0; skip_host && i < n; ++i)

@@ -132,6 +132,7 @@ hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int
 // signal_pass.hip: statistics, sum and projections of up to 16 bf16 submissions against one fp32 reference in one pass.  Writes
 // ceil(T / 16) records per submission, sum_out as the score pass does and P[n][L][Tpad] without its padding.
 bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, const float* m, const void* U, int L, int64_t T, int D);
+bool signal_pass_pays(int n, int64_t T, int D, bool summed);     // against the separate passes; summed: they leave the sum too
 hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,
                               uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st);
 // api.hip: what sv_score_and_sum and sv_sw_against_projection do together for the verifier loop, over one pass of the submissions;

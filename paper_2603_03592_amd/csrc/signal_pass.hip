@@ -252,6 +252,20 @@ bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, cons
          a16(X) && a16(m) && a16(U);
 }
 
+// The pass reads every submission once where the separate ones read it twice (three times where the score pass leaves no sum), but a
+// workgroup walks its 16 tokens' whole row with all submissions, chunk behind chunk, where those spread submissions and rows over
+// the chip.  So it is the longer way where there are too few tokens to be short of memory.  Times of a forward and a
+// backward call of one stage, separate -> one pass, us, 32 directions (submissions x tokens x columns):
+//   16 x 128 x 4032   226 -> 377     12 x 2000 x 3136  396 -> 384     16 x 8192 x 4032  1636 -> 987     2 x 8192 x 4032  528 -> 548
+//   4 x 4000 x 4032   426 -> 400     8 x 128 x 384     160 -> 152     16 x 47 x 384      164 -> 172     4 x 500 x 1024   194 -> 187
+// With a sum from the score pass (summed: one read less on that side, but a longer chain of its own) the pass is even or better
+// where its waves have work for three of four places: 16 x 128 x 4096 456 -> 381, 9 x 128 x 4096 339 -> 367, 2 x 500 x 4096 263 -> 298.
+bool signal_pass_pays(int n, int64_t T, int D, bool summed) {
+  if (T * n >= 24576 || D <= 320 || (D <= 1024 && n <= 4)) return true;
+  const int places = n <= 4 ? 4 : n <= 8 ? 8 : 16;
+  return summed && T >= 16 && 4 * n >= 3 * places;
+}
+
 hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,
                               uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st) {
   // Four waves, two workgroups on a CU, or where that many workgroups are not there eight waves with half the submissions each: a

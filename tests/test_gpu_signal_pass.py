@@ -28,7 +28,8 @@ def _signals(n, T, D, t):
 
 
 @pytest.mark.parametrize("n,T,D,L", [(1, 1, 64, 32), (2, 15, 64, 64), (4, 16, 128, 64), (5, 17, 192, 32), (8, 100, 64, 64), (9, 33, 1024, 64),
-                                     (12, 47, 320, 32), (13, 64, 192, 64), (16, 130, 1024, 64)])
+                                     (12, 47, 320, 32), (13, 64, 192, 64), (16, 130, 1024, 64), (3, 4099, 64, 32), (6, 4100, 128, 64), (8, 4097, 64, 32),
+                                     (11, 4111, 64, 64), (12, 4098, 192, 32), (15, 4100, 64, 64)])
 def test_one_pass_equals_the_separate_passes(n, T, D, L):
     ver, (one, sep) = _loops(n, T, D, L)
     for t in range(4):
@@ -65,3 +66,20 @@ def test_non_finite_signals_stay_with_their_worker(bad):
             assert 3 in ta and not np.isfinite(ga[3, 0]) and not np.isfinite(ga[3, 4])
         assert np.isfinite(one.ema(0, "h")).all()
     one.close(); sep.close(); ver.close()
+
+
+@pytest.mark.parametrize("n,T,D,one", [(9, 128, 1728, False), (16, 64, 448, False), (5, 700, 1088, False), (2, 33, 1088, False), (16, 1535, 384, False),
+                                       (4, 64, 960, True), (16, 64, 320, True), (16, 1536, 384, True), (6, 4096, 448, True)])
+def test_few_tokens_take_the_separate_passes(n, T, D, one):
+    """Rows that the score pass cannot sum, so that the average's update tells which way a call went: from the sum that the one pass
+    leaves, or from the signals."""
+    ver, (a, b) = _loops(n, T, D, 32)
+    x = _signals(n, T, D, 0)
+    for loop, dtype in ((a, "bf16"), (b, "f32")):
+        loop.begin_iteration(True)
+    (_, ga), (_, gb) = a.forward(0, dev(x, "bf16")), b.forward(0, dev(x, "f32"))
+    np.testing.assert_allclose(ga, gb, rtol=2e-5, atol=1e-7)
+    c = a.counters()
+    assert (c["ema_from_sum"], c["calls"]) == (int(one), 1)
+    assert np.linalg.norm(a.ema(0, "h") - b.ema(0, "h")) <= 1e-6 * np.linalg.norm(b.ema(0, "h"))
+    a.close(); b.close(); ver.close()
