@@ -59,7 +59,7 @@ inline int xcd_grid(int n_tiles, int G, int Hkv, int B) {
 // the same amount of work -- unless one workgroup per tile still leaves every workgroup a CU of its own: then the longest
 // tile alone (n of a pair's n + 1 units) is the shorter way.  Workgroups per (batch, head) -- the middle tile of an odd
 // count stands alone -- and tiles of workgroup r:
-inline bool pair_tiles(int causal, int n_tiles, int64_t heads) { return causal && n_tiles > 1 && heads * n_tiles > 256; }
+inline bool pair_tiles(int causal, int n_tiles, int64_t heads) { return causal && n_tiles > 1 && heads * n_tiles > cu_count(); }
 __host__ __device__ __forceinline__ int paired_tiles(bool pair, int n) { return pair ? (n + 1) / 2 : n; }
 __device__ __forceinline__ int n_passes(bool pair, int n, int r) { return pair && 2 * r != n - 1 ? 2 : 1; }
 

@@ -140,6 +140,8 @@ hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float*
 sv_status check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, const float* m, int64_t T, int D, uint32_t metric_mask,
                         const float* tau4, sv_result* results, const uint8_t* skip_host, float* sum_out, const void* directions, int L,
                         const float* ref_proj, float* claim_proj_out, float* sw_out, hipStream_t st);
+// gemm_mfma.hip: compute units of the device (256 on a whole MI355X); grids and the rules that ask whether a launch fills the chip count with it
+int cu_count();
 // api.hip: error text for entry points without a context (sv_last_error(NULL) returns it on the same thread)
 void set_global_error(const char* fmt, ...);
 // With sum_out the score pass also writes sum_out[t, :] = sum of the submissions whose bit in `skip` is clear (fp32, index

@@ -27,6 +27,16 @@
 #include "common.h"
 
 namespace sv {
+
+int cu_count() {
+  static const int n = [] {
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8) return 256;
+    return v;
+  }();
+  return n;
+}
+
 namespace {
 
 constexpr int BK = 64;
@@ -1127,16 +1137,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
   }
 #undef SV_MEET
 #undef SV_SB
-}
-
-// compute units of the current device: the persistent kernel's grid and the tile rule count with it
-int cu_count() {
-  static const int n = [] {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 8) return 256;
-    return v;
-  }();
-  return n;
 }
 
 template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false>

@@ -526,7 +526,7 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
       continue;
     }
     const int64_t tiles4 = (T + 3) / 4;                // up to one record of 16 tokens per CU: smaller ones (see the kernel)
-    const bool few = tiles * nc <= 256 && tiles4 * nc <= scratch_elems;
+    const bool few = tiles * nc <= cu_count() && tiles4 * nc <= scratch_elems;
     const int tpc = (int)(few ? tiles4 : tiles);
     const dim3 gridt((unsigned)(8 * ((tpc + 7) / 8) * nc));
 #define SV_LAUNCH_SCORE3(EC, ER, L1, Z, SFR)                                                                           \

@@ -270,7 +270,7 @@ hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float*
                               uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st) {
   // Four waves, two workgroups on a CU, or where that many workgroups are not there eight waves with half the submissions each: a
   // workgroup's time is then its chain of chunks, and a chunk takes as long as a wave's work on it.
-  const bool few = T <= 16 * 256;
+  const bool few = T <= 16 * cu_count();
 #define SV_PASS(CPW, NW)                                                                                                       \
   (L == 32 ? launch<2, CPW, NW>((const bf16*)X, stride, n, m, (const bf16*)U, T, D, Tpad, skip, sum_out, P, partials, st)       \
            : launch<4, CPW, NW>((const bf16*)X, stride, n, m, (const bf16*)U, T, D, Tpad, skip, sum_out, P, partials, st))
