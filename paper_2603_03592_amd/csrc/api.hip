@@ -170,8 +170,8 @@ size_t carve(sv_ctx* c, char* base) {
   c->score_scratch = (ScorePartial*)a.take(kScoreScratchElems * sizeof(ScorePartial));
   c->split_ws = nullptr; c->split_ws_floats = 0;
   if (d.dtype == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS)) {
-    // up to 8 partial products of the widest product a split can serve (below 160 tiles of 128 x 128, or below 192 tiles
-    // of 256 x 256 with as many runs as this holds), and no more than this context's token bound allows
+    // for products over runs of k: up to 8 partial products of this context's largest, and no more than 84 MB.  A plan takes as
+    // many runs as fit here, so for one input the order of a sum can depend on max_tokens as well (never on what else is in use)
     const size_t widest = std::max(std::max(D, (size_t)c->Dq), std::max(Fd, (size_t)d.ffn_hidden));
     c->split_ws_floats = std::min((size_t)8 * 160 * 128 * 128, (size_t)8 * T * widest);
     c->split_ws = (float*)a.take(c->split_ws_floats * sizeof(float));

@@ -130,7 +130,8 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
 hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
                                  int reduce, sv_result* results, hipStream_t st);
 // signal_pass.hip: statistics, sum and projections of up to 16 bf16 submissions against one fp32 reference in one pass.  Writes
-// ceil(T / 16) records per submission, sum_out as the score pass does and P[n][L][Tpad] without its padding.
+// ceil(T / 16) records per submission, sum_out (per wave in index order, then over the waves: other last bits than the score pass's)
+// and P[n][L][Tpad] without its padding.
 bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, const float* m, const void* U, int L, int64_t T, int D);
 bool signal_pass_pays(int n, int64_t T, int D, bool summed);     // against the separate passes; summed: they leave the sum too
 hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,

@@ -809,9 +809,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 //
 // What bounds it: LDS.  A 128x128 tile moves 32 KB into LDS (64 B/clk) and 64 KB out of it (about 200 B/clk) per slice
 // of 512 matrix cycles, so a CU is busy with LDS about 1.5 x as long as with MFMAs; the 256x256 tile (0.75 x) stays the
-// better one wherever it fills the chip.  NST: the loads of slice k + NST - 1 are issued when slice k is multiplied.
-// With two workgroups on a CU (2 stages each) they cover each other's wait for memory; where there is at most about one
-// tile per CU, one workgroup runs alone and 4 stages keep three slices in flight instead.
+// better one wherever it fills the chip.  NST: the loads of slice k + NST - 1 are issued when slice k is multiplied.  As many
+// stages as a CU's 160 KB hold for one workgroup (256x128: 3, 128x128: 4, 64x64: 8), since a CU has about one tile where these
+// serve; 64x128 takes 3, and its 72 KB let two workgroups share a CU.  (128x128 with two stages and two workgroups on a CU,
+// each under the other's wait for memory, measured slower than one with four.)
 //
 // The one wait + barrier per slice stands before the last of its four 16-wide k steps, whose fragments are in registers
 // by then: behind it the first fragments of the next slice are asked for, and the step's MFMAs hide their latency.
@@ -1194,7 +1195,10 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // ---- which kernel and tile serves a product.  Every choice is priced as rounds of workgroups over the CUs times (a fixed part
 // + slices x time per slice), plus for runs of k slices the reduction launch and the traffic of the partial products; the
 // cheapest is taken.  The figures are microseconds fitted to a sweep over 64 .. 8192 rows, 320 .. 14336 columns and K =
-// 512 .. 14336 with every tile forced (within 15 % of the measured times there).  Where the lines come out, with both
+// 512 .. 14336 with every tile forced (within 15 % of the measured times there).  They are those of a plain store: the dearer
+// epilogues (SwiGLU with its stashes, SwiGLU-backward) cost the same here, and a tile more than the last full round counts as a
+// round.  Against 256x256 tiles over runs of k, which these replaced, k of 9000 and more for 500 .. 1500 rows of 3072 .. 4096 columns
+// is left 5 .. 15 % slower (1453 x 3072, K = 9728: 97 -> 112 us), everything else even or faster.  Where the lines come out, with both
 // sides as measured on that sweep: 4096 x 1024, K = 1024 (256 tiles of 128 x 128) 13.4 us against 19 on 256 x 128 and 33 on
 // 256 x 256 over runs; 8192 x 1024, K = 8192 (256 tiles of 256 x 128) 113 us against 121 and 124; 8192 x 2048, K = 2048
 // (256 tiles of 256 x 256) 59 us against 64 on 256 x 128; 512 x 4096, K = 14336 (256 x 128 over 4 runs) 63 us against 85 whole;
@@ -1301,9 +1305,11 @@ hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
 }  // namespace
 
 // Which expert a token takes is decided by sums that start here, and a near-tie follows their last bits: the products that lead to
-// a router keep their sums cut the way verifiers of this library have cut them (a second verifier, or the same one after an
-// update, then routes every token alike), while tile and launch are free.  The cut: runs that once brought 256x256 tiles to one
-// workgroup per CU, or 128x64 tiles to three.
+// a router keep their sums cut the way verifiers of this library have cut them, while tile and launch are free.  The cut: runs that
+// once brought 256x256 tiles to one workgroup per CU, or 128x64 tiles to three.  What it makes alike: the routing of two verifiers of
+// one stage and token count whose scratch is the same or holds the runs either way (`fit`; the scratch grows with max_tokens up to
+// a cap, and only q | k | v of narrow experts can be short of it), forward only or with backward.  Not covered: widths that were
+// no multiple of 128 (of 64 along k, and in the experts' own products), which the vector kernels summed before these tiles took them.
 int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats) {
   const int slices = K / BK;
   const int64_t fit = ws_floats / std::max<int64_t>(1, M * N);
