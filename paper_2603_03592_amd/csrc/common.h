@@ -129,18 +129,19 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
 // the scores and the flag from the records of one score pass, `tiles` per submission
 hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
                                  int reduce, sv_result* results, hipStream_t st);
-// signal_pass.hip: statistics, sum and projections of up to 16 bf16 submissions against one fp32 reference in one pass.  Writes
-// ceil(T / 16) records per submission, sum_out (per wave in index order, then over the waves: other last bits than the score pass's)
-// and P[n][L][Tpad] without its padding.
+// signal_pass.hip: statistics, EMA update and projections of up to 16 bf16 submissions against one fp32 reference, their EMA, in one
+// pass.  Writes ceil(T / 16) records per submission, P[n][L][Tpad] without its padding, and m <- beta m + (1 - beta) mean of the
+// submissions whose bit in `skip` is clear (nobody: m as it is), with what m was before in m_prev.
 bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, const float* m, const void* U, int L, int64_t T, int D);
 bool signal_pass_pays(int n, int64_t T, int D, bool summed);     // against the separate passes; summed: they leave the sum too
-hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,
-                              uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st);
-// api.hip: what sv_score_and_sum and sv_sw_against_projection do together for the verifier loop, over one pass of the submissions;
-// SV_EUNSUPPORTED (and nothing enqueued) where they have to be called one after the other
-sv_status check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, const float* m, int64_t T, int D, uint32_t metric_mask,
-                        const float* tau4, sv_result* results, const uint8_t* skip_host, float* sum_out, const void* directions, int L,
-                        const float* ref_proj, float* claim_proj_out, float* sw_out, hipStream_t st);
+hipError_t launch_signal_pass(const void* X, int64_t stride, int n, float* m, float* m_prev, float beta, const void* U, int L, int64_t T, int D,
+                              int64_t Tpad, uint32_t skip, float* P, ScorePartial* partials, hipStream_t st);
+// api.hip: what sv_score_and_sum, sv_ema_from_sum and sv_sw_against_projection do together for the verifier loop, over one pass of the
+// submissions; SV_EUNSUPPORTED (and nothing enqueued) where they have to be called one after the other.  *updated: the pass is
+// enqueued, so m holds the next EMA and m_prev the present one, whatever is returned
+sv_status check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, float* m, float* m_prev, float beta, int64_t T, int D,
+                        uint32_t metric_mask, const float* tau4, sv_result* results, const uint8_t* skip_host, const void* directions, int L,
+                        const float* ref_proj, float* claim_proj_out, float* sw_out, bool* updated, hipStream_t st);
 // gemm_mfma.hip: compute units of the device (256 on a whole MI355X); grids and the rules that ask whether a launch fills the chip count with it
 int cu_count();
 // api.hip: error text for entry points without a context (sv_last_error(NULL) returns it on the same thread)
@@ -150,7 +151,7 @@ void set_global_error(const char* fmt, ...);
 bool score_sum_supported(int n_claims, int64_t ref_stride, int claim_dtype, int D);
 hipError_t launch_ema_from_sum(float* m, const float* sum, int n_summed, int64_t T, int D, float beta, hipStream_t st);
 hipError_t launch_ema(float* m, const void* claims, int64_t claim_stride, int n_claims, int claim_dtype,
-                      const uint8_t* flags, int64_t T, int D, float beta, hipStream_t st);
+                      const uint8_t* flags, int64_t T, int D, float beta, hipStream_t st, const float* m_from = nullptr);   // m_from: m starts from there
 
 hipError_t launch_replace(void* signals, int64_t stride, int n, int dtype, const uint8_t* mask, const float* m, int64_t T, int D,
                           hipStream_t st);

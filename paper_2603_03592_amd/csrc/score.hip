@@ -413,8 +413,8 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial*
 }
 
 template <typename E>
-__global__ __launch_bounds__(256) void ema_update_kernel(float* __restrict__ m, const E* __restrict__ claims, int64_t claim_stride,
-                                                         int n_claims, const uint8_t* __restrict__ flags, int64_t n_vec, float beta) {
+__global__ __launch_bounds__(256) void ema_update_kernel(float* m, const E* __restrict__ claims, int64_t claim_stride,
+                                                         int n_claims, const uint8_t* __restrict__ flags, int64_t n_vec, float beta, const float* m_from) {
   // the un-flagged submissions of this step, compacted once per workgroup
   __shared__ int clean[1024];
   __shared__ int s_n;
@@ -427,7 +427,13 @@ __global__ __launch_bounds__(256) void ema_update_kernel(float* __restrict__ m, 
   __syncthreads();
   const int n_clean = s_n;
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v >= n_vec || n_clean == 0) return;   // every submission flagged: the EMA is left as it is
+  if (v >= n_vec) return;
+  float mv[8];
+  load8(m_from + v * 8, mv);
+  if (n_clean == 0) {                       // every submission flagged: the EMA is left as it is
+    if (m_from != m) store8(m + v * 8, mv);
+    return;
+  }
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   const E* base = claims + v * 8;
   int i = 0;
@@ -446,8 +452,6 @@ __global__ __launch_bounds__(256) void ema_update_kernel(float* __restrict__ m, 
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] += x[j];
   }
-  float mv[8];
-  load8(m + v * 8, mv);
   const float w = (1.0f - beta) / (float)n_clean;
 #pragma unroll
   for (int j = 0; j < 8; ++j) mv[j] = beta * mv[j] + w * acc[j];
@@ -582,14 +586,15 @@ hipError_t launch_replace(void* signals, int64_t stride, int n, int dtype, const
 }
 
 hipError_t launch_ema(float* m, const void* claims, int64_t claim_stride, int n_claims, int claim_dtype,
-                      const uint8_t* flags, int64_t T, int D, float beta, hipStream_t st) {
+                      const uint8_t* flags, int64_t T, int D, float beta, hipStream_t st, const float* m_from) {
   if (n_claims <= 0 || T <= 0) return hipSuccess;
+  if (!m_from) m_from = m;
   const int64_t n_vec = T * D / 8;
   const dim3 grid((unsigned)((n_vec + 255) / 256)), block(256);
   if (claim_dtype == SV_BF16)
-    hipLaunchKernelGGL(ema_update_kernel<bf16>, grid, block, 0, st, m, (const bf16*)claims, claim_stride, n_claims, flags, n_vec, beta);
+    hipLaunchKernelGGL(ema_update_kernel<bf16>, grid, block, 0, st, m, (const bf16*)claims, claim_stride, n_claims, flags, n_vec, beta, m_from);
   else
-    hipLaunchKernelGGL(ema_update_kernel<float>, grid, block, 0, st, m, (const float*)claims, claim_stride, n_claims, flags, n_vec, beta);
+    hipLaunchKernelGGL(ema_update_kernel<float>, grid, block, 0, st, m, (const float*)claims, claim_stride, n_claims, flags, n_vec, beta, m_from);
   return hipGetLastError();
 }
 

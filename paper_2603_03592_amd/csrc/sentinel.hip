@@ -28,7 +28,8 @@ struct sv_sentinel {
   sv_result* res_dev = nullptr;
   float* sw_dev = nullptr;
   uint8_t* mask_dev = nullptr;             // two rows of d bytes: replacement mask, EMA exclusion mask
-  float* sum_dev = nullptr;                // [T, D]: sum over the signals not excluded beforehand, written by the score pass
+  float* sum_dev = nullptr;                // [T, D]: sum over the signals not excluded beforehand, written by the score pass; where one
+                                           // pass has updated the EMA as well: what it was before
   // sliced Wasserstein against the EMA without projecting the EMA: its projections follow from the signals' (linearity)
   std::vector<float*> pm[2];               // [kind][stage] device fp32 [n_dirs, Tpad]: <u_l, m_t>, kept up to date with m
   float* cproj = nullptr;                  // [d, n_dirs, Tpad]: the current signals' projections
@@ -60,22 +61,37 @@ void set_err(sv_sentinel* s, const char* fmt, ...) {
     if (st_ != SV_OK) { set_err(s, "%s: %s", #call, sv_last_error((s)->ctx)); return st_; } \
   } while (0)
 
-// Gamma [d, n_metrics] of the d signals against the reference point m, on the host (waits for the stream).
+// A stage call's EMA while the call is under way.  Where one pass did the checks it has updated m already, over the signals not
+// excluded beforehand, and left what it was in sum_dev.  A call that ends before its verdicts stand leaves m as it was.
+struct CallEma {
+  sv_sentinel* s;
+  float* m;
+  float beta;
+  hipStream_t st;
+  bool updated = false;
+  const float* now() const { return updated ? s->sum_dev : m; }
+  ~CallEma() {
+    if (updated) (void)hipMemcpyAsync(m, s->sum_dev, (size_t)s->cfg.T * s->cfg.D * sizeof(float), hipMemcpyDeviceToDevice, st);
+  }
+};
+
+// Gamma [d, n_metrics] of the d signals against the reference point ema.m, on the host (waits for the stream).
 // `skip` [d]: the signals known to be excluded from the EMA before they are scored.  Where the score pass can do it,
-// it also leaves the sum over the others in sum_dev (*summed = true), which saves the EMA update its own pass over the
-// signals whenever the verdicts exclude nobody else.
-sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, const float* m, const float* pm, const uint8_t* skip, bool* summed,
+// it also leaves the sum over the others in sum_dev, or updates the EMA with it (*summed = true), which saves the EMA update its own
+// pass over the signals whenever the verdicts exclude nobody else.
+sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, CallEma& ema, const float* pm, const uint8_t* skip, bool* summed,
                    std::vector<double>& gamma, hipStream_t st) {
   const sv_sentinel_cfg& c = s->cfg;
   const int d = c.n_workers;
   const int64_t stride = c.T * c.D;
   const float inf = std::numeric_limits<float>::infinity();
   const float tau[4] = {inf, inf, inf, inf};      // nothing is decided on the device here: the fences live in the policy
-  // statistics, sum and projections in one pass over the signals where the shape allows it
+  float* m = ema.m;
+  // statistics, EMA update and projections in one pass over the signals where the shape allows it
   sv_status one = SV_EUNSUPPORTED;
   if ((c.metric_mask & SV_M_SW) && pm && s->sum_dev) {
-    one = sv::check_signals(s->ctx, signals, stride, d, dtype, m, c.T, c.D, c.metric_mask & 15u, tau, s->res_dev, skip, s->sum_dev, c.directions, c.n_dirs,
-                            pm, s->cproj, s->sw_dev, st);
+    one = sv::check_signals(s->ctx, signals, stride, d, dtype, m, s->sum_dev, ema.beta, c.T, c.D, c.metric_mask & 15u, tau, s->res_dev, skip, c.directions,
+                            c.n_dirs, pm, s->cproj, s->sw_dev, &ema.updated, st);
     if (one != SV_OK && one != SV_EUNSUPPORTED) { set_err(s, "the loop's pass: %s", sv_last_error(s->ctx)); return one; }
   }
   sv_status sum_st = one == SV_OK ? SV_OK : s->sum_dev ? sv_score_and_sum(s->ctx, signals, stride, d, m, dtype, SV_F32, c.T, c.D, c.metric_mask & 15u, tau,
@@ -112,24 +128,28 @@ sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, const float* 
 }
 
 // Eq. momentum_def over the signals with excl[r] == 0.  If the score pass has left the sum over the signals with
-// skip[r] == 0 and the verdicts excluded nobody beyond those, the update is one pass over m and that sum; otherwise
+// skip[r] == 0 and the verdicts excluded nobody beyond those, the update is one pass over m and that sum, or done already; otherwise
 // the update reads the signals itself.
-sv_status update_ema(sv_sentinel* s, float* m, float* pm, const void* signals, int dtype, const uint8_t* excl, const uint8_t* skip,
-                     bool summed, float beta, hipStream_t hs, bool mask_uploaded = false) {
+sv_status update_ema(sv_sentinel* s, CallEma& ema, float* pm, const void* signals, int dtype, const uint8_t* excl, const uint8_t* skip,
+                     bool summed, bool mask_uploaded = false) {
   const int d = s->cfg.n_workers;
-  if (pm) SN_SV(s, sv_sw_projection_ema(s->ctx, pm, s->cproj, d, excl, s->cfg.T, s->cfg.n_dirs, beta, hs));
+  const hipStream_t hs = ema.st;
+  if (pm) SN_SV(s, sv_sw_projection_ema(s->ctx, pm, s->cproj, d, excl, s->cfg.T, s->cfg.n_dirs, ema.beta, hs));
   bool same = summed;
   int n = 0;
   for (int r = 0; r < d; ++r) { same = same && (excl[r] != 0) == (skip[r] != 0); n += excl[r] == 0; }
   ++s->n_calls;
   if (same) {
     ++s->n_from_sum;
-    SN_SV(s, sv_ema_from_sum(s->ctx, m, s->sum_dev, n, s->cfg.T, s->cfg.D, beta, hs));
+    if (!ema.updated) SN_SV(s, sv_ema_from_sum(s->ctx, ema.m, s->sum_dev, n, s->cfg.T, s->cfg.D, ema.beta, hs));
+    ema.updated = false;
     return SV_OK;
   }
   ++s->n_from_signals;
   if (!mask_uploaded) SN_HIP(s, hipMemcpyAsync(s->mask_dev + d, excl, (size_t)d, hipMemcpyHostToDevice, hs));
-  SN_SV(s, sv_ema_update(s->ctx, m, signals, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev + d, s->cfg.T, s->cfg.D, beta, hs));
+  if (ema.updated) SN_HIP(s, sv::launch_ema(ema.m, signals, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev + d, s->cfg.T, s->cfg.D, ema.beta, hs, s->sum_dev));
+  else SN_SV(s, sv_ema_update(s->ctx, ema.m, signals, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev + d, s->cfg.T, s->cfg.D, ema.beta, hs));
+  ema.updated = false;
   return SV_OK;
 }
 
@@ -251,7 +271,8 @@ sv_status sv_sentinel_forward(sv_sentinel* s, int32_t stage, const void* h, int3
   }
   bool summed = false;
   float* pm = s->pm[0].empty() ? nullptr : s->pm[0][stage];
-  st = gamma_of(s, h, dtype, s->m[0][stage], pm, skip.data(), &summed, gamma, hs);
+  CallEma ema{s, s->m[0][stage], s->cfg.beta_h, hs};
+  st = gamma_of(s, h, dtype, ema, pm, skip.data(), &summed, gamma, hs);
   if (st != SV_OK) return st;
   if (gamma_out) memcpy(gamma_out, gamma.data(), gamma.size() * sizeof(double));
   uint8_t* excl = s->mask_host + d;
@@ -266,7 +287,7 @@ sv_status sv_sentinel_forward(sv_sentinel* s, int32_t stage, const void* h, int3
       excl[r] = banned[r] | upstream[r] | tainted_out[r];
     }
   }
-  return update_ema(s, s->m[0][stage], pm, h, dtype, excl, skip.data(), summed, s->cfg.beta_h, hs);
+  return update_ema(s, ema, pm, h, dtype, excl, skip.data(), summed);
 }
 
 sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t dtype, uint8_t* tainted_out, double* gamma_out, void* stream) {
@@ -287,7 +308,8 @@ sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t d
   }
   bool summed = false;
   float* pm = s->pm[1].empty() ? nullptr : s->pm[1][stage];
-  st = gamma_of(s, g, dtype, s->m[1][stage], pm, skip.data(), &summed, gamma, hs);
+  CallEma ema{s, s->m[1][stage], s->cfg.beta_g, hs};
+  st = gamma_of(s, g, dtype, ema, pm, skip.data(), &summed, gamma, hs);
   if (st != SV_OK) return st;
   if (gamma_out) memcpy(gamma_out, gamma.data(), gamma.size() * sizeof(double));
   uint8_t* repl = s->mask_host;
@@ -305,12 +327,12 @@ sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t d
     }
   }
   SN_HIP(s, hipMemcpyAsync(s->mask_dev, s->mask_host, 2 * (size_t)d, hipMemcpyHostToDevice, hs));
-  // the EMA reads only signals that are not replaced, and the replacement reads m before it is updated
+  // the EMA reads only signals that are not replaced, and the replacement reads what m was before it is updated
   bool any_repl = false;
   for (int r = 0; r < d; ++r) any_repl |= repl[r] != 0;
-  if (any_repl) SN_SV(s, sv_replace_with_ema(s->ctx, g, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev, s->m[1][stage], s->cfg.T, s->cfg.D, hs));
+  if (any_repl) SN_SV(s, sv_replace_with_ema(s->ctx, g, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev, ema.now(), s->cfg.T, s->cfg.D, hs));
   // (the sum the score pass left was taken before the replacement, over signals that are not replaced)
-  return update_ema(s, s->m[1][stage], pm, g, dtype, excl, skip.data(), summed, s->cfg.beta_g, hs, /*mask_uploaded=*/true);
+  return update_ema(s, ema, pm, g, dtype, excl, skip.data(), summed, /*mask_uploaded=*/true);
 }
 
 sv_status sv_sentinel_state(const sv_sentinel* s, int32_t stage, int32_t kind, const float** ema_dev, int32_t* violations, uint8_t* banned,

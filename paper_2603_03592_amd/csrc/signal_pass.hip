@@ -1,245 +1,317 @@
-// One pass of the verifier loop over a stage's submissions (bf16) and their EMA (fp32): the sums of every statistic, the sum of
-// the submissions that are not excluded (for the EMA update) and the projections on the sliced-Wasserstein directions.
+// One pass of the verifier loop over a stage's submissions (bf16) and their EMA (fp32): the sums of every statistic, the EMA's
+// next value over the submissions that are not excluded, and the projections on the sliced-Wasserstein directions.
 //
 // As separate passes (score_parts_kernel, sw_project_kernel) the submissions come from memory twice, which is most of what
-// a stage call costs: 16 x [8192, 4096] are 1.07 GB, 297 us with the EMA and the sum, and again 202 us for the projections.
-// Here it is one read, 371 us in all (3.6 TB/s with the EMA and the sum): about half memory, half the vector ALUs' share.
+// a stage call costs: 16 x [8192, 4096] are 1.07 GB, 297 us with the EMA and the sum, again 202 us for the projections, and 60 us
+// for an EMA update from the sum.  In one pass 374 us with the submissions in registers, and those 60; in this form 320 us with the
+// update, 4.6 TB/s of reads and writes together (a large copy reaches 4.7).
 //
-// A workgroup owns 16 tokens and all submissions, a wave up to four of them; the row is walked in chunks of 64 features.  A lane
-// holds 8 consecutive features of one token (lane & 15; features 8 (lane >> 4) of each half chunk): that is a B fragment of
-// v_mfma_f32_16x16x32_bf16 as it comes from memory, so the submissions go straight to registers, are used there by the
-// statistics and by the matrix cores (directions in the A slot, staged through LDS for the workgroup), and are never stored.
-// The submissions of a wave share the EMA's values, the reference's own sums and one class mask per element for the
-// sign test (as in score_parts_kernel).  A register is asked for again, for the next chunk, right behind its last use: one
-// chunk of every wave is always in flight.  The waves' partial sums over submissions meet in LDS, one barrier per chunk.
-// Sums are taken over a chunk's 16 elements per lane first and then over the chunks, so that no fp32 sum is longer than
-// those of the separate pass.
+// What bounds it is memory: without its statistics it takes 340 us of 347 (before the non-temporal loads), without the two stores 243.  How
+// much is on its way decides: with the submissions in registers, one chunk ahead, 324 us with the statistics and 319 without, while
+// loads in this pattern and nothing else read the submissions in 175 us with 8 to 16 KB of every wave in flight.  Two chunks ahead
+// do not fit the registers beside the projections' accumulators.  So the submissions go straight to LDS, three to five chunks ahead
+// (non-temporal, since nobody reads them twice: 347 -> 320 us), and every wave can read every submission:
+//   - A workgroup of eight waves owns 16 tokens and all submissions and walks the rows in chunks of 64 features: per chunk 16 x 128
+//     bytes of each submission and the directions' 64 columns.
+//   - Statistics: a wave takes two tokens, a lane two neighbouring features of one of them, of all submissions one after the other.
+//     They share the EMA's values and one class mask per element for the sign test (as in score_parts_kernel), their sum stays
+//     in the lane, and so does the EMA's update: m is written in place and its former value beside it (a verdict that
+//     excludes somebody else goes back to it).
+//   - Projections on v_mfma_f32_16x16x32_bf16, directions in the A slot: a wave takes half the blocks of 16 directions for every
+//     fourth submission; fragments are 16-byte reads of the swizzled rows.  The same fragments against ones and against themselves
+//     give a token's sum and, on the diagonal, its sum of squares: exact products, added in fp32.
+// Workgroups start at different chunks, so that they do not all ask for the same 128 bytes of every 8 KB row at once (374 -> 324 us
+// for the register form).
+#include <type_traits>
+
 #include "common.h"
 
 namespace sv {
 namespace {
 
-__device__ __forceinline__ double xor_sum(double v, int from, int to) {
-  for (int o = from; o <= to; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 
-template <int LB, int kCPW, int NW>          // blocks of 16 directions; submissions per wave; waves
-__global__ __launch_bounds__(64 * NW, 2) void signal_pass_kernel(const bf16* __restrict__ X, int64_t x_stride, int n, const float* __restrict__ m,
-                                                             const bf16* __restrict__ U, int64_t T, int D, int64_t Tpad, uint32_t skip,
-                                                             float* __restrict__ sum_out, float* __restrict__ P, int tiles,
-                                                             ScorePartial* __restrict__ partials) {
-  constexpr int UB = LB * 16 * 128;          // bytes of the directions' chunk: rows of 64 bf16, 16-byte pieces XOR-swizzled by the row
+constexpr int kStream = 2;   // of a buffer load: its bytes come by once (non-temporal)
+
+template <int LB, int NS> struct PassCfg {       // blocks of 16 directions; places for submissions (a multiple of 4)
+  static constexpr int XB = NS * 2048;           // a chunk's bytes: the submissions' [NS][16 tokens][64 bf16]
+  static constexpr int UB = LB * 2048;           // ... the directions' [16 LB][64 bf16]
+  static constexpr int NST = NS == 16 ? 4 : NS == 12 ? 5 : 6, NU = 3;      // chunks of either in LDS: NST - 1 and two on their way
+  static constexpr int LDS = NST * XB + NU * UB;
+  static constexpr int XW = NS / 4, UW = (2 * LB + 7) / 8;                 // direct-to-LDS loads of 1 KB per wave and chunk
+  // What a wave has issued behind the directions it needs next: the submissions and the EMA's values of two chunks, the stores of two
+  // and the directions of one.  (What it needs of the submissions next is older.)
+  static constexpr int YOUNGER = 2 * (XW + 1 + 2) + UW;
+  static_assert(YOUNGER < 64 && LDS <= 160 * 1024, "the wait count has 6 bits, a CU 160 KB");
+  // the statistics' reduction: the lanes' sums, every token's sums, the matches
+  static constexpr int NV = 2 * NS + 2, RED = 8 * NV * 64 * 4, TOK = 16 * (4 * NS + 2) * 8, CNT = 8 * NS * 4;
+  static_assert(RED + TOK + CNT <= LDS, "the reduction fits the chunks' place");
+};
+
+template <int LB, int NS, bool ALL>              // ALL: every place holds a submission that enters the EMA
+__global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restrict__ X, int64_t x_stride, int n, float* m, float* m_prev, float beta,
+                                                             float w_new, const bf16* __restrict__ U, int64_t T, int D, int64_t Tpad, uint32_t skip,
+                                                             float* __restrict__ P, int tiles, ScorePartial* __restrict__ partials) {
+  using C = PassCfg<LB, NS>;
+  constexpr int NST = C::NST, SPW = NS / 4, BPW = LB / 2;        // submissions and blocks of directions of a wave's projections
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int nthreads = 64 * NW, nw = NW;
-  char* ubuf = smem;                         // two chunks of the directions
-  char* sbuf = smem + 2 * UB;                // two chunks of the waves' sums: [wave][16 tokens][64 floats], pieces swizzled too
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, lq = lane >> 4;
-  const int64_t t0 = (int64_t)blockIdx.x * 16, t = t0 + l15;
-  const bool live = t < T;
-  const uint64_t live_lanes = __ballot(live);
+  const int64_t t0 = (int64_t)blockIdx.x * 16;
+  const int last_row = (int)(min(t0 + 15, T - 1) - t0);
   const int nchunk = D >> 6;
-  // buffer loads: a descriptor per tensor based at the tile's first token, the lane's place in it, the chunk as scalar offset
-  const int rel_row = (int)(min(t, T - 1) - t0);
-  const int vx = (rel_row * D + lq * 8) * 2, vm = (rel_row * D + lq * 8) * 4;
-  auto desc = [&](const void* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, -1, 0x00020000); };
-  const bf16* xp[kCPW];
-  uint32_t take[kCPW];                                              // all ones for a submission that enters the sum, else zero
-#pragma unroll
-  for (int c = 0; c < kCPW; ++c) {
-    const int i = wave * kCPW + c;
-    xp[c] = X + (int64_t)min(i, n - 1) * x_stride + t0 * D;         // a wave's missing submissions repeat the last one, unused
-    take[c] = i < n && !((skip >> i) & 1u) ? ~0u : 0u;
-  }
-  const float* mp = m + t0 * D;
+  auto swz = [](int r) { return (r ^ (r >> 3)) & 7; };           // which 16-byte piece of a 128-byte row goes where
 
-  // directions: piece p (16 bytes) of the chunk is row p / 8, piece p % 8 of it
-  constexpr int UPT = (LB * 16 * 8 + nthreads - 1) / nthreads;
-  bf16x8 ureg[UPT];
-  auto load_u = [&](int chunk) {
+  auto desc = [&](const void* p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00020000); };
+  // ---- the streams.  A load fills 1 KB of LDS: 8 rows of a submission's chunk (load 2 c and 2 c + 1 of submission c) or of the
+  // directions'.  Rows past the last token repeat it, places past the last submission repeat that one (neither is used).
+  const bf16* xp = X + t0 * D;
+  float* mp = m + t0 * D;
+  const int r8 = lane >> 3, p8 = lane & 7;
+  const int hi_row = (wave & 1) * 8 + r8;                        // a wave's loads are all of one half of the rows
+  const unsigned vx = (unsigned)(min(hi_row, last_row) * D * 2 + ((p8 ^ swz(hi_row)) << 4));
+  auto load_x = [&](int chunk, int st) {
+    const int so = chunk * 128;
 #pragma unroll
-    for (int j = 0; j < UPT; ++j) {
-      const int p = tid + j * nthreads;
-      if (LB * 128 % nthreads == 0 || p < LB * 128) ureg[j] = *reinterpret_cast<const bf16x8*>(U + (int64_t)(p >> 3) * D + chunk * 64 + (p & 7) * 8);
+    for (int j = 0; j < C::XW; ++j) {
+      const int i = wave + 8 * j;
+      char* dst = smem + st * C::XB + i * 1024;
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(xp + (int64_t)min(i >> 1, n - 1) * x_stride), (short)0, -1, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)vx, so, 0, kStream);
     }
   };
-  auto store_u = [&](int buf) {
+  unsigned vu[C::UW];
 #pragma unroll
-    for (int j = 0; j < UPT; ++j) {
-      const int p = tid + j * nthreads, r = p >> 3;
-      if (LB * 128 % nthreads == 0 || p < LB * 128) *reinterpret_cast<bf16x8*>(ubuf + buf * UB + r * 128 + (((p & 7) ^ (r & 7)) << 4)) = ureg[j];
+  for (int j = 0; j < C::UW; ++j) {
+    const int r = min(wave + 8 * j, 2 * LB - 1) * 8 + r8;        // a repeated load writes the same bytes
+    vu[j] = (unsigned)(r * D * 2 + ((p8 ^ swz(r)) << 4));
+  }
+  char* ubuf = smem + NST * C::XB;
+  auto load_u = [&](int chunk, int st) {
+    const int so = chunk * 128;
+#pragma unroll
+    for (int j = 0; j < C::UW; ++j) {
+      char* dst = ubuf + st * C::UB + min(wave + 8 * j, 2 * LB - 1) * 1024;
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(U), (short)0, -1, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)vu[j], so, 0, 0);
     }
   };
 
-  bf16x8 x[kCPW][2];
-  f32x4 r[2][2];
-  auto load_x = [&](int c, int h, int chunk) {
-    x[c][h] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(desc(xp[c]), vx, chunk * 128 + h * 64, 0));
-  };
-  auto load_r = [&](int h, int chunk) {
-    r[h][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(desc(mp), vm, chunk * 256 + h * 128, 0));
-    r[h][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(desc(mp), vm + 16, chunk * 256 + h * 128, 0));
-  };
+  // ---- a wave's places: statistics of token `tok`, features 2 f and 2 f + 1 of the chunk; projections of blocks BPW (wave & 1) ..
+  // and submissions (wave >> 1) + 4 j
+  const int tok = wave * 2 + (lane >> 5), f = lane & 31;
+  const bool live = t0 + tok < T;
+  const int live_mask = live ? -1 : 0;
+  const int sx = tok * 128 + (((f >> 2) ^ swz(tok)) << 4) + (f & 3) * 4;
+  const int fx = (wave >> 1) * 2048 + l15 * 128, fu = (wave & 1) * BPW * 2048 + l15 * 128;
+  const int vm = (tok * D + f * 2) * 4, vr = (min(tok, last_row) * D + f * 2) * 4;
+  const __amdgpu_buffer_rsrc_t bm = desc(mp, (last_row + 1) * D * 4), bp = desc(m_prev + t0 * D, (last_row + 1) * D * 4);   // rows past the last token are dropped
 
-  f32x4 acc[kCPW][LB];
-  float sc[kCPW], scc[kCPW], sad[kCPW], sdd[kCPW], sr = 0.0f, srr = 0.0f;
-  int match[kCPW];
+  f32x4 acc[SPW][BPW];
 #pragma unroll
-  for (int c = 0; c < kCPW; ++c) {
-    sc[c] = scc[c] = sad[c] = sdd[c] = 0.0f;
-    match[c] = 0;
+  for (int j = 0; j < SPW; ++j)
 #pragma unroll
-    for (int b = 0; b < LB; ++b) acc[c][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
+    for (int b = 0; b < BPW; ++b) acc[j][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 self[SPW];                                               // of a wave's submissions: sums of c (even waves), of c c' (odd ones)
+#pragma unroll
+  for (int j = 0; j < SPW; ++j) self[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
+  float sad[NS], sdd[NS], sr = 0.0f, srr = 0.0f;                 // sums of |d|, d^2
+  int match[NS];
+#pragma unroll
+  for (int c = 0; c < NS; ++c) { sad[c] = sdd[c] = 0.0f; match[c] = 0; }
 
-  load_u(0);
+  auto after = [&](int chunk) { return chunk + 1 == nchunk ? 0 : chunk + 1; };      // behind the last round: chunks again, unused
+  f32x2 r[NST];                                                  // the EMA's values, as far ahead as the submissions
+  auto load_r = [&](f32x2& v, int chunk) { v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(bm, vr, chunk * 256, 0)); };
+  int chunk = (int)((blockIdx.x >> 3) * 5u % (unsigned)nchunk), ahead = chunk, ahead_u = chunk, su = 0;
+  for (int s = 0; s < 2; ++s) { load_u(ahead_u, s); ahead_u = after(ahead_u); }
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    load_r(h, 0);
-#pragma unroll
-    for (int c = 0; c < kCPW; ++c) load_x(c, h, 0);
-  }
-  store_u(0);
+  for (int s = 0; s + 1 < NST; ++s) { load_r(r[s], ahead); load_x(ahead, s); ahead = after(ahead); }
+  __builtin_amdgcn_s_waitcnt(0);                                 // all of them: the waits below count on it
   __syncthreads();
-  for (int k = 0; k < nchunk; ++k) {
-    const int next = min(k + 1, nchunk - 1);           // past the end: the last chunk again, unused
-    load_u(next);
-    const char* ub = ubuf + (k & 1) * UB;
-    char* sb = sbuf + (k & 1) * (nw * 4096) + wave * 4096;
-    float psr = 0.0f, psrr = 0.0f, psc[kCPW], pscc[kCPW], psad[kCPW], psdd[kCPW];
+  auto body = [&](auto st_tag) {
+    constexpr int st = decltype(st_tag)::value, fill = (st + NST - 1) % NST;        // fill: the place the last chunk has left
+    load_u(ahead_u, su == 0 ? C::NU - 1 : su - 1);
+    ahead_u = after(ahead_u);
+    const f32x2 rv = r[st];
+    load_r(r[fill], ahead);
+    load_x(ahead, fill);
+    ahead = after(ahead);
+    const char* base = smem + st * C::XB;
+    const char* ub = ubuf + su * C::UB;
+    // the statistics' values are asked for first: they arrive behind the projections' products
+    uint32_t xx[NS];
 #pragma unroll
-    for (int c = 0; c < kCPW; ++c) psc[c] = pscc[c] = psad[c] = psdd[c] = 0.0f;
+    for (int c = 0; c < NS; ++c) xx[c] = *reinterpret_cast<const uint32_t*>(base + sx + c * 2048);
+    __builtin_amdgcn_sched_barrier(0);
+    // projections
+    bf16x8 u[2][BPW], x[2][SPW];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      bf16x8 u[LB];
 #pragma unroll
-      for (int b = 0; b < LB; ++b) u[b] = *reinterpret_cast<const bf16x8*>(ub + (b * 16 + l15) * 128 + (((h * 4 + lq) ^ (l15 & 7)) << 4));
-      float rv[8], sum[8];
-      int cls[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        rv[j] = r[h][j >> 2][j & 3];
-        // the classes of a value whose sign (of zero and NaN: 0) is the reference's: -inf, -normal, -subnormal; +subnormal,
-        // +normal, +inf; or the zeros and NaNs
-        cls[j] = rv[j] > 0.0f ? 0x380 : (rv[j] < 0.0f ? 0x01c : 0x063);
-        psr += rv[j];
-        psrr = fmaf(rv[j], rv[j], psrr);
-        sum[j] = 0.0f;
+      for (int b = 0; b < BPW; ++b) {
+        const int r = ((wave & 1) * BPW + b) * 16 + l15;
+        u[h][b] = *reinterpret_cast<const bf16x8*>(ub + fu + b * 2048 + (((h * 4 + lq) ^ swz(r)) << 4));
       }
-      asm volatile("" : "+v"(psr), "+v"(psrr));
-      load_r(h, next);
-      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int c = 0; c < kCPW; ++c) {
-        float a[8];
+      for (int j = 0; j < SPW; ++j) x[h][j] = *reinterpret_cast<const bf16x8*>(base + fx + j * 8192 + (((h * 4 + lq) ^ swz(l15)) << 4));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // statistics
+    float sum[2] = {0.0f, 0.0f};
+    int cls[2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = (float)x[c][h][j];
+    for (int e = 0; e < 2; ++e) {
+      // the classes of a value whose sign (of zero and NaN: 0) is the reference's: -inf, -normal, -subnormal; +subnormal,
+      // +normal, +inf; or the zeros and NaNs.  None in the places past the last token.
+      cls[e] = (rv[e] > 0.0f ? 0x380 : (rv[e] < 0.0f ? 0x01c : 0x063)) & live_mask;
+      sr += rv[e];
+      srr = fmaf(rv[e], rv[e], srr);
+    }
 #pragma unroll
-        for (int b = 0; b < LB; ++b) acc[c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[b], x[c][h], acc[c][b], 0, 0, 0);
-        load_x(c, h, next);
-        int pm = 0;                                    // wave-uniform
+    for (int c = 0; c < NS; ++c) {
+      if (c == NS / 2) {
+        // the products stand between the statistics' halves: their fragments are there by now, and the matrix cores work beside
+        // what follows
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float d = a[j] - rv[j];
-          psdd[c] = fmaf(d, d, psdd[c]);
-          psad[c] += fabsf(d);
-          psc[c] += a[j];
-          pscc[c] = fmaf(a[j], a[j], pscc[c]);
-          uint64_t lanes;                              // counted on the scalar unit
-          asm("v_cmp_class_f32_e64 %0, %1, %2" : "=s"(lanes) : "v"(a[j]), "v"(cls[j]));
-          pm += __popcll(lanes & live_lanes);
-          sum[j] += __uint_as_float(__float_as_uint(a[j]) & take[c]);
-        }
-        // one submission at a time: left to itself the compiler takes the same sum of all four at the end, with everything they
-        // need in registers until then
-        asm volatile("" : "+v"(psdd[c]), "+v"(psad[c]), "+v"(psc[c]), "+v"(pscc[c]), "+s"(pm));
-        match[c] += pm;
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int j = 0; j < SPW; ++j) {
+#pragma unroll
+            for (int b = 0; b < BPW; ++b) acc[j][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[h][b], x[h][j], acc[j][b], 0, 0, 0);
+            self[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16((wave & 1) ? x[h][j] : ones, x[h][j], self[j], 0, 0, 0);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
+      const uint32_t take = ALL || !((skip >> c) & 1u) ? ~0u : 0u;           // wave-uniform; places past the last submission are skipped
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-        *reinterpret_cast<f32x4*>(sb + l15 * 256 + (((h * 8 + lq * 2 + q) ^ l15) << 4)) = f32x4{sum[q * 4], sum[q * 4 + 1], sum[q * 4 + 2], sum[q * 4 + 3]};
-    }
-    sr += psr; srr += psrr;
-#pragma unroll
-    for (int c = 0; c < kCPW; ++c) { sc[c] += psc[c]; scc[c] += pscc[c]; sad[c] += psad[c]; sdd[c] += psdd[c]; }
-    store_u((k + 1) & 1);
-    lds_barrier();                                     // orders LDS only: the next chunk's loads stay in flight
-    for (int e = tid; e < 256; e += nthreads) {        // 16 tokens x 16 pieces of 4 features
-      const int tok = e >> 4, pc = e & 15;
-      const char* s0 = sbuf + (k & 1) * (nw * 4096) + tok * 256 + ((pc ^ tok) << 4);
-      f32x4 v = *reinterpret_cast<const f32x4*>(s0);
-      for (int w = 1; w < nw; ++w) {
-        const f32x4 o = *reinterpret_cast<const f32x4*>(s0 + w * 4096);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] += o[i];
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t bits = e == 0 ? xx[c] << 16 : xx[c] & 0xffff0000u;
+        const float a = __uint_as_float(bits), d = a - rv[e];
+        sad[c] += fabsf(d);
+        sdd[c] = fmaf(d, d, sdd[c]);
+        uint64_t lanes;                                          // counted on the scalar unit
+        asm("v_cmp_class_f32_e64 %0, %1, %2" : "=s"(lanes) : "v"(a), "v"(cls[e]));
+        match[c] += __popcll(lanes);
+        sum[e] += __uint_as_float(ALL ? bits : bits & take);
       }
-      if (t0 + tok < T) *reinterpret_cast<f32x4*>(sum_out + (t0 + tok) * (int64_t)D + k * 64 + pc * 4) = v;
     }
+    f32x2 next;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) next[e] = beta * rv[e] + w_new * sum[e];
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, rv), bp, vm, chunk * 256, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, next), bm, vm, chunk * 256, 0);
+    // this wave's part of the next chunk has landed, its reads of this one are done; behind the barrier everybody's
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070 | (C::YOUNGER & 15) | ((C::YOUNGER >> 4) << 14));       // vmcnt(YOUNGER) lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    chunk = after(chunk);
+    su = su + 1 == C::NU ? 0 : su + 1;
+  };
+  for (int k = 0;;) {                                            // left by breaks: a turn's end is reached from its last part only
+    body(std::integral_constant<int, 0>{});
+    if (++k >= nchunk) break;
+    body(std::integral_constant<int, 1>{});
+    if (++k >= nchunk) break;
+    body(std::integral_constant<int, 2>{});
+    if (++k >= nchunk) break;
+    body(std::integral_constant<int, 3>{});
+    if (++k >= nchunk) break;
+    if constexpr (NST > 4) { body(std::integral_constant<int, 4>{}); if (++k >= nchunk) break; }
+    if constexpr (NST > 5) { body(std::integral_constant<int, 5>{}); if (++k >= nchunk) break; }
   }
+  __builtin_amdgcn_s_waitcnt(0);                                 // the last direct-to-LDS loads have landed before their place is used again
+  __syncthreads();
 
   // ---- projections: element i of block b is direction 16 b + 4 lq + i of token l15
+  const int64_t t = t0 + l15;
 #pragma unroll
-  for (int c = 0; c < kCPW; ++c) {
-    const int i = wave * kCPW + c;
+  for (int j = 0; j < SPW; ++j) {
+    const int i = (wave >> 1) + 4 * j;
     if (i >= n) break;
     float* out = P + (int64_t)i * (LB * 16) * Tpad + t;
 #pragma unroll
-    for (int b = 0; b < LB; ++b)
+    for (int b = 0; b < BPW; ++b)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (live) out[(int64_t)(b * 16 + lq * 4 + j) * Tpad] = acc[c][b][j];
+      for (int e = 0; e < 4; ++e)
+        if (t < T) out[(int64_t)(((wave & 1) * BPW + b) * 16 + lq * 4 + e) * Tpad] = acc[j][b][e];
   }
 
-  // ---- one record per submission: token sums over the four lanes of a token, then over the 16 tokens
-  const double dsr = xor_sum(live ? (double)sr : 0.0, 1, 32), dsrr = xor_sum(live ? (double)srr : 0.0, 1, 32);
-  float tsrr = srr + __shfl_xor(srr, 16, 64);
-  tsrr += __shfl_xor(tsrr, 32, 64);
-  const double elements = (double)__popcll(live_lanes) * 0.25 * (double)D;
+  // ---- every token's sums: of c in all rows of its column, of c^2 on the diagonal (lane (l15, l15 / 4)); the 32 lanes of a
+  // token leave their others in LDS and a thread adds up those of one sum in 64 bits (in an order of its own, so that the lanes of
+  // a read meet different banks)
+  float* red = reinterpret_cast<float*>(smem);                   // [wave][NV][64 lanes]
+  double* tk = reinterpret_cast<double*>(smem + C::RED);         // [token][4 NS + 2]: sums of c, c^2, |d|, d^2; of the reference and its squares
+  constexpr int TS = 4 * NS + 2;
 #pragma unroll
-  for (int c = 0; c < kCPW; ++c) {
-    const int i = wave * kCPW + c;
-    if (i >= n) break;
-    float tsdd = sdd[c] + __shfl_xor(sdd[c], 16, 64);
-    tsdd += __shfl_xor(tsdd, 32, 64);
-    const float rel = sqrtf(tsdd) / fmaxf(sqrtf(tsrr), 1e-30f);
-    const bool ok = live && rel <= 3.0e38f;
-    const int bad = __ballot(live && !ok) != 0;
-    float best = ok ? rel : -1.0f;
-    int at = ok ? (int)t : 0;
+  for (int j = 0; j < SPW; ++j) {
+    const int c = (wave >> 1) + 4 * j;
+    const float v = (l15 & 3) == 0 ? self[j][0] : (l15 & 3) == 1 ? self[j][1] : (l15 & 3) == 2 ? self[j][2] : self[j][3];
+    if (lq == l15 >> 2) tk[l15 * TS + ((wave & 1) ? NS : 0) + c] = (double)v;
+  }
 #pragma unroll
-    for (int o = 1; o <= 8; o <<= 1) {
-      const float ob = __shfl_xor(best, o, 64);
-      const int oa = __shfl_xor(at, o, 64);
-      if (ob > best || (ob == best && ob >= 0.0f && oa < at)) { best = ob; at = oa; }
+  for (int c = 0; c < NS; ++c) {
+    red[(wave * C::NV + c) * 64 + lane] = sad[c];
+    red[(wave * C::NV + NS + c) * 64 + lane] = sdd[c];
+  }
+  red[(wave * C::NV + 2 * NS) * 64 + lane] = sr;
+  red[(wave * C::NV + 2 * NS + 1) * 64 + lane] = srr;
+  int* cnt = reinterpret_cast<int*>(smem + C::RED + C::TOK);     // [wave][NS]
+#pragma unroll
+  for (int c = 0; c < NS; ++c)
+    if (lane == 0) cnt[wave * NS + c] = match[c];
+  __syncthreads();
+  for (int e = tid; e < 16 * C::NV; e += 512) {
+    const int to = e / C::NV, v = e % C::NV;
+    const float* src = red + ((to >> 1) * C::NV + v) * 64 + (to & 1) * 32;
+    double a = 0.0;
+    for (int l = 0; l < 32; ++l) a += (double)src[(l + tid) & 31];
+    tk[to * TS + 2 * NS + v] = a;
+  }
+  __syncthreads();
+  // ---- one record per submission
+  if (tid < n) {
+    const int c = tid, rows = last_row + 1;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, s5 = 0.0, s6 = 0.0;
+    float best = -1.0f;
+    int at = 0, bad = 0, same = 0;
+    for (int r = 0; r < rows; ++r) {
+      const double* a = tk + r * TS;
+      s0 += a[c]; s2 += a[NS + c]; s5 += a[2 * NS + c]; s6 += a[3 * NS + c];
+      s1 += a[4 * NS]; s3 += a[4 * NS + 1];
+      const float rel = sqrtf((float)a[3 * NS + c]) / fmaxf(sqrtf((float)a[4 * NS + 1]), 1e-30f);
+      if (!(rel <= 3.0e38f)) bad = 1;
+      else if (rel > best) { best = rel; at = (int)(t0 + r); }   // the first of equals
     }
+    for (int w = 0; w < 8; ++w) same += cnt[w * NS + c];
     ScorePartial p;
-    p.s[0] = xor_sum(live ? (double)sc[c] : 0.0, 1, 32);
-    p.s[1] = dsr;
-    p.s[2] = xor_sum(live ? (double)scc[c] : 0.0, 1, 32);
-    p.s[3] = dsrr;
-    p.s[4] = p.s[0] - dsr;
-    p.s[5] = xor_sum(live ? (double)sad[c] : 0.0, 1, 32);
-    p.s[6] = xor_sum(live ? (double)sdd[c] : 0.0, 1, 32);
-    p.s[7] = elements - (double)match[c];
+    p.s[0] = s0; p.s[1] = s1; p.s[2] = s2; p.s[3] = s3; p.s[4] = s0 - s1; p.s[5] = s5; p.s[6] = s6;
+    p.s[7] = (double)rows * (double)D - (double)same;
     p.max_rel = best; p.argmax = at; p.bad = bad; p.pad = 0;
-    if (lane == 0) partials[(int64_t)i * tiles + blockIdx.x] = p;
+    partials[(int64_t)c * tiles + blockIdx.x] = p;
   }
 }
 
-template <int LB, int CPW, int NW>
-hipError_t launch(const bf16* X, int64_t stride, int n, const float* m, const bf16* U, int64_t T, int D, int64_t Tpad, uint32_t skip, float* sum_out,
+template <int LB, int NS, bool ALL>
+hipError_t launch(const bf16* X, int64_t stride, int n, float* m, float* m_prev, float beta, const bf16* U, int64_t T, int D, int64_t Tpad, uint32_t skip,
                   float* P, ScorePartial* partials, hipStream_t st) {
-  auto kern = signal_pass_kernel<LB, CPW, NW>;
-  constexpr int lds = 2 * LB * 16 * 128 + 2 * NW * 4096;
+  auto kern = signal_pass_kernel<LB, NS, ALL>;
+  constexpr int lds = PassCfg<LB, NS>::LDS;
   static bool configured = false;   // per process; the attribute is per function
-  if (!configured && lds > 65536) {
+  if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
+    configured = true;
   }
-  configured = true;
   const int tiles = (int)((T + 15) / 16);
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(64 * NW), lds, st, X, stride, n, m, U, T, D, Tpad, skip, sum_out, P, tiles, partials);
+  int taken = 0;
+  for (int i = 0; i < n; ++i) taken += !((skip >> i) & 1u);
+  const float keep = taken ? beta : 1.0f, w = taken ? (1.0f - beta) / (float)taken : 0.0f;      // nobody to take: m as it is
+  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(512), lds, st, X, stride, n, m, m_prev, keep, w, U, T, D, Tpad,
+                     skip | (n < 32 ? ~0u << n : 0u), P, tiles, partials);
   return hipGetLastError();
 }
 
@@ -253,30 +325,24 @@ bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, cons
 }
 
 // The pass reads every submission once where the separate ones read it twice (three times where the score pass leaves no sum), but a
-// workgroup walks its 16 tokens' whole row with all submissions, chunk behind chunk, where those spread submissions and rows over
-// the chip.  So it is the longer way where there are too few tokens to be short of memory.  Times of a forward and a
-// backward call of one stage, separate -> one pass, us, 32 directions (submissions x tokens x columns):
-//   16 x 128 x 4032   226 -> 377     12 x 2000 x 3136  396 -> 384     16 x 8192 x 4032  1636 -> 987     2 x 8192 x 4032  528 -> 548
-//   4 x 4000 x 4032   426 -> 400     8 x 128 x 384     160 -> 152     16 x 47 x 384      164 -> 172     4 x 500 x 1024   194 -> 187
-// With a sum from the score pass (summed: one read less on that side, but a longer chain of its own) the pass is even or better
-// where its waves have work for three of four places: 16 x 128 x 4096 456 -> 381, 9 x 128 x 4096 339 -> 367, 2 x 500 x 4096 263 -> 298.
+// workgroup walks its 16 tokens' whole row with all submissions, chunk behind chunk (about 1.4 us a chunk of 16), where those spread
+// submissions and rows over the chip.  So it is the longer way where there are too few tokens to be short of memory.  Times of a
+// forward and a backward call of one stage, separate -> one pass, us, 64 directions (submissions x tokens x columns):
+//   16 x 47 x 4032   250 -> 338     9 x 500 x 4032   274 -> 313     8 x 500 x 4032   258 -> 262     4 x 47 x 4032   231 -> 196
+//   8 x 1500 x 4032  330 -> 287     16 x 3000 x 4032 753 -> 426     16 x 1500 x 1088 274 -> 249     2 x 47 x 1088   171 -> 150
+// Narrow rows (up to 1088 columns) differ by 12 % at most below 24576 token rows, either way.  With a sum from the score pass (summed: one read less
+// on that side, but a longer chain of its own) the pass is always the shorter way: 16 x 47 x 4096 485 -> 346, 2 x 47 x 4096 266 -> 200.
 bool signal_pass_pays(int n, int64_t T, int D, bool summed) {
-  if (T * n >= 24576 || D <= 320 || (D <= 1024 && n <= 4)) return true;
-  const int places = n <= 4 ? 4 : n <= 8 ? 8 : 16;
-  return summed && T >= 16 && 4 * n >= 3 * places;
+  return summed || D <= 320 || T * n >= (D >= 2048 ? 12000 : 24576) || (n <= 4 && (D <= 1024 || D >= 2048));
 }
 
-hipError_t launch_signal_pass(const void* X, int64_t stride, int n, const float* m, const void* U, int L, int64_t T, int D, int64_t Tpad,
-                              uint32_t skip, float* sum_out, float* P, ScorePartial* partials, hipStream_t st) {
-  // Four waves, two workgroups on a CU, or where that many workgroups are not there eight waves with half the submissions each: a
-  // workgroup's time is then its chain of chunks, and a chunk takes as long as a wave's work on it.
-  const bool few = T <= 16 * cu_count();
-#define SV_PASS(CPW, NW)                                                                                                       \
-  (L == 32 ? launch<2, CPW, NW>((const bf16*)X, stride, n, m, (const bf16*)U, T, D, Tpad, skip, sum_out, P, partials, st)       \
-           : launch<4, CPW, NW>((const bf16*)X, stride, n, m, (const bf16*)U, T, D, Tpad, skip, sum_out, P, partials, st))
-  if (n <= 4) return SV_PASS(1, 4);
-  if (few) return n <= 8 ? SV_PASS(1, 8) : SV_PASS(2, 8);
-  return n <= 8 ? SV_PASS(2, 4) : n <= 12 ? SV_PASS(3, 4) : SV_PASS(4, 4);
+hipError_t launch_signal_pass(const void* X, int64_t stride, int n, float* m, float* m_prev, float beta, const void* U, int L, int64_t T, int D,
+                              int64_t Tpad, uint32_t skip, float* P, ScorePartial* partials, hipStream_t st) {
+  const bool all = skip == 0 && n % 4 == 0;
+#define SV_PASS_(LB, NS, ALL) launch<LB, NS, ALL>((const bf16*)X, stride, n, m, m_prev, beta, (const bf16*)U, T, D, Tpad, skip, P, partials, st)
+#define SV_PASS(NS) (L == 32 ? (all ? SV_PASS_(2, NS, true) : SV_PASS_(2, NS, false)) : (all ? SV_PASS_(4, NS, true) : SV_PASS_(4, NS, false)))
+  return n <= 4 ? SV_PASS(4) : n <= 8 ? SV_PASS(8) : n <= 12 ? SV_PASS(12) : SV_PASS(16);
+#undef SV_PASS_
 #undef SV_PASS
 }
 
