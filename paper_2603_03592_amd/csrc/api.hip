@@ -1077,7 +1077,7 @@ sv_status sv_sw_against_projection(sv_ctx* c, const void* claims, int64_t claim_
   hipStream_t st = (hipStream_t)stream;
   SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(c->sw_proj, L, T, Tpad, nullptr, 0, L, nullptr, 0, st, ref_proj));
   SV_OP(c, SV_OP_SW_PROJECT, 2.0 * (double)T * D * L * n_claims, st,
-        launch_sw_project(claims, claim_stride, n_claims, claim_dtype, directions, L, D, T, Tpad, claim_proj_out, st));
+        launch_sw_project(claims, claim_stride, n_claims, claim_dtype, directions, L, D, T, Tpad, claim_proj_out, st, /*pad=*/true));
   // rows of one LDS chunk: the last sort pass adds up |a - b| against the reference and leaves the projections as they are
   SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(claim_proj_out, n_claims * L, T, Tpad, c->sw_proj, 1, L, c->sw_w1, 0, st));
   SV_HIP(c, launch_sw_finalize(c->sw_w1, n_claims, L, T, tau, sw_out, results_dev, st));

@@ -159,7 +159,7 @@ hipError_t launch_replace(void* signals, int64_t stride, int n, int dtype, const
 // sw.hip: sliced Wasserstein.  P holds rows of Tpad = sw_padded_len(T) floats, L rows per tensor.
 int64_t sw_padded_len(int64_t T);
 hipError_t launch_sw_project(const void* X, int64_t stride, int count, int dtype, const void* U, int L, int D, int64_t T, int64_t Tpad,
-                             float* P, hipStream_t st);
+                             float* P, hipStream_t st, bool pad = false);      // pad: infinities from T to Tpad
 // One launch for a single reference tensor (into Pref) and `count` submissions (into P); only for the dtype pairs
 // sw_project_with_ref_supported names.
 bool sw_project_with_ref_supported(int dtype, int ref_dtype);

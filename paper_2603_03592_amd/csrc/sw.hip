@@ -16,12 +16,12 @@ namespace {
 constexpr int kSortChunkMax = (int)kSwSortChunkMax;   // floats sorted in LDS by one workgroup (64 KB)
 
 // ---------------------------------------------------------------------------------------------
-// Projection.  A workgroup of 4 waves owns 256 tokens (64 per wave, two blocks of 32) and all
+// Projection.  A workgroup of 4 waves owns 128 or 256 tokens (kSwTB blocks of 32 per wave) and all
 // L = 32 * LB directions; the contraction runs over the feature axis in steps of 16 on
 // v_mfma_f32_32x32x16_bf16 with the directions in the A slot, so a lane ends up with one token
 // (lane & 31) and the directions 8q + 4 (lane >> 5) + r of each block of 32.
 // The signal is streamed in chunks of 128 bytes per row (64 bf16 or 32 fp32 features): the
-// [256 rows x 128 B] tile goes global -> LDS with global_load_lds (8 lanes fetch one row's 128
+// [rows x 128 B] tile goes global -> LDS with global_load_lds (8 lanes fetch one row's 128
 // contiguous bytes; the 16-byte pieces are XOR-swizzled by choosing which piece a lane fetches),
 // three tiles deep, so that two chunks are always in flight and the wait at the end of a chunk
 // leaves the youngest one outstanding.  The matching [L x chunk] piece of the directions takes the same
@@ -53,20 +53,23 @@ __device__ __forceinline__ void mac_f32(const bf16x8 (&u)[LB], const f32x4& x0, 
   mac_bf16<LB>(u, hi, acc);
 }
 
-constexpr int kSwTile = 256 * 128;     // bytes of one signal tile in LDS
+// Blocks of 32 tokens per wave: with up to 64 directions one, so that a tile's three chunks take 72 KB and two workgroups share a
+// CU, one streaming while the other starts or ends; with more the directions' chunk is as large as the signal's and two blocks share it.
+template <int LB> constexpr int kSwTB = LB <= 2 ? 1 : 2;
+template <int LB> constexpr int kSwTile = kSwTB<LB> * 128 * 128;     // bytes of one signal tile in LDS
 constexpr int kSwDepth = 3;            // signal tiles (and direction chunks) in LDS: two chunks in flight
 
 template <int N> __device__ __forceinline__ void wait_vm_lds_barrier() {      // wait until at most N vector-memory loads are in flight
-  static_assert(N >= 9 && N <= 12, "8 signal loads + 1..4 direction loads per chunk");
-  if (N == 9) asm volatile("s_waitcnt vmcnt(9) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else if (N == 10) asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else if (N == 11) asm volatile("s_waitcnt vmcnt(11) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  static_assert(N >= 5 && N <= 12, "4 or 8 signal loads + 1..4 direction loads per chunk");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | N);                          // vmcnt(N) lgkmcnt(0)
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <typename E, int LB>
 __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, const bf16* __restrict__ U, int D, int64_t T, int64_t Tpad,
-                                                float* __restrict__ out, char* smem, unsigned sig) {
+                                                float* __restrict__ out, char* smem, unsigned sig, bool pad) {
   constexpr bool kBf16 = sizeof(E) == 2;
   constexpr int KC = 128 / (int)sizeof(E);            // features per chunk
   constexpr int NSTEP = KC / 16;                      // MFMA k steps per chunk
@@ -75,14 +78,15 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
   constexpr int UINSTR = UTILE / 1024;                // direct-to-LDS instructions per directions' chunk
   constexpr int UW = (UINSTR + 3) / 4;                // ... per wave (every wave issues the same number: the waits count them)
   constexpr int RPI = 1024 / UPITCH;                  // direction rows per instruction: 8 or 16
+  constexpr int TB = kSwTB<LB>, XI = 4 * TB, XTILE = kSwTile<LB>;      // direct-to-LDS instructions of a wave per signal chunk
   char* xs = smem;                                    // kSwDepth signal tiles
-  char* us = smem + kSwDepth * kSwTile;               // kSwDepth direction chunks
+  char* us = smem + kSwDepth * XTILE;               // kSwDepth direction chunks
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l31 = lane & 31, lhi = lane >> 5;
-  const int64_t tile0 = (int64_t)blockIdx.x * 256;
+  const int64_t tile0 = (int64_t)blockIdx.x * (128 * TB);
   // direct-to-LDS plan: instruction i of this wave covers the tile rows (wave + 4 i) * 8 .. + 7
-  int64_t xoff[8];
+  int64_t xoff[XI];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < XI; ++i) {
     const int r = (wave + 4 * i) * 8 + (lane >> 3), c = (lane & 7) ^ sw_swz(r);
     xoff[i] = min(tile0 + r, T - 1) * (int64_t)D * (int64_t)sizeof(E) + c * 16;     // rows past the end re-read the last one
   }
@@ -113,13 +117,13 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)U + uoff[j] + (int64_t)ck * UPITCH),
                                        (__attribute__((address_space(3))) void*)(us + stage * UTILE + ulds[j]), 16, 0, 0);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < XI; ++i)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xbase + xoff[i] + (int64_t)ck * 128),
-                                       (__attribute__((address_space(3))) void*)(xs + stage * kSwTile + (wave + 4 * i) * 1024), 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(xs + stage * XTILE + (wave + 4 * i) * 1024), 16, 0, 0);
   };
-  f32x16 acc[2][LB];
+  f32x16 acc[TB][LB];
 #pragma unroll
-  for (int tb = 0; tb < 2; ++tb)
+  for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
     for (int b = 0; b < LB; ++b)
 #pragma unroll
@@ -127,12 +131,12 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
 
   dma(0, 0);
   dma(nchunk > 1 ? 1 : 0, 1);                          // a second chunk is always issued: the waits below count on it
-  wait_vm_lds_barrier<8 + UW>();
+  wait_vm_lds_barrier<XI + UW>();
   int st = 0;                                          // LDS tile of chunk kc
   for (int kc = 0; kc < nchunk; ++kc) {
     const int st2 = st == 0 ? kSwDepth - 1 : st - 1;   // tile of chunk kc + 2: the one chunk kc - 1 was read from
     dma(kc + 2 < nchunk ? kc + 2 : nchunk - 1, st2);   // past the end: re-read the last chunk (never used)
-    const char* xt = xs + st * kSwTile;
+    const char* xt = xs + st * XTILE;
     const char* ub = us + st * UTILE;
 #pragma unroll
     for (int s = 0; s < NSTEP; ++s) {
@@ -143,8 +147,8 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
         u[b] = *reinterpret_cast<const bf16x8*>(ub + r * UPITCH + (((2 * s + lhi) ^ u_swz(r)) << 4));
       }
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        const int r = wave * 64 + tb * 32 + l31;
+      for (int tb = 0; tb < TB; ++tb) {
+        const int r = (wave * TB + tb) * 32 + l31;
         if (kBf16) {
           const bf16x8 x = *reinterpret_cast<const bf16x8*>(xt + r * 128 + (((2 * s + lhi) ^ sw_swz(r)) << 4));
           mac_bf16<LB>(u, x, acc[tb]);
@@ -158,21 +162,28 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
     }
     // chunk kc + 1 has landed (only the loads of chunk kc + 2 may still be in flight) and this wave is done with
     // tile st; after the barrier that holds for the whole workgroup
-    wait_vm_lds_barrier<8 + UW>();
+    wait_vm_lds_barrier<XI + UW>();
     st = st + 1 >= kSwDepth ? 0 : st + 1;
   }
   __builtin_amdgcn_s_waitcnt(0);                       // every direct-to-LDS load has landed before the LDS is given back
-  const float inf = __builtin_huge_valf();             // padding sorts behind every real sample
-  const int64_t t0 = tile0 + wave * 64;
+  const int64_t t0 = tile0 + wave * (32 * TB);
 #pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
+  for (int tb = 0; tb < TB; ++tb) {
     const int64_t t = t0 + tb * 32 + l31;
-    if (t >= Tpad) continue;
+    if (t >= T) continue;
 #pragma unroll
     for (int b = 0; b < LB; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        out[(int64_t)(b * 32 + (i >> 2) * 8 + lhi * 4 + (i & 3)) * Tpad + t] = t < T ? acc[tb][b][i] : inf;
+        out[(int64_t)(b * 32 + (i >> 2) * 8 + lhi * 4 + (i & 3)) * Tpad + t] = acc[tb][b][i];
+  }
+  // The sort does not look at a row's padding.  Where the rows are the caller's it is filled with infinities all the same, a share by
+  // every workgroup of the signal (tiles past the last token, which did it before, read and multiplied for nothing: 191 -> 172 us
+  // for 33 signals of 6000 x 2048).
+  if (pad) {
+    const int64_t w = (Tpad - T + gridDim.x - 1) / gridDim.x, p0 = T + (int64_t)blockIdx.x * w;
+    const int n = (int)max((int64_t)0, min(w, Tpad - p0));
+    for (int e = tid; e < n * LB * 32; e += 256) out[(int64_t)(e / n) * Tpad + p0 + e % n] = __builtin_huge_valf();
   }
 }
 
@@ -182,16 +193,16 @@ __device__ __forceinline__ void sw_project_body(const char* __restrict__ xbase, 
 template <typename E, typename E2, int LB>
 __global__ __launch_bounds__(256) void sw_project_kernel(const E* __restrict__ X, int64_t x_stride, const E2* __restrict__ X2, int n2,
                                                          const bf16* __restrict__ U, int D, int64_t T, int64_t Tpad,
-                                                         float* __restrict__ P, float* __restrict__ P2) {
+                                                         float* __restrict__ P, float* __restrict__ P2, bool pad) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int y = blockIdx.y;                           // uniform
   if constexpr (sizeof(E) == sizeof(E2)) {
     const char* xb = y < n2 ? (const char*)X2 : (const char*)(X + (int64_t)(y - n2) * x_stride);
     float* out = y < n2 ? P2 : P + (int64_t)(y - n2) * (LB * 32) * Tpad;
-    sw_project_body<E, LB>(xb, U, D, T, Tpad, out, smem, y < n2 ? y : y - n2);
+    sw_project_body<E, LB>(xb, U, D, T, Tpad, out, smem, y < n2 ? y : y - n2, pad);
   } else {
-    if (y < n2) sw_project_body<E2, LB>((const char*)X2, U, D, T, Tpad, P2, smem, y);
-    else sw_project_body<E, LB>((const char*)(X + (int64_t)(y - n2) * x_stride), U, D, T, Tpad, P + (int64_t)(y - n2) * (LB * 32) * Tpad, smem, y - n2);
+    if (y < n2) sw_project_body<E2, LB>((const char*)X2, U, D, T, Tpad, P2, smem, y, pad);
+    else sw_project_body<E, LB>((const char*)(X + (int64_t)(y - n2) * x_stride), U, D, T, Tpad, P + (int64_t)(y - n2) * (LB * 32) * Tpad, smem, y - n2, pad);
   }
 }
 
@@ -433,28 +444,29 @@ __global__ __launch_bounds__(256) void sw_proj_ema_kernel(float* __restrict__ pm
 
 template <typename E, typename E2, int LB>
 hipError_t project_launch(const void* X, int64_t stride, int count, const void* X2, int n2, const void* U, int D, int64_t T, int64_t Tpad,
-                          float* P, float* P2, hipStream_t st) {
+                          float* P, float* P2, bool pad, hipStream_t st) {
   auto kern = sw_project_kernel<E, E2, LB>;
-  constexpr int lds = kSwDepth * (kSwTile + LB * 32 * 128);   // direction chunks of 128 (bf16 signal) or 64 bytes per row
+  constexpr int lds = kSwDepth * (kSwTile<LB> + LB * 32 * 128);   // direction chunks of 128 (bf16 signal) or 64 bytes per row
   static bool configured = false;   // per process; the attribute is per function
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  dim3 grid((unsigned)((Tpad + 255) / 256), (unsigned)(count + n2));
-  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, (const E*)X, stride, (const E2*)X2, n2, (const bf16*)U, D, T, Tpad, P, P2);
+  constexpr int rows = 128 * kSwTB<LB>;
+  dim3 grid((unsigned)((T + rows - 1) / rows), (unsigned)(count + n2));
+  hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, (const E*)X, stride, (const E2*)X2, n2, (const bf16*)U, D, T, Tpad, P, P2, pad);
   return hipGetLastError();
 }
 
 template <typename E, typename E2>
 hipError_t project_dispatch(const void* X, int64_t stride, int count, const void* X2, int n2, const void* U, int L, int D, int64_t T,
-                            int64_t Tpad, float* P, float* P2, hipStream_t st) {
+                            int64_t Tpad, float* P, float* P2, bool pad, hipStream_t st) {
   switch (L / 32) {
-    case 1: return project_launch<E, E2, 1>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, st);
-    case 2: return project_launch<E, E2, 2>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, st);
-    case 3: return project_launch<E, E2, 3>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, st);
-    default: return project_launch<E, E2, 4>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, st);
+    case 1: return project_launch<E, E2, 1>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, pad, st);
+    case 2: return project_launch<E, E2, 2>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, pad, st);
+    case 3: return project_launch<E, E2, 3>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, pad, st);
+    default: return project_launch<E, E2, 4>(X, stride, count, X2, n2, U, D, T, Tpad, P, P2, pad, st);
   }
 }
 
@@ -467,10 +479,10 @@ int64_t sw_padded_len(int64_t T) {
 }
 
 hipError_t launch_sw_project(const void* X, int64_t stride, int count, int dtype, const void* U, int L, int D, int64_t T, int64_t Tpad,
-                             float* P, hipStream_t st) {
+                             float* P, hipStream_t st, bool pad) {
   if (count <= 0) return hipSuccess;
-  return dtype == SV_BF16 ? project_dispatch<bf16, bf16>(X, stride, count, nullptr, 0, U, L, D, T, Tpad, P, nullptr, st)
-                          : project_dispatch<float, float>(X, stride, count, nullptr, 0, U, L, D, T, Tpad, P, nullptr, st);
+  return dtype == SV_BF16 ? project_dispatch<bf16, bf16>(X, stride, count, nullptr, 0, U, L, D, T, Tpad, P, nullptr, pad, st)
+                          : project_dispatch<float, float>(X, stride, count, nullptr, 0, U, L, D, T, Tpad, P, nullptr, pad, st);
 }
 
 bool sw_project_with_ref_supported(int dtype, int ref_dtype) { return dtype == ref_dtype || (dtype == SV_BF16 && ref_dtype == SV_F32); }
@@ -478,9 +490,9 @@ bool sw_project_with_ref_supported(int dtype, int ref_dtype) { return dtype == r
 hipError_t launch_sw_project_with_ref(const void* X, int64_t stride, int count, int dtype, const void* ref, int ref_dtype, const void* U,
                                       int L, int D, int64_t T, int64_t Tpad, float* P, float* Pref, hipStream_t st) {
   if (count <= 0 || !sw_project_with_ref_supported(dtype, ref_dtype)) return hipErrorInvalidValue;
-  if (dtype == SV_BF16 && ref_dtype == SV_F32) return project_dispatch<bf16, float>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, st);
-  return dtype == SV_BF16 ? project_dispatch<bf16, bf16>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, st)
-                          : project_dispatch<float, float>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, st);
+  if (dtype == SV_BF16 && ref_dtype == SV_F32) return project_dispatch<bf16, float>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, false, st);
+  return dtype == SV_BF16 ? project_dispatch<bf16, bf16>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, false, st)
+                          : project_dispatch<float, float>(X, stride, count, ref, 1, U, L, D, T, Tpad, P, Pref, false, st);
 }
 
 hipError_t launch_sw_sort(float* P, int n_seg, int64_t T, int64_t Tpad, const float* ref, int ref_shared, int L, float* w1,
