@@ -150,8 +150,8 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same statistics for several submissions against ONE shared reference, rows of any multiple of 2 KB.  A wave
-// owns a token and takes its row in parts of NU KB (NU = 2 or 4): it loads the reference part into registers once,
+// The same statistics for several submissions against ONE shared reference.  A wave
+// owns a token and takes its row in parts of NU KB (NU = 2 .. 4): it loads the reference part into registers once,
 // forms the reference's own sums and -- for the sign-flip ratio -- one class mask per element, and then streams the
 // same part of every submission of its group past them, the next submission's loads in flight while the current one
 // is reduced.  Compared with score_tokens_kernel the reference is read once per group instead of once per submission,
@@ -159,6 +159,8 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
 // all-statistics pass from the vector ALUs' bound to the memory's.
 //   sign test: sign(a) == sign(b), with sign(0) = sign(NaN) = 0, is one v_cmp_class of a against the set of classes
 //   that b's sign allows; the matches are counted on the scalar unit from the lane mask.
+// TAIL: rows of any multiple of 8 elements; the last part's lanes past the row's end see zeros on both sides and no sign class.
+// ONCE: the submissions' loads are non-temporal (128 of 8192 x 4096 in bf16 read at 5.4 -> 6.2 TB/s).
 // Lane c of a wave adds up submission c's sums over the parts of a token (a predicated add after each wave
 // reduction) and closes the token -- per-token relative L2, running sums -- for all submissions at once; the four
 // waves' sums are folded per submission at the end, into the same per-(submission, tile) records as above.
@@ -169,22 +171,27 @@ constexpr int kGroupMax = 32;                 // submissions per group (<= 64: o
 
 template <typename E, int N> struct RawUnit;                     // N consecutive elements as they come from memory
 template <> struct RawUnit<bf16, 8> { bf16x8 v; __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const bf16x8*>(p); }
+                                      __device__ __forceinline__ void load_once(const bf16* p) { v = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(p)); }
                                       __device__ __forceinline__ float get(int i) const { return static_cast<float>(v[i]); } };
 template <> struct RawUnit<bf16, 4> { bf16x4 v; __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const bf16x4*>(p); }
+                                      __device__ __forceinline__ void load_once(const bf16* p) { v = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(p)); }
                                       __device__ __forceinline__ float get(int i) const { return static_cast<float>(v[i]); } };
 template <> struct RawUnit<float, 4> { f32x4 v; __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const f32x4*>(p); }
+                                      __device__ __forceinline__ void load_once(const float* p) { v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p)); }
                                        __device__ __forceinline__ float get(int i) const { return v[i]; } };
 template <> struct RawUnit<float, 8> { f32x4 a, b; __device__ __forceinline__ void load(const float* p) { a = *reinterpret_cast<const f32x4*>(p); b = *reinterpret_cast<const f32x4*>(p + 4); }
+                                      __device__ __forceinline__ void load_once(const float* p) { a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p)); b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p + 4)); }
                                        __device__ __forceinline__ float get(int i) const { return i < 4 ? a[i] : b[i - 4]; } };
 
-template <typename EC, typename ER, int NU, bool FULL, bool SUM>
+template <typename EC, typename ER, int NU, bool FULL, bool SUM, bool TAIL, bool ONCE>
 __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__ claims, int64_t claim_stride, const ER* __restrict__ ref,
                                                           int64_t T, int D, int n_claims, int G, int n_groups, int tiles_per_claim,
                                                           float* __restrict__ token_scores, ScorePartial* __restrict__ partials,
                                                           uint32_t skip, float* __restrict__ sum_out) {
   constexpr int EPU = 16 / (int)sizeof(EC);            // elements per 16-byte unit of a submission's row
   constexpr int PE = NU * 64 * EPU;                    // elements per part
-  const int parts = D / PE;
+  const int parts = TAIL ? (D + PE - 1) / PE : D / PE;
+  static_assert(!(SUM && TAIL), "the sum is written for whole parts");
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int group = slot % n_groups;
   const int tile = xcd * ((tiles_per_claim + 7) >> 3) + slot / n_groups;
@@ -204,8 +211,12 @@ __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__
     auto fetch = [&](RawUnit<EC, EPU> (&buf)[NU], int q) {       // q = part * nc + submission
       const int part = q / nc, c = q - part * nc;
       const EC* p = cb + (int64_t)c * claim_stride + part * PE;
+      // TAIL: lanes past the row's end load its last unit; what they hold counts as zero against a zero of the reference
 #pragma unroll
-      for (int m = 0; m < NU; ++m) buf[m].load(p + m * 64 * EPU);
+      for (int m = 0; m < NU; ++m) {
+        const EC* q_m = TAIL ? p + min(m * 64 * EPU, D - EPU - lane * EPU - part * PE) : p + m * 64 * EPU;
+        if (ONCE) buf[m].load_once(q_m); else buf[m].load(q_m);
+      }
     };
     float sr = 0, srr = 0;                             // the reference's sums: per lane until the token is closed
     float tsdd = 0, tsc = 0, tscc = 0, tsad = 0;       // lane c: submission c's sums over the parts done so far
@@ -219,10 +230,11 @@ __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__
 #pragma unroll
       for (int m = 0; m < NU; ++m) {
         RawUnit<ER, EPU> u;
-        u.load(r + m * 64 * EPU);
+        const bool in = !TAIL || part * PE + (m * 64 + lane) * EPU < D;
+        u.load(TAIL ? r + min(m * 64 * EPU, D - EPU - lane * EPU - part * PE) : r + m * 64 * EPU);
 #pragma unroll
         for (int j = 0; j < EPU; ++j) {
-          const float b = u.get(j);
+          const float b = in ? u.get(j) : 0.0f;
           rv[m][j] = b;
           srr = fmaf(b, b, srr);
           if (SUM) ssum[m][j] = 0.0f;
@@ -230,6 +242,7 @@ __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__
             sr += b;
             // classes a may have for sign(a) == sign(b): {+denormal, +normal, +inf}, {-inf, -normal, -denormal}, {NaNs, -0, +0}
             cls[m][j] = b > 0.0f ? 0x380 : (b < 0.0f ? 0x01C : 0x063);
+            if (TAIL) cls[m][j] = in ? cls[m][j] : 0;
           }
         }
       }
@@ -241,7 +254,7 @@ __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__
         for (int m = 0; m < NU; ++m)
 #pragma unroll
           for (int j = 0; j < EPU; ++j) {
-            const float a = buf[m].get(j), d = a - rv[m][j];
+            const float a = !TAIL || part * PE + (m * 64 + lane) * EPU < D ? buf[m].get(j) : 0.0f, d = a - rv[m][j];
             sdd = fmaf(d, d, sdd);
             if (SUM && add) ssum[m][j] += a;
             if (FULL) {
@@ -500,29 +513,44 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     const dim3 grid((unsigned)(8 * ((tiles + 7) / 8) * nc)), block(256);
     const int64_t row_bytes = (int64_t)D * csz;
     const bool full = (mask & (SV_M_L1 | SV_M_ZL2 | SV_M_SFR)) != 0;
-    // shared reference and several submissions (or their sum wanted), rows of a multiple of 2 KB: the kernel that
-    // keeps the reference in registers
-    if (ref_stride == 0 && row_bytes % 2048 == 0 && (sum_out || nc >= 2)) {
+    // Shared reference and several submissions (or their sum wanted): the kernel that keeps the reference in registers.  Rows that are
+    // no multiple of 2 KB take it from two workgroups per CU on; below, its tokens' chains are longer than what it saves.  Without -> with
+    // it, us: 78 x 3243 x 2304 308 -> 208, 64 x 2500 x 2880 241 -> 174, 8 x 4935 x 1280 (618 workgroups) 42.5 -> 35.6, 2 x 8000 x 1216
+    // (500) 23.4 -> 23.2, 4 x 4000 x 3520 (250) 36 -> 49, 16 x 1000 x 2368 (252) 28 -> 40.
+    int G = sum_out ? nc : 16;
+    while (!sum_out && G > 4 && tiles * ((nc + G - 1) / G) < 1024) G >>= 1;
+    const int n_groups = (nc + G - 1) / G;
+    G = (nc + n_groups - 1) / n_groups;                  // groups alike: every group reads the reference once
+    const bool whole = row_bytes % 2048 == 0;
+    if (ref_stride == 0 && (sum_out || nc >= 2) && (whole || tiles * n_groups >= 2 * cu_count())) {
       if (sum_out && (nc != n_claims || nc * tiles > scratch_elems)) return hipErrorInvalidValue;   // one launch, one group
-      int G = sum_out ? nc : 16;
-      while (!sum_out && G > 4 && tiles * ((nc + G - 1) / G) < 1024) G >>= 1;
-      const int n_groups = (nc + G - 1) / G;
       const dim3 ggrid((unsigned)(8 * ((tiles + 7) / 8) * n_groups));
-#define SV_LAUNCH_PARTS5(EC, ER, NU, FULL, SUM)                                                                       \
-  hipLaunchKernelGGL((score_parts_kernel<EC, ER, NU, FULL, SUM>), ggrid, block, 0, st, (const EC*)cp, claim_stride, (const ER*)rp, T, D, nc, \
-                     G, n_groups, (int)tiles, ts, scratch, skip, sum_out)
-#define SV_LAUNCH_PARTS3(EC, ER, NU)                                                                                  \
-  do {                                                                                                                \
-    if (sum_out) { if (full) SV_LAUNCH_PARTS5(EC, ER, NU, true, true); else SV_LAUNCH_PARTS5(EC, ER, NU, false, true); } \
-    else { if (full) SV_LAUNCH_PARTS5(EC, ER, NU, true, false); else SV_LAUNCH_PARTS5(EC, ER, NU, false, false); }     \
-  } while (0)
+#define SV_LAUNCH_PARTS5(EC, ER, NU, FULL, SUM, TAIL, ONCE)                                                           \
+  hipLaunchKernelGGL((score_parts_kernel<EC, ER, NU, FULL, SUM, TAIL, ONCE>), ggrid, block, 0, st, (const EC*)cp, claim_stride, (const ER*)rp, T, D, \
+                     nc, G, n_groups, (int)tiles, ts, scratch, skip, sum_out)
+#define SV_LAUNCH_PARTS4(EC, ER, NU, SUM, TAIL, ONCE)                                                                 \
+  do { if (full) SV_LAUNCH_PARTS5(EC, ER, NU, true, SUM, TAIL, ONCE); else SV_LAUNCH_PARTS5(EC, ER, NU, false, SUM, TAIL, ONCE); } while (0)
+#define SV_LAUNCH_PARTS3(EC, ER, NU, TAIL)                                                                            \
+  do { if (once) SV_LAUNCH_PARTS4(EC, ER, NU, false, TAIL, true); else SV_LAUNCH_PARTS4(EC, ER, NU, false, TAIL, false); } while (0)
+#define SV_LAUNCH_WHOLE(EC, ER, NU)                                                                                   \
+  do { if (sum_out) SV_LAUNCH_PARTS4(EC, ER, NU, true, false, false); else SV_LAUNCH_PARTS3(EC, ER, NU, false); } while (0)
 #define SV_LAUNCH_PARTS(EC, ER)                                                                                       \
-  do { if (row_bytes % 4096 == 0) SV_LAUNCH_PARTS3(EC, ER, 4); else SV_LAUNCH_PARTS3(EC, ER, 2); } while (0)
+  do { if (!whole) { if (nu == 4) SV_LAUNCH_PARTS3(EC, ER, 4, true); else if (nu == 3) SV_LAUNCH_PARTS3(EC, ER, 3, true); else SV_LAUNCH_PARTS3(EC, ER, 2, true); } \
+       else if (row_bytes % 4096 == 0) SV_LAUNCH_WHOLE(EC, ER, 4); else SV_LAUNCH_WHOLE(EC, ER, 2); } while (0)
+      // more than the memory-side cache holds (256 MB): loads that leave nothing behind.  128 x 8192 x 4096 1587 -> 1394 us, 16 x 4096 x
+      // 4096 (0.5 GB) 121 -> 114.5; but 4 x 2048 x 2048 (33 MB) 27.7 -> 28.6
+      const bool once = row_bytes * T * nc > ((int64_t)256 << 20);
+      const int units = (int)((row_bytes + 1023) / 1024);
+      int nu = 4;                                        // units per part: as few as possible for nothing
+      for (int u = 3; u >= 2; --u)
+        if ((units + u - 1) / u * u < (units + nu - 1) / nu * nu) nu = u;
       if (claim_dtype == SV_BF16 && ref_dtype == SV_BF16) SV_LAUNCH_PARTS(bf16, bf16);
       else if (claim_dtype == SV_BF16) SV_LAUNCH_PARTS(bf16, float);
       else if (ref_dtype == SV_BF16) SV_LAUNCH_PARTS(float, bf16);
       else SV_LAUNCH_PARTS(float, float);
 #undef SV_LAUNCH_PARTS
+#undef SV_LAUNCH_WHOLE
+#undef SV_LAUNCH_PARTS4
 #undef SV_LAUNCH_PARTS3
 #undef SV_LAUNCH_PARTS5
       hipError_t e = launch_score_finalize(scratch, nc, (int)tiles, T, D, mask, tau4, reduce, results + c0, st);
