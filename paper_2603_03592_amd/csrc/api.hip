@@ -1167,7 +1167,7 @@ sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32
 
 sv_status sv::check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, float* m, float* m_prev, float beta, int64_t T, int D,
                             uint32_t metric_mask, const float* tau4, sv_result* results, const uint8_t* skip_host, const void* directions, int L,
-                            const float* ref_proj, float* claim_proj_out, float* sw_out, bool* updated, hipStream_t st) {
+                            const float* ref_proj, const float* ref_sorted, float* claim_proj_out, float* sw_out, bool* updated, hipStream_t st) {
   *updated = false;
   const int64_t Tpad = sw_padded_len(T), tiles = (T + 15) / 16;
   if (!(c->flags & SV_FLAG_SLICED_W) || !m_prev || !ref_proj || !claim_proj_out || T > c->max_tokens || Tpad > kSwSortChunkMax ||
@@ -1181,8 +1181,11 @@ sv_status sv::check_signals(sv_ctx* c, const void* signals, int64_t stride, int 
         launch_signal_pass(signals, stride, n, m, m_prev, beta, directions, L, T, D, Tpad, skip, claim_proj_out, c->score_scratch, st));
   *updated = true;
   SV_HIP(c, launch_score_finalize(c->score_scratch, n, (int)tiles, T, D, metric_mask, tau4, SV_REDUCE_GLOBAL, results, st));
-  SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(c->sw_proj, L, T, Tpad, nullptr, 0, L, nullptr, 0, st, ref_proj));
-  SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(claim_proj_out, n * L, T, Tpad, c->sw_proj, 1, L, c->sw_w1, 0, st));
+  if (!ref_sorted) {
+    SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(c->sw_proj, L, T, Tpad, nullptr, 0, L, nullptr, 0, st, ref_proj));
+    ref_sorted = c->sw_proj;
+  }
+  SV_OP(c, SV_OP_SW_SORT, 0, st, launch_sw_sort(claim_proj_out, n * L, T, Tpad, ref_sorted, 1, L, c->sw_w1, 0, st));
   SV_HIP(c, launch_sw_finalize(c->sw_w1, n, L, T, std::numeric_limits<float>::infinity(), sw_out, nullptr, st));
   return SV_OK;
 }

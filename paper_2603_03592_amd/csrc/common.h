@@ -138,10 +138,10 @@ hipError_t launch_signal_pass(const void* X, int64_t stride, int n, float* m, fl
                               int64_t Tpad, uint32_t skip, float* P, ScorePartial* partials, hipStream_t st);
 // api.hip: what sv_score_and_sum, sv_ema_from_sum and sv_sw_against_projection do together for the verifier loop, over one pass of the
 // submissions; SV_EUNSUPPORTED (and nothing enqueued) where they have to be called one after the other.  *updated: the pass is
-// enqueued, so m holds the next EMA and m_prev the present one, whatever is returned
+// enqueued, so m holds the next EMA and m_prev the present one, whatever is returned.  ref_sorted: ref_proj's rows sorted, if at hand
 sv_status check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, float* m, float* m_prev, float beta, int64_t T, int D,
                         uint32_t metric_mask, const float* tau4, sv_result* results, const uint8_t* skip_host, const void* directions, int L,
-                        const float* ref_proj, float* claim_proj_out, float* sw_out, bool* updated, hipStream_t st);
+                        const float* ref_proj, const float* ref_sorted, float* claim_proj_out, float* sw_out, bool* updated, hipStream_t st);
 // gemm_mfma.hip: compute units of the device (256 on a whole MI355X); grids and the rules that ask whether a launch fills the chip count with it
 int cu_count();
 // api.hip: error text for entry points without a context (sv_last_error(NULL) returns it on the same thread)

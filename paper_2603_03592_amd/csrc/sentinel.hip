@@ -25,16 +25,19 @@ struct sv_sentinel {
   std::vector<sv_policy*> pol[2];
   std::vector<uint8_t> tainted;            // [stage * d + r] of the current iteration
   bool warm = true;
-  sv_result* res_dev = nullptr;
-  float* sw_dev = nullptr;
   uint8_t* mask_dev = nullptr;             // two rows of d bytes: replacement mask, EMA exclusion mask
   float* sum_dev = nullptr;                // [T, D]: sum over the signals not excluded beforehand, written by the score pass; where one
                                            // pass has updated the EMA as well: what it was before
   // sliced Wasserstein against the EMA without projecting the EMA: its projections follow from the signals' (linearity)
   std::vector<float*> pm[2];               // [kind][stage] device fp32 [n_dirs, Tpad]: <u_l, m_t>, kept up to date with m
+  // their rows sorted, for the next call's one pass: made where they are updated, behind the verdicts, while the host is on its
+  // way to the next call (at the start of that call the stream waited 27 us for them); sorted_ok: they are those of pm as it is
+  std::vector<float*> ps[2];
+  std::vector<uint8_t> sorted_ok[2];
   float* cproj = nullptr;                  // [d, n_dirs, Tpad]: the current signals' projections
   int64_t n_calls = 0, n_from_sum = 0, n_from_signals = 0, n_sw_carried = 0;
-  // pinned staging
+  // pinned host memory; the statistics' last kernels write their few scalars straight into the first two, and the call waits for the
+  // stream before it reads them (as copies they were two launches more in every call's chain)
   sv_result* res_host = nullptr;
   float* sw_host = nullptr;
   uint8_t* mask_host = nullptr;
@@ -65,10 +68,12 @@ void set_err(sv_sentinel* s, const char* fmt, ...) {
 // excluded beforehand, and left what it was in sum_dev.  A call that ends before its verdicts stand leaves m as it was.
 struct CallEma {
   sv_sentinel* s;
-  float* m;
+  int kind, stage;
   float beta;
   hipStream_t st;
-  bool updated = false;
+  float* m = s->m[kind][stage];
+  float* pm = s->pm[kind].empty() ? nullptr : s->pm[kind][stage];       // its projections, or none
+  bool one_pass = false, updated = false;
   const float* now() const { return updated ? s->sum_dev : m; }
   ~CallEma() {
     if (updated) (void)hipMemcpyAsync(m, s->sum_dev, (size_t)s->cfg.T * s->cfg.D * sizeof(float), hipMemcpyDeviceToDevice, st);
@@ -79,7 +84,7 @@ struct CallEma {
 // `skip` [d]: the signals known to be excluded from the EMA before they are scored.  Where the score pass can do it,
 // it also leaves the sum over the others in sum_dev, or updates the EMA with it (*summed = true), which saves the EMA update its own
 // pass over the signals whenever the verdicts exclude nobody else.
-sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, CallEma& ema, const float* pm, const uint8_t* skip, bool* summed,
+sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, CallEma& ema, const uint8_t* skip, bool* summed,
                    std::vector<double>& gamma, hipStream_t st) {
   const sv_sentinel_cfg& c = s->cfg;
   const int d = c.n_workers;
@@ -87,32 +92,32 @@ sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, CallEma& ema,
   const float inf = std::numeric_limits<float>::infinity();
   const float tau[4] = {inf, inf, inf, inf};      // nothing is decided on the device here: the fences live in the policy
   float* m = ema.m;
+  const float* pm = ema.pm;
   // statistics, EMA update and projections in one pass over the signals where the shape allows it
   sv_status one = SV_EUNSUPPORTED;
   if ((c.metric_mask & SV_M_SW) && pm && s->sum_dev) {
-    one = sv::check_signals(s->ctx, signals, stride, d, dtype, m, s->sum_dev, ema.beta, c.T, c.D, c.metric_mask & 15u, tau, s->res_dev, skip, c.directions,
-                            c.n_dirs, pm, s->cproj, s->sw_dev, &ema.updated, st);
+    one = sv::check_signals(s->ctx, signals, stride, d, dtype, m, s->sum_dev, ema.beta, c.T, c.D, c.metric_mask & 15u, tau, s->res_host, skip, c.directions,
+                            c.n_dirs, pm, s->sorted_ok[ema.kind][ema.stage] ? s->ps[ema.kind][ema.stage] : nullptr, s->cproj, s->sw_host, &ema.updated, st);
+    ema.one_pass = ema.updated;
     if (one != SV_OK && one != SV_EUNSUPPORTED) { set_err(s, "the loop's pass: %s", sv_last_error(s->ctx)); return one; }
   }
   sv_status sum_st = one == SV_OK ? SV_OK : s->sum_dev ? sv_score_and_sum(s->ctx, signals, stride, d, m, dtype, SV_F32, c.T, c.D, c.metric_mask & 15u, tau,
-                                                   SV_REDUCE_GLOBAL, nullptr, s->res_dev, skip, s->sum_dev, st)
+                                                   SV_REDUCE_GLOBAL, nullptr, s->res_host, skip, s->sum_dev, st)
                                 : SV_EUNSUPPORTED;
   *summed = sum_st == SV_OK;
   if (sum_st == SV_EUNSUPPORTED)                  // shapes the summing pass does not take: the plain one
     SN_SV(s, sv_score_and_flag(s->ctx, signals, stride, d, m, 0, dtype, SV_F32, c.T, c.D, c.metric_mask & 15u, tau, SV_REDUCE_GLOBAL, nullptr,
-                               s->res_dev, st));
+                               s->res_host, st));
   else if (sum_st != SV_OK) { set_err(s, "sv_score_and_sum: %s", sv_last_error(s->ctx)); return sum_st; }
-  SN_HIP(s, hipMemcpyAsync(s->res_host, s->res_dev, sizeof(sv_result) * d, hipMemcpyDeviceToHost, st));
   if (c.metric_mask & SV_M_SW) {
     if (pm) ++s->n_sw_carried;
     if (one == SV_OK) {
     } else if (pm)
-      SN_SV(s, sv_sw_against_projection(s->ctx, signals, stride, d, dtype, c.T, c.D, c.directions, c.n_dirs, pm, s->cproj, inf, s->sw_dev,
+      SN_SV(s, sv_sw_against_projection(s->ctx, signals, stride, d, dtype, c.T, c.D, c.directions, c.n_dirs, pm, s->cproj, inf, s->sw_host,
                                         nullptr, st));
     else
-      SN_SV(s, sv_sliced_wasserstein(s->ctx, signals, stride, d, m, 0, dtype, SV_F32, c.T, c.D, c.directions, c.n_dirs, inf, s->sw_dev,
+      SN_SV(s, sv_sliced_wasserstein(s->ctx, signals, stride, d, m, 0, dtype, SV_F32, c.T, c.D, c.directions, c.n_dirs, inf, s->sw_host,
                                      nullptr, st));
-    SN_HIP(s, hipMemcpyAsync(s->sw_host, s->sw_dev, sizeof(float) * d, hipMemcpyDeviceToHost, st));
   }
   SN_HIP(s, hipStreamSynchronize(st));
   gamma.assign((size_t)d * s->n_metrics, 0.0);
@@ -130,14 +135,22 @@ sv_status gamma_of(sv_sentinel* s, const void* signals, int dtype, CallEma& ema,
 // Eq. momentum_def over the signals with excl[r] == 0.  If the score pass has left the sum over the signals with
 // skip[r] == 0 and the verdicts excluded nobody beyond those, the update is one pass over m and that sum, or done already; otherwise
 // the update reads the signals itself.
-sv_status update_ema(sv_sentinel* s, CallEma& ema, float* pm, const void* signals, int dtype, const uint8_t* excl, const uint8_t* skip,
+sv_status update_ema(sv_sentinel* s, CallEma& ema, const void* signals, int dtype, const uint8_t* excl, const uint8_t* skip,
                      bool summed, bool mask_uploaded = false) {
   const int d = s->cfg.n_workers;
   const hipStream_t hs = ema.st;
-  if (pm) SN_SV(s, sv_sw_projection_ema(s->ctx, pm, s->cproj, d, excl, s->cfg.T, s->cfg.n_dirs, ema.beta, hs));
   bool same = summed;
   int n = 0;
   for (int r = 0; r < d; ++r) { same = same && (excl[r] != 0) == (skip[r] != 0); n += excl[r] == 0; }
+  if (ema.pm) {
+    uint8_t& ok = s->sorted_ok[ema.kind][ema.stage];
+    if (n > 0) ok = 0;                             // with nobody to take the projections stay as they are
+    SN_SV(s, sv_sw_projection_ema(s->ctx, ema.pm, s->cproj, d, excl, s->cfg.T, s->cfg.n_dirs, ema.beta, hs));
+    if (ema.one_pass && !ok) {
+      SN_HIP(s, sv::launch_sw_sort(s->ps[ema.kind][ema.stage], s->cfg.n_dirs, s->cfg.T, sv_sw_row_len(s->cfg.T), nullptr, 0, s->cfg.n_dirs, nullptr, 0, hs, ema.pm));
+      ok = 1;
+    }
+  }
   ++s->n_calls;
   if (same) {
     ++s->n_from_sum;
@@ -191,8 +204,6 @@ sv_status sv_sentinel_create(sv_ctx* ctx, const sv_sentinel_cfg* cfg, sv_sentine
       e = hipMalloc(&p, m_bytes);
       if (e == hipSuccess) { s->m[kind].push_back(p); e = hipMemset(p, 0, m_bytes); }     // m_0 = 0
     }
-  if (st == SV_OK && e == hipSuccess) e = hipMalloc(&s->res_dev, sizeof(sv_result) * d);
-  if (st == SV_OK && e == hipSuccess) e = hipMalloc(&s->sw_dev, sizeof(float) * d);
   if (st == SV_OK && e == hipSuccess) e = hipMalloc(&s->mask_dev, 2 * (size_t)d);
   if (st == SV_OK && e == hipSuccess && (cfg->metric_mask & SV_M_SW) && d <= 32 && cfg->n_dirs % 32 == 0 && cfg->D % 64 == 0 &&
       sv_sw_row_len(cfg->T) <= 16384) {               // optional: without them the EMA itself is projected in every check
@@ -203,10 +214,14 @@ sv_status sv_sentinel_create(sv_ctx* ctx, const sv_sentinel_cfg* cfg, sv_sentine
         float* p = nullptr;
         ok = hipMalloc(&p, p_bytes) == hipSuccess;
         if (ok) { s->pm[kind].push_back(p); ok = hipMemset(p, 0, p_bytes) == hipSuccess; }     // projections of m_0 = 0
+        float* q = nullptr;
+        ok = ok && hipMalloc(&q, p_bytes) == hipSuccess;
+        if (ok) { s->ps[kind].push_back(q); s->sorted_ok[kind].push_back(0); }
       }
     if (!ok) {
       (void)hipGetLastError();
-      for (int kind = 0; kind < 2; ++kind) { for (float* p : s->pm[kind]) (void)hipFree(p); s->pm[kind].clear(); }
+      for (int kind = 0; kind < 2; ++kind)
+        for (std::vector<float*>* v : {&s->pm[kind], &s->ps[kind]}) { for (float* p : *v) (void)hipFree(p); v->clear(); }
       if (s->cproj) { (void)hipFree(s->cproj); s->cproj = nullptr; }
     }
   }
@@ -231,12 +246,11 @@ void sv_sentinel_destroy(sv_sentinel* s) {
     for (float* p : s->m[kind]) (void)hipFree(p);
     for (sv_policy* p : s->pol[kind]) sv_policy_destroy(p);
   }
-  if (s->res_dev) (void)hipFree(s->res_dev);
-  if (s->sw_dev) (void)hipFree(s->sw_dev);
   if (s->mask_dev) (void)hipFree(s->mask_dev);
   if (s->sum_dev) (void)hipFree(s->sum_dev);
   for (int kind = 0; kind < 2; ++kind)
-    for (float* p : s->pm[kind]) (void)hipFree(p);
+    for (const std::vector<float*>* v : {&s->pm[kind], &s->ps[kind]})
+      for (float* p : *v) (void)hipFree(p);
   if (s->cproj) (void)hipFree(s->cproj);
   if (s->res_host) (void)hipHostFree(s->res_host);
   if (s->sw_host) (void)hipHostFree(s->sw_host);
@@ -270,9 +284,8 @@ sv_status sv_sentinel_forward(sv_sentinel* s, int32_t stage, const void* h, int3
     for (int r = 0; r < d; ++r) skip[r] = banned[r] | upstream[r];
   }
   bool summed = false;
-  float* pm = s->pm[0].empty() ? nullptr : s->pm[0][stage];
-  CallEma ema{s, s->m[0][stage], s->cfg.beta_h, hs};
-  st = gamma_of(s, h, dtype, ema, pm, skip.data(), &summed, gamma, hs);
+  CallEma ema{s, 0, stage, s->cfg.beta_h, hs};
+  st = gamma_of(s, h, dtype, ema, skip.data(), &summed, gamma, hs);
   if (st != SV_OK) return st;
   if (gamma_out) memcpy(gamma_out, gamma.data(), gamma.size() * sizeof(double));
   uint8_t* excl = s->mask_host + d;
@@ -287,7 +300,7 @@ sv_status sv_sentinel_forward(sv_sentinel* s, int32_t stage, const void* h, int3
       excl[r] = banned[r] | upstream[r] | tainted_out[r];
     }
   }
-  return update_ema(s, ema, pm, h, dtype, excl, skip.data(), summed);
+  return update_ema(s, ema, h, dtype, excl, skip.data(), summed);
 }
 
 sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t dtype, uint8_t* tainted_out, double* gamma_out, void* stream) {
@@ -307,9 +320,8 @@ sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t d
     for (int r = 0; r < d; ++r) skip[r] = banned[r] | s->tainted[(size_t)stage * d + r] | down[r];
   }
   bool summed = false;
-  float* pm = s->pm[1].empty() ? nullptr : s->pm[1][stage];
-  CallEma ema{s, s->m[1][stage], s->cfg.beta_g, hs};
-  st = gamma_of(s, g, dtype, ema, pm, skip.data(), &summed, gamma, hs);
+  CallEma ema{s, 1, stage, s->cfg.beta_g, hs};
+  st = gamma_of(s, g, dtype, ema, skip.data(), &summed, gamma, hs);
   if (st != SV_OK) return st;
   if (gamma_out) memcpy(gamma_out, gamma.data(), gamma.size() * sizeof(double));
   uint8_t* repl = s->mask_host;
@@ -326,13 +338,13 @@ sv_status sv_sentinel_backward(sv_sentinel* s, int32_t stage, void* g, int32_t d
       excl[r] = banned[r] | repl[r];
     }
   }
-  SN_HIP(s, hipMemcpyAsync(s->mask_dev, s->mask_host, 2 * (size_t)d, hipMemcpyHostToDevice, hs));
   // the EMA reads only signals that are not replaced, and the replacement reads what m was before it is updated
   bool any_repl = false;
   for (int r = 0; r < d; ++r) any_repl |= repl[r] != 0;
+  if (any_repl) SN_HIP(s, hipMemcpyAsync(s->mask_dev, s->mask_host, 2 * (size_t)d, hipMemcpyHostToDevice, hs));
   if (any_repl) SN_SV(s, sv_replace_with_ema(s->ctx, g, s->cfg.T * s->cfg.D, d, dtype, s->mask_dev, ema.now(), s->cfg.T, s->cfg.D, hs));
   // (the sum the score pass left was taken before the replacement, over signals that are not replaced)
-  return update_ema(s, ema, pm, g, dtype, excl, skip.data(), summed, /*mask_uploaded=*/true);
+  return update_ema(s, ema, g, dtype, excl, skip.data(), summed, /*mask_uploaded=*/any_repl);
 }
 
 sv_status sv_sentinel_state(const sv_sentinel* s, int32_t stage, int32_t kind, const float** ema_dev, int32_t* violations, uint8_t* banned,
