@@ -576,11 +576,11 @@ sv_status block_forward(sv_ctx* c, int l, const sv_block_weights& w, const void*
     {
       GemmArgs g = nt((int)Mp, F, D, c->xp, D, w.w_gate, c->actp, F, EPI_SWIGLU);
       g.B2 = w.w_up; g.ldb2 = D;
-      g.tile_group = r.tile_expert; g.group_stride = (int64_t)F * D; g.m_dev = r.meta;
+      g.groups = E; g.tile_group = r.tile_expert; g.group_stride = (int64_t)F * D; g.m_dev = r.meta;
       if (keep) { g.C2 = keep->gate_p; g.C3 = keep->up_p; }
       SV_OP(c, SV_OP_GEMM_GATEUP, 4.0 * rows * F * D, st, gemm(c, g, st));
       GemmArgs h = nt((int)Mp, D, F, c->actp, F, w.w_down, yp, D, EPI_STORE);
-      h.tile_group = r.tile_expert; h.group_stride = (int64_t)D * F; h.m_dev = r.meta;
+      h.groups = E; h.tile_group = r.tile_expert; h.group_stride = (int64_t)D * F; h.m_dev = r.meta;
       SV_OP(c, SV_OP_GEMM_DOWN, 2.0 * rows * D * F, st, gemm(c, h, st));
     }
     SV_OP(c, SV_OP_MOE_PERMUTE, 0, st, launch_moe_combine(base, yp, T, D, K, r, y, dt, st));
@@ -669,7 +669,7 @@ sv_status block_backward(sv_ctx* c, int l, const sv_block_weights& w, const void
     const int64_t Mp = moe_padded_rows(T, K, E);
     const double rows = Td * K;
     auto grouped = [&](GemmArgs& g) {
-      g.M = (int)Mp; g.tile_group = r.tile_expert; g.group_stride = (int64_t)D * F; g.m_dev = r.meta;
+      g.M = (int)Mp; g.groups = E; g.tile_group = r.tile_expert; g.group_stride = (int64_t)D * F; g.m_dev = r.meta;
     };
     if (Fs > 0) {                                                // shared experts: the dense backward into dn
       GemmArgs g = args(Fs, c->dgate, Fs, EPI_SWIGLU_BWD);

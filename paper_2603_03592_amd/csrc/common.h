@@ -211,6 +211,7 @@ struct GemmArgs {
   // group tile_group[i], found group_stride elements apart behind every seg[].B and B2; with m_dev the row count is
   // read from device memory (*m_dev <= M, a multiple of 256) and M only bounds the launch
   const int32_t* tile_group; int64_t group_stride;
+  int groups;             // how many there are (each adds up to 255 rows of padding)
   const int32_t* m_dev;
   // optional: fp32 scratch for split-k partial products (small row counts against a long k); none = never split
   float* split_ws; int64_t split_ws_floats;
@@ -222,6 +223,9 @@ struct GemmArgs {
   //           every 128 columns j, rowsq[j * rowsq_ld + m] = the sum of squares of the 128 values it stored (rowsq_ld >= M)
   const float* rscale;
   float* rowsq; int rowsq_ld;
+  // set by the launch of a product on 256 x 256 tiles whose last round of them is left to a second launch on smaller ones: that
+  // round's workgroups per XCD (0: it is not)
+  int tail;
 };
 
 // kernels_plain.hip: any shape, fp32 math, E = float | bf16 by `dtype`

@@ -60,6 +60,17 @@ struct Cfg {
   static_assert(WCH % 8 == 0, "a [K,N] operand is staged in whole 8x8 blocks per thread");
 };
 
+// ---- The last round of the persistent kernel's tiles.  Every XCD has `slots` workgroups and walks per_xcd tiles; what its last round
+// would leave idle for a whole tile's time goes to a second launch on smaller tiles: those of the last round only, if they are at most a
+// quarter of the workgroups (one round of 128x128), or half of them where the k loop is long enough for two (in groups) or for one of
+// 256x128.  50 176 x 1024 in groups, 784 tiles (3.06 rounds, paid as 4), K = 4096 and 8192: 643 -> 516 + 62 us on average; 8568 x 2048,
+// K = 6528 in a check 2170 -> 1980 us; 8192 x 5632 gate/up, 5.5 rounds: 340 -> 291 + 36 us (a half-empty round runs at a higher
+// clock, so less than the half is saved).  Returns the tiles per XCD that are left to it.
+__host__ __device__ inline int tail_tiles(int per_xcd, int slots, int slices) {
+  const int rem = per_xcd % slots;
+  return per_xcd > slots && rem > 0 && (4 * rem <= slots || (2 * rem <= slots && slices >= 32)) ? rem : 0;
+}
+
 // x of the lane N places further on in its row of 16 lanes (cyclic)
 template <int N> __device__ __forceinline__ float dpp_row_ror(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
@@ -424,8 +435,11 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   // kGroupM row tiles.  gridDim.x is a multiple of 8, so a workgroup stays on its XCD's run.
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = (nblk + 7) >> 3;
+  int nslices = 0;
+  for (int s = 0; s < a.nseg; ++s) nslices += a.seg[s].K / BK;
+  const int own = a.tail ? per_xcd - tail_tiles(per_xcd, a.tail, nslices) : per_xcd;     // tiles per XCD of this launch
   auto tile_of = [&](int vb, int& m0, int& n0) -> bool {
-    if (vb >= per_xcd * 8) return false;
+    if (vb >= own * 8) return false;
     const int pid = (vb & 7) * per_xcd + (vb >> 3);
     if (pid >= nblk) return false;
     const int in_group = kGroupM * tiles_n;
@@ -445,8 +459,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
                                                                            // (a per-slice kernel-argument load would share
                                                                            // its wait counter with the LDS reads)
   bool d_valid = tile_of(d_vb, d_m0, d_n0);
-  int nslices = 0;
-  for (int s = 0; s < a.nseg; ++s) nslices += a.seg[s].K / BK;
   const char *gA, *gB, *gB2;
   __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the stream reads: base = first row, no bound
   unsigned voffA[8], voffB[8];
@@ -830,7 +842,8 @@ struct MidCfg {
 // SPLIT: a tile's k slices are dealt to nsplit workgroups in contiguous runs, each leaves its fp32 partial product in
 // a.split_ws[run][M][N] and splitk_reduce_kernel adds the runs in order.  SUMMED: the same sum of runs (GemmArgs::runs) in one
 // workgroup, the running total beside the accumulators: bit for bit what the partial products and their reduction give.
-template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT, bool SUMMED>
+// TAIL: the last round of a product on 256x256 tiles (GemmArgs::tail).
+template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT, bool SUMMED, bool TAIL>
 __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, int tiles_m, int tiles_n, int nsplit) {
   constexpr bool DUAL = EPI == EPI_SWIGLU;
   static_assert(!SPLIT || (EPI == EPI_STORE && !GROUPED), "a split run stores bare partial products");
@@ -842,18 +855,33 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
 
   const int M = GROUPED ? *a.m_dev : a.M;
   if (GROUPED) tiles_m = (M + BM - 1) / BM;
-  // tile assignment as in the 256x256 kernel: ids congruent mod 8 (one XCD) walk a contiguous run of tiles
+  // tile assignment as in the 256x256 kernel: ids congruent mod 8 (one XCD) walk a contiguous run of tiles.  As that kernel's last
+  // round: its map and its tiles, each in SUB pieces next to each other.
+  constexpr int SUBN = 256 / BN, SUB = 256 / BM * SUBN;
+  static_assert(!TAIL || (!SPLIT && !SUMMED), "a tail's tiles are whole");
+  int group = kGroup, skip = 0, sub = 0, slot = blockIdx.x >> 3;
+  if (TAIL) {
+    int slices = 0;
+    for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
+    tiles_m = (M + 255) / 256; tiles_n = a.N / (DUAL ? 128 : 256);
+    const int all = (tiles_m * tiles_n + 7) >> 3, rem = tail_tiles(all, a.tail, slices);
+    sub = slot % SUB; slot /= SUB;
+    if (slot >= rem) return;
+    skip = all - rem;
+    group = kGroupM;
+  }
   const int nblk = tiles_m * tiles_n, nvb = SPLIT ? nblk * nsplit : nblk;
   const int per_xcd = (nvb + 7) >> 3;
-  int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || pid >= nvb) return;
+  int pid = (blockIdx.x & 7) * per_xcd + skip + slot;
+  if (skip + slot >= per_xcd || pid >= nvb) return;
   int run = 0;
   if (SPLIT) { run = pid / nblk; pid -= run * nblk; }
-  const int in_group = kGroup * tiles_n;
-  const int first_m = (pid / in_group) * kGroup;
-  const int gsz = min(tiles_m - first_m, kGroup);
-  const int m0 = (first_m + (pid % in_group) % gsz) * BM;
-  const int n0 = ((pid % in_group) / gsz) * C::NOUT;
+  const int in_group = group * tiles_n;
+  const int first_m = (pid / in_group) * group;
+  const int gsz = min(tiles_m - first_m, group);
+  const int m0 = (first_m + (pid % in_group) % gsz) * (TAIL ? 256 : BM) + sub / SUBN * BM;
+  const int n0 = ((pid % in_group) / gsz) * (TAIL ? SUBN * C::NOUT : C::NOUT) + sub % SUBN * C::NOUT;
+  if (TAIL && m0 >= M) return;
 
   const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lhi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % WM, wn = wave / WM;
@@ -1140,10 +1168,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
 #undef SV_SB
 }
 
-template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false>
-hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st) {
+template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false, bool TAIL = false>
+hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st, int tail_max = 0) {      // tail_max: tiles per XCD a tail has at most
   using C = MidCfg<WM, WN, MI, NI, NST, EPI == EPI_SWIGLU>;
-  auto kern = gemm_mid_kernel<WM, WN, MI, NI, NST, EPI, GROUPED, SPLIT, SUMMED>;
+  auto kern = gemm_mid_kernel<WM, WN, MI, NI, NST, EPI, GROUPED, SPLIT, SUMMED, TAIL>;
   static bool configured = false;   // per process; the attribute is per function
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
@@ -1151,7 +1179,7 @@ hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st) {
     configured = true;
   }
   const int tiles_m = (a.M + C::BM - 1) / C::BM, tiles_n = (a.N + C::NOUT - 1) / C::NOUT;
-  const int64_t per_xcd = ((int64_t)tiles_m * tiles_n * nsplit + 7) / 8;
+  const int64_t per_xcd = TAIL ? (int64_t)tail_max * (256 / C::BM) * (256 / C::BN) : ((int64_t)tiles_m * tiles_n * nsplit + 7) / 8;
   hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(C::NT), C::LDS, st, a, tiles_m, tiles_n, nsplit);
   return hipGetLastError();
 }
@@ -1197,7 +1225,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // cheapest is taken.  The figures are microseconds fitted to a sweep over 64 .. 8192 rows, 320 .. 14336 columns and K =
 // 512 .. 14336 with every tile forced (within 15 % of the measured times there).  They are those of a plain store: the dearer
 // epilogues (SwiGLU with its stashes, SwiGLU-backward) cost the same here, and a tile more than the last full round counts as a
-// round.  Against 256x256 tiles over runs of k, which these replaced, k of 9000 and more for 500 .. 1500 rows of 3072 .. 4096 columns
+// round (on 256x256 tiles: as a second launch on smaller ones, where tail_tiles says so).  Against 256x256 tiles over runs of k, which these replaced, k of 9000 and more for 500 .. 1500 rows of 3072 .. 4096 columns
 // is left 5 .. 15 % slower (1453 x 3072, K = 9728: 97 -> 112 us), everything else even or faster.  Where the lines come out, with both
 // sides as measured on that sweep: 4096 x 1024, K = 1024 (256 tiles of 128 x 128) 13.4 us against 19 on 256 x 128 and 33 on
 // 256 x 256 over runs; 8192 x 1024, K = 8192 (256 tiles of 256 x 128) 113 us against 121 and 124; 8192 x 2048, K = 2048
@@ -1207,6 +1235,9 @@ enum TileKind { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTile64, kTil
 struct TileCost { int bm, bn; double fixed, slice; };
 constexpr TileCost kTileCost[kTileKinds] = {{256, 256, 4.0, 1.55}, {256, 128, 6.5, 0.86}, {128, 128, 5.0, 0.52}, {64, 128, 4.0, 0.36}, {64, 64, 3.5, 0.21}};
 struct Plan { int kind, runs; };
+
+// workgroups of the persistent kernel per XCD
+int tile_slots() { return std::max(8, cu_count() / 8 * 8) / 8; }
 
 bool panels_fit(const GemmArgs& a) {      // 32-bit byte offsets inside a panel of 256 rows, and inside a tile's outputs
   for (int s = 0; s < a.nseg; ++s)
@@ -1249,7 +1280,14 @@ Plan plan_gemm(const GemmArgs& a) {
       if (runs > 1 && (slices < 4 * runs || (int64_t)runs * a.M * a.N > a.split_ws_floats)) break;
       const double rounds = (double)((tiles * runs + (int64_t)cus - 1) / (int64_t)cus);
       double cost = rounds * (t.fixed + t.slice * ((slices + runs - 1) / runs));
-      if (k == kTile256) cost += 4.0;
+      if (k == kTile256) {
+        cost += 4.0;
+        const int per_xcd = (int)((tiles + 7) / 8), slots = tile_slots(), left = a.rowsq || a.tile_group ? 0 : tail_tiles(per_xcd, slots, slices);
+        if (left > 0) {                                  // its last round on smaller tiles, in a launch of their own
+          const TileCost& s = kTileCost[4 * left <= slots ? kTile128 : kTile256x128];
+          cost = 7.0 + per_xcd / slots * (t.fixed + t.slice * slices) + s.fixed + s.slice * slices;
+        }
+      }
       if (runs > 1) cost += 4.0 + (4.0 * runs + 4.0) * a.M * (double)a.N / 4.5e6;
       if (best.kind < 0 || cost < best_cost) { best = Plan{k, runs}; best_cost = cost; }
     }
@@ -1257,13 +1295,50 @@ Plan plan_gemm(const GemmArgs& a) {
   return best;
 }
 
+// Tiles per XCD (at most) that a product on 256x256 tiles leaves to a second launch, or 0.  In groups the rows are known on the device
+// only: somewhere between none and 255 of padding per group more than the tokens' rows; the second launch (4.5 us where it
+// finds nothing to do) is made if half of the likely counts have a tail.
+template <int EPI, bool GROUPED>
+int tail_pays(const GemmArgs& a) {
+  if (a.rowsq || !fits_mid(a)) return 0;                 // row sums come from whole 256 x 256 tiles only
+  const int tiles_n = a.N / (EPI == EPI_SWIGLU ? 128 : 256), slots = tile_slots();
+  int slices = 0;
+  for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
+  if (!GROUPED) return tail_tiles(((a.M + 255) / 256 * tiles_n + 7) / 8, slots, slices);
+  const int most = a.M / 256, pad = std::min(most - 1, a.groups);
+  int with = 0, all = 0, left = 0;
+  for (int b = most - pad + pad / 4; b <= most - pad / 4; ++b, ++all) {
+    const int t = tail_tiles((b * tiles_n + 7) / 8, slots, slices);
+    with += t > 0;
+  }
+  for (int b = std::max(1, most - pad); b <= most; ++b) left = std::max(left, tail_tiles((b * tiles_n + 7) / 8, slots, slices));
+  return 2 * with >= all ? left : 0;
+}
+
+// the form that scales rows, where there is one
+template <int EPI, bool GROUPED>
+hipError_t launch_dma_nf(const GemmArgs& a, hipStream_t st) {
+  if constexpr (!GROUPED && EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD) return launch_dma<EPI, false, true>(a, st);
+  else return hipErrorInvalidValue;
+}
+
 template <int EPI, bool GROUPED>
 hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
   switch (kind) {
-    case kTile256:
+    case kTile256: {
+      const int left = tail_pays<EPI, GROUPED>(a);
+      if (left > 0) {
+        GemmArgs g = a;
+        g.tail = tile_slots();
+        hipError_t e = g.rscale ? launch_dma_nf<EPI, GROUPED>(g, st) : launch_dma<EPI, GROUPED>(g, st);
+        if (e != hipSuccess) return e;
+        if (GROUPED || 4 * left <= g.tail) return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED, false, false, true>(g, 1, st, left);
+        if constexpr (!GROUPED) return launch_mid<4, 2, 2, 2, 3, EPI, false, false, false, true>(g, 1, st, left);
+      }
       if constexpr (!GROUPED && EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD)
         if (a.rscale || a.rowsq) return launch_dma<EPI, false, true>(a, st);   // the ends of a norm that runs inside the products
       return launch_dma<EPI, GROUPED>(a, st);
+    }
     case kTile256x128: return launch_mid<4, 2, 2, 2, 3, EPI, GROUPED>(a, 1, st);
     case kTile128: return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED>(a, 1, st);
     case kTile64x128: return launch_mid<2, 2, 1, 2, 3, EPI, GROUPED>(a, 1, st);
