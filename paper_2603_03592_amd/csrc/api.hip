@@ -85,6 +85,7 @@ struct sv_ctx {
   const void* rowsq_of = nullptr;
   float* delta;
   ScorePartial* score_scratch;
+  uint32_t* score_arrivals;                       // zero between calls
   float* attn_part;    // fp32 dk | dv contributions per query head of a group (backward, bf16 matrix-core path, one long sequence)
   size_t attn_part_floats;
   float* split_ws;     // fp32 partial products of the split-k GEMMs (bf16 matrix-core path, few tokens against a long k)
@@ -168,6 +169,7 @@ size_t carve(sv_ctx* c, char* base) {
   Arena a; a.base = base;
   c->rope_cs = (float*)a.take((size_t)c->max_seq * (c->hd / 2) * 2 * sizeof(float));
   c->score_scratch = (ScorePartial*)a.take(kScoreScratchElems * sizeof(ScorePartial));
+  c->score_arrivals = (uint32_t*)a.take(kScoreArrivals * sizeof(uint32_t));
   c->split_ws = nullptr; c->split_ws_floats = 0;
   if (d.dtype == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS)) {
     // for products over runs of k: up to 8 partial products of this context's largest, and no more than 84 MB.  A plan takes as
@@ -805,8 +807,10 @@ sv_status sv_create(const sv_stage_desc* desc, int64_t max_tokens, int32_t max_s
       cs[((size_t)p * half + i) * 2 + 1] = (float)sin(ang);
     }
   e = hipMemcpy(c->rope_cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
+  const std::vector<uint32_t> nobody(kScoreArrivals, 0u);
+  if (e == hipSuccess) e = hipMemcpy(c->score_arrivals, nobody.data(), nobody.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
-    set_err(nullptr, "uploading the RoPE table: %s", hipGetErrorString(e));
+    set_err(nullptr, "uploading the RoPE table and the counters: %s", hipGetErrorString(e));
     (void)hipFree(c->ws);
     delete c;
     return SV_EHIP;
@@ -879,7 +883,7 @@ sv_status sv_verify_forward(sv_ctx* c, const sv_block_weights* w, const void* h_
   }
   if (claimed_h)
     SV_OP(c, SV_OP_SCORE, 0, st, launch_score(claimed_h, 0, 1, y, 0, c->d.dtype, c->d.dtype, (int64_t)B * S, c->d.d_model, metric_mask, tau, reduce,
-                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st));
+                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, c->score_arrivals));
   return SV_OK;
 }
 
@@ -912,7 +916,7 @@ sv_status sv_verify_backward(sv_ctx* c, const sv_block_weights* w, const void* h
   }
   if (claimed_g)
     SV_OP(c, SV_OP_SCORE, 0, st, launch_score(claimed_g, 0, 1, dx, 0, c->d.dtype, c->d.dtype, (int64_t)B * S, c->d.d_model, metric_mask, tau, reduce,
-                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st));
+                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, c->score_arrivals));
   return SV_OK;
 }
 
@@ -965,7 +969,7 @@ sv_status sv_score_and_flag(sv_ctx* c, const void* claims, int64_t claim_stride,
   if (T > 0x7fffffffLL || claim_stride < 0 || ref_stride < 0) { set_err(c, "T or a stride is out of range"); return SV_EINVAL; }
   if ((T + kScoreTokensPerWG - 1) / kScoreTokensPerWG > kScoreScratchElems) { set_err(c, "T too large for the score scratch"); return SV_EUNSUPPORTED; }
   SV_HIP(c, launch_score(claims, claim_stride, n_claims, ref, ref_stride, claim_dtype, ref_dtype, T, D, metric_mask, tau, reduce,
-                         token_scores_out, results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream));
+                         token_scores_out, results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, c->score_arrivals));
   return SV_OK;
 }
 
@@ -989,7 +993,7 @@ sv_status sv_score_and_sum(sv_ctx* c, const void* claims, int64_t claim_stride, 
   for (int i = 0; skip_host && i < n_claims; ++i)
     if (skip_host[i]) skip |= 1u << i;
   SV_HIP(c, launch_score(claims, claim_stride, n_claims, ref, 0, claim_dtype, ref_dtype, T, D, metric_mask, tau, reduce, token_scores_out,
-                         results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, skip, sum_out));
+                         results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, c->score_arrivals, skip, sum_out));
   return SV_OK;
 }
 

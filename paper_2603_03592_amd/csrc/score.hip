@@ -5,8 +5,8 @@
 //                         whole distance family needs (Omega_L1, Omega_L2, Omega_SFR of the
 //                         paragraph "Choice of Distance Measure", and the per-token relative
 //                         L2), then folds 16 tokens into one partial record.
-//   score_finalize_kernel: deterministic reduction of the records of one submission, the
-//                         scores, and the flag Gamma > tau (Eq. test_statistic; a submission
+//   score_finalize_kernel: deterministic reduction of the records of one submission (few records: by the
+//                         workgroup of the pass that comes last), the scores, and the flag Gamma > tau (Eq. test_statistic; a submission
 //                         is flagged when any enabled metric exceeds its threshold).
 //   ema_update_kernel   : Eq. momentum_def over the un-flagged submissions.
 #include <mutex>
@@ -41,6 +41,84 @@ __device__ __forceinline__ float wave_sum_rows(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+struct Tau4 { float v[4]; };
+
+// What turns a submission's records into its scores and flag.
+struct Verdict { uint32_t mask; Tau4 tau; int reduce; sv_result* results; };
+
+inline __host__ __device__ int finalize_threads(int tiles_per_claim) { return tiles_per_claim <= 128 ? 64 : 256; }
+
+// The scores and the flag of one submission, by the first nt threads of a workgroup (all of which call).
+__device__ void finalize_claim(const ScorePartial* p, int tiles_per_claim, int claim, int64_t T, int D, const Verdict& verdict, int nt) {
+  const int tid = threadIdx.x;
+  const uint32_t mask = verdict.mask;
+  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  float best = -1.0f; int bt = 0, bad = 0;
+  for (int i = tid; i < tiles_per_claim && tid < nt; i += nt) {      // tiles visited in increasing order
+    const ScorePartial q = p[i];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] += q.s[j];
+    bad |= q.bad;
+    if (q.max_rel > best) { best = q.max_rel; bt = q.argmax; }
+  }
+  __shared__ double s_acc[256][8];
+  __shared__ float s_best[256];
+  __shared__ int s_bt[256], s_bad[256];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) s_acc[tid][j] = acc[j];
+  s_best[tid] = best; s_bt[tid] = bt; s_bad[tid] = bad;
+  __syncthreads();
+  for (int stride = nt >> 1; stride > 0; stride >>= 1) { // fixed tree: run-to-run identical
+    if (tid < stride) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s_acc[tid][j] += s_acc[tid + stride][j];
+      s_bad[tid] |= s_bad[tid + stride];
+      const float o = s_best[tid + stride];
+      if (o > s_best[tid] || (o == s_best[tid] && s_bt[tid + stride] < s_bt[tid])) { s_best[tid] = o; s_bt[tid] = s_bt[tid + stride]; }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    const double n = (double)T * (double)D;
+    const double Sc = s_acc[0][0], Sr = s_acc[0][1], Scc = s_acc[0][2], Srr = s_acc[0][3];
+    const double Sd = s_acc[0][4], Sad = s_acc[0][5], Sdd = s_acc[0][6], Ns = s_acc[0][7];
+    const double nan = __longlong_as_double(0x7ff8000000000000LL);
+    double sc[4];
+    const double grel = sqrt(Sdd) / fmax(sqrt(Srr), 1e-30);
+    const double mrel = s_bad[0] ? nan : (double)fmaxf(s_best[0], 0.0f);
+    sc[SV_IDX_RELL2] = (verdict.reduce == SV_REDUCE_MAX_TOKEN) ? mrel : grel;
+    sc[SV_IDX_L1] = Sad / n;
+    // z-scored L2 = 2 (1 - rho) = (var_d - (sd_c - sd_r)^2) / (sd_c sd_r): no cancellation for rho ~ 1
+    const double mc = Sc / n, mr = Sr / n, md = Sd / n;
+    const double vc = Scc / n - mc * mc, vr = Srr / n - mr * mr, vd = fmax(Sdd / n - md * md, 0.0);
+    const bool const_c = !(vc > 1e-10 * (Scc / n)), const_r = !(vr > 1e-10 * (Srr / n));
+    if (Scc != Scc || Srr != Srr) sc[SV_IDX_ZL2] = nan;
+    else if (const_c && const_r) sc[SV_IDX_ZL2] = 0.0;
+    else if (const_c || const_r) sc[SV_IDX_ZL2] = 2.0;
+    else {
+      const double a = sqrt(vc), b = sqrt(vr);
+      sc[SV_IDX_ZL2] = fmax(vd - (a - b) * (a - b), 0.0) / (a * b);
+    }
+    sc[SV_IDX_SFR] = Ns / n;
+    sv_result r;
+    uint32_t flag = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool on = ((mask >> i) & 1u) || i == SV_IDX_RELL2;         // the relative L2 is always formed
+      r.score[i] = on ? (float)sc[i] : 0.0f;
+      if (((mask >> i) & 1u) && !(r.score[i] <= verdict.tau.v[i])) flag = 1;   // strict '>'; non-finite scores are flagged
+    }
+    r.flag = flag; r.metric_mask = mask;
+    r.max_token_rell2 = (float)mrel; r.argmax_token = s_bt[0];
+    verdict.results[claim] = r;
+  }
+}
+
+__global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial* __restrict__ partials, int tiles_per_claim, int64_t T, int D,
+                                                             Verdict verdict) {
+  finalize_claim(partials + (int64_t)blockIdx.x * tiles_per_claim, tiles_per_claim, blockIdx.x, T, D, verdict, blockDim.x);
+}
+
 // NEED_L1 / NEED_Z / NEED_SFR prune the sums a launch does not need (the statistic family is
 // requested by mask): with only the relative L2 enabled a token costs two FMAs per element and the
 // pass is bound by HBM; with all eight sums it is bound by the vector ALUs (about 18 ops/element).
@@ -51,7 +129,7 @@ template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, in
 __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
                                                            const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
                                                            int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
-                                                           ScorePartial* __restrict__ partials) {
+                                                           ScorePartial* partials, uint32_t* arrivals, Verdict verdict) {
   // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): ids congruent mod 8 get a contiguous run of
   // token tiles, and within a run the claim index varies fastest, so the submissions that share a tile of the
   // reference run together on one XCD and fetch it from memory once instead of once per XCD.
@@ -137,9 +215,10 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
   }
   __syncthreads();
   ScorePartial* p = partials + (int64_t)claim * tiles_per_claim + tile;
-  if (threadIdx.x < 8) {                             // one sum each, the waves in order
+  // one sum each, the waves in order; the worst token by the next thread.  All in the first wave, which then counts the record.
+  if (threadIdx.x < 8) {
     p->s[threadIdx.x] = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
-  } else if (threadIdx.x == 64) {
+  } else if (threadIdx.x == 8) {
     float b = -1.0f; int bt = 0, bd = 0;
     for (int w = 0; w < 4; ++w) {
       bd |= s_bad[w];
@@ -147,6 +226,21 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
     }
     p->max_rel = b; p->argmax = bt; p->bad = bd; p->pad = 0;
   }
+  if (!arrivals) return;                             // the records go to score_finalize_kernel
+  // The workgroup that comes last with a record of its submission forms the scores: nobody waits, and there is one launch instead of
+  // two (1 x 256 tokens of 512: a call 14.7 -> 11.9 us, most of it the host's; the smallest fp32 check 46.6 -> 43.0).  The records are
+  // summed in the same order as there.
+  __shared__ int s_last;
+  if (wave == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (lane == 0)
+      s_last = __hip_atomic_fetch_add(&arrivals[claim], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (uint32_t)tiles_per_claim;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  finalize_claim(partials + (int64_t)claim * tiles_per_claim, tiles_per_claim, claim, T, D, verdict, finalize_threads(tiles_per_claim));
+  if (threadIdx.x == 0) arrivals[claim] = 0;         // for the next call on the stream
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -356,75 +450,6 @@ __global__ __launch_bounds__(256) void ema_from_sum_kernel(float* __restrict__ m
   store8(m + v * 8, mv);
 }
 
-struct Tau4 { float v[4]; };
-
-__global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial* __restrict__ partials, int tiles_per_claim,
-                                                             int64_t T, int D, uint32_t mask, Tau4 tau, int reduce,
-                                                             sv_result* __restrict__ results) {
-  const int claim = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-  const ScorePartial* p = partials + (int64_t)claim * tiles_per_claim;
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float best = -1.0f; int bt = 0, bad = 0;
-  for (int i = tid; i < tiles_per_claim; i += nt) {      // tiles visited in increasing order
-    const ScorePartial q = p[i];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += q.s[j];
-    bad |= q.bad;
-    if (q.max_rel > best) { best = q.max_rel; bt = q.argmax; }
-  }
-  __shared__ double s_acc[256][8];
-  __shared__ float s_best[256];
-  __shared__ int s_bt[256], s_bad[256];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) s_acc[tid][j] = acc[j];
-  s_best[tid] = best; s_bt[tid] = bt; s_bad[tid] = bad;
-  __syncthreads();
-  for (int stride = nt >> 1; stride > 0; stride >>= 1) { // fixed tree: run-to-run identical
-    if (tid < stride) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s_acc[tid][j] += s_acc[tid + stride][j];
-      s_bad[tid] |= s_bad[tid + stride];
-      const float o = s_best[tid + stride];
-      if (o > s_best[tid] || (o == s_best[tid] && s_bt[tid + stride] < s_bt[tid])) { s_best[tid] = o; s_bt[tid] = s_bt[tid + stride]; }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const double n = (double)T * (double)D;
-    const double Sc = s_acc[0][0], Sr = s_acc[0][1], Scc = s_acc[0][2], Srr = s_acc[0][3];
-    const double Sd = s_acc[0][4], Sad = s_acc[0][5], Sdd = s_acc[0][6], Ns = s_acc[0][7];
-    const double nan = __longlong_as_double(0x7ff8000000000000LL);
-    double sc[4];
-    const double grel = sqrt(Sdd) / fmax(sqrt(Srr), 1e-30);
-    const double mrel = s_bad[0] ? nan : (double)fmaxf(s_best[0], 0.0f);
-    sc[SV_IDX_RELL2] = (reduce == SV_REDUCE_MAX_TOKEN) ? mrel : grel;
-    sc[SV_IDX_L1] = Sad / n;
-    // z-scored L2 = 2 (1 - rho) = (var_d - (sd_c - sd_r)^2) / (sd_c sd_r): no cancellation for rho ~ 1
-    const double mc = Sc / n, mr = Sr / n, md = Sd / n;
-    const double vc = Scc / n - mc * mc, vr = Srr / n - mr * mr, vd = fmax(Sdd / n - md * md, 0.0);
-    const bool const_c = !(vc > 1e-10 * (Scc / n)), const_r = !(vr > 1e-10 * (Srr / n));
-    if (Scc != Scc || Srr != Srr) sc[SV_IDX_ZL2] = nan;
-    else if (const_c && const_r) sc[SV_IDX_ZL2] = 0.0;
-    else if (const_c || const_r) sc[SV_IDX_ZL2] = 2.0;
-    else {
-      const double a = sqrt(vc), b = sqrt(vr);
-      sc[SV_IDX_ZL2] = fmax(vd - (a - b) * (a - b), 0.0) / (a * b);
-    }
-    sc[SV_IDX_SFR] = Ns / n;
-    sv_result r;
-    uint32_t flag = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool on = ((mask >> i) & 1u) || i == SV_IDX_RELL2;         // the relative L2 is always formed
-      r.score[i] = on ? (float)sc[i] : 0.0f;
-      if (((mask >> i) & 1u) && !(r.score[i] <= tau.v[i])) flag = 1;   // strict '>'; non-finite scores are flagged
-    }
-    r.flag = flag; r.metric_mask = mask;
-    r.max_token_rell2 = (float)mrel; r.argmax_token = s_bt[0];
-    results[claim] = r;
-  }
-}
-
 template <typename E>
 __global__ __launch_bounds__(256) void ema_update_kernel(float* m, const E* __restrict__ claims, int64_t claim_stride,
                                                          int n_claims, const uint8_t* __restrict__ flags, int64_t n_vec, float beta, const float* m_from) {
@@ -473,11 +498,18 @@ __global__ __launch_bounds__(256) void ema_update_kernel(float* m, const E* __re
 
 }  // namespace
 
+namespace {
+Verdict make_verdict(uint32_t mask, const float* tau4, int reduce, sv_result* results) {
+  Verdict v{mask, {}, reduce, results};
+  for (int i = 0; i < 4; ++i) v.tau.v[i] = tau4 ? tau4[i] : 0.0f;
+  return v;
+}
+}  // namespace
+
 hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
                                  int reduce, sv_result* results, hipStream_t st) {
-  Tau4 tau;
-  for (int i = 0; i < 4; ++i) tau.v[i] = tau4 ? tau4[i] : 0.0f;
-  hipLaunchKernelGGL(score_finalize_kernel, dim3(n_claims), dim3(tiles <= 128 ? 64 : 256), 0, st, partials, tiles, T, D, mask, tau, reduce, results);
+  hipLaunchKernelGGL(score_finalize_kernel, dim3(n_claims), dim3(finalize_threads(tiles)), 0, st, partials, tiles, T, D,
+                     make_verdict(mask, tau4, reduce, results));
   return hipGetLastError();
 }
 
@@ -497,7 +529,7 @@ hipError_t launch_ema_from_sum(float* m, const float* sum, int n_summed, int64_t
 hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, const void* ref, int64_t ref_stride,
                         int claim_dtype, int ref_dtype, int64_t T, int D, uint32_t mask, const float* tau4, int reduce,
                         float* token_scores, sv_result* results, ScorePartial* scratch, int64_t scratch_elems,
-                        hipStream_t st, uint32_t skip, float* sum_out) {
+                        hipStream_t st, uint32_t* arrivals, uint32_t skip, float* sum_out) {
   if (n_claims <= 0 || T <= 0) return hipSuccess;
   if (sum_out && !score_sum_supported(n_claims, ref_stride, claim_dtype, D)) return hipErrorInvalidValue;
   const int64_t tiles = (T + kScoreTokensPerWG - 1) / kScoreTokensPerWG;
@@ -561,12 +593,16 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     const bool few = tiles * nc <= cu_count() && tiles4 * nc <= scratch_elems;
     const int tpc = (int)(few ? tiles4 : tiles);
     const dim3 gridt((unsigned)(8 * ((tpc + 7) / 8) * nc));
+    // Few records: every workgroup pays for making its record visible to the other XCDs and for counting it.  With a reduction launch ->
+    // without: 32 records 14.5 -> 12.2 us, 64 14.7 -> 11.9, but 1024 of one submission 16.5 -> 85.
+    uint32_t* const arrive = (int64_t)tpc * nc <= kScoreArrivals ? arrivals : nullptr;
+    const Verdict verdict = make_verdict(mask, tau4, reduce, results + c0);
 #define SV_LAUNCH_SCORE3(EC, ER, L1, Z, SFR)                                                                           \
   do {                                                                                                                 \
     if (few) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
-                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch);                          \
+                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);         \
     else hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, kScoreTokensPerWG>), gridt, block, 0, st, (const EC*)cp, claim_stride, \
-                            (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch);                              \
+                            (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);             \
   } while (0)
 #define SV_LAUNCH_SCORE(EC, ER)                                                                                          \
   do {                                                                                                                   \
@@ -583,6 +619,7 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     else SV_LAUNCH_SCORE(float, float);
 #undef SV_LAUNCH_SCORE
 #undef SV_LAUNCH_SCORE3
+    if (arrive) continue;
     hipError_t e = launch_score_finalize(scratch, nc, tpc, T, D, mask, tau4, reduce, results + c0, st);
     if (e != hipSuccess) return e;
   }
@@ -689,7 +726,7 @@ extern "C" sv_status sv_score_and_flag_noalloc(const void* claims, int64_t claim
   // every record the finalize step reads is written by the pass before it in this same call, so nothing has to be
   // cleared between calls; the records of an earlier, larger call beyond this call's range are simply not read
   e = sv::launch_score(claims, claim_stride, n_claims, ref, ref_stride, claim_dtype, ref_dtype, T, D, metric_mask, tau, reduce,
-                       token_scores_out, results_dev, records, kStaticScoreRecords, (hipStream_t)stream);
+                       token_scores_out, results_dev, records, kStaticScoreRecords, (hipStream_t)stream, nullptr);
   if (e != hipSuccess) { set_global_error("launching the score pass failed: %s", hipGetErrorString(e)); return SV_EHIP; }
   return SV_OK;
 }
