@@ -39,8 +39,8 @@ struct Arena {
 
 constexpr int64_t kScoreScratchElems = 1 << 18;   // ScorePartial records (20 MiB)
 constexpr int kSwMaxDirs = 128, kSwMaxClaims = 4096;
-// Heads narrower than the matrix-core attention's widths (32, 64, 128) are zero-padded to the next one: 0 = no padding
-inline int attn_pad_width(int hd) { return hd < 32 ? 32 : (hd > 32 && hd < 64 ? 64 : 0); }
+// Heads between the matrix-core attention's widths (16, 32, 64, 128) are zero-padded to 32 or 64: 0 = no padding
+inline int attn_pad_width(int hd) { return hd == 16 ? 0 : hd < 32 ? 32 : (hd > 32 && hd < 64 ? 64 : 0); }
 constexpr int kSwSlots = 33;                      // projected tensors (kSwMaxDirs rows each) the scratch holds at max_tokens
 
 }  // namespace
@@ -353,9 +353,8 @@ hipError_t gemm(sv_ctx* c, const GemmArgs& a, hipStream_t st) {
   return plain_gemm(a, c->d.dtype, st);
 }
 
-// Heads of 8, 16 or 32 columns run on the 64-column matrix-core kernels through zero-padded copies (the products are
-// unchanged by zero columns; the softmax scale stays 1/sqrt(hd)); three quarters or more of those MFMAs multiply zeros,
-// which is still several times faster than the scalar kernels.
+// Heads of 8, 24, 40, 48 or 56 columns run on the 32- or 64-column matrix-core kernels through zero-padded copies (the products are
+// unchanged by zero columns; the softmax scale stays 1/sqrt(hd)), which is several times faster than the scalar kernels.
 bool attn_padded(const sv_ctx* c, int S) {
   const sv_stage_desc& d = c->d;
   return c->qkv_pad != nullptr && mfma_attn_supported(S, d.n_heads, d.n_kv_heads, c->pad_hd, (int64_t)(d.n_heads + 2 * d.n_kv_heads) * c->pad_hd);

@@ -1,5 +1,5 @@
 // Causal / full softmax attention of the block recompute on the gfx950 matrix cores
-// (bf16 inputs, fp32 scores, softmax statistics and accumulation; head_dim 64 or 128; GQA).
+// (bf16 inputs, fp32 scores, softmax statistics and accumulation; head_dim 16, 32, 64 or 128; GQA).
 //
 // Forward: one workgroup = 128 queries of one (sequence, query head); each of its 4 waves owns
 // 32 queries.  Keys/values stream through LDS in tiles of 64, double buffered.  Per tile a wave
@@ -110,11 +110,15 @@ __device__ __forceinline__ void dma16(const char* g_lane, char* lds) {          
 // which the loads it does not know of would turn into waits for the next tile.
 __device__ __forceinline__ void dma_wait_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }     // vmcnt(0) only
 
+// HW: columns of a head in memory, where they are fewer than a tile row's: the chunks behind them repeat the head's own, and whoever
+// reads a row along its columns stops at the head's last.
+template <int HD, int HW> __device__ __forceinline__ int own_chunk(int c) { return HW < HD ? c & (HW / 8 - 1) : c; }
+
 // Two 64-row tiles (rows r0 .. r0 + 63 of a and of b, HD bf16 each, row pitches lda / ldb, clamped to the last valid
 // row) go global -> LDS
 // row-major with global_load_lds: no registers, no LDS write instructions.  One wave instruction moves 1 KB = RPI rows;
 // lane (row, position p) fetches the 16-byte chunk that belongs at position p of its row under rm_pos.  256 threads.
-template <int HD, int SW = 0>
+template <int HD, int SW = 0, int HW = HD>
 __device__ __forceinline__ void stage_two_tiles(const bf16* a, int64_t lda, const bf16* b, int64_t ldb, int r0, int last_row, char* ta,
                                                 char* tb, int wave, int lane) {
   constexpr int KCH = HD / 8, KROW = HD * 2, RPI = 1024 / KROW, IPW = (64 / RPI) / 4;
@@ -123,7 +127,7 @@ __device__ __forceinline__ void stage_two_tiles(const bf16* a, int64_t lda, cons
   for (int i = 0; i < IPW; ++i) {
     const int ii = wave * IPW + i, r = ii * RPI + s_row;
     const int rr = min(r, last_row - r0);                       // row within the tile, clamped to the last valid one
-    const int col = rm_pos<HD, SW>(s_pos, r) * 8;
+    const int col = own_chunk<HD, HW>(rm_pos<HD, SW>(s_pos, r)) * 8;
     dma16((const char*)(a + (int64_t)r0 * lda), (unsigned)((int64_t)rr * lda + col) * 2u, ta + ii * 1024);
     dma16((const char*)(b + (int64_t)r0 * ldb), (unsigned)((int64_t)rr * ldb + col) * 2u, tb + ii * 1024);
   }
@@ -132,7 +136,7 @@ __device__ __forceinline__ void stage_two_tiles(const bf16* a, int64_t lda, cons
 // The same transfer for tiles that lie inside the valid rows, with the per-lane part of the addresses made once per
 // kernel: 32-bit byte offsets (row within the tile, swizzled chunk) that are added to a wave-uniform tile pointer, so a
 // tile costs its load instructions and a few scalar adds instead of a 64-bit multiply chain per load.
-template <int HD, int NW = 4, int SW = 0>
+template <int HD, int NW = 4, int SW = 0, int HW = HD>
 struct TileOffsets {
   static constexpr int KCH = HD / 8, KROW = HD * 2, RPI = 1024 / KROW, IPW = (64 / RPI) / NW;
   unsigned off[IPW];
@@ -141,12 +145,12 @@ struct TileOffsets {
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
       const int r = (wave * IPW + i) * RPI + s_row;
-      off[i] = (unsigned)((int64_t)r * ld + rm_pos<HD, SW>(s_pos, r) * 8) * 2u;
+      off[i] = (unsigned)((int64_t)r * ld + own_chunk<HD, HW>(rm_pos<HD, SW>(s_pos, r)) * 8) * 2u;
     }
   }
 };
-template <int HD, int NW = 4, int SW = 0>
-__device__ __forceinline__ void stage_tile_fast(const bf16* tile_rows, const TileOffsets<HD, NW, SW>& o, char* dst, int wave) {
+template <int HD, int NW = 4, int SW = 0, int HW = HD>
+__device__ __forceinline__ void stage_tile_fast(const bf16* tile_rows, const TileOffsets<HD, NW, SW, HW>& o, char* dst, int wave) {
   const char* g = (const char*)tile_rows;           // wave-uniform: first row of the tile
 #pragma unroll
   for (int i = 0; i < TileOffsets<HD, NW, SW>::IPW; ++i)
@@ -174,13 +178,13 @@ __device__ __forceinline__ bf16x8 tr_fragment(const char* tile, int g, int db, i
   return f;
 }
 
-template <int HD, bool CAUSAL>
+template <int HD, bool CAUSAL, int HW = HD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_mfma_kernel(const bf16* __restrict__ qkv, int64_t ld, bf16* __restrict__ o,
                                                             float* __restrict__ lse, int B, int S, int H, int Hkv, float scale_log2e, int pair) {
   constexpr int KCH = HD / 8;                       // 16-byte chunks per K row
   constexpr int KROW = HD * 2;                      // bytes per K row in LDS
   constexpr int KSTAGE = BKV * KROW, VSTAGE = BKV * KROW, STAGE = KSTAGE + VSTAGE;
-  constexpr int NKK = HD / 16, NDB = HD / 32;
+  constexpr int NKK = HW / 16, NDB = HD / 32;        // heads of 16 columns: half of a tile row's, and one k step
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int nqt = (S + BQ - 1) / BQ;
@@ -188,8 +192,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (!xcd_map((int)blockIdx.x, paired_tiles(pair, nqt), H / Hkv, Hkv, B, rank, h, b)) return;
   const int kvh = h / (H / Hkv);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, half = lane >> 5;
-  const int Dq = H * HD, Dkv = Hkv * HD;
-  TileOffsets<HD> toff;
+  const int Dq = H * HW, Dkv = Hkv * HW;
+  TileOffsets<HD, 4, 0, HW> toff;
   toff.init(ld, wave, lane);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   // Per-lane LDS byte offsets of the fragment reads, made once: the swizzle only looks at the low four bits of a row, so
@@ -211,8 +215,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int pass = 0; pass < n_passes(pair, nqt, rank); ++pass) {
   const int qt = pass == 0 ? nqt - 1 - rank : rank;
   const int q0 = qt * BQ, wq0 = q0 + wave * 32;
-  const bf16* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * HD;
-  const bf16* kbase = qkv + (int64_t)b * S * ld + Dq + (int64_t)kvh * HD;
+  const bf16* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * HW;
+  const bf16* kbase = qkv + (int64_t)b * S * ld + Dq + (int64_t)kvh * HW;
   const bf16* vbase = kbase + Dkv;
 
   bf16x8 qf[NKK];
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       stage_tile_fast<HD>(kbase + (int64_t)j * BKV * ld, toff, ks, wave_u);
       stage_tile_fast<HD>(vbase + (int64_t)j * BKV * ld, toff, ks + KSTAGE, wave_u);
     } else {
-      stage_two_tiles<HD>(kbase, ld, vbase, ld, j * BKV, S - 1, ks, ks + KSTAGE, wave, lane);   // keys past the end: masked later
+      stage_two_tiles<HD, 0, HW>(kbase, ld, vbase, ld, j * BKV, S - 1, ks, ks + KSTAGE, wave, lane);   // keys past the end: masked later
     }
   };
 
@@ -353,14 +357,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // phase 0
 #pragma unroll
       for (int kk = 0; kk < NKK; ++kk) {
-        kf[(kk + KD) % (KD + 1)] = kread(kk + KD);
+        if (kk + KD < 2 * NKK) kf[(kk + KD) % (KD + 1)] = kread(kk + KD);
         __builtin_amdgcn_sched_barrier(0);
         s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk % (KD + 1)], qf[kk], s[0], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (SPREAD) {                                  // NKK = the wave's load instructions per tile: K then V
+        if (SPREAD) {                                  // the wave's load instructions of the tile, K then V: one per MFMA (heads of 16: both)
           constexpr int IPW = TileOffsets<HD>::IPW;
-          const bf16* src = (kk / IPW ? vbase : kbase) + (int64_t)(j + 1) * BKV * ld;
-          dma16((const char*)src, toff.off[kk % IPW], smem + ((j + 1) & 1) * STAGE + (kk / IPW) * KSTAGE + (wave_u * IPW + kk % IPW) * 1024);
+#pragma unroll
+          for (int u = kk * 2 * IPW / NKK; u < (kk + 1) * 2 * IPW / NKK; ++u) {
+            const bf16* src = (u / IPW ? vbase : kbase) + (int64_t)(j + 1) * BKV * ld;
+            dma16((const char*)src, toff.off[u % IPW], smem + ((j + 1) & 1) * STAGE + (u / IPW) * KSTAGE + (wave_u * IPW + u % IPW) * 1024);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -373,7 +380,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = kk * NPV / NKK; u < (kk + 1) * NPV / NKK; ++u) vf[0][u] = vread(u / NDB, u % NDB);
-        soft_slice(0, kk, NKK);
+        constexpr int NS = NKK > 1 ? NKK : 2;
+#pragma unroll
+        for (int u = kk * NS / NKK; u < (kk + 1) * NS / NKK; ++u) soft_slice(0, u, NS);
         __builtin_amdgcn_sched_barrier(0);
       }
       soft_end();
@@ -417,6 +426,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
+        if (db * 32 + g4 * 8 >= HW) continue;
         bf16x4 pk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) pk[i] = (bf16)(oacc[db][g4 * 4 + i] * inv);
@@ -429,7 +439,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int it = 0; it < 32 / RPO; ++it) {
       const int row = it * RPO + orow, q = wq0 + row;
       const bf16x8 v = *reinterpret_cast<const LDS bf16x8*>(patch + row * KROW + ((ochunk ^ (row & (NCH - 1))) << 4));
-      if (q < S) *reinterpret_cast<bf16x8*>(o + ((int64_t)b * S + q) * Dq + (int64_t)h * HD + ochunk * 8) = v;
+      if (q < S && (HW == HD || ochunk < HW / 8)) *reinterpret_cast<bf16x8*>(o + ((int64_t)b * S + q) * Dq + (int64_t)h * HW + ochunk * 8) = v;
     }
     if (myq < S && half == 0) lse[((int64_t)b * H + h) * S + myq] = (m_run + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994531f;
   }
@@ -468,12 +478,12 @@ __device__ __forceinline__ void unrope4(float (&v)[4], const float* __restrict__
   v[3] = b1 * t[2] - a1 * t[3];
 }
 
-template <int HD, bool CAUSAL>
+template <int HD, bool CAUSAL, int HW = HD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_mfma_kernel(const bf16* __restrict__ qkv, int64_t ld, const bf16* __restrict__ o,
                                                                const bf16* __restrict__ dout, const float* __restrict__ lse,
                                                                float* __restrict__ delta, bf16* __restrict__ dqkv, int B, int S, int H, int Hkv,
                                                                float scale, const float* __restrict__ rope_cs, int pair) {
-  constexpr int KCH = HD / 8, NKK = HD / 16, NDB = HD / 32;
+  constexpr int KCH = HD / 8, NKK = HW / 16, NDB = HD / 32;
   constexpr int TILE = BKV * HD * 2;                 // bytes of one 64-row tile (row-major or transposed)
   constexpr int STAGE = 2 * TILE;                    // K and V, both row-major (K is read along its rows and transposed)
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -482,11 +492,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (!xcd_map((int)blockIdx.x, paired_tiles(pair, nqt), H / Hkv, Hkv, B, rank, h, b)) return;
   const int kvh = h / (H / Hkv);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l31 = lane & 31, half = lane >> 5;
-  const int Dq = H * HD, Dkv = Hkv * HD;
+  const int Dq = H * HW, Dkv = Hkv * HW;
   const float c2 = scale * 1.4426950408889634f;
-  const bf16* kbase = qkv + (int64_t)b * S * ld + Dq + (int64_t)kvh * HD;
+  const bf16* kbase = qkv + (int64_t)b * S * ld + Dq + (int64_t)kvh * HW;
   const bf16* vbase = kbase + Dkv;
-  TileOffsets<HD> toff;
+  TileOffsets<HD, 4, 0, HW> toff;
   toff.init(ld, wave, lane);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   for (int pass = 0; pass < n_passes(pair, nqt, rank); ++pass) {
@@ -497,9 +507,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   bf16x8 qf[NKK], dof[NKK];
   float dl = 0.0f;
   {
-    const bf16* qp = qkv + ((int64_t)b * S + qrow) * ld + (int64_t)h * HD;
-    const bf16* op = o + ((int64_t)b * S + qrow) * Dq + (int64_t)h * HD;
-    const bf16* dp = dout + ((int64_t)b * S + qrow) * Dq + (int64_t)h * HD;
+    const bf16* qp = qkv + ((int64_t)b * S + qrow) * ld + (int64_t)h * HW;
+    const bf16* op = o + ((int64_t)b * S + qrow) * Dq + (int64_t)h * HW;
+    const bf16* dp = dout + ((int64_t)b * S + qrow) * Dq + (int64_t)h * HW;
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) {
       qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16 + half * 8);
@@ -522,7 +532,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       stage_tile_fast<HD>(kbase + (int64_t)j * BKV * ld, toff, base, wave_u);
       stage_tile_fast<HD>(vbase + (int64_t)j * BKV * ld, toff, base + TILE, wave_u);
     } else {
-      stage_two_tiles<HD>(kbase, ld, vbase, ld, j * BKV, S - 1, base, base + TILE, wave, lane);
+      stage_two_tiles<HD, 0, HW>(kbase, ld, vbase, ld, j * BKV, S - 1, base, base + TILE, wave, lane);
     }
   };
 
@@ -603,10 +613,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
+        if (db * 32 + g4 * 8 >= HW) continue;
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = dq[db][g4 * 4 + i] * scale;
-        if (rope_cs) unrope4<HD>(v, rope_cs, pq, db * 32 + g4 * 8 + half * 4);
+        if (rope_cs) unrope4<HW>(v, rope_cs, pq, db * 32 + g4 * 8 + half * 4);
         bf16x4 pk;
 #pragma unroll
         for (int i = 0; i < 4; ++i) pk[i] = (bf16)v[i];
@@ -619,7 +630,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int it = 0; it < 32 / RPO; ++it) {
       const int row = it * RPO + orow, q = wq0 + row;
       const bf16x8 v = *reinterpret_cast<const LDS bf16x8*>(patch + row * (HD * 2) + ((ochunk ^ (row & (KCH - 1))) << 4));
-      if (q < S) *reinterpret_cast<bf16x8*>(dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * HD + ochunk * 8) = v;
+      if (q < S && (HW == HD || ochunk < HW / 8)) *reinterpret_cast<bf16x8*>(dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * HW + ochunk * 8) = v;
     }
   }
   }  // pass
@@ -655,7 +666,7 @@ __device__ __forceinline__ bf16x8 tr16_fragment(const char* tile, int jj, int fb
 // S = Q K^T and dP = dO V^T with the QUERIES in the row dimension, so each lane owns one key column and four queries
 // per block; P and dS of two blocks are, as they sit in the lane, one B operand (32 queries deep) for
 // dV^T += dO^T P and dK^T += Q^T dS, whose A operands come out of the same row-major LDS tiles by transposing reads.
-template <int HD, bool CAUSAL>
+template <int HD, bool CAUSAL, int HW = HD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_mfma_kernel(
     const bf16* __restrict__ qkv, int64_t ld, const bf16* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
     bf16* __restrict__ dqkv, int B, int S, int H, int Hkv, float scale, const float* __restrict__ rope_cs, float* __restrict__ part, int pair) {
@@ -675,9 +686,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     kvh = hsel / G;
   } else if (!xcd_map((int)blockIdx.x, paired_tiles(pair, nkt), 1, Hkv, B, rank, kvh, b)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, lg = lane >> 4;
-  const int Dq = H * HD, Dkv = Hkv * HD;
+  const int Dq = H * HW, Dkv = Hkv * HW;
   const float c2 = scale * 1.4426950408889634f;
-  TileOffsets<HD, 4, 1> toff_q, toff_d;
+  TileOffsets<HD, 4, 1, HW> toff_q, toff_d;
   toff_q.init(ld, wave, lane);
   toff_d.init(Dq, wave, lane);
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -688,11 +699,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   bf16x8 kf[NK], vf[NK];                              // this lane's key / value row, 8 features of every 32
   {
-    const bf16* kp = qkv + ((int64_t)b * S + krow) * ld + Dq + (int64_t)kvh * HD;
+    const bf16* kp = qkv + ((int64_t)b * S + krow) * ld + Dq + (int64_t)kvh * HW;
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
-      kf[kk] = *reinterpret_cast<const bf16x8*>(kp + kk * 32 + lg * 8);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(kp + Dkv + kk * 32 + lg * 8);
+      const int col = kk * 32 + lg * 8;
+      if (HW % 32) kf[kk] = vf[kk] = bf16x8{};
+      if (HW % 32 && col >= HW) continue;              // of the 32 columns of the step a head has 16
+      kf[kk] = *reinterpret_cast<const bf16x8*>(kp + col);
+      vf[kk] = *reinterpret_cast<const bf16x8*>(kp + Dkv + col);
     }
   }
   const int qstart = CAUSAL ? k0 : 0;                // a multiple of 64
@@ -702,8 +716,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto stage_tile = [&](int j, int stage) {            // Q and dO tiles straight to LDS; the two per-query scalars via registers
     const int h = part ? hsel : kvh * G + j / nq, q0 = qstart + (j % nq) * 64;
     char* base = smem + stage * STAGE;
-    const bf16* qrows = qkv + (int64_t)b * S * ld + (int64_t)h * HD;
-    const bf16* drows = dout + (int64_t)b * S * Dq + (int64_t)h * HD;
+    const bf16* qrows = qkv + (int64_t)b * S * ld + (int64_t)h * HW;
+    const bf16* drows = dout + (int64_t)b * S * Dq + (int64_t)h * HW;
     // the two scalar loads go first: they are waited for when the tile is nearly done, and a wait for a load also
     // waits for every older one -- behind the tile loads they would drag those along
     if (tid < 64) {
@@ -712,10 +726,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       dlreg = delta[li];
     }
     if (q0 + 64 <= S) {                              // whole tile inside the sequence (uniform)
-      stage_tile_fast<HD, 4, 1>(qrows + (int64_t)q0 * ld, toff_q, base, wave_u);
-      stage_tile_fast<HD, 4, 1>(drows + (int64_t)q0 * Dq, toff_d, base + TILE, wave_u);
+      stage_tile_fast<HD, 4, 1, HW>(qrows + (int64_t)q0 * ld, toff_q, base, wave_u);
+      stage_tile_fast<HD, 4, 1, HW>(drows + (int64_t)q0 * Dq, toff_d, base + TILE, wave_u);
     } else {
-      stage_two_tiles<HD, 1>(qrows, ld, drows, Dq, q0, S - 1, base, base + TILE, wave, lane);
+      stage_two_tiles<HD, 1, HW>(qrows, ld, drows, Dq, q0, S - 1, base, base + TILE, wave, lane);
     }
   };
   auto store_scalars = [&](int stage) {
@@ -756,8 +770,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, dp = {0.0f, 0.0f, 0.0f, 0.0f};
   #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
-          const bf16x8 qf = *reinterpret_cast<const bf16x8*>(qs + rm_off<HD, 1>(row, kk * 4 + lg));
-          const bf16x8 df = *reinterpret_cast<const bf16x8*>(ds_ + rm_off<HD, 1>(row, kk * 4 + lg));
+          bf16x8 qf = *reinterpret_cast<const bf16x8*>(qs + rm_off<HD, 1>(row, kk * 4 + lg));
+          bf16x8 df = *reinterpret_cast<const bf16x8*>(ds_ + rm_off<HD, 1>(row, kk * 4 + lg));
+          if (HW % 32 && lg * 8 >= HW) qf = df = bf16x8{};     // not the repeated columns times zero: they may be infinite
           s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf, kf[kk], s, 0, 0, 0);
           dp = __builtin_amdgcn_mfma_f32_16x16x32_bf16(df, vf[kk], dp, 0, 0, 0);
         }
@@ -780,7 +795,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
 #pragma unroll
-    for (int fb = 0; fb < NFB; ++fb)
+    for (int fb = 0; fb < HW / 16; ++fb)
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const bf16x8 dtf = tr16_fragment<HD>(ds_, jj, fb, lane);
@@ -794,13 +809,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   // this lane: key mykey, features 16 fb + 4 lg .. + 3 of dK and dV
   if (mykey < S && part) {                           // the rotation is linear: undone per contribution
-    float* out = part + (((int64_t)(hsel - kvh * G) * B + b) * S + mykey) * (2 * Dkv) + (int64_t)kvh * HD;
+    float* out = part + (((int64_t)(hsel - kvh * G) * B + b) * S + mykey) * (2 * Dkv) + (int64_t)kvh * HW;
 #pragma unroll
-    for (int fb = 0; fb < NFB; ++fb) {
+    for (int fb = 0; fb < HW / 16; ++fb) {
       float v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = dk[fb][i] * scale;
-      if (rope_cs) unrope4<HD>(v, rope_cs, mykey, fb * 16 + lg * 4);
+      if (rope_cs) unrope4<HW>(v, rope_cs, mykey, fb * 16 + lg * 4);
       f32x4 ok;
 #pragma unroll
       for (int i = 0; i < 4; ++i) ok[i] = v[i];
@@ -816,11 +831,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int e15 = l15, elg = lg, elane = lane;            // opaque: the patch addresses are not to live across the tile loop
     asm volatile("" : "+v"(e15), "+v"(elg), "+v"(elane));
 #pragma unroll
-    for (int fb = 0; fb < NFB; ++fb) {
+    for (int fb = 0; fb < HW / 16; ++fb) {
       float v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = dk[fb][i] * scale;
-      if (rope_cs) unrope4<HD>(v, rope_cs, krow, fb * 16 + lg * 4);
+      if (rope_cs) unrope4<HW>(v, rope_cs, krow, fb * 16 + lg * 4);
       bf16x4 pk, pv;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { pk[i] = (bf16)v[i]; pv[i] = (bf16)dv[fb][i]; }
@@ -837,8 +852,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       LDS const char* const at = patch + row * ROWB + ((ochunk ^ (row & (KCH - 1))) << 4);
       const bf16x8 vk = *reinterpret_cast<const LDS bf16x8*>(at);
       const bf16x8 vv = *reinterpret_cast<const LDS bf16x8*>(at + 16 * ROWB);
-      if (key < S) {
-        bf16* out = dqkv + ((int64_t)b * S + key) * ld + Dq + (int64_t)kvh * HD + ochunk * 8;
+      if (key < S && (HW == HD || ochunk < HW / 8)) {
+        bf16* out = dqkv + ((int64_t)b * S + key) * ld + Dq + (int64_t)kvh * HW + ochunk * 8;
         *reinterpret_cast<bf16x8*>(out) = vk;
         *reinterpret_cast<bf16x8*>(out + Dkv) = vv;
       }
@@ -871,7 +886,7 @@ __global__ __launch_bounds__(256) void attn_dkv_sum_kernel(const float* __restri
 }  // namespace
 
 bool mfma_attn_supported(int S, int H, int Hkv, int hd, int64_t ld) {
-  return (hd == 32 || hd == 64 || hd == 128) && S >= 1 && H % Hkv == 0 && ld % 8 == 0;
+  return (hd == 16 || hd == 32 || hd == 64 || hd == 128) && S >= 1 && H % Hkv == 0 && ld % 8 == 0;
 }
 
 hipError_t mfma_attn_fwd(const void* qkv, int64_t ld, void* o, float* lse, int B, int S, int H, int Hkv, int hd, int causal, hipStream_t st,
@@ -882,9 +897,9 @@ hipError_t mfma_attn_fwd(const void* qkv, int64_t ld, void* o, float* lse, int B
   const int pair = pair_tiles(causal, nqt, (int64_t)B * H);
   const dim3 grid(xcd_grid(paired_tiles(pair, nqt), H / Hkv, Hkv, B)), block(256);
   const float c = 1.4426950408889634f / sqrtf((float)(scale_hd > 0 ? scale_hd : hd));
-#define SV_ATTN_LAUNCH(HDV, CZ)                                                                                         \
+#define SV_ATTN_LAUNCH(HDV, CZ, HWV)                                                                                     \
   do {                                                                                                                  \
-    auto kern = attn_fwd_mfma_kernel<HDV, CZ>;                                                                          \
+    auto kern = attn_fwd_mfma_kernel<HDV, CZ, HWV>;                                                                     \
     constexpr int lds = 2 * (BKV * HDV * 2 + HDV * 128);                                                                \
     static bool configured = false;                                                                                     \
     if (!configured) {                                                                                                  \
@@ -894,9 +909,10 @@ hipError_t mfma_attn_fwd(const void* qkv, int64_t ld, void* o, float* lse, int B
     }                                                                                                                   \
     hipLaunchKernelGGL(kern, grid, block, lds, st, (const bf16*)qkv, ld, (bf16*)o, lse, B, S, H, Hkv, c, pair);                  \
   } while (0)
-  if (hd == 128) { if (causal) SV_ATTN_LAUNCH(128, true); else SV_ATTN_LAUNCH(128, false); }
-  else if (hd == 64) { if (causal) SV_ATTN_LAUNCH(64, true); else SV_ATTN_LAUNCH(64, false); }
-  else { if (causal) SV_ATTN_LAUNCH(32, true); else SV_ATTN_LAUNCH(32, false); }
+  if (hd == 128) { if (causal) SV_ATTN_LAUNCH(128, true, 128); else SV_ATTN_LAUNCH(128, false, 128); }
+  else if (hd == 64) { if (causal) SV_ATTN_LAUNCH(64, true, 64); else SV_ATTN_LAUNCH(64, false, 64); }
+  else if (hd == 32) { if (causal) SV_ATTN_LAUNCH(32, true, 32); else SV_ATTN_LAUNCH(32, false, 32); }
+  else { if (causal) SV_ATTN_LAUNCH(32, true, 16); else SV_ATTN_LAUNCH(32, false, 16); }
 #undef SV_ATTN_LAUNCH
   return hipGetLastError();
 }
@@ -918,10 +934,10 @@ hipError_t mfma_attn_bwd(const void* qkv, int64_t ld, const void* o, const void*
   float* part = split ? part_ws : nullptr;
   const dim3 gq(xcd_grid(paired_tiles(pair_q, nqt), G, Hkv, B)), gk(xcd_grid(paired_tiles(pair_k, nkt), split ? G : 1, Hkv, B)), block(256);
   const float scale = 1.0f / sqrtf((float)(scale_hd > 0 ? scale_hd : hd));
-#define SV_ATTN_BWD_LAUNCH(HDV, CZ)                                                                                     \
+#define SV_ATTN_BWD_LAUNCH(HDV, CZ, HWV)                                                                                 \
   do {                                                                                                                  \
-    auto kq = attn_bwd_dq_mfma_kernel<HDV, CZ>;                                                                         \
-    auto kk = attn_bwd_dkv_mfma_kernel<HDV, CZ>;                                                                        \
+    auto kq = attn_bwd_dq_mfma_kernel<HDV, CZ, HWV>;                                                                    \
+    auto kk = attn_bwd_dkv_mfma_kernel<HDV, CZ, HWV>;                                                                   \
     constexpr int lq = 2 * 2 * (64 * HDV * 2), lk = 2 * (2 * 64 * HDV * 2 + 512);                                       \
     static bool configured = false;                                                                                     \
     if (!configured) {                                                                                                  \
@@ -935,9 +951,10 @@ hipError_t mfma_attn_bwd(const void* qkv, int64_t ld, const void* o, const void*
     hipLaunchKernelGGL(kk, gk, block, lk, st, (const bf16*)qkv, ld, (const bf16*)dout, lse, delta, (bf16*)dqkv, B, S,   \
                        H, Hkv, scale, rope_cs, part, pair_k);                                                           \
   } while (0)
-  if (hd == 128) { if (causal) SV_ATTN_BWD_LAUNCH(128, true); else SV_ATTN_BWD_LAUNCH(128, false); }
-  else if (hd == 64) { if (causal) SV_ATTN_BWD_LAUNCH(64, true); else SV_ATTN_BWD_LAUNCH(64, false); }
-  else { if (causal) SV_ATTN_BWD_LAUNCH(32, true); else SV_ATTN_BWD_LAUNCH(32, false); }
+  if (hd == 128) { if (causal) SV_ATTN_BWD_LAUNCH(128, true, 128); else SV_ATTN_BWD_LAUNCH(128, false, 128); }
+  else if (hd == 64) { if (causal) SV_ATTN_BWD_LAUNCH(64, true, 64); else SV_ATTN_BWD_LAUNCH(64, false, 64); }
+  else if (hd == 32) { if (causal) SV_ATTN_BWD_LAUNCH(32, true, 32); else SV_ATTN_BWD_LAUNCH(32, false, 32); }
+  else { if (causal) SV_ATTN_BWD_LAUNCH(32, true, 16); else SV_ATTN_BWD_LAUNCH(32, false, 16); }
 #undef SV_ATTN_BWD_LAUNCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !split) return e;

@@ -300,7 +300,7 @@ hipError_t f32_gemm(const GemmArgs& a, hipStream_t st);
 bool f32_attn_supported(const void* qkv, int64_t ld, int B, int H, int hd);
 hipError_t f32_attn_fwd(const float* qkv, int64_t ld, float* o, float* lse, int B, int S, int H, int Hkv, int hd, int causal, hipStream_t st);
 
-// attn_mfma.hip: bf16, head_dim 64 | 128.  scale_hd (0 = hd): the head dimension the softmax scale 1/sqrt(.) is taken from,
+// attn_mfma.hip: bf16, head_dim 16 | 32 | 64 | 128.  scale_hd (0 = hd): the head dimension the softmax scale 1/sqrt(.) is taken from,
 // for inputs whose heads were zero-padded from scale_hd to hd columns
 bool mfma_attn_supported(int S, int H, int Hkv, int hd, int64_t ld);
 hipError_t mfma_attn_fwd(const void* qkv, int64_t ld, void* o, float* lse, int B, int S, int H, int Hkv, int hd, int causal,
