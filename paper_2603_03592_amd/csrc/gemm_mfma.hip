@@ -1231,7 +1231,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // 256 x 256 over runs; 8192 x 1024, K = 8192 (256 tiles of 256 x 128) 113 us against 121 and 124; 8192 x 2048, K = 2048
 // (256 tiles of 256 x 256) 59 us against 64 on 256 x 128; 512 x 4096, K = 14336 (256 x 128 over 4 runs) 63 us against 85 whole;
 // 1024^3 (256 tiles of 64 x 64) 7.0 us against 8.1 on 64 x 128 and 9.6 on 128 x 128.
-enum TileKind { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTile64, kTileKinds };
+enum TileKind { kTile256 = 0, kTile256x128, kTile128, kTile64x128, kTile64, kTileKinds, kTile192x256 = kTileKinds };
 struct TileCost { int bm, bn; double fixed, slice; };
 constexpr TileCost kTileCost[kTileKinds] = {{256, 256, 4.0, 1.55}, {256, 128, 6.5, 0.86}, {128, 128, 5.0, 0.52}, {64, 128, 4.0, 0.36}, {64, 64, 3.5, 0.21}};
 struct Plan { int kind, runs; };
@@ -1258,6 +1258,18 @@ bool fits_mid(const GemmArgs& a) {        // buffer descriptors over a tile's ro
 }
 
 bool summed_runs(const GemmArgs& a) { return a.runs[0] > 1 || a.runs[1] > 1 || a.runs[2] > 1; }
+
+// The epilogues that form an activation or its derivative are a fifth to a third of a product's time at K = 1024, and a launch of fewer
+// 256x256 tiles than CUs does them on part of the chip.  192x256 tiles (eight waves, two stages), while they too are one round, give every
+// CU three quarters of a tile.  256x256 -> 192x256, us: GELU 2331 x 3840, K = 960 (150 tiles, 195 of these) 38.1 -> 31.4, its backward
+// 37.4 -> 30.9; 4096 x 2560, K = 1024 39.1 -> 33.1; SwiGLU with its stashes 2331 x 1920, K = 960 30.7 -> 25.6, its backward at 3840
+// columns 34.9 -> 32.1; 900 x 5120, K = 2048 48.3 -> 43.3; 800 x 6144, K = 3072 68.2 -> 62.6.  With a longer k loop the bare product
+// decides: GELU 768 x 16384, K = 4096 104 -> 112.  (Plain stores and residual sums gain 1 - 9 % and stay where they are: what they run
+// on is what sv_gemm_plan tells.)
+bool narrower_pays(const GemmArgs& a, int slices) {
+  if (a.epi != EPI_GELU && a.epi != EPI_GELU_BWD && a.epi != EPI_SWIGLU && a.epi != EPI_SWIGLU_BWD) return false;
+  return !a.tile_group && slices <= 48 && fits_mid(a) && (int64_t)((a.M + 191) / 192) * (a.N / (a.epi == EPI_SWIGLU ? 128 : 256)) <= cu_count();
+}
 
 // Asked twice for a product that may leave row sums, once to know whether it will (mfma_gemm_emits_rowsq) and once to launch it:
 // with a.rowsq set the answer does not depend on the scratch, which only runs of k use.
@@ -1292,6 +1304,7 @@ Plan plan_gemm(const GemmArgs& a) {
       if (best.kind < 0 || cost < best_cost) { best = Plan{k, runs}; best_cost = cost; }
     }
   }
+  if (best.kind == kTile256 && narrower_pays(a, slices)) best.kind = kTile192x256;
   return best;
 }
 
@@ -1342,6 +1355,10 @@ hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
     case kTile256x128: return launch_mid<4, 2, 2, 2, 3, EPI, GROUPED>(a, 1, st);
     case kTile128: return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED>(a, 1, st);
     case kTile64x128: return launch_mid<2, 2, 1, 2, 3, EPI, GROUPED>(a, 1, st);
+    case kTile192x256:
+      if constexpr (!GROUPED && (EPI == EPI_GELU || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD))
+        return launch_mid<2, 4, 3, 2, 2, EPI, false>(a, 1, st);
+      return hipErrorInvalidValue;
     default:
       if constexpr (EPI != EPI_SWIGLU) return launch_mid<2, 2, 1, 1, 8, EPI, GROUPED>(a, 1, st);
       return hipErrorInvalidValue;
@@ -1408,10 +1425,11 @@ bool mfma_gemm_emits_rowsq(const GemmArgs& a) {
 }
 
 void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs) {
-  constexpr int number[kTileKinds] = {1, 3, 2, 4, 5};
+  constexpr int number[kTileKinds] = {1, 3, 2, 4, 5};       // of the kinds a plain product takes
   *tile = 0; *runs = 1;
   if (a.b_is_kn || !mfma_gemm_supported(a)) return;
   const Plan p = plan_gemm(a);
+  if (p.kind >= kTileKinds) return;
   *tile = number[p.kind]; *runs = p.runs;
 }
 
