@@ -125,7 +125,9 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial*
 // TW: tokens per workgroup, and per record.  With few records of 16 (one submission of up to 4096 tokens) the pass is a chain of
 // memory round trips, one per token of a wave, on a part of the CUs: 4 tokens then, one per wave on four times the workgroups
 // (512 tokens of 4096, both sides bf16: 13 -> 6 us; 2331 of 960: 10 -> 5.5).
-template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, int TW>
+// COUNTED: the workgroup that comes last with a record of its submission forms the scores (an instantiation of its own: with the code
+// for it behind a branch the pass over 4096 tokens of 1024 took 5 us more).
+template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, int TW, bool COUNTED>
 __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
                                                            const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
                                                            int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
@@ -215,10 +217,10 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
   }
   __syncthreads();
   ScorePartial* p = partials + (int64_t)claim * tiles_per_claim + tile;
-  // one sum each, the waves in order; the worst token by the next thread.  All in the first wave, which then counts the record.
+  // one sum each, the waves in order; the worst token beside them, by the first wave too if that then counts the record
   if (threadIdx.x < 8) {
     p->s[threadIdx.x] = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
-  } else if (threadIdx.x == 8) {
+  } else if (threadIdx.x == (COUNTED ? 8 : 64)) {
     float b = -1.0f; int bt = 0, bd = 0;
     for (int w = 0; w < 4; ++w) {
       bd |= s_bad[w];
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
     }
     p->max_rel = b; p->argmax = bt; p->bad = bd; p->pad = 0;
   }
-  if (!arrivals) return;                             // the records go to score_finalize_kernel
+  if constexpr (!COUNTED) return;                    // the records go to score_finalize_kernel
   // The workgroup that comes last with a record of its submission forms the scores: nobody waits, and there is one launch instead of
   // two (1 x 256 tokens of 512: a call 14.7 -> 11.9 us, most of it the host's; the smallest fp32 check 46.6 -> 43.0).  The records are
   // summed in the same order as there.
@@ -595,13 +597,15 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     const dim3 gridt((unsigned)(8 * ((tpc + 7) / 8) * nc));
     // Few records: every workgroup pays for making its record visible to the other XCDs and for counting it.  With a reduction launch ->
     // without: 32 records 14.5 -> 12.2 us, 64 14.7 -> 11.9, but 1024 of one submission 16.5 -> 85.
-    uint32_t* const arrive = (int64_t)tpc * nc <= kScoreArrivals ? arrivals : nullptr;
+    uint32_t* const arrive = few && (int64_t)tpc * nc <= kScoreArrivals ? arrivals : nullptr;
     const Verdict verdict = make_verdict(mask, tau4, reduce, results + c0);
 #define SV_LAUNCH_SCORE3(EC, ER, L1, Z, SFR)                                                                           \
   do {                                                                                                                 \
-    if (few) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
+    if (arrive) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4, true>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
                                 (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);         \
-    else hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, kScoreTokensPerWG>), gridt, block, 0, st, (const EC*)cp, claim_stride, \
+    else if (few) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4, false>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
+                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);         \
+    else hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, kScoreTokensPerWG, false>), gridt, block, 0, st, (const EC*)cp, claim_stride, \
                             (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);             \
   } while (0)
 #define SV_LAUNCH_SCORE(EC, ER)                                                                                          \
