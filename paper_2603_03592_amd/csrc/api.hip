@@ -169,7 +169,6 @@ size_t carve(sv_ctx* c, char* base) {
   Arena a; a.base = base;
   c->rope_cs = (float*)a.take((size_t)c->max_seq * (c->hd / 2) * 2 * sizeof(float));
   c->score_scratch = (ScorePartial*)a.take(kScoreScratchElems * sizeof(ScorePartial));
-  c->score_arrivals = (uint32_t*)a.take(kScoreArrivals * sizeof(uint32_t));
   c->split_ws = nullptr; c->split_ws_floats = 0;
   if (d.dtype == SV_BF16 && !(c->flags & SV_FLAG_PLAIN_KERNELS)) {
     // for products over runs of k: up to 8 partial products of this context's largest, and no more than 84 MB.  A plan takes as
@@ -282,6 +281,7 @@ size_t carve(sv_ctx* c, char* base) {
       }
     }
   }
+  c->score_arrivals = (uint32_t*)a.take(kScoreArrivals * sizeof(uint32_t));
   return a.off + 256;
 }
 
