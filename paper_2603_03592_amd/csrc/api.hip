@@ -85,7 +85,7 @@ struct sv_ctx {
   const void* rowsq_of = nullptr;
   float* delta;
   ScorePartial* score_scratch;
-  uint32_t* score_arrivals;                       // zero between calls
+  uint32_t score_launches = 0;                    // launches of the score pass that carry a number
   float* attn_part;    // fp32 dk | dv contributions per query head of a group (backward, bf16 matrix-core path, one long sequence)
   size_t attn_part_floats;
   float* split_ws;     // fp32 partial products of the split-k GEMMs (bf16 matrix-core path, few tokens against a long k)
@@ -281,7 +281,6 @@ size_t carve(sv_ctx* c, char* base) {
       }
     }
   }
-  c->score_arrivals = (uint32_t*)a.take(kScoreArrivals * sizeof(uint32_t));
   return a.off + 256;
 }
 
@@ -806,10 +805,10 @@ sv_status sv_create(const sv_stage_desc* desc, int64_t max_tokens, int32_t max_s
       cs[((size_t)p * half + i) * 2 + 1] = (float)sin(ang);
     }
   e = hipMemcpy(c->rope_cs, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice);
-  const std::vector<uint32_t> nobody(kScoreArrivals, 0u);
-  if (e == hipSuccess) e = hipMemcpy(c->score_arrivals, nobody.data(), nobody.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+  const std::vector<ScorePartial> nobody(kScoreAloneRecords, ScorePartial{});
+  if (e == hipSuccess) e = hipMemcpy(c->score_scratch, nobody.data(), nobody.size() * sizeof(ScorePartial), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
-    set_err(nullptr, "uploading the RoPE table and the counters: %s", hipGetErrorString(e));
+    set_err(nullptr, "uploading the RoPE table and the empty records: %s", hipGetErrorString(e));
     (void)hipFree(c->ws);
     delete c;
     return SV_EHIP;
@@ -882,7 +881,7 @@ sv_status sv_verify_forward(sv_ctx* c, const sv_block_weights* w, const void* h_
   }
   if (claimed_h)
     SV_OP(c, SV_OP_SCORE, 0, st, launch_score(claimed_h, 0, 1, y, 0, c->d.dtype, c->d.dtype, (int64_t)B * S, c->d.d_model, metric_mask, tau, reduce,
-                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, c->score_arrivals));
+                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, &c->score_launches));
   return SV_OK;
 }
 
@@ -915,7 +914,7 @@ sv_status sv_verify_backward(sv_ctx* c, const sv_block_weights* w, const void* h
   }
   if (claimed_g)
     SV_OP(c, SV_OP_SCORE, 0, st, launch_score(claimed_g, 0, 1, dx, 0, c->d.dtype, c->d.dtype, (int64_t)B * S, c->d.d_model, metric_mask, tau, reduce,
-                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, c->score_arrivals));
+                           token_scores_out, result_dev, c->score_scratch, kScoreScratchElems, st, &c->score_launches));
   return SV_OK;
 }
 
@@ -968,7 +967,7 @@ sv_status sv_score_and_flag(sv_ctx* c, const void* claims, int64_t claim_stride,
   if (T > 0x7fffffffLL || claim_stride < 0 || ref_stride < 0) { set_err(c, "T or a stride is out of range"); return SV_EINVAL; }
   if ((T + kScoreTokensPerWG - 1) / kScoreTokensPerWG > kScoreScratchElems) { set_err(c, "T too large for the score scratch"); return SV_EUNSUPPORTED; }
   SV_HIP(c, launch_score(claims, claim_stride, n_claims, ref, ref_stride, claim_dtype, ref_dtype, T, D, metric_mask, tau, reduce,
-                         token_scores_out, results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, c->score_arrivals));
+                         token_scores_out, results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, &c->score_launches));
   return SV_OK;
 }
 
@@ -992,7 +991,7 @@ sv_status sv_score_and_sum(sv_ctx* c, const void* claims, int64_t claim_stride, 
   for (int i = 0; skip_host && i < n_claims; ++i)
     if (skip_host[i]) skip |= 1u << i;
   SV_HIP(c, launch_score(claims, claim_stride, n_claims, ref, 0, claim_dtype, ref_dtype, T, D, metric_mask, tau, reduce, token_scores_out,
-                         results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, c->score_arrivals, skip, sum_out));
+                         results_dev, c->score_scratch, kScoreScratchElems, (hipStream_t)stream, &c->score_launches, skip, sum_out));
   return SV_OK;
 }
 

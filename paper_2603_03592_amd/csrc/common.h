@@ -117,17 +117,17 @@ struct ScorePartial {   // per (claim, token tile)
   float max_rel;        // max over the tile's tokens of the per-token relative L2
   int32_t argmax;       // token index of that maximum (lowest on ties)
   int32_t bad;          // a non-finite per-token value was seen
-  int32_t pad;
+  uint32_t launch;      // 0, or the number of the launch that wrote it (launch_score)
 };
 constexpr int kScoreTokensPerWG = 16;
 
-// score.hip.  arrivals: kScoreArrivals counters, zero between the calls on one stream, with which few records are reduced by the
-// pass that writes them; none = always in a launch of its own
-constexpr int kScoreArrivals = 64;
+// score.hip.  launches: the context's count of launches that reduce their few records themselves, which use the first kScoreAloneRecords
+// records of the scratch (whose last words were zero before the first of them); none = always in a launch of its own
+constexpr int kScoreAloneRecords = 64;
 hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, const void* ref, int64_t ref_stride,
                         int claim_dtype, int ref_dtype, int64_t T, int D, uint32_t mask, const float* tau4,
                         int reduce, float* token_scores, sv_result* results, ScorePartial* scratch,
-                        int64_t scratch_elems, hipStream_t st, uint32_t* arrivals, uint32_t skip = 0, float* sum_out = nullptr);
+                        int64_t scratch_elems, hipStream_t st, uint32_t* launches, uint32_t skip = 0, float* sum_out = nullptr);
 // the scores and the flag from the records of one score pass, `tiles` per submission
 hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
                                  int reduce, sv_result* results, hipStream_t st);

@@ -5,8 +5,8 @@
 //                         whole distance family needs (Omega_L1, Omega_L2, Omega_SFR of the
 //                         paragraph "Choice of Distance Measure", and the per-token relative
 //                         L2), then folds 16 tokens into one partial record.
-//   score_finalize_kernel: deterministic reduction of the records of one submission (few records: by the
-//                         workgroup of the pass that comes last), the scores, and the flag Gamma > tau (Eq. test_statistic; a submission
+//   score_finalize_kernel: deterministic reduction of the records of one submission (few records: in the
+//                         pass itself), the scores, and the flag Gamma > tau (Eq. test_statistic; a submission
 //                         is flagged when any enabled metric exceeds its threshold).
 //   ema_update_kernel   : Eq. momentum_def over the un-flagged submissions.
 #include <mutex>
@@ -46,16 +46,44 @@ struct Tau4 { float v[4]; };
 // What turns a submission's records into its scores and flag.
 struct Verdict { uint32_t mask; Tau4 tau; int reduce; sv_result* results; };
 
+// What a pass that forms the scores itself is given beside; nothing for the others.
+template <bool ALONE> struct Alone { uint32_t launch; Verdict verdict; };
+template <> struct Alone<false> {};
+
 inline __host__ __device__ int finalize_threads(int tiles_per_claim) { return tiles_per_claim <= 128 ? 64 : 256; }
 
+// Records that another workgroup of the same launch reads.  The XCDs' L2 caches do not see each other's plain stores within a launch,
+// and a release fence would write a whole L2 back for 80 bytes (and leave what follows in the check to find it so): the words go
+// past it one by one, and are read past it.
+__device__ __forceinline__ void publish(ScorePartial* p, int word, uint64_t v) {      // one of a record's ten 8-byte words
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t published(const ScorePartial* p, int word) {
+  return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p) + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// what this wave has published is there for every XCD
+__device__ __forceinline__ void published_so_far() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
 // The scores and the flag of one submission, by the first nt threads of a workgroup (all of which call).
+template <bool PUBLISHED>
 __device__ void finalize_claim(const ScorePartial* p, int tiles_per_claim, int claim, int64_t T, int D, const Verdict& verdict, int nt) {
   const int tid = threadIdx.x;
   const uint32_t mask = verdict.mask;
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   float best = -1.0f; int bt = 0, bad = 0;
   for (int i = tid; i < tiles_per_claim && tid < nt; i += nt) {      // tiles visited in increasing order
-    const ScorePartial q = p[i];
+    ScorePartial q;
+    if constexpr (PUBLISHED) {
+      struct Words { uint64_t w[10]; } words;
+      static_assert(sizeof(Words) == sizeof(ScorePartial), "a record is ten words");
+#pragma unroll
+      for (int j = 0; j < 10; ++j) words.w[j] = published(p + i, j);
+      q = __builtin_bit_cast(ScorePartial, words);
+    } else q = p[i];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] += q.s[j];
     bad |= q.bad;
@@ -116,7 +144,7 @@ __device__ void finalize_claim(const ScorePartial* p, int tiles_per_claim, int c
 
 __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial* __restrict__ partials, int tiles_per_claim, int64_t T, int D,
                                                              Verdict verdict) {
-  finalize_claim(partials + (int64_t)blockIdx.x * tiles_per_claim, tiles_per_claim, blockIdx.x, T, D, verdict, blockDim.x);
+  finalize_claim<false>(partials + (int64_t)blockIdx.x * tiles_per_claim, tiles_per_claim, blockIdx.x, T, D, verdict, blockDim.x);
 }
 
 // NEED_L1 / NEED_Z / NEED_SFR prune the sums a launch does not need (the statistic family is
@@ -125,13 +153,17 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(const ScorePartial*
 // TW: tokens per workgroup, and per record.  With few records of 16 (one submission of up to 4096 tokens) the pass is a chain of
 // memory round trips, one per token of a wave, on a part of the CUs: 4 tokens then, one per wave on four times the workgroups
 // (512 tokens of 4096, both sides bf16: 13 -> 6 us; 2331 of 960: 10 -> 5.5).
-// COUNTED: the workgroup that comes last with a record of its submission forms the scores (an instantiation of its own: with the code
-// for it behind a branch the pass over 4096 tokens of 1024 took 5 us more).
-template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, int TW, bool COUNTED>
+// ALONE: the pass forms the scores too, without a second launch (an instantiation of its own: with the code for it behind a branch the
+// pass over 4096 tokens of 1024 took 5 us more).  A record carries the launch's number, written behind the rest of it, and a workgroup
+// that then finds that number in every record of its submission forms the scores from them, in the order of score_finalize_kernel.  One
+// of them does (the one whose number was there last); if several do, they write the same bytes.  Nobody waits, and nothing has to be as an
+// earlier launch should have left it: launches that overlapped on one context, which share the records and are not supported, can
+// spoil their own scores but not a later launch's.
+template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, int TW, bool ALONE>
 __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
                                                            const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
                                                            int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
-                                                           ScorePartial* partials, uint32_t* arrivals, Verdict verdict) {
+                                                           ScorePartial* partials, Alone<ALONE> alone) {
   // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): ids congruent mod 8 get a contiguous run of
   // token tiles, and within a run the claim index varies fastest, so the submissions that share a tile of the
   // reference run together on one XCD and fetch it from memory once instead of once per XCD.
@@ -217,32 +249,39 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
   }
   __syncthreads();
   ScorePartial* p = partials + (int64_t)claim * tiles_per_claim + tile;
-  // one sum each, the waves in order; the worst token beside them, by the first wave too if that then counts the record
-  if (threadIdx.x < 8) {
-    p->s[threadIdx.x] = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
-  } else if (threadIdx.x == (COUNTED ? 8 : 64)) {
-    float b = -1.0f; int bt = 0, bd = 0;
+  // one sum each, the waves in order; the worst token beside them, by the first wave too if that then looks at the other records
+  double sum = 0.0;
+  float b = -1.0f; int bt = 0, bd = 0;
+  if (threadIdx.x < 8) sum = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
+  else if (threadIdx.x == (ALONE ? 8 : 64)) {
     for (int w = 0; w < 4; ++w) {
       bd |= s_bad[w];
       if (s_best[w] > b || (s_best[w] == b && s_best[w] >= 0.0f && s_bt[w] < bt)) { b = s_best[w]; bt = s_bt[w]; }
     }
-    p->max_rel = b; p->argmax = bt; p->bad = bd; p->pad = 0;
   }
-  if constexpr (!COUNTED) return;                    // the records go to score_finalize_kernel
-  // The workgroup that comes last with a record of its submission forms the scores: nobody waits, and there is one launch instead of
-  // two (1 x 256 tokens of 512: a call 14.7 -> 11.9 us, most of it the host's; the smallest fp32 check 46.6 -> 43.0).  The records are
-  // summed in the same order as there.
-  __shared__ int s_last;
-  if (wave == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    if (lane == 0)
-      s_last = __hip_atomic_fetch_add(&arrivals[claim], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (uint32_t)tiles_per_claim;
+  if constexpr (!ALONE) {                              // the records go to score_finalize_kernel
+    if (threadIdx.x < 8) p->s[threadIdx.x] = sum;
+    else if (threadIdx.x == 64) { p->max_rel = b; p->argmax = bt; p->bad = bd; p->launch = 0; }
+  } else {
+    // 1 x 256 tokens of 512: a call 14.7 -> 11.7 us, the host's time for a launch.  (With a counter between fences the call is as short, but
+    // the checks around it were longer, by an L2 written back and emptied: 256 tokens of 256 columns, forward, 45.5 us instead of 44.4.)
+    __shared__ int s_all;
+    if (wave == 0) {
+      if (lane < 8) publish(p, lane, (uint64_t)__double_as_longlong(sum));
+      else if (lane == 8) publish(p, 8, (uint64_t)__float_as_uint(b) | (uint64_t)(uint32_t)bt << 32);
+      published_so_far();
+      if (lane == 8) publish(p, 9, (uint64_t)(uint32_t)bd | (uint64_t)alone.launch << 32);
+      published_so_far();
+      int missing = 0;
+      for (int i = lane; i < tiles_per_claim; i += 64)
+        missing |= (uint32_t)(published(partials + (int64_t)claim * tiles_per_claim + i, 9) >> 32) != alone.launch;
+      const bool all = __ballot(missing) == 0;
+      if (lane == 0) s_all = all;
+    }
+    __syncthreads();
+    if (!s_all) return;
+    finalize_claim<true>(partials + (int64_t)claim * tiles_per_claim, tiles_per_claim, claim, T, D, alone.verdict, finalize_threads(tiles_per_claim));
   }
-  __syncthreads();
-  if (!s_last) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  finalize_claim(partials + (int64_t)claim * tiles_per_claim, tiles_per_claim, claim, T, D, verdict, finalize_threads(tiles_per_claim));
-  if (threadIdx.x == 0) arrivals[claim] = 0;         // for the next call on the stream
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -435,7 +474,7 @@ __global__ __launch_bounds__(256) void score_parts_kernel(const EC* __restrict__
       bd |= s_bad[w][c];
       if (s_best[w][c] > b || (s_best[w][c] == b && s_best[w][c] >= 0.0f && s_bt[w][c] < bt)) { b = s_best[w][c]; bt = s_bt[w][c]; }
     }
-    p.max_rel = b; p.argmax = bt; p.bad = bd; p.pad = 0;
+    p.max_rel = b; p.argmax = bt; p.bad = bd; p.launch = 0;
     partials[(int64_t)(c0 + c) * tiles_per_claim + tile] = p;
   }
 }
@@ -506,6 +545,11 @@ Verdict make_verdict(uint32_t mask, const float* tau4, int reduce, sv_result* re
   for (int i = 0; i < 4; ++i) v.tau.v[i] = tau4 ? tau4[i] : 0.0f;
   return v;
 }
+
+bool being_captured(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
+}
 }  // namespace
 
 hipError_t launch_score_finalize(const ScorePartial* partials, int n_claims, int tiles, int64_t T, int D, uint32_t mask, const float* tau4,
@@ -531,7 +575,7 @@ hipError_t launch_ema_from_sum(float* m, const float* sum, int n_summed, int64_t
 hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, const void* ref, int64_t ref_stride,
                         int claim_dtype, int ref_dtype, int64_t T, int D, uint32_t mask, const float* tau4, int reduce,
                         float* token_scores, sv_result* results, ScorePartial* scratch, int64_t scratch_elems,
-                        hipStream_t st, uint32_t* arrivals, uint32_t skip, float* sum_out) {
+                        hipStream_t st, uint32_t* launches, uint32_t skip, float* sum_out) {
   if (n_claims <= 0 || T <= 0) return hipSuccess;
   if (sum_out && !score_sum_supported(n_claims, ref_stride, claim_dtype, D)) return hipErrorInvalidValue;
   const int64_t tiles = (T + kScoreTokensPerWG - 1) / kScoreTokensPerWG;
@@ -595,18 +639,23 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     const bool few = tiles * nc <= cu_count() && tiles4 * nc <= scratch_elems;
     const int tpc = (int)(few ? tiles4 : tiles);
     const dim3 gridt((unsigned)(8 * ((tpc + 7) / 8) * nc));
-    // Few records: every workgroup pays for making its record visible to the other XCDs and for counting it.  With a reduction launch ->
-    // without: 32 records 14.5 -> 12.2 us, 64 14.7 -> 11.9, but 1024 of one submission 16.5 -> 85.
-    uint32_t* const arrive = few && (int64_t)tpc * nc <= kScoreArrivals ? arrivals : nullptr;
+    // Few records, where the host's launches are what a caller waits for: one launch.  32 records 14.7 -> 11.8 us, 64 14.8 -> 11.8; every
+    // workgroup pays for publishing its record and reading the others' numbers, about a microsecond of the GPU's time.  Under capture
+    // a launch's number would be that of its every replay: two launches.
+    uint32_t launch = 0;
+    if (launches && few && (int64_t)tpc * nc <= kScoreAloneRecords && !being_captured(st)) {
+      if (++*launches == 0) ++*launches;                 // 0 is in the records of other launches
+      launch = *launches;
+    }
     const Verdict verdict = make_verdict(mask, tau4, reduce, results + c0);
 #define SV_LAUNCH_SCORE3(EC, ER, L1, Z, SFR)                                                                           \
   do {                                                                                                                 \
-    if (arrive) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4, true>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
-                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);         \
+    if (launch) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4, true>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
+                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, Alone<true>{launch, verdict});         \
     else if (few) hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, 4, false>), gridt, block, 0, st, (const EC*)cp, claim_stride,  \
-                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);         \
+                                (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, Alone<false>{});         \
     else hipLaunchKernelGGL((score_tokens_kernel<EC, ER, L1, Z, SFR, kScoreTokensPerWG, false>), gridt, block, 0, st, (const EC*)cp, claim_stride, \
-                            (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, arrive, verdict);             \
+                            (const ER*)rp, ref_stride, T, D, nc, tpc, ts, scratch, Alone<false>{});             \
   } while (0)
 #define SV_LAUNCH_SCORE(EC, ER)                                                                                          \
   do {                                                                                                                   \
@@ -623,8 +672,7 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     else SV_LAUNCH_SCORE(float, float);
 #undef SV_LAUNCH_SCORE
 #undef SV_LAUNCH_SCORE3
-    if (arrive) continue;
-    hipError_t e = launch_score_finalize(scratch, nc, tpc, T, D, mask, tau4, reduce, results + c0, st);
+    hipError_t e = launch ? hipGetLastError() : launch_score_finalize(scratch, nc, tpc, T, D, mask, tau4, reduce, results + c0, st);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
     ScorePartial p;
     p.s[0] = s0; p.s[1] = s1; p.s[2] = s2; p.s[3] = s3; p.s[4] = s0 - s1; p.s[5] = s5; p.s[6] = s6;
     p.s[7] = (double)rows * (double)D - (double)same;
-    p.max_rel = best; p.argmax = at; p.bad = bad; p.pad = 0;
+    p.max_rel = best; p.argmax = at; p.bad = bad; p.launch = 0;
     partials[(int64_t)c * tiles + blockIdx.x] = p;
   }
 }
