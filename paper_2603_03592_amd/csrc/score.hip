@@ -163,7 +163,7 @@ template <typename EC, typename ER, bool NEED_L1, bool NEED_Z, bool NEED_SFR, in
 __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict__ claims, int64_t claim_stride,
                                                            const ER* __restrict__ ref, int64_t ref_stride, int64_t T, int D,
                                                            int n_claims, int tiles_per_claim, float* __restrict__ token_scores,
-                                                           ScorePartial* partials, Alone<ALONE> alone) {
+                                                           ScorePartial* __restrict__ partials, Alone<ALONE> alone) {
   // Workgroup ids go round-robin over the 8 XCDs (each with its own L2): ids congruent mod 8 get a contiguous run of
   // token tiles, and within a run the claim index varies fastest, so the submissions that share a tile of the
   // reference run together on one XCD and fetch it from memory once instead of once per XCD.
@@ -249,25 +249,30 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
   }
   __syncthreads();
   ScorePartial* p = partials + (int64_t)claim * tiles_per_claim + tile;
-  // one sum each, the waves in order; the worst token beside them, by the first wave too if that then looks at the other records
-  double sum = 0.0;
-  float b = -1.0f; int bt = 0, bd = 0;
-  if (threadIdx.x < 8) sum = s_acc[0][threadIdx.x] + s_acc[1][threadIdx.x] + s_acc[2][threadIdx.x] + s_acc[3][threadIdx.x];
-  else if (threadIdx.x == (ALONE ? 8 : 64)) {
+  // one sum each, the waves in order; the worst token beside them
+  auto sum_of = [&](int j) { return s_acc[0][j] + s_acc[1][j] + s_acc[2][j] + s_acc[3][j]; };
+  auto worst = [&](float& b, int& bt, int& bd) {
+    b = -1.0f; bt = 0; bd = 0;
     for (int w = 0; w < 4; ++w) {
       bd |= s_bad[w];
       if (s_best[w] > b || (s_best[w] == b && s_best[w] >= 0.0f && s_bt[w] < bt)) { b = s_best[w]; bt = s_bt[w]; }
     }
-  }
+  };
+  float b; int bt, bd;
   if constexpr (!ALONE) {                              // the records go to score_finalize_kernel
-    if (threadIdx.x < 8) p->s[threadIdx.x] = sum;
-    else if (threadIdx.x == 64) { p->max_rel = b; p->argmax = bt; p->bad = bd; p->launch = 0; }
+    if (threadIdx.x < 8) {
+      p->s[threadIdx.x] = sum_of(threadIdx.x);
+    } else if (threadIdx.x == 64) {
+      worst(b, bt, bd);
+      p->max_rel = b; p->argmax = bt; p->bad = bd; p->launch = 0;
+    }
   } else {
     // 1 x 256 tokens of 512: a call 14.7 -> 11.7 us, the host's time for a launch.  (With a counter between fences the call is as short, but
     // the checks around it were longer, by an L2 written back and emptied: 256 tokens of 256 columns, forward, 45.5 us instead of 44.4.)
     __shared__ int s_all;
     if (wave == 0) {
-      if (lane < 8) publish(p, lane, (uint64_t)__double_as_longlong(sum));
+      worst(b, bt, bd);
+      if (lane < 8) publish(p, lane, (uint64_t)__double_as_longlong(sum_of(lane)));
       else if (lane == 8) publish(p, 8, (uint64_t)__float_as_uint(b) | (uint64_t)(uint32_t)bt << 32);
       published_so_far();
       if (lane == 8) publish(p, 9, (uint64_t)(uint32_t)bd | (uint64_t)alone.launch << 32);
