@@ -551,6 +551,31 @@ Verdict make_verdict(uint32_t mask, const float* tau4, int reduce, sv_result* re
   return v;
 }
 
+// Rows of no multiple of 2 KB against a shared reference: does the kernel that keeps the reference in registers beat the one that reads it
+// with every submission?  It saves the more, the more submissions share a part of it (n in groups of G) and the more sums there are to
+// form (full), and its workgroups are longer: just above two of them on a CU, the few CUs with a third set the time, and where memory
+// takes most of it anyway (the relative L2 alone, rows of 3 KB and more) a fifth does so again, until there are many.  An fp32 reference
+// of bf16 submissions (mixed) is the other kernel's cheapest form.  Without -> with it, us, submissions x tokens x columns, bf16 unless
+// said, all sums: 8 x 8200 x 960 (4.0 workgroups on a CU) 55 -> 41, 16 x 2060 x 2304 (2.0) 52 -> 57, 16 x 3000 x 2304 (2.9) 65 -> 58; 2 x 8200 x
+// 64 (2.0) 19.3 -> 20.5, mixed 17.6 -> 20.3, in fp32 19.4 -> 17.4; 3 x 8200 x 3520 (2.0) 52 -> 59.  The relative L2 alone: 64 x 8200 x 504 (8.0)
+// 237 -> 103, 16 x 4100 x 1600 (4.0) 40 -> 48, 16 x 7000 x 1600 (6.8) 78 -> 70, 2 x 20000 x 1600 (4.9) 35 -> 40, 6 x 8200 x 3520 (4.0) 79 -> 88, 10 x
+// 7000 x 960 in fp32 (5.1) 53 -> 61, 16 x 2560 x 2304 in fp32 (2.5) 90 -> 69.
+bool ragged_parts_pay(int n, int G, int64_t workgroups, int units, bool full, int claim_dtype, int ref_dtype) {
+  const double per_cu = (double)workgroups / cu_count();
+  const bool past_three = per_cu > 2.6, many = per_cu >= 6.5;
+  const bool mixed = claim_dtype == SV_BF16 && ref_dtype == SV_F32, all16 = claim_dtype == SV_BF16 && ref_dtype == SV_BF16;
+  const int share = n < G ? n : G;
+  if (per_cu < 2.0) return false;
+  if (units > 8 && share > 2) return true;               // three parts and more: the start of a chain is a small share of it
+  if (units > 4) {
+    const bool fifth = per_cu >= 4.0 && per_cu < 4.5;
+    return share == 2 ? many : past_three && (!fifth || (share > 3 ? full || !all16 : mixed));
+  }
+  if (full) return units == 2 || (mixed ? past_three && (units > 2 || share > 2) : past_three || units > 2 || share > 3);
+  if (units > 2) return share > 2 && per_cu >= (share == 3 && !mixed ? 6.5 : 5.7);
+  return past_three || share > 3;
+}
+
 bool being_captured(hipStream_t st) {
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone;
@@ -596,16 +621,16 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
     const dim3 grid((unsigned)(8 * ((tiles + 7) / 8) * nc)), block(256);
     const int64_t row_bytes = (int64_t)D * csz;
     const bool full = (mask & (SV_M_L1 | SV_M_ZL2 | SV_M_SFR)) != 0;
-    // Shared reference and several submissions (or their sum wanted): the kernel that keeps the reference in registers.  Rows that are
-    // no multiple of 2 KB take it from two workgroups per CU on; below, its tokens' chains are longer than what it saves.  Without -> with
-    // it, us: 78 x 3243 x 2304 308 -> 208, 64 x 2500 x 2880 241 -> 174, 8 x 4935 x 1280 (618 workgroups) 42.5 -> 35.6, 2 x 8000 x 1216
-    // (500) 23.4 -> 23.2, 4 x 4000 x 3520 (250) 36 -> 49, 16 x 1000 x 2368 (252) 28 -> 40.
+    // Shared reference and several submissions (or their sum wanted): the kernel that keeps the reference in registers; where the rows
+    // are no multiple of 2 KB, if it pays.
     int G = sum_out ? nc : 16;
     while (!sum_out && G > 4 && tiles * ((nc + G - 1) / G) < 1024) G >>= 1;
     const int n_groups = (nc + G - 1) / G;
     G = (nc + n_groups - 1) / n_groups;                  // groups alike: every group reads the reference once
     const bool whole = row_bytes % 2048 == 0;
-    if (ref_stride == 0 && (sum_out || nc >= 2) && (whole || tiles * n_groups >= 2 * cu_count())) {
+    const int units = (int)((row_bytes + 1023) / 1024);  // KB of a row
+    if (ref_stride == 0 && (sum_out || nc >= 2) &&
+        (whole || ragged_parts_pay(nc, G, tiles * n_groups, units, full, claim_dtype, ref_dtype))) {
       if (sum_out && (nc != n_claims || nc * tiles > scratch_elems)) return hipErrorInvalidValue;   // one launch, one group
       const dim3 ggrid((unsigned)(8 * ((tiles + 7) / 8) * n_groups));
 #define SV_LAUNCH_PARTS5(EC, ER, NU, FULL, SUM, TAIL, ONCE)                                                           \
@@ -623,7 +648,6 @@ hipError_t launch_score(const void* claims, int64_t claim_stride, int n_claims, 
       // more than the memory-side cache holds (256 MB): loads that leave nothing behind.  128 x 8192 x 4096 1587 -> 1394 us, 16 x 4096 x
       // 4096 (0.5 GB) 121 -> 114.5; but 4 x 2048 x 2048 (33 MB) 27.7 -> 28.6
       const bool once = row_bytes * T * nc > ((int64_t)256 << 20);
-      const int units = (int)((row_bytes + 1023) / 1024);
       int nu = 4;                                        // units per part: as few as possible for nothing
       for (int u = 3; u >= 2; --u)
         if ((units + u - 1) / u * u < (units + nu - 1) / nu * nu) nu = u;
