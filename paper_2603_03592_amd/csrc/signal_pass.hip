@@ -19,7 +19,12 @@
 //     excludes somebody else goes back to it).
 //   - Projections on v_mfma_f32_16x16x32_bf16, directions in the A slot: a wave takes half the blocks of 16 directions for every
 //     fourth submission; fragments are 16-byte reads of the swizzled rows.  The same fragments against ones and against themselves
-//     give a token's sum and, on the diagonal, its sum of squares: exact products, added in fp32.
+//     give a token's sum and, on the diagonal, its sum of squares: exact products, added in fp32 within a chunk.
+// No fp32 sum is long.  The matrix cores' sums of a chunk (64 terms; they do not round to nearest) go on in 64 bits, the reference's too, and
+// the statistics' many are closed after every turn of the places (4 to 6 chunks: 8 to 12 additions one after the other) into a second
+// fp32 sum (16 additions at 4096 columns); the lanes meet in 64 bits.  With one fp32 sum over the row the z-scored statistic of signals whose
+// mean is 30 deviations was off by 5.8e-4 (2000 tokens of 4096), with these by 5e-5, and of those around zero by 2.0e-6 and 6e-8 (8192
+// tokens).  It costs 0.7 % of a loop call on average and 3 % at most (4 x 47 x 4032 185 -> 191 us, 16 x 2000 x 4032 379 -> 389).
 // Workgroups start at different chunks, so that they do not all ask for the same 128 bytes of every 8 KB row at once (374 -> 324 us
 // for the register form).
 #include <type_traits>
@@ -112,14 +117,15 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
   for (int j = 0; j < SPW; ++j)
 #pragma unroll
     for (int b = 0; b < BPW; ++b) acc[j][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  f32x4 self[SPW];                                               // of a wave's submissions: sums of c (even waves), of c c' (odd ones)
+  double self[SPW];                                              // of a wave's submissions: sums of c (even waves), of c c' (odd ones)
 #pragma unroll
-  for (int j = 0; j < SPW; ++j) self[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j = 0; j < SPW; ++j) self[j] = 0.0;
   const bf16x8 ones = {(bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f, (bf16)1.0f};
-  float sad[NS], sdd[NS], sr = 0.0f, srr = 0.0f;                 // sums of |d|, d^2
+  float sad[NS], sdd[NS], sad_all[NS], sdd_all[NS];              // sums of |d|, d^2: of this turn of the places, of those before
+  double sr = 0.0, srr = 0.0;
   int match[NS];
 #pragma unroll
-  for (int c = 0; c < NS; ++c) { sad[c] = sdd[c] = 0.0f; match[c] = 0; }
+  for (int c = 0; c < NS; ++c) { sad[c] = sdd[c] = sad_all[c] = sdd_all[c] = 0.0f; match[c] = 0; }
 
   auto after = [&](int chunk) { return chunk + 1 == nchunk ? 0 : chunk + 1; };      // behind the last round: chunks again, unused
   f32x2 r[NST];                                                  // the EMA's values, as far ahead as the submissions
@@ -159,6 +165,7 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
     }
     __builtin_amdgcn_sched_barrier(0);
     // statistics
+    f32x4 piece[SPW];                                            // the chunk's part of self: 64 terms
     float sum[2] = {0.0f, 0.0f};
     int cls[2];
 #pragma unroll
@@ -166,8 +173,8 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
       // the classes of a value whose sign (of zero and NaN: 0) is the reference's: -inf, -normal, -subnormal; +subnormal,
       // +normal, +inf; or the zeros and NaNs.  None in the places past the last token.
       cls[e] = (rv[e] > 0.0f ? 0x380 : (rv[e] < 0.0f ? 0x01c : 0x063)) & live_mask;
-      sr += rv[e];
-      srr = fmaf(rv[e], rv[e], srr);
+      sr += (double)rv[e];
+      srr = fma((double)rv[e], (double)rv[e], srr);
     }
 #pragma unroll
     for (int c = 0; c < NS; ++c) {
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
           for (int j = 0; j < SPW; ++j) {
 #pragma unroll
             for (int b = 0; b < BPW; ++b) acc[j][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u[h][b], x[h][j], acc[j][b], 0, 0, 0);
-            self[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16((wave & 1) ? x[h][j] : ones, x[h][j], self[j], 0, 0, 0);
+            piece[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16((wave & 1) ? x[h][j] : ones, x[h][j], h ? piece[j] : f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
           }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -197,7 +204,14 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
         match[c] += __popcll(lanes);
         sum[e] += __uint_as_float(ALL ? bits : bits & take);
       }
+      if constexpr (st == NST - 1) {
+        sad_all[c] += sad[c]; sdd_all[c] += sdd[c];
+        sad[c] = sdd[c] = 0.0f;
+      }
     }
+#pragma unroll
+    for (int j = 0; j < SPW; ++j)
+      self[j] += (double)((l15 & 3) == 0 ? piece[j][0] : (l15 & 3) == 1 ? piece[j][1] : (l15 & 3) == 2 ? piece[j][2] : piece[j][3]);
     f32x2 next;
 #pragma unroll
     for (int e = 0; e < 2; ++e) next[e] = beta * rv[e] + w_new * sum[e];
@@ -249,16 +263,15 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
 #pragma unroll
   for (int j = 0; j < SPW; ++j) {
     const int c = (wave >> 1) + 4 * j;
-    const float v = (l15 & 3) == 0 ? self[j][0] : (l15 & 3) == 1 ? self[j][1] : (l15 & 3) == 2 ? self[j][2] : self[j][3];
-    if (lq == l15 >> 2) tk[l15 * TS + ((wave & 1) ? NS : 0) + c] = (double)v;
+    if (lq == l15 >> 2) tk[l15 * TS + ((wave & 1) ? NS : 0) + c] = self[j];
   }
 #pragma unroll
   for (int c = 0; c < NS; ++c) {
-    red[(wave * C::NV + c) * 64 + lane] = sad[c];
-    red[(wave * C::NV + NS + c) * 64 + lane] = sdd[c];
+    red[(wave * C::NV + c) * 64 + lane] = sad_all[c] + sad[c];
+    red[(wave * C::NV + NS + c) * 64 + lane] = sdd_all[c] + sdd[c];
   }
-  red[(wave * C::NV + 2 * NS) * 64 + lane] = sr;
-  red[(wave * C::NV + 2 * NS + 1) * 64 + lane] = srr;
+  red[(wave * C::NV + 2 * NS) * 64 + lane] = (float)sr;
+  red[(wave * C::NV + 2 * NS + 1) * 64 + lane] = (float)srr;
   int* cnt = reinterpret_cast<int*>(smem + C::RED + C::TOK);     // [wave][NS]
 #pragma unroll
   for (int c = 0; c < NS; ++c)
