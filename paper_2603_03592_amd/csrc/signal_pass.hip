@@ -139,6 +139,7 @@ __global__ __launch_bounds__(512, 2) void signal_pass_kernel(const bf16* __restr
   auto body = [&](auto st_tag) {
     constexpr int st = decltype(st_tag)::value, fill = (st + NST - 1) % NST;        // fill: the place the last chunk has left
     load_u(ahead_u, su == 0 ? C::NU - 1 : su - 1);
+    __builtin_amdgcn_sched_barrier(0);                           // the oldest of the chunk's: the wait below counts what is behind it
     ahead_u = after(ahead_u);
     const f32x2 rv = r[st];
     load_r(r[fill], ahead);
