@@ -449,6 +449,14 @@ sv_status sv_gemm_bf16_runs(const void *A, int64_t lda, const void *B, int64_t l
 sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32_t row_sums, int32_t *leaves_row_sums,
                        int32_t *tile, int32_t *runs);
 
+/* Test aid, no device call: what a product C[M,N] = A[M,K] * B[N,K]^T of a block runs on, by its epilogue: 0 = store, 1 = residual,
+ * 2 = GELU, 3 = SwiGLU (N columns of gate and of up), 4 = SwiGLU backward, 5 = GELU backward, 6 = rotation of q and k.
+ * groups: 0, or the number of groups of expert-sorted rows, M (a multiple of 256) then being the bound on their number.
+ * *tile, *runs: as above, and 6 = 192x256.  *tail: how many of the 256x256 tiles that one XCD walks are left to a second
+ * launch on smaller tiles, if those are what the product runs on (in groups: the most that the launch is made for). */
+sv_status sv_gemm_tiles(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t groups, int64_t ws_floats, int32_t *tile,
+                        int32_t *runs, int32_t *tail);
+
 #ifdef __cplusplus
 }
 #endif

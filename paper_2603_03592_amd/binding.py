@@ -157,6 +157,8 @@ def _load():
     L.sv_gemm_bf16_runs.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp, i64, vp]
     L.sv_gemm_plan.restype = C.c_int
     L.sv_gemm_plan.argtypes = [i32, i32, i32, i64, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
+    L.sv_gemm_tiles.restype = C.c_int
+    L.sv_gemm_tiles.argtypes = [i32, i32, i32, i32, i32, i64, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     return L
 
 
@@ -197,6 +199,18 @@ def sv_gemm_plan(M: int, N: int, K: int, ws_floats: int = 0, row_sums: bool = Fa
     if st != SV_OK:
         raise SVError(st, "sv_gemm_plan")
     return bool(leaves.value), tile.value, runs.value
+
+
+GEMM_EPILOGUES = ("store", "residual", "gelu", "swiglu", "swiglu_bwd", "gelu_bwd", "rope")
+
+
+def sv_gemm_tiles(M: int, N: int, K: int, epilogue: str, groups: int = 0, ws_floats: int = 0):
+    """(tile, runs, tail) of a block's product with that epilogue (see stageverify.h); no device call."""
+    tile, runs, tail = C.c_int32(), C.c_int32(), C.c_int32()
+    st = lib.sv_gemm_tiles(M, N, K, GEMM_EPILOGUES.index(epilogue), groups, ws_floats, C.byref(tile), C.byref(runs), C.byref(tail))
+    if st != SV_OK:
+        raise SVError(st, "sv_gemm_tiles")
+    return tile.value, runs.value, tail.value
 
 
 def _policy_cfg(c=5, t_forgive=100, window=100, k0=1.5, alpha=0.01, grow=1.1, shrink=0.9, n_max=10, min_dist_mult=0.0,

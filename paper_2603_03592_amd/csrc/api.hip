@@ -1170,6 +1170,23 @@ sv_status sv_gemm_plan(int32_t M, int32_t N, int32_t K, int64_t ws_floats, int32
   return SV_OK;
 }
 
+sv_status sv_gemm_tiles(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t groups, int64_t ws_floats, int32_t* tile, int32_t* runs,
+                        int32_t* tail) {
+  if (M < 1 || N < 1 || K < 1 || epilogue < EPI_STORE || epilogue > EPI_ROPE || groups < 0 || ws_floats < 0 || !tile || !runs || !tail) return SV_EINVAL;
+  alignas(16) static float some[4];
+  static int32_t whose[1];
+  GemmArgs g = nt(M, N, K, some, K, some, some, N, epilogue);
+  g.B2 = some; g.ldb2 = K;
+  g.R = g.R2 = some; g.ldr = N;
+  g.C2 = some;
+  g.rope_cs = some; g.rope_S = 1; g.rope_hd = 8; g.rope_cols = N;
+  if (groups) { g.groups = groups; g.tile_group = g.m_dev = whose; g.group_stride = (int64_t)N * K; }
+  g.split_ws = ws_floats ? some : nullptr; g.split_ws_floats = ws_floats;
+  mfma_gemm_plan(g, tile, runs);
+  *tail = mfma_gemm_tail(g);
+  return SV_OK;
+}
+
 }  // extern "C"
 
 sv_status sv::check_signals(sv_ctx* c, const void* signals, int64_t stride, int n, int dtype, float* m, float* m_prev, float beta, int64_t T, int D,

@@ -290,7 +290,8 @@ bool mfma_gemm_supported(const GemmArgs& a);             // both, for the automa
 bool mfma_gemm_emits_rowsq(const GemmArgs& a);          // would mfma_gemm(a, st) fill a.rowsq?
 // EPI_STORE on one of the tiles 2 .. 5 with k in that many runs (sv_gemm_bf16_runs): in a.split_ws if there is one, else in one workgroup
 hipError_t mfma_gemm_runs(const GemmArgs& a, int tile, int runs, hipStream_t st);
-void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs);   // what mfma_gemm(a, st) would run on (numbers of sv_gemm_plan)
+void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs);   // what mfma_gemm(a, st) would run on (numbers of sv_gemm_tiles)
+int mfma_gemm_tail(const GemmArgs& a);                          // tiles per XCD that it would leave to a second launch on 256x256 tiles
 int mfma_settled_runs(int64_t M, int N, int K, int64_t ws_floats);   // the GemmArgs::runs of an [N,K] product before a router
 hipError_t mfma_gemm(const GemmArgs& a, hipStream_t st, int tile = 0);   // tile: 0 auto, 1 = 256x256, 2 = 128x128, 3 = 256x128, 4 = 64x128
 

@@ -1425,12 +1425,17 @@ bool mfma_gemm_emits_rowsq(const GemmArgs& a) {
 }
 
 void mfma_gemm_plan(const GemmArgs& a, int* tile, int* runs) {
-  constexpr int number[kTileKinds] = {1, 3, 2, 4, 5};       // of the kinds a plain product takes
+  constexpr int number[kTileKinds + 1] = {1, 3, 2, 4, 5, 6};
   *tile = 0; *runs = 1;
   if (a.b_is_kn || !mfma_gemm_supported(a)) return;
   const Plan p = plan_gemm(a);
-  if (p.kind >= kTileKinds) return;
   *tile = number[p.kind]; *runs = p.runs;
+}
+
+int mfma_gemm_tail(const GemmArgs& a) {
+  if (a.b_is_kn || !mfma_gemm_supported(a) || !fits_256(a)) return 0;
+  if (a.tile_group) return a.epi == EPI_SWIGLU ? tail_pays<EPI_SWIGLU, true>(a) : tail_pays<EPI_STORE, true>(a);
+  return a.epi == EPI_SWIGLU ? tail_pays<EPI_SWIGLU, false>(a) : tail_pays<EPI_STORE, false>(a);
 }
 
 bool mfma_gemm_shape(const GemmArgs& a) {
