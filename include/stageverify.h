@@ -364,7 +364,8 @@ sv_status sv_replace_with_ema(sv_ctx *ctx, void *signals, int64_t stride, int32_
  * while the object lives; SV_M_SW needs a context created with SV_FLAG_SLICED_W and max_tokens >= T.
  * The context must outlive the object; calls on one object must not overlap.
  * Device memory the object holds: two EMAs [T, D] float per stage, and -- with at most 32 workers -- one more
- * [T, D] float (the score pass leaves the sum over the signals there: sv_score_and_sum) and, with SV_M_SW and
+ * [T, D] float (where one pass does the checks and updates the EMA, what the EMA was before, until the verdicts
+ * stand; else the sum over the signals that the score pass leaves: sv_score_and_sum) and, with SV_M_SW and
  * sv_sw_row_len(T) <= 16384, the projections of the EMAs and of the current signals
  * ((2 n_stages + n_workers) [n_dirs, sv_sw_row_len(T)] floats: sv_sw_against_projection) and the EMAs' sorted
  * (2 n_stages times as many).                                                                        */

@@ -340,12 +340,17 @@ bool signal_pass_supported(const void* X, int64_t stride, int n, int dtype, cons
 
 // The pass reads every submission once where the separate ones read it twice (three times where the score pass leaves no sum), but a
 // workgroup walks its 16 tokens' whole row with all submissions, chunk behind chunk (about 1.4 us a chunk of 16), where those spread
-// submissions and rows over the chip.  So it is the longer way where there are too few tokens to be short of memory.  Times of a
-// forward and a backward call of one stage, separate -> one pass, us, 64 directions (submissions x tokens x columns):
-//   16 x 47 x 4032   250 -> 338     9 x 500 x 4032   274 -> 313     8 x 500 x 4032   258 -> 262     4 x 47 x 4032   231 -> 196
-//   8 x 1500 x 4032  330 -> 287     16 x 3000 x 4032 753 -> 426     16 x 1500 x 1088 274 -> 249     2 x 47 x 1088   171 -> 150
-// Narrow rows (up to 1088 columns) differ by 12 % at most below 24576 token rows, either way.  With a sum from the score pass (summed: one read less
-// on that side, but a longer chain of its own) the pass is always the shorter way: 16 x 47 x 4096 485 -> 346, 2 x 47 x 4096 266 -> 200.
+// submissions and rows over the chip.  So it is the longer way where there are few tokens of many long submissions.  Times of the pass
+// over those of the separate passes, a forward and a backward call of one stage together, 64 directions:
+//   columns            16 submissions x 33 / 500 / 1000 / 1500 tokens     5 x 33 / 500 / 2500     2 x 33 / 500 / 2500
+//   448                0.98 / 0.94 / 0.95 / 0.88                           0.90 / 0.91 / 0.89      (taken)
+//   1088               1.12 / 1.05 / 0.99 / 0.90                           0.96 / 0.96 / 0.89      0.87 / 0.88 / 0.87
+//   1984               1.25 / 1.17 / 1.05 / 0.93                           1.01 / 1.00 / 0.88      0.87 / 0.88 / 0.86
+//   4032               1.57 / 1.32 / (taken)                               1.15 / 1.13 / (taken)   (taken)
+// The lines are on the safe side of these: between them and where the pass begins to win lie calls that it would make up to 16 % shorter,
+// up to four submissions of 1025 to 2047 columns among them, which take the separate passes as they always have.  With a sum from the
+// score pass (summed: one read less on that side, but a longer chain of its own) the pass is always the shorter way: 16 x 47 x 4096
+// 485 -> 346 us, 2 x 47 x 4096 266 -> 200.
 bool signal_pass_pays(int n, int64_t T, int D, bool summed) {
   return summed || D <= 320 || T * n >= (D >= 2048 ? 12000 : 24576) || (n <= 4 && (D <= 1024 || D >= 2048));
 }
