@@ -41,6 +41,8 @@ STAGES = {
     "narrower_gelu": Case("gelu", 1536, 1024, 9, 1229, 1, {"up": (6, _any), "dact": (6, _any)}),
     "narrower_gelu_ragged": Case("gelu", 768, 3840, 3, 777, 1, {"up": (6, _any), "dact": (6, _any)}),
     "narrower_swiglu": Case("swiglu", 512, 1536, 5, 777, 1, {"up": (6, _any)}),
+    "narrower_row_factors": Case("swiglu", 512, 1536, 5, 777, 1, {"up": (6, _any)}, fuse=True),
+    "narrower_row_factors_gelu": Case("gelu", 768, 3840, 3, 777, 1, {"up": (6, _any)}, fuse=True),
     "narrower_swiglu_bwd": Case("swiglu", 768, 1024, 11, 777, 1, {"dact": (6, _any), "up": (1, _some)}),
 }
 
