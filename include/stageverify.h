@@ -41,7 +41,8 @@
  *   - Errors are returned as sv_status; sv_last_error(ctx) gives a text.  Shapes a kernel
  *     does not support are rejected with SV_EUNSUPPORTED, never mis-computed.
  *   - A context is bound to the device current at sv_create, owns only its workspace, and
- *     is not thread-safe: use one context per stream.
+ *     is not thread-safe: use one context per stream.  Calls on one context that overlap in time share its
+ *     workspace and may spoil each other's results (not those of later calls).
  */
 #ifndef STAGEVERIFY_H
 #define STAGEVERIFY_H
