@@ -115,8 +115,10 @@ void sv::set_global_error(const char* fmt, ...) {
 namespace {
 
 // For launch_score: a context with backward is there for checks that keep the GPU busier than the host, where a reduction in the pass is
-// the longer way (256 tokens, 2048 columns 167.7 -> 169.1 us; 180 tokens, 256 columns 120.5 -> 123.2); elsewhere few tokens wait for the
-// host's launches (forward checks of 64 tokens 42.7 -> 41.0, of 128 in fp32 41.3 -> 39.3, a scoring call 14.7 -> 11.7).
+// the longer way (two launches -> one: 256 tokens of 2048 columns 168.4 -> 169.7 us, of 256 columns 126.8 -> 127.9, 96 tokens 111.8 ->
+// 113.7).  With up to 64 tokens the host's launches show there too, but one process differs from the next by more than the two ways do (16
+// tokens of 256 columns: 97 to 102 with two, 97 to 100 with one).  Elsewhere few tokens wait for the host's launches (forward checks of 64 tokens 42.9 -> 41.0,
+// of 128 in fp32 41.7 -> 39.9, a scoring call 14.8 -> 11.8).
 uint32_t* score_launches(sv_ctx* c) { return c->flags & SV_FLAG_BACKWARD ? nullptr : &c->score_launches; }
 
 void set_err(sv_ctx* c, const char* fmt, ...) {

@@ -267,8 +267,8 @@ __global__ __launch_bounds__(256) void score_tokens_kernel(const EC* __restrict_
       p->max_rel = b; p->argmax = bt; p->bad = bd; p->launch = 0;
     }
   } else {
-    // 1 x 256 tokens of 512: a call 14.7 -> 11.7 us, the host's time for a launch.  (With a counter between fences the call is as short, but
-    // the checks around it were longer, by an L2 written back and emptied: 256 tokens of 256 columns, forward, 45.5 us instead of 44.4.)
+    // 1 x 256 tokens of 512: a call 14.8 -> 11.8 us, the host's time for a launch.  (With a counter between fences the call is as short, but
+    // the checks around it were longer, by an L2 written back and emptied: 256 tokens of 512 columns, forward, 45.8 us instead of 44.4.)
     __shared__ int s_all;
     if (wave == 0) {
       worst(b, bt, bd);
