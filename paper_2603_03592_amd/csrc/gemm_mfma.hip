@@ -11,9 +11,8 @@
 //
 // Common shape: a BM x BN output tile per workgroup, K walked in slices of 64.  Both operand
 // slices are staged in LDS as rows of 64 bf16 (128 bytes) whose eight 16-byte chunks are
-// XOR-swizzled by the row index, so that the 16-byte fragment reads of v_mfma_f32_32x32x16_bf16
-// (a lane reads 8 consecutive k of one row) and the 16-byte staging writes are bank-conflict
-// free.
+// XOR-swizzled by the row index, so that the 16-byte fragment reads (a lane reads 8 consecutive
+// k of one row) and the 16-byte staging writes are bank-conflict free.
 //
 // The weight tile takes the MFMA "A" slot and the activation tile the "B" slot: each lane then
 // owns one token row and groups of 4 consecutive output features, which makes every epilogue
@@ -175,8 +174,9 @@ __device__ __forceinline__ float epilogue_apply4(const GemmArgs& a, int m, int n
 }
 
 // How many trips ahead of its stores the direct-to-LDS kernel's epilogue reads its inputs (a trip: two rows per lane).  One trip
-// of work is shorter than a memory round trip, so one trip ahead leaves the epilogue waiting once per trip.
-template <int EPI> constexpr int kEpiAhead = EPI == EPI_ROPE ? 2 : EPI == EPI_SWIGLU_BWD ? 3 : 4;   // as far as the registers go
+// of work is shorter than a memory round trip, so one trip ahead leaves the epilogue waiting once per trip.  (2, 2 and 3 measure the
+// same within 1 %, 8 for the residual spills.)
+template <int EPI> constexpr int kEpiAhead = EPI == EPI_ROPE ? 4 : EPI == EPI_SWIGLU_BWD ? 4 : 6;   // as far as the registers go
 
 // does this kind of epilogue take GemmArgs::rscale?
 template <int EPI> constexpr bool kEpiScaled = EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_ROPE;
@@ -398,20 +398,27 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int nspl
 }
 
 // ------------------------------------------------------------------------------------------
-// 256x256x64 NT kernel with direct global->LDS loads (buffer_load_dwordx4 ... lds, 16 bytes per lane).
+// 256x256x64 NT kernel with direct global->LDS loads (buffer_load_dwordx4 ... lds, 16 bytes per lane), four waves of 128x128.
 //
-// Each wave instruction copies 64 x 16 bytes to one contiguous 1 KB block of LDS = 8 tile rows;
-// the XOR swizzle is applied by choosing WHICH global chunk each lane fetches, so the LDS image
-// is the same swizzled layout the fragment reads expect and no VGPR staging or ds_write is
-// needed.  The loads are buffer loads: a descriptor per operand panel in scalar registers, the
-// lane's byte offset in one vector register, the slice's k offset as the scalar offset -- no
-// 64-bit address arithmetic per slice.  Two LDS stages; the 16 loads a wave owes for slice k+1 and
-// the 8 fragment reads of the next 16-wide k step are issued ONE AT A TIME BEHIND AN MFMA, in the
-// 32 cycles the matrix pipe is busy with it (one wave per SIMD: whatever is issued between two
-// MFMAs after the pipe has drained idles it; grouping them between blocks of four MFMAs measured
-// 1-3 % slower), fragments double buffered in registers.  The loop is rotated so that the one
-// full wait + barrier per slice sits at the loop top: after it the compiler's counter tracking
-// is exact and no other wait stalls the MFMA stream.
+// Each wave instruction copies 64 x 16 bytes to one contiguous 1 KB block of LDS = 8 tile rows; the XOR swizzle is applied by
+// choosing WHICH global chunk each lane fetches, so no VGPR staging or ds_write is needed.  The loads are buffer loads: a
+// descriptor per operand panel in scalar registers, the lane's byte offset in one vector register, the slice's k offset as the
+// scalar offset.
+//
+// v_mfma_f32_16x16x32_bf16: a product's accumulators pass the register file once per 32 k instead of once per 16, and at sizes where
+// the chip's power sets the clock that shows: 8192 x 28672, K = 4096 1405 -> 1322 us, with the same bits, the same loads and as many
+// LDS reads as on v_mfma_f32_32x32x16_bf16.  Its fragment reads (16 rows x 64 bytes) need a swizzle of their own (swz16): with the
+// other kernels' it was slower, 1490.
+//
+// Where the loads go: slice k + 1 of the weights and slice k + 2 of the activations are on their way while slice k is multiplied,
+// into two and three buffers of 32 KB, all of the CU's 160 KB.  A slice is two steps of 32 k; a step is 64 MFMAs, and behind
+// every second one stands one of the 16 fragment reads of the next step or of 8 loads, activations in the one step and weights in
+// the other: loads in one step only left them too little time (K = 14336: 693 against 645 us).  One wait and barrier per slice,
+// which leaves the youngest eight loads in flight.
+//
+// The stream of slices runs on across tiles: behind a tile's last MFMAs the next tile's first slice has landed, its first fragments
+// are in registers and the loads of the slices behind it are on their way, so a tile begins without a wait.  A tile's first MFMAs
+// take zero for their accumulators, no instruction clears them.
 //
 // GROUPED: the grouped form (per-row-block weight group, row count from device memory) as its own instantiation, so
 // that the dense form's code -- in particular its waits, which scalar loads in the tile-change path would disturb
@@ -419,12 +426,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int nspl
 //
 // NF: the forms that stand at the two ends of an RMSNorm run inside the products (their own instantiations, for the same
 // reason): the kinds that can follow a norm multiply every row by GemmArgs::rscale, EPI_RESID also writes GemmArgs::rowsq.
+// the stores a full tile's epilogue makes last of all (at least: 6 bits of a wait count hold no more than 63 with the eight loads)
+template <int EPI> constexpr int kEpiStores = EPI == EPI_SWIGLU ? 16 : EPI == EPI_SWIGLU_BWD ? 55 : 32;
+constexpr int meet_wait(int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14); }       // vmcnt(vm) lgkmcnt(0)
+
+// A buffer descriptor without a bound, from a base that is the same in every lane, said explicitly: kept across the loops, the
+// compiler moves one to vector registers otherwise and walks over the lanes at every load.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t open_rsrc(const void* base) {
+  const uint64_t v = (uint64_t)base;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, -1, 0x00020000);
+}
+
+struct Stream { int vb, m0, n0, seg, k, K; bool ok; };
+__device__ __forceinline__ int swz16(int row) { return (row >> 1) & 7; }
+
 template <int EPI, bool GROUPED, bool NF = false>
 __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tiles_m, int tiles_n) {
   constexpr bool DUAL = EPI == EPI_SWIGLU;
   constexpr bool RS = NF && kEpiScaled<EPI>, SQ = NF && EPI == EPI_RESID;
-  constexpr int BM = 256, BN = 256, STAGE = (BM + BN) * 128, MI = 4, NI = 4;
+  constexpr bool kHasInputs = EPI == EPI_RESID || EPI == EPI_SWIGLU_BWD || EPI == EPI_GELU_BWD || EPI == EPI_ROPE;
+  constexpr int BM = 256, MI = 8, NI = 8;
   constexpr int NOUT = DUAL ? 128 : 256;
+  constexpr int BUF = 256 * 128, WBUF = 3 * BUF;          // activations: three buffers from 0; weights: two from WBUF
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   // grouped form: the row count lives in device memory and the launch covers its bound
@@ -450,366 +474,398 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     return true;
   };
 
-  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lhi = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lhi = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
 
-  // ---- DMA side: one continuous stream of slices across this workgroup's tiles, always one slice
-  // ahead of the multiply.  State: virtual block d_vb (tile d_m0, d_n0), segment dseg, offset dk.
-  int d_vb = blockIdx.x, d_m0 = 0, d_n0 = 0, dseg = 0, dk = 0, d_K = 0;   // d_K: length of segment dseg, kept in a register
-                                                                           // (a per-slice kernel-argument load would share
-                                                                           // its wait counter with the LDS reads)
-  bool d_valid = tile_of(d_vb, d_m0, d_n0);
-  const char *gA, *gB, *gB2;
-  __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the stream reads: base = first row, no bound
+  // ---- the two streams of slices across this workgroup's tiles.  State: virtual block vb (tile m0, n0), segment seg, offset k in
+  // it; K is the segment's length, kept in a register (a per-slice kernel-argument load would share its wait counter with the
+  // LDS reads).  A finished stream stays on a slice it has read and keeps reading that.
+  Stream sa{(int)blockIdx.x, 0, 0, 0, 0, 0, false};
+  sa.ok = tile_of(sa.vb, sa.m0, sa.n0);
+  if (!sa.ok) return;
+  Stream sb = sa;
+  __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the streams read: base = first row, no bound
   unsigned voffA[8], voffB[8];
-  auto set_segment = [&]() {
-    const GemmSeg& sg = a.seg[dseg];
-    d_K = sg.K;
-    gA = (const char*)((const bf16*)sg.A + (int64_t)d_m0 * sg.lda);
-    const int64_t goff = GROUPED ? (int64_t)a.tile_group[d_m0 >> 8] * a.group_stride : 0;
-    if (!DUAL && a.nbcol > 0) {
-      int start = 0, j = 0;
-      while (j + 1 < a.nbcol && d_n0 >= start + a.ncol[j]) { start += a.ncol[j]; ++j; }
-      gB = (const char*)((const bf16*)a.Bcol[j] + (int64_t)(d_n0 - start) * sg.ldb);
-    } else {
-      gB = (const char*)((const bf16*)sg.B + goff + (int64_t)d_n0 * sg.ldb);
-    }
-    gB2 = DUAL ? (const char*)((const bf16*)a.B2 + goff + (int64_t)d_n0 * a.ldb2) : gB;
-    rA = __builtin_amdgcn_make_buffer_rsrc((void*)gA, (short)0, -1, 0x00020000);
-    rB = __builtin_amdgcn_make_buffer_rsrc((void*)gB, (short)0, -1, 0x00020000);
-    rB2 = __builtin_amdgcn_make_buffer_rsrc((void*)gB2, (short)0, -1, 0x00020000);
+  // (the lane's number is opaque here: the offsets of a product of one segment would otherwise be kept twice)
+  auto set_a = [&]() {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const GemmSeg& sg = a.seg[sa.seg];
+    sa.K = sg.K;
+    const unsigned lda2 = (unsigned)sg.lda * 2u;             // panels_fit: a panel's offsets have 32 bits
+    rA = open_rsrc((const bf16*)sg.A + (int64_t)sa.m0 * sg.lda);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int r = (wave + 4 * i) * 8 + (lane >> 3), c = (lane & 7) ^ swz(r);
-      const int ra = min(r, M - 1 - d_m0);                  // ragged row tail: re-read the last row
-      voffA[i] = (unsigned)((int64_t)ra * sg.lda + c * 8) * 2u;
-      if (DUAL) voffB[i] = (unsigned)((int64_t)(r & 127) * (i >= 4 ? a.ldb2 : sg.ldb) + c * 8) * 2u;
-      else voffB[i] = (unsigned)((int64_t)r * sg.ldb + c * 8) * 2u;
+      const int r = (wave + 4 * i) * 8 + (ln >> 3), c = (ln & 7) ^ swz16(r);
+      voffA[i] = (unsigned)min(r, M - 1 - sa.m0) * lda2 + c * 16u;      // ragged row tail: re-read the last row
     }
   };
-  auto dma = [&](int stage, int j) {                          // j: 0..7 activation rows, 8..15 weight rows
-    const int i = j & 7;
-    const unsigned off = j < 8 ? voffA[i] : voffB[i];
-    char* dst = smem + stage * STAGE + (j < 8 ? 0 : BM * 128) + (wave + 4 * i) * 1024;
-    // buffer form of the direct-to-LDS load: per-lane byte offset in a register, the slice's offset k * 2 as the scalar offset
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(j < 8 ? rA : ((DUAL && i >= 4) ? rB2 : rB), (__attribute__((address_space(3))) void*)dst, 16,
-                                             (int)off, dk * 2, 0, 0);
-  };
-  auto advance = [&]() {                                      // to the next slice of the stream
-    dk += BK;
-    if (dk < d_K) return;
-    dk = 0;
-    if (dseg + 1 < a.nseg) { ++dseg; set_segment(); return; }
-    dseg = 0;
-    d_vb += gridDim.x;
-    d_valid = tile_of(d_vb, d_m0, d_n0);
-    if (d_valid) set_segment();
-  };
-
-  int xrow[MI], wrow[NI];
+  auto set_b = [&]() {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const GemmSeg& sg = a.seg[sb.seg];
+    sb.K = sg.K;
+    const unsigned ldb2 = (unsigned)sg.ldb * 2u, ldu2 = DUAL ? (unsigned)a.ldb2 * 2u : 0u;
+    const int64_t goff = GROUPED ? (int64_t)a.tile_group[sb.m0 >> 8] * a.group_stride : 0;
+    const bf16* B;
+    if (!DUAL && a.nbcol > 0) {
+      int start = 0, j = 0;
+      while (j + 1 < a.nbcol && sb.n0 >= start + a.ncol[j]) { start += a.ncol[j]; ++j; }
+      B = (const bf16*)a.Bcol[j] + (int64_t)(sb.n0 - start) * sg.ldb;
+    } else {
+      B = (const bf16*)sg.B + goff + (int64_t)sb.n0 * sg.ldb;
+    }
+    rB = open_rsrc(B);
+    rB2 = DUAL ? open_rsrc((const bf16*)a.B2 + goff + (int64_t)sb.n0 * a.ldb2) : rB;
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) xrow[mi] = wm * 128 + mi * 32 + l31;
+    for (int i = 0; i < 8; ++i) {
+      const int r = (wave + 4 * i) * 8 + (ln >> 3), c = (ln & 7) ^ swz16(r);
+      voffB[i] = (unsigned)(DUAL ? r & 127 : r) * (DUAL && i >= 4 ? ldu2 : ldb2) + c * 16u;
+    }
+  };
+  auto advance = [&](Stream& s, auto&& set) {                 // to the next slice
+    if (!s.ok) return;
+    s.k += BK;
+    if (s.k < s.K) return;
+    s.k = 0;
+    if (s.seg + 1 < a.nseg) { ++s.seg; set(); return; }
+    s.seg = 0;
+    s.vb += gridDim.x;
+    s.ok = tile_of(s.vb, s.m0, s.n0);
+    if (s.ok) set();
+  };
+  auto dma_a = [&](int buf, int i) {                          // 1 KB: the wave's i-th group of 8 rows
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i],
+                                             sa.k * 2, 0, 0);
+  };
+  auto dma_b = [&](int buf, int i) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(DUAL && i >= 4 ? rB2 : rB, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16,
+                                             (int)voffB[i], sb.k * 2, 0, 0);
+  };
+  auto behind = [](int buf) { return buf == 2 * BUF ? 0 : buf + BUF; };      // the next of the activations' buffers
+
+  // ---- fragment addresses: rows 16 b + (lane & 15) of an operand, chunk 4 s + (lane >> 4); swz16 does not see b
+  unsigned offX[2], offW[2];
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) wrow[ni] = (DUAL ? (ni < 2 ? wn * 64 + ni * 32 : 128 + wn * 64 + (ni - 2) * 32) : wn * 128 + ni * 32) + l31;
+  for (int s = 0; s < 2; ++s) {
+    const int chunk = ((s * 4 + lhi) ^ swz16(l15)) << 4;
+    offX[s] = (unsigned)((wm * 128 + l15) * 128 + chunk);
+    offW[s] = (unsigned)((wn * (DUAL ? 64 : 128) + l15) * 128 + chunk);
+  }
+  auto read_x = [&](int buf, int s, int b) { return *reinterpret_cast<const bf16x8*>(smem + buf + offX[s] + b * 2048); };
+  auto read_w = [&](int buf, int s, int b) {                  // SwiGLU: blocks 0..3 gate, 4..7 up, which begin at row 128
+    return *reinterpret_cast<const bf16x8*>(smem + buf + offW[s] + (DUAL && b >= 4 ? b + 4 : b) * 2048);
+  };
 
-  f32x16 acc[NI][MI];
-
+  f32x4 acc[NI][MI];
 #define SV_SB __builtin_amdgcn_sched_barrier(0)
-  // One 16-wide k step: MFMAs on (xc, wc); fragments (rstage, rkk) are read into (xn, wn_) and the
-  // DMAs [d0, d0 + 8) of the stream's next slice are issued into dstage, both spread over the four MFMA groups.
-  auto step = [&](bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], bool do_read, int rstage, int rkk,
-                  bool do_dma, int dstage, int d0) {
-    const char* xs = smem + rstage * STAGE;
-    const char* ws = xs + BM * 128;
-    // The fragments this step multiplies were requested during the previous step, the youngest of them four MFMAs
-    // ago: wait for them here, before this step's own requests are queued behind them.
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    SV_SB;
+  // One step of 32 k: MFMAs on (xc, wc), on zero accumulators if `first`; the fragments of step s of the slice in buffers ra, rw
+  // are read into (xn, wn_), and the eight loads of a stream's next slice are issued (into_w: weights) into buffer db.
+  auto step = [&](auto first, auto into_w, auto reads, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
+    const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      // every other instruction of the group is issued behind an MFMA, in the 32 cycles the matrix pipe is busy with it
-      acc[g][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[g], xc[0], acc[g][0], 0, 0, 0);
+    for (int q = 0; q < 32; ++q) {                            // two MFMAs, then one memory instruction
+      const int g = q >> 2;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = (q & 3) * 2 + h, m = g & 1 ? 7 - j : j; // back and forth, so that neighbours share an operand
+        acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[g], xc[m], decltype(first)::value ? zero : acc[g][m], 0, 0, 0);
+      }
       SV_SB;
-      if (do_read) xn[g] = *reinterpret_cast<const bf16x8*>(xs + lds_off(xrow[g], rkk * 2 + lhi));
-      SV_SB;
-      acc[g][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[g], xc[1], acc[g][1], 0, 0, 0);
-      SV_SB;
-      if (do_read) wn_[g] = *reinterpret_cast<const bf16x8*>(ws + lds_off(wrow[g], rkk * 2 + lhi));
-      SV_SB;
-      acc[g][2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[g], xc[2], acc[g][2], 0, 0, 0);
-      SV_SB;
-      if (do_dma) dma(dstage, d0 + 2 * g);
-      SV_SB;
-      acc[g][3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wc[g], xc[3], acc[g][3], 0, 0, 0);
-      SV_SB;
-      if (do_dma) dma(dstage, d0 + 2 * g + 1);
-      SV_SB;
+      if (q < 24) {
+        const int r = q - q / 3;
+        if (q % 3 == 2) { if (decltype(into_w)::value) dma_b(db, q / 3); else dma_a(db, q / 3); }
+        else if (decltype(reads)::value) { if (r < 8) xn[r] = read_x(ra, s, r); else wn_[r - 8] = read_w(rw, s, r - 8); }
+        SV_SB;
+      }
     }
   };
+  // this wave's wait, then the workgroup's barrier: slice k + 1 is complete (its youngest load is older than the last eight), and
+  // everybody has read what they need of slice k
+#define SV_MEET(imm) do { SV_SB; __builtin_amdgcn_s_waitcnt(imm); asm volatile("s_barrier" ::: "memory"); SV_SB; } while (0)
+  constexpr int kLgkm0 = 0xc07f;                              // lgkmcnt(0), nothing else
+  using Yes = std::true_type;
+  using No = std::false_type;
 
-  if (!d_valid) return;
-  bf16x8 xf0[MI], wf0[NI], xf1[MI], wf1[NI];
-  set_segment();
+  bf16x8 x0[MI], w0[NI], x1[MI], w1[NI];
+  int ca = 0, cw = WBUF;                                      // the buffers of the slice being multiplied
+  constexpr int kOther = WBUF ^ (WBUF + BUF);
+  set_a();
+  set_b();
 #pragma unroll
-  for (int j = 0; j < 16; ++j) dma(0, j);                     // slice 0 of the first tile
-  advance();
-  int par = 0;                                                // LDS stage of the current tile's slice 0
+  for (int j = 0; j < 8; ++j) dma_a(0, j);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) dma_b(WBUF, j);
+  advance(sa, set_a);
+  advance(sb, set_b);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) dma_a(BUF, j);
+  advance(sa, set_a);
+  SV_MEET(meet_wait(8));
+#pragma unroll
+  for (int j = 0; j < 8; ++j) dma_b(cw ^ kOther, j);
+  advance(sb, set_b);
+  if (!kHasInputs) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) { x0[b] = read_x(ca, 0, b); w0[b] = read_w(cw, 0, b); }
+  }
 
   int m0, n0;
+  bool stored = false;                                        // this workgroup's stores may be on their way
   for (int vb = blockIdx.x; tile_of(vb, m0, n0); vb += gridDim.x) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < MI; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    // ---- what the epilogue's global accesses need, set up here because a full tile asks for its first inputs a slice early.
-    // In the read-back of the epilogue a lane serves row er of each group of 4 rows, 16-byte chunk ec4 (and 16 + ec4).
+    // ---- what the epilogue's global accesses need, set up here because a full tile asks for its first inputs early.
+    // In the read-back of the epilogue a lane serves row er of each group of 4 rows, 8 columns from 8 ec.
     // One buffer descriptor per tensor, based at the tile's first row and the wave's first column; inside it a lane's
     // byte offset is (row * ld + column) * 2, of which the lane's part never changes and the row block's part is a scalar:
     // no 64-bit address arithmetic per access.
-    constexpr bool kHasInputs = EPI == EPI_RESID || EPI == EPI_SWIGLU_BWD || EPI == EPI_GELU_BWD || EPI == EPI_ROPE;
     constexpr int PD = kEpiAhead<EPI>;                   // trips the epilogue's global reads run ahead of its stores
-    const int er = lane >> 4, ec4 = lane & 15;
+    const int er = lhi, ec8 = l15;
     const int ncol0 = n0 + wn * (DUAL ? 64 : 128);
     auto desc = [&](const void* base, int ld) {
       return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16*)base + (int64_t)m0 * ld + ncol0), (short)0, -1, 0x00020000);
     };
     const __amdgpu_buffer_rsrc_t bC = desc(a.C, a.ldc), bC2 = desc(a.C2, a.ldc), bC3 = desc(a.C3, a.ldc);
     const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr), bR2 = desc(a.R2, a.ldr);
-    const int vC = ((wm * 128 + er) * a.ldc + ec4 * 4) * 2, vR = ((wm * 128 + er) * a.ldr + ec4 * 4) * 2;
-    // offsets of row block rb (rows rb .. rb + 3 of the wave's 128): per lane (vo) and scalar (so).  A ragged tile
+    // offsets of rows rb + row of the wave's 128, `bytes` into a row: per lane (vo) and scalar (so).  A ragged tile
     // re-reads its last row for the rows past the end, which takes the row into the lane's part.
-    auto place = [&](auto check_tag, int rb, int ld, int vlane, int& vo, int& so) {
-      if (decltype(check_tag)::value) { vo = (min(wm * 128 + rb + er, M - 1 - m0) * ld + ec4 * 4) * 2; so = 0; }
-      else { vo = vlane; so = rb * ld * 2; }
+    auto place = [&](auto check_tag, int rb, int row, int ld, int bytes, int& vo, int& so) {
+      if (decltype(check_tag)::value) { vo = min(wm * 128 + rb + row, M - 1 - m0) * ld * 2 + bytes; so = 0; }
+      else { vo = (wm * 128 + row) * ld * 2 + bytes; so = rb * ld * 2; }
     };
-    int rope_p0 = 0, rope_v_lo = 0, rope_v_hi = 0;      // first row's position; byte offsets of the lane's feature pairs in a table row
+    int rope_p0 = 0, rope_v = 0;                         // first row's position; byte offset of the lane's feature pairs in a table row
     if (EPI == EPI_ROPE) {
       rope_p0 = (m0 + wm * 128) % a.rope_S;
-      rope_v_lo = (((ncol0 + ec4 * 4) % a.rope_hd) >> 1) * 8;
-      rope_v_hi = (((ncol0 + 64 + ec4 * 4) % a.rope_hd) >> 1) * 8 - rope_v_lo;
+      rope_v = (((ncol0 + ec8 * 8) % a.rope_hd) >> 1) * 8;
     }
     const __amdgpu_buffer_rsrc_t bT = __builtin_amdgcn_make_buffer_rsrc((void*)a.rope_cs, (short)0, -1, 0x00020000);
-    auto ld8 = [&](__amdgpu_buffer_rsrc_t b, int vo, int so) { return __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(b, vo, so, 0)); };
-    // the inputs of trip `trip` (two rows of row block mi = trip / 4 per lane): residual, gate / up, RoPE table
-    auto load_inputs = [&](auto check_tag, int trip, EpiIn (&lo)[2], EpiIn (&hi)[2]) {
-      const int mi = trip >> 2, it = (trip & 3) * 2;
+    auto ld16 = [&](__amdgpu_buffer_rsrc_t b, int vo, int so, bf16x4& lo, bf16x4& hi) {
+      const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, vo, so, 0));
+      lo = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+      hi = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+    };
+    // the inputs of trip `trip` (rows 8 trip .. 8 trip + 7 of the wave's 128, two per lane): residual, gate / up, RoPE table
+    auto load_inputs = [&](auto check_tag, int trip, int er, EpiIn (&lo)[2], EpiIn (&hi)[2]) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        const int rb = mi * 32 + (it + k) * 4;
+        const int rb = trip * 8 + k * 4;
         if (EPI == EPI_ROPE) {
           // position of the row in its sequence without a division per row: the wave's first row is reduced once
           // per tile, the rows of the tile follow it consecutively
           int p = rope_p0 + rb + er;
           if (a.rope_S >= 256) p -= p >= a.rope_S ? a.rope_S : 0; else p %= a.rope_S;
-          const int vo = p * (a.rope_hd >> 1) * 8 + rope_v_lo;      // the table entry (position p, feature pair) is 8 bytes
+          const int vo = p * (a.rope_hd >> 1) * 8 + rope_v;         // the table entry (position p, feature pair) is 8 bytes
           lo[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo, 0, 0));
-          hi[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo + rope_v_hi, 0, 0));
+          hi[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo + 16, 0, 0));
         } else if (kHasInputs) {
           int vo, so;
-          place(check_tag, rb, a.ldr, vR, vo, so);
-          lo[k].r = ld8(bR, vo, so);
-          hi[k].r = ld8(bR, vo + 128, so);
-          if (EPI == EPI_SWIGLU_BWD) { lo[k].r2 = ld8(bR2, vo, so); hi[k].r2 = ld8(bR2, vo + 128, so); }
+          place(check_tag, rb, er, a.ldr, ec8 * 16, vo, so);
+          ld16(bR, vo, so, lo[k].r, hi[k].r);
+          if (EPI == EPI_SWIGLU_BWD) ld16(bR2, vo, so, lo[k].r2, hi[k].r2);
         }
       }
     };
     EpiIn in_lo[PD][2], in_hi[PD][2];                    // [trip mod PD][row of the pair]
     const bool full_tile = m0 + 256 <= M;
-    auto first_inputs = [&]() {                          // of a full tile, a slice before the epilogue
+    auto first_inputs = [&]() {                          // of a full tile, before its last step
       if (kHasInputs && full_tile) {
 #pragma unroll
-        for (int t = 0; t < PD; ++t) load_inputs(std::false_type{}, t, in_lo[t], in_hi[t]);
+        for (int t = 0; t < PD; ++t) load_inputs(No{}, t, er, in_lo[t], in_hi[t]);
       }
     };
-    // ---- slice 0 (its loads were issued during the previous tile's last slice, or above)
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    SV_SB;
-    // the row factors of the wave's 128 rows are asked for here, a whole k loop before the epilogue wants them (its
-    // first loads would otherwise start with a memory round trip per tile); the next wait for memory is a slice away
+    // the row factors of the wave's 128 rows, lane l those of rows l and 64 + l, are asked for here, a k loop before the epilogue wants them
     float rs_pre0 = 1.0f, rs_pre1 = 1.0f;
     if (RS) {
       rs_pre0 = a.rscale[min(m0 + wm * 128 + lane, M - 1)];
       rs_pre1 = a.rscale[min(m0 + wm * 128 + 64 + lane, M - 1)];
     }
-    if (nslices == 1) first_inputs();
+    // ---- the k loop.  The tile's first slice has landed; its first fragments have been asked for, unless the epilogue has inputs,
+    // which need the registers.
+    if (kHasInputs) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      xf0[g] = *reinterpret_cast<const bf16x8*>(smem + par * STAGE + lds_off(xrow[g], lhi));
-      wf0[g] = *reinterpret_cast<const bf16x8*>(smem + par * STAGE + BM * 128 + lds_off(wrow[g], lhi));
+      for (int b = 0; b < 8; ++b) { x0[b] = read_x(ca, 0, b); w0[b] = read_w(cw, 0, b); }
     }
-    step(xf0, wf0, xf1, wf1, true, par, 1, true, par ^ 1, 0);
-    step(xf1, wf1, xf0, wf0, true, par, 2, true, par ^ 1, 8);
-    if (d_valid) advance();
-    step(xf0, wf0, xf1, wf1, true, par, 3, false, 0, 0);
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    SV_SB;
+    step(Yes{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+    advance(sa, set_a);
+    ca = behind(ca); cw ^= kOther;
     for (int kt = 1; kt < nslices; ++kt) {
-      const int st = (par + kt) & 1;
-      __builtin_amdgcn_s_waitcnt(0);   // my DMAs of slice kt have landed, my fragment reads of slice kt-1 are done
-      __syncthreads();                 // ... and so have everybody's: stage st is complete, stage st^1 is free
+      // the tile's second slice was asked for before the last tile's results were stored: those may still be on their way
+      if (kt == 1 && stored) SV_MEET(meet_wait(8 + kEpiStores<EPI>));
+      else SV_MEET(meet_wait(8));
+      step(No{}, Yes{}, Yes{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+      advance(sb, set_b);
+      __builtin_amdgcn_s_waitcnt(kLgkm0);
       SV_SB;
-      if (kt == nslices - 1) first_inputs();     // their round trip hides behind the last slice's products
-      SV_SB;
-      step(xf1, wf1, xf0, wf0, true, st, 0, true, st ^ 1, 0);     // MFMAs of (kt-1, k step 3)
-      step(xf0, wf0, xf1, wf1, true, st, 1, true, st ^ 1, 8);
-      if (d_valid) advance();
-      step(xf1, wf1, xf0, wf0, true, st, 2, false, 0, 0);
-      step(xf0, wf0, xf1, wf1, true, st, 3, false, 0, 0);
+      step(No{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+      advance(sa, set_a);
+      ca = behind(ca); cw ^= kOther;
     }
-    step(xf1, wf1, xf0, wf0, false, 0, 0, false, 0, 0);
+    SV_SB;
+    first_inputs();                                      // their round trip hides behind the last step's products
+    if (kHasInputs && full_tile) SV_MEET(meet_wait(8 + PD * (EPI == EPI_SWIGLU_BWD || EPI == EPI_ROPE ? 4 : 2)));
+    else SV_MEET(meet_wait(8));
+    step(No{}, Yes{}, std::integral_constant<bool, !kHasInputs>{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+    advance(sb, set_b);
+    SV_SB;
+    stored = full_tile;
 
-    // ---- epilogue through LDS (the next tile's slice 0 is landing in the other stage meanwhile).
-    // In the accumulator layout a lane owns one token row and scattered groups of 4 features, so a
-    // store instruction would touch 32 rows with 16 bytes each; the memory pipeline then takes ~11 us
-    // per tile.  Each wave instead writes its 32 x 128 fp32 block into its own 16 KB patch of the
-    // stage that was just consumed (16-byte chunks XOR-swizzled by the row: conflict-free both ways)
-    // and reads it back so that 16 consecutive lanes cover 128 contiguous bytes of an output row;
-    // every global access of the epilogue (result, residual, gate / up) becomes a full-line run.
-    const int sl = (par + nslices - 1) & 1;
-    par = (par + nslices) & 1;
-    __syncthreads();                                   // everybody is done reading stage sl
-    char* patch = smem + sl * STAGE + wave * 16384;
-    // per wave, behind the two stages: the row factors of its 128 rows (each lane of the read-back needs those of the
-    // rows it serves) and the rows' sums of squares (stored in one piece when the tile is done)
-    float* rsbuf = reinterpret_cast<float*>(smem + 2 * STAGE) + wave * 256;
-    float* sqbuf = rsbuf + 128;
-    if (RS) { rsbuf[lane] = rs_pre0; rsbuf[64 + lane] = rs_pre1; }
-    // Sixteen trips per tile: row block mi = trip / 4, two rows per lane and trip.  The epilogue's global reads (residual,
-    // gate / up, RoPE table) run kEpiAhead trips ahead of its stores; the first of them were asked for when the last slice
-    // began.  (The memory counter retires in order: a read is waited for together with every store issued before it, so
-    // the reads of a trip are issued before the stores they must not wait for have piled up.)  Tiles that lie
-    // inside the M rows run without any per-lane condition (CHECK = false): around divergent branches the compiler's
-    // wait insertion falls back to waiting for (nearly) everything in flight, one memory round trip per store.
+    // ---- epilogue through LDS (the next tile's first slices are landing meanwhile).
+    // In the accumulator layout a lane owns one token row and groups of 4 features, so a store instruction would touch 16 rows
+    // with 32 bytes each (with the weights' rows dealt so that a lane holds 8 neighbouring features, 64 or, after an exchange
+    // between lanes, 128 bytes, the stores were still 2 - 4 % of a K = 2048 product slower than this way).  Each wave instead turns
+    // 16 rows at a time over in a patch of its own of the activations' free buffer and reads them back so that consecutive lanes
+    // hold 16 bytes each of an output row: every global access of the epilogue (result, residual, gate / up) is a run of full lines.
+    // The patch is what this wave's own loads will fill next, 1 KB pieces 4 KB apart, so that no barrier
+    // stands between the waves' epilogues and the loads behind them.
+    char* patch = smem + behind(behind(ca)) + wave * 1024;
     auto run_epilogue = [&](auto check_tag) {
       constexpr bool CHECK = decltype(check_tag)::value;
+      // The lane's row and chunk numbers are made opaque once per tile: otherwise every address below is loop invariant, gets
+      // hoisted out of the tile loop and crowds the fragments and the epilogue's inputs out of the registers.
+      int e15 = l15, eer = er;
+      asm volatile("" : "+v"(e15), "+v"(eer));
+      // The accumulators stay in the accumulation registers until their row block's turn: seen through, the compiler copies whole
+      // blocks of them ahead, for both forms of this epilogue at once, and spills.
+      auto take = [&](int ni, int mi) {
+        f32x4 v = acc[ni][mi];
+        asm volatile("" : "+a"(v));
+        return v;
+      };
+      // (Around divergent branches the compiler's wait insertion falls back to waiting for (nearly) everything in flight, one
+      // memory round trip per store: tiles that lie inside the M rows run without any per-lane condition, CHECK = false.)
+      auto put16 = [&](__amdgpu_buffer_rsrc_t b, bf16x8 v, int rb, int row, int bytes) {
+        int vo, so;
+        place(check_tag, rb, row, a.ldc, bytes, vo, so);
+        if (!CHECK || wm * 128 + rb + row < M - m0) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, vo, so, 0);
+      };
       if constexpr (DUAL) {
-        if (!a.C2 && !a.C3) {
-          // Forward-only check (no stash of g and u).  Gate and up of one feature sit in the same lane and register
-          // index, so SiLU(g) * u is taken in the accumulator layout and only its bf16 result goes through the patch:
-          // 128 token rows x 64 features x 2 bytes = the 16 KB patch in one piece (16-byte chunks XOR-swizzled by bits
-          // 1..3 of the row), a quarter of the fp32 way's LDS traffic, and the read-back gives every lane 16 bytes of a
-          // row, so 8 lanes store one full 128-byte line.  (With the stashes, three such passes measured slower than
-          // the fp32 way below, which serves them.)
-          // The lane's row and chunk numbers are made opaque once per tile: otherwise every address below is loop
-          // invariant, gets hoisted out of the tile loop and spilled, and its reloads cost a memory round trip each.
-          int r31 = l31, rhi = lhi, ln = lane;
-          asm volatile("" : "+v"(r31), "+v"(rhi), "+v"(ln));
-          // The accumulators are read where they are, in the accumulation registers, by an instruction the compiler
-          // cannot merge with the reads of the other way: left to it, it keeps copies of whole accumulator blocks in
-          // ordinary registers from one use to the next and spills them.  The matrix pipe's last write is long
-          // finished (a workgroup barrier lies in between); the wait states make that formal, since the compiler's
-          // own hazard handling does not look into assembly.
-          float rsv[MI];
-          if (RS) { __builtin_amdgcn_s_waitcnt(0xc07f); __builtin_amdgcn_wave_barrier(); }   // the factors are in LDS
+        // Gate and up of one feature sit in the same lane and register index, so SiLU(g) * u is taken in the accumulator layout
+        // and the patch holds bf16 results: 16 rows x 64 features x 2 bytes each of the result and, where backward wants them, gate
+        // and up (16-byte chunks XOR-swizzled by bits 1..3 of the row), three quarters of the fp32 way's LDS traffic and half
+        // its stores.  A row block's arithmetic stands behind the read-back of the one before.
+        const bool stash = a.C2 || a.C3;
+        const int lr = eer * 2 + (e15 >> 3), cc = e15 & 7;       // read-back: rows lr and 8 + lr, chunk cc
+        char* const wr = patch + (e15 >> 3) * 4096 + (e15 & 7) * 128 + (eer & 1) * 8;
+        const int wx = (e15 >> 1) & 7, wc = eer >> 1;
+        bf16x4 act[4], gt[4], ut[4];
+        auto math = [&](int mi) {
+          const float rs = RS ? __shfl(mi < 4 ? rs_pre0 : rs_pre1, (mi & 3) * 16 + e15) : 1.0f;
 #pragma unroll
-          for (int mi = 0; mi < MI; ++mi) rsv[mi] = RS ? rsbuf[mi * 32 + r31] : 1.0f;
-          asm volatile("s_nop 15\n\ts_nop 15");
-          auto rd = [&](int ni, int mi, int r) {
-            float x;
-            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[ni][mi][r]));
-            return x;
-          };
+          for (int ni = 0; ni < 4; ++ni) {
+            const f32x4 gate = take(ni, mi), up = take(ni + 4, mi);
 #pragma unroll
-          for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                bf16x4 pk;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pk[i] = (bf16)(silu_f(rd(ni, mi, q * 4 + i) * rsv[mi]) * (rd(ni + 2, mi, q * 4 + i) * rsv[mi]));
-                const int row = mi * 32 + r31;
-                *reinterpret_cast<bf16x4*>(patch + row * 128 + (((ni * 4 + q) ^ ((r31 >> 1) & 7)) << 4) + rhi * 8) = pk;
-                if (q == 3) SV_SB;                       // one feature block at a time
-              }
-          __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0): the patch is complete before it is read back
-          __builtin_amdgcn_wave_barrier();
-#pragma unroll
-          for (int it = 0; it < 16; ++it) {
-            const int row = it * 8 + (ln >> 3), cc = ln & 7;
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(patch + row * 128 + ((cc ^ ((row >> 1) & 7)) << 4));
-            const int m = m0 + wm * 128 + row;
-            if (CHECK && m >= M) continue;
-            *reinterpret_cast<bf16x8*>((bf16*)a.C + (int64_t)m * a.ldc + n0 + wn * 64 + cc * 8) = v;
-            if ((it & 3) == 3) SV_SB;
-          }
-          return;
-        }
-      }
-      // The lane's row and chunk numbers in the patch are made opaque once per tile, as above: the patch addresses below
-      // are the same for every tile, and kept in registers across the k loop they crowd the epilogue's inputs out.
-      int e31 = l31, eer = er, ec = ec4;
-      asm volatile("" : "+v"(e31), "+v"(eer), "+v"(ec));
-      if (kHasInputs && CHECK) {                         // a ragged tile asks for its first inputs here, a full one did so a slice ago
-#pragma unroll
-        for (int t = 0; t < PD; ++t) load_inputs(check_tag, t, in_lo[t], in_hi[t]);
-      }
-#pragma unroll
-      for (int trip = 0; trip < 16; ++trip) {
-        const int mi = trip >> 2, it = (trip & 3) * 2;
-        if ((trip & 3) == 0) {
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              f32x4 v;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) v[i] = acc[ni][mi][q * 4 + i];
-              const int chunk = ni * 8 + q * 2 + lhi;    // features 4*chunk .. +3 of the wave's 128
-              *reinterpret_cast<f32x4*>(patch + e31 * 512 + ((chunk ^ e31) << 4)) = v;
+            for (int i = 0; i < 4; ++i) {
+              const float g = RS ? gate[i] * rs : gate[i], u = RS ? up[i] * rs : up[i];
+              act[ni][i] = (bf16)(silu_f(g) * u); gt[ni][i] = (bf16)g; ut[ni][i] = (bf16)u;
             }
-          __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0): the patch is complete before it is read back
+          }
+        };
+        math(0);
+        SV_SB;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+          for (int ni = 0; ni < 4; ++ni) *reinterpret_cast<bf16x4*>(wr + (((ni * 2 + wc) ^ wx) << 4)) = act[ni];
+          if (stash) {
+#pragma unroll
+            for (int ni = 0; ni < 4; ++ni) {
+              *reinterpret_cast<bf16x4*>(wr + 8192 + (((ni * 2 + wc) ^ wx) << 4)) = gt[ni];
+              *reinterpret_cast<bf16x4*>(wr + 16384 + (((ni * 2 + wc) ^ wx) << 4)) = ut[ni];
+            }
+          }
+          __builtin_amdgcn_s_waitcnt(kLgkm0);            // the patch is complete before it is read back
+          __builtin_amdgcn_wave_barrier();
+          bf16x8 oc[2], og[2], ou[2];
+#pragma unroll
+          for (int it = 0; it < 2; ++it) {
+            const char* rd = patch + it * 4096 + lr * 128 + ((cc ^ ((it * 4 + (lr >> 1)) & 7)) << 4);
+            oc[it] = *reinterpret_cast<const bf16x8*>(rd);
+            if (stash) { og[it] = *reinterpret_cast<const bf16x8*>(rd + 8192); ou[it] = *reinterpret_cast<const bf16x8*>(rd + 16384); }
+          }
+          SV_SB;
+          if (mi + 1 < MI) math(mi + 1);
+          SV_SB;
+#pragma unroll
+          for (int it = 0; it < 2; ++it) put16(bC, oc[it], mi * 16 + it * 8, lr, cc * 16);
+          if (stash) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+              if (a.C2) put16(bC2, og[it], mi * 16 + it * 8, lr, cc * 16);
+              if (a.C3) put16(bC3, ou[it], mi * 16 + it * 8, lr, cc * 16);
+            }
+          }
           __builtin_amdgcn_wave_barrier();
         }
+      } else {
+        // 16 rows of 128 fp32 accumulators in the patch; a lane's 8 columns lie in chunks c and 16 + c of 16 bytes, XOR-swizzled by
+        // the row: conflict-free both ways.  Sixteen trips per tile, two rows per lane and trip.  The epilogue's global
+        // reads (residual, gate / up, RoPE table) run kEpiAhead trips ahead of its stores; the first of them were asked for before
+        // the last step.  (The memory counter retires in order: a read is waited for together with every store issued
+        // before it, so the reads of a trip are issued before the stores they must not wait for have piled up.)
+        if (kHasInputs && CHECK) {                       // a ragged tile asks for its first inputs here, a full one did so before its last step
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int row = (it + k) * 4 + eer, rb = mi * 32 + (it + k) * 4;
-          const f32x4 a_lo = *reinterpret_cast<const f32x4*>(patch + row * 512 + ((ec ^ row) << 4));
-          const f32x4 a_hi = *reinterpret_cast<const f32x4*>(patch + row * 512 + (((16 + ec) ^ row) << 4));
-          float lo[4], hi[4];
+          for (int t = 0; t < PD; ++t) load_inputs(check_tag, t, eer, in_lo[t], in_hi[t]);
+        }
+        auto prow = [](int row) { return (row >> 1) * 4096 + (row & 1) * 512; };
+        float sq0 = 0.0f, sq1 = 0.0f;                    // SQ: the sums of rows 4 l15 + lhi and 64 + 4 l15 + lhi
 #pragma unroll
-          for (int i = 0; i < 4; ++i) { lo[i] = a_lo[i]; hi[i] = a_hi[i]; }
-          const bool ok = !CHECK || wm * 128 + rb + er < M - m0;
-          int vo, so;
-          place(check_tag, rb, a.ldc, vC, vo, so);
-          auto put_lo = [&](int w, bf16x4 pk) {
-            if (ok) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pk), w == 0 ? bC : w == 1 ? bC2 : bC3, vo, so, 0);
-          };
-          auto put_hi = [&](int w, bf16x4 pk) {
-            if (ok) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pk), w == 0 ? bC : w == 1 ? bC2 : bC3, vo + 128, so, 0);
-          };
-          const float rs = RS ? rsbuf[mi * 32 + row] : 1.0f;
-          const EpiIn& i_lo = in_lo[trip % PD][k];
-          const EpiIn& i_hi = in_hi[trip % PD][k];
-          if (DUAL) epilogue_math4<EPI>(a, false, lo, hi, i_lo, rs, put_lo);   // patch columns 0..63: gate, 64..127: up
-          else {
-            float sq = epilogue_math4<EPI>(a, EPI == EPI_ROPE && ncol0 + ec4 * 4 < a.rope_cols, lo, hi, i_lo, rs, put_lo);
-            sq += epilogue_math4<EPI>(a, EPI == EPI_ROPE && ncol0 + 64 + ec4 * 4 < a.rope_cols, hi, lo, i_hi, rs, put_hi);
+        for (int trip = 0; trip < 16; ++trip) {
+          const int mi = trip >> 1, it = (trip & 1) * 2;
+          if ((trip & 1) == 0) {
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+              *reinterpret_cast<f32x4*>(patch + prow(e15) + (((ni * 2 + (eer >> 1) + (eer & 1) * 16) ^ e15) << 4)) = take(ni, mi);
+            __builtin_amdgcn_s_waitcnt(kLgkm0);          // the patch is complete before it is read back
+            __builtin_amdgcn_wave_barrier();
+          }
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int row = (it + k) * 4 + eer, rb = trip * 8 + k * 4;
+            const f32x4 a_lo = *reinterpret_cast<const f32x4*>(patch + prow(row) + ((e15 ^ row) << 4));
+            const f32x4 a_hi = *reinterpret_cast<const f32x4*>(patch + prow(row) + (((16 + e15) ^ row) << 4));
+            float lo[4], hi[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { lo[i] = a_lo[i]; hi[i] = a_hi[i]; }
+            bf16x4 olo[2], ohi[2];
+            auto put_lo = [&](int w, bf16x4 pk) { olo[w] = pk; };
+            auto put_hi = [&](int w, bf16x4 pk) { ohi[w] = pk; };
+            const float rs = RS ? __shfl(trip < 8 ? rs_pre0 : rs_pre1, (rb & 63) + eer) : 1.0f;
+            const bool roped = EPI == EPI_ROPE && ncol0 + ec8 * 8 < a.rope_cols;
+            float sq = epilogue_math4<EPI>(a, roped, lo, hi, in_lo[trip % PD][k], rs, put_lo);
+            sq += epilogue_math4<EPI>(a, roped, hi, lo, in_hi[trip % PD][k], rs, put_hi);
+            put16(bC, __builtin_shufflevector(olo[0], ohi[0], 0, 1, 2, 3, 4, 5, 6, 7), rb, eer, e15 * 16);
+            if (EPI == EPI_SWIGLU_BWD || (EPI == EPI_GELU && a.C2))
+              put16(bC2, __builtin_shufflevector(olo[1], ohi[1], 0, 1, 2, 3, 4, 5, 6, 7), rb, eer, e15 * 16);
             if (SQ) {
               // the 16 lanes of a row hold its 128 stored values: rotate-and-add within the row of 16 lanes leaves the
-              // sum in all of them, and all of them write it (one LDS address per row, no per-lane condition)
+              // sum in all of them, and the one whose turn it is keeps it
               sq += dpp_row_ror<8>(sq); sq += dpp_row_ror<4>(sq); sq += dpp_row_ror<2>(sq); sq += dpp_row_ror<1>(sq);
-              if (ok) sqbuf[mi * 32 + row] = sq;
+              if (trip < 8) sq0 = e15 == trip * 2 + k ? sq : sq0;
+              else sq1 = e15 == trip * 2 + k - 16 ? sq : sq1;
             }
           }
+          if (kHasInputs && trip + PD < 16) load_inputs(check_tag, trip + PD, eer, in_lo[trip % PD], in_hi[trip % PD]);
+          SV_SB;                                         // one trip at a time
+          if (trip & 1) __builtin_amdgcn_wave_barrier(); // the reads of this block are issued before the next block's writes
         }
-        if (kHasInputs && trip + PD < 16) load_inputs(check_tag, trip + PD, in_lo[trip % PD], in_hi[trip % PD]);
-      }
-      if (SQ) {                                          // 128 consecutive floats of plane (n0 / 128 + wn): two full-line stores
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_wave_barrier();
-        float* plane = a.rowsq + (int64_t)((n0 >> 7) + wn) * a.rowsq_ld + m0 + wm * 128;
-        if (!CHECK || m0 + wm * 128 + lane < M) plane[lane] = sqbuf[lane];
-        if (!CHECK || m0 + wm * 128 + 64 + lane < M) plane[64 + lane] = sqbuf[64 + lane];
+        if (SQ) {                                        // 128 consecutive floats of plane (n0 / 128 + wn): two full-line stores
+          const int r = wm * 128 + e15 * 4 + eer;
+          float* plane = a.rowsq + (int64_t)((n0 >> 7) + wn) * a.rowsq_ld + m0;
+          if (!CHECK || m0 + r < M) plane[r] = sq0;
+          if (!CHECK || m0 + 64 + r < M) plane[64 + r] = sq1;
+        }
       }
     };
-    if (m0 + 256 <= M) run_epilogue(std::false_type{});
-    else run_epilogue(std::true_type{});
+    if (full_tile) run_epilogue(No{});
+    else run_epilogue(Yes{});
+    __builtin_amdgcn_s_waitcnt(kLgkm0);                  // the patch has been read: this wave's loads may fill it
+    SV_SB;
   }
-  // A finished stream keeps re-reading its last slice into the free stage (the loop has no branch for it): every
+  // The finished streams keep reading into the free buffers (the loop has no branch for it): every
   // such load must have landed before the workgroup gives its LDS back.
   __builtin_amdgcn_s_waitcnt(0);
+#undef SV_MEET
 #undef SV_SB
 }
 
@@ -1187,7 +1243,7 @@ hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st, int tail_ma
 template <int EPI, bool GROUPED, bool NF = false>
 hipError_t launch_dma(const GemmArgs& a, hipStream_t st) {
   auto kern = gemm_mfma_dma_kernel<EPI, GROUPED, NF>;
-  constexpr int lds = 2 * 512 * 128 + 4 * 1024;           // two stages, and per wave 128 row factors + 128 row sums
+  constexpr int lds = 5 * 256 * 128;                      // three buffers of activations, two of weights
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -1196,7 +1252,7 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t st) {
   }
   const int tiles_m = (a.M + 255) / 256, tiles_n = a.N / (EPI == EPI_SWIGLU ? 128 : 256);
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
-  const int n_cu = std::max(8, cu_count() / 8 * 8);       // one persistent workgroup per CU (128 KB of LDS each)
+  const int n_cu = std::max(8, cu_count() / 8 * 8);       // one persistent workgroup per CU (all of its LDS)
   const int grid = per_xcd * 8 < n_cu ? per_xcd * 8 : n_cu;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a, tiles_m, tiles_n);
   return hipGetLastError();
