@@ -228,6 +228,7 @@ struct GemmArgs {
   // set by the launch of a product on 256 x 256 tiles whose last round of them is left to a second launch on smaller ones: that
   // round's workgroups per XCD (0: it is not)
   int tail;
+  int slices;             // set by the launch: slices of 64 in all of k
 };
 
 // kernels_plain.hip: any shape, fp32 math, E = float | bf16 by `dtype`

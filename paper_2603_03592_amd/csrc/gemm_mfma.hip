@@ -430,12 +430,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int nspl
 template <int EPI> constexpr int kEpiStores = EPI == EPI_SWIGLU ? 16 : EPI == EPI_SWIGLU_BWD ? 55 : 32;
 constexpr int meet_wait(int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14); }       // vmcnt(vm) lgkmcnt(0)
 
-// A buffer descriptor without a bound, from a base that is the same in every lane, said explicitly: kept across the loops, the
+// A buffer descriptor, without a bound or of no bytes, from a base that is the same in every lane, said explicitly: kept across the loops, the
 // compiler moves one to vector registers otherwise and walks over the lanes at every load.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t open_rsrc(const void* base) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t open_rsrc(const void* base, int bytes = -1) {
   const uint64_t v = (uint64_t)base;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, -1, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, bytes, 0x00020000);
 }
 
 struct Stream { int vb, m0, n0, seg, k, K; bool ok; };
@@ -459,8 +459,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   // kGroupM row tiles.  gridDim.x is a multiple of 8, so a workgroup stays on its XCD's run.
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = (nblk + 7) >> 3;
-  int nslices = 0;
-  for (int s = 0; s < a.nseg; ++s) nslices += a.seg[s].K / BK;
+  const int nslices = a.slices;
   const int own = a.tail ? per_xcd - tail_tiles(per_xcd, a.tail, nslices) : per_xcd;     // tiles per XCD of this launch
   auto tile_of = [&](int vb, int& m0, int& n0) -> bool {
     if (vb >= own * 8) return false;
@@ -479,7 +478,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 
   // ---- the two streams of slices across this workgroup's tiles.  State: virtual block vb (tile m0, n0), segment seg, offset k in
   // it; K is the segment's length, kept in a register (a per-slice kernel-argument load would share its wait counter with the
-  // LDS reads).  A finished stream stays on a slice it has read and keeps reading that.
+  // LDS reads).  A finished stream's loads go on (the loop has no branch for it) through a descriptor of no bytes, which costs no memory.
   Stream sa{(int)blockIdx.x, 0, 0, 0, 0, 0, false};
   sa.ok = tile_of(sa.vb, sa.m0, sa.n0);
   if (!sa.ok) return;
@@ -487,11 +486,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the streams read: base = first row, no bound
   unsigned voffA[8], voffB[8];
   // (the lane's number is opaque here: the offsets of a product of one segment would otherwise be kept twice)
-  auto set_a = [&]() {
+  auto set_a = [&](const GemmSeg& sg) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    const GemmSeg& sg = a.seg[sa.seg];
-    sa.K = sg.K;
+    sa.K = __builtin_amdgcn_readfirstlane(sg.K);
     const unsigned lda2 = (unsigned)sg.lda * 2u;             // panels_fit: a panel's offsets have 32 bits
     rA = open_rsrc((const bf16*)sg.A + (int64_t)sa.m0 * sg.lda);
 #pragma unroll
@@ -500,11 +498,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       voffA[i] = (unsigned)min(r, M - 1 - sa.m0) * lda2 + c * 16u;      // ragged row tail: re-read the last row
     }
   };
-  auto set_b = [&]() {
+  auto set_b = [&](const GemmSeg& sg) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    const GemmSeg& sg = a.seg[sb.seg];
-    sb.K = sg.K;
+    sb.K = __builtin_amdgcn_readfirstlane(sg.K);
     const unsigned ldb2 = (unsigned)sg.ldb * 2u, ldu2 = DUAL ? (unsigned)a.ldb2 * 2u : 0u;
     const int64_t goff = GROUPED ? (int64_t)a.tile_group[sb.m0 >> 8] * a.group_stride : 0;
     const bf16* B;
@@ -523,17 +520,19 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       voffB[i] = (unsigned)(DUAL ? r & 127 : r) * (DUAL && i >= 4 ? ldu2 : ldb2) + c * 16u;
     }
   };
-  auto advance = [&](Stream& s, auto&& set) {                 // to the next slice
+  auto advance = [&](Stream& s, auto&& set, auto&& close) {   // to the next slice
     if (!s.ok) return;
     s.k += BK;
     if (s.k < s.K) return;
     s.k = 0;
-    if (s.seg + 1 < a.nseg) { ++s.seg; set(); return; }
+    if (s.seg + 1 < a.nseg) { ++s.seg; set(a.seg[s.seg]); return; }
     s.seg = 0;
     s.vb += gridDim.x;
     s.ok = tile_of(s.vb, s.m0, s.n0);
-    if (s.ok) set();
+    if (s.ok) set(a.seg[0]); else close();
   };
+  auto close_a = [&]() { rA = open_rsrc(a.seg[0].A, 0); };
+  auto close_b = [&]() { rB = open_rsrc(a.seg[0].B, 0); rB2 = rB; };
   auto dma_a = [&](int buf, int i) {                          // 1 KB: the wave's i-th group of 8 rows
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i],
                                              sa.k * 2, 0, 0);
@@ -563,8 +562,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   // are read into (xn, wn_), and the eight loads of a stream's next slice are issued (into_w: weights) into buffer db.
   auto step = [&](auto first, auto into_w, auto reads, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
     const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {                            // two MFMAs, then one memory instruction
+    auto two = [&](int q) {
       const int g = q >> 2;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -572,13 +570,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
         acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[g], xc[m], decltype(first)::value ? zero : acc[g][m], 0, 0, 0);
       }
       SV_SB;
-      if (q < 24) {
-        const int r = q - q / 3;
-        if (q % 3 == 2) { if (decltype(into_w)::value) dma_b(db, q / 3); else dma_a(db, q / 3); }
-        else if (decltype(reads)::value) { if (r < 8) xn[r] = read_x(ra, s, r); else wn_[r - 8] = read_w(rw, s, r - 8); }
-        SV_SB;
-      }
+    };
+#pragma unroll
+    for (int q = 0; q < 24; ++q) {                            // two MFMAs, then one memory instruction
+      two(q);
+      const int r = q - q / 3;
+      if (q % 3 == 2) { if (decltype(into_w)::value) dma_b(db, q / 3); else dma_a(db, q / 3); }
+      else if (decltype(reads)::value) { if (r < 8) xn[r] = read_x(ra, s, r); else wn_[r - 8] = read_w(rw, s, r - 8); }
+      SV_SB;
     }
+    // between MFMAs: behind the last of them its scalar chain would idle the matrix pipe
+    if (decltype(into_w)::value) advance(sb, set_b, close_b); else advance(sa, set_a, close_a);
+    SV_SB;
+#pragma unroll
+    for (int q = 24; q < 32; ++q) two(q);
   };
   // this wave's wait, then the workgroup's barrier: slice k + 1 is complete (its youngest load is older than the last eight), and
   // everybody has read what they need of slice k
@@ -590,21 +595,21 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   bf16x8 x0[MI], w0[NI], x1[MI], w1[NI];
   int ca = 0, cw = WBUF;                                      // the buffers of the slice being multiplied
   constexpr int kOther = WBUF ^ (WBUF + BUF);
-  set_a();
-  set_b();
+  set_a(a.seg[0]);
+  set_b(a.seg[0]);
 #pragma unroll
   for (int j = 0; j < 8; ++j) dma_a(0, j);
 #pragma unroll
   for (int j = 0; j < 8; ++j) dma_b(WBUF, j);
-  advance(sa, set_a);
-  advance(sb, set_b);
+  advance(sa, set_a, close_a);
+  advance(sb, set_b, close_b);
 #pragma unroll
   for (int j = 0; j < 8; ++j) dma_a(BUF, j);
-  advance(sa, set_a);
+  advance(sa, set_a, close_a);
   SV_MEET(meet_wait(8));
 #pragma unroll
   for (int j = 0; j < 8; ++j) dma_b(cw ^ kOther, j);
-  advance(sb, set_b);
+  advance(sb, set_b, close_b);
   if (!kHasInputs) {
 #pragma unroll
     for (int b = 0; b < 8; ++b) { x0[b] = read_x(ca, 0, b); w0[b] = read_w(cw, 0, b); }
@@ -613,25 +618,23 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   int m0, n0;
   bool stored = false;                                        // this workgroup's stores may be on their way
   for (int vb = blockIdx.x; tile_of(vb, m0, n0); vb += gridDim.x) {
-    // ---- what the epilogue's global accesses need, set up here because a full tile asks for its first inputs early.
+    // ---- what the epilogue's global accesses need, set up here because the first inputs are asked for early.
     // In the read-back of the epilogue a lane serves row er of each group of 4 rows, 8 columns from 8 ec.
-    // One buffer descriptor per tensor, based at the tile's first row and the wave's first column; inside it a lane's
+    // One buffer descriptor per tensor, based at the tile's first row and the wave's first column, up to the last of the M rows: what
+    // lies past them is dropped or read as zero, and a ragged tile runs the same code as a full one.  Inside it a lane's
     // byte offset is (row * ld + column) * 2, of which the lane's part never changes and the row block's part is a scalar:
     // no 64-bit address arithmetic per access.
     constexpr int PD = kEpiAhead<EPI>;                   // trips the epilogue's global reads run ahead of its stores
     const int er = lhi, ec8 = l15;
     const int ncol0 = n0 + wn * (DUAL ? 64 : 128);
+    const int rows = min(M - m0, BM);
     auto desc = [&](const void* base, int ld) {
-      return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16*)base + (int64_t)m0 * ld + ncol0), (short)0, -1, 0x00020000);
+      return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16*)base + (int64_t)m0 * ld + ncol0), (short)0, (rows * ld - ncol0) * 2, 0x00020000);
     };
     const __amdgpu_buffer_rsrc_t bC = desc(a.C, a.ldc), bC2 = desc(a.C2, a.ldc), bC3 = desc(a.C3, a.ldc);
     const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr), bR2 = desc(a.R2, a.ldr);
-    // offsets of rows rb + row of the wave's 128, `bytes` into a row: per lane (vo) and scalar (so).  A ragged tile
-    // re-reads its last row for the rows past the end, which takes the row into the lane's part.
-    auto place = [&](auto check_tag, int rb, int row, int ld, int bytes, int& vo, int& so) {
-      if (decltype(check_tag)::value) { vo = min(wm * 128 + rb + row, M - 1 - m0) * ld * 2 + bytes; so = 0; }
-      else { vo = (wm * 128 + row) * ld * 2 + bytes; so = rb * ld * 2; }
-    };
+    // byte offset of row `row` of a group of the wave's 128 rows, `bytes` into it: the lane's part; the group's first row is the scalar part
+    auto place = [&](int row, int ld, int bytes) { return (wm * 128 + row) * ld * 2 + bytes; };
     int rope_p0 = 0, rope_v = 0;                         // first row's position; byte offset of the lane's feature pairs in a table row
     if (EPI == EPI_ROPE) {
       rope_p0 = (m0 + wm * 128) % a.rope_S;
@@ -644,7 +647,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       hi = __builtin_shufflevector(v, v, 4, 5, 6, 7);
     };
     // the inputs of trip `trip` (rows 8 trip .. 8 trip + 7 of the wave's 128, two per lane): residual, gate / up, RoPE table
-    auto load_inputs = [&](auto check_tag, int trip, int er, EpiIn (&lo)[2], EpiIn (&hi)[2]) {
+    auto load_inputs = [&](int trip, int er, EpiIn (&lo)[2], EpiIn (&hi)[2]) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int rb = trip * 8 + k * 4;
@@ -657,21 +660,13 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
           lo[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo, 0, 0));
           hi[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo + 16, 0, 0));
         } else if (kHasInputs) {
-          int vo, so;
-          place(check_tag, rb, er, a.ldr, ec8 * 16, vo, so);
+          const int vo = place(er, a.ldr, ec8 * 16), so = rb * a.ldr * 2;
           ld16(bR, vo, so, lo[k].r, hi[k].r);
           if (EPI == EPI_SWIGLU_BWD) ld16(bR2, vo, so, lo[k].r2, hi[k].r2);
         }
       }
     };
     EpiIn in_lo[PD][2], in_hi[PD][2];                    // [trip mod PD][row of the pair]
-    const bool full_tile = m0 + 256 <= M;
-    auto first_inputs = [&]() {                          // of a full tile, before its last step
-      if (kHasInputs && full_tile) {
-#pragma unroll
-        for (int t = 0; t < PD; ++t) load_inputs(No{}, t, er, in_lo[t], in_hi[t]);
-      }
-    };
     // the row factors of the wave's 128 rows, lane l those of rows l and 64 + l, are asked for here, a k loop before the epilogue wants them
     float rs_pre0 = 1.0f, rs_pre1 = 1.0f;
     if (RS) {
@@ -687,28 +682,26 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
     step(Yes{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
-    advance(sa, set_a);
     ca = behind(ca); cw ^= kOther;
     for (int kt = 1; kt < nslices; ++kt) {
       // the tile's second slice was asked for before the last tile's results were stored: those may still be on their way
       if (kt == 1 && stored) SV_MEET(meet_wait(8 + kEpiStores<EPI>));
       else SV_MEET(meet_wait(8));
       step(No{}, Yes{}, Yes{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
-      advance(sb, set_b);
       __builtin_amdgcn_s_waitcnt(kLgkm0);
       SV_SB;
       step(No{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
-      advance(sa, set_a);
       ca = behind(ca); cw ^= kOther;
     }
     SV_SB;
-    first_inputs();                                      // their round trip hides behind the last step's products
-    if (kHasInputs && full_tile) SV_MEET(meet_wait(8 + PD * (EPI == EPI_SWIGLU_BWD || EPI == EPI_ROPE ? 4 : 2)));
-    else SV_MEET(meet_wait(8));
+    if (kHasInputs) {                                    // the epilogue's first inputs: their round trip hides behind the last step's products
+#pragma unroll
+      for (int t = 0; t < PD; ++t) load_inputs(t, er, in_lo[t], in_hi[t]);
+    }
+    SV_MEET(meet_wait(8 + (kHasInputs ? PD * (EPI == EPI_SWIGLU_BWD || EPI == EPI_ROPE ? 4 : 2) : 0)));
     step(No{}, Yes{}, std::integral_constant<bool, !kHasInputs>{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
-    advance(sb, set_b);
     SV_SB;
-    stored = full_tile;
+    stored = true;
 
     // ---- epilogue through LDS (the next tile's first slices are landing meanwhile).
     // In the accumulator layout a lane owns one token row and groups of 4 features, so a store instruction would touch 16 rows
@@ -719,25 +712,20 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     // The patch is what this wave's own loads will fill next, 1 KB pieces 4 KB apart, so that no barrier
     // stands between the waves' epilogues and the loads behind them.
     char* patch = smem + behind(behind(ca)) + wave * 1024;
-    auto run_epilogue = [&](auto check_tag) {
-      constexpr bool CHECK = decltype(check_tag)::value;
+    {
       // The lane's row and chunk numbers are made opaque once per tile: otherwise every address below is loop invariant, gets
       // hoisted out of the tile loop and crowds the fragments and the epilogue's inputs out of the registers.
       int e15 = l15, eer = er;
       asm volatile("" : "+v"(e15), "+v"(eer));
       // The accumulators stay in the accumulation registers until their row block's turn: seen through, the compiler copies whole
-      // blocks of them ahead, for both forms of this epilogue at once, and spills.
+      // blocks of them ahead and spills.
       auto take = [&](int ni, int mi) {
         f32x4 v = acc[ni][mi];
         asm volatile("" : "+a"(v));
         return v;
       };
-      // (Around divergent branches the compiler's wait insertion falls back to waiting for (nearly) everything in flight, one
-      // memory round trip per store: tiles that lie inside the M rows run without any per-lane condition, CHECK = false.)
       auto put16 = [&](__amdgpu_buffer_rsrc_t b, bf16x8 v, int rb, int row, int bytes) {
-        int vo, so;
-        place(check_tag, rb, row, a.ldc, bytes, vo, so);
-        if (!CHECK || wm * 128 + rb + row < M - m0) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, vo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, place(row, a.ldc, bytes), rb * a.ldc * 2, 0);
       };
       if constexpr (DUAL) {
         // Gate and up of one feature sit in the same lane and register index, so SiLU(g) * u is taken in the accumulator layout
@@ -803,10 +791,6 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
         // reads (residual, gate / up, RoPE table) run kEpiAhead trips ahead of its stores; the first of them were asked for before
         // the last step.  (The memory counter retires in order: a read is waited for together with every store issued
         // before it, so the reads of a trip are issued before the stores they must not wait for have piled up.)
-        if (kHasInputs && CHECK) {                       // a ragged tile asks for its first inputs here, a full one did so before its last step
-#pragma unroll
-          for (int t = 0; t < PD; ++t) load_inputs(check_tag, t, eer, in_lo[t], in_hi[t]);
-        }
         auto prow = [](int row) { return (row >> 1) * 4096 + (row & 1) * 512; };
         float sq0 = 0.0f, sq1 = 0.0f;                    // SQ: the sums of rows 4 l15 + lhi and 64 + 4 l15 + lhi
 #pragma unroll
@@ -845,53 +829,49 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
               else sq1 = e15 == trip * 2 + k - 16 ? sq : sq1;
             }
           }
-          if (kHasInputs && trip + PD < 16) load_inputs(check_tag, trip + PD, eer, in_lo[trip % PD], in_hi[trip % PD]);
+          if (kHasInputs && trip + PD < 16) load_inputs(trip + PD, eer, in_lo[trip % PD], in_hi[trip % PD]);
           SV_SB;                                         // one trip at a time
           if (trip & 1) __builtin_amdgcn_wave_barrier(); // the reads of this block are issued before the next block's writes
         }
         if (SQ) {                                        // 128 consecutive floats of plane (n0 / 128 + wn): two full-line stores
           const int r = wm * 128 + e15 * 4 + eer;
-          float* plane = a.rowsq + (int64_t)((n0 >> 7) + wn) * a.rowsq_ld + m0;
-          if (!CHECK || m0 + r < M) plane[r] = sq0;
-          if (!CHECK || m0 + 64 + r < M) plane[64 + r] = sq1;
+          const __amdgpu_buffer_rsrc_t bQ = __builtin_amdgcn_make_buffer_rsrc((void*)(a.rowsq + (int64_t)((n0 >> 7) + wn) * a.rowsq_ld + m0), (short)0, rows * 4, 0x00020000);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq0), bQ, r * 4, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq1), bQ, r * 4, 256, 0);
         }
       }
-    };
-    if (full_tile) run_epilogue(No{});
-    else run_epilogue(Yes{});
+    }
     __builtin_amdgcn_s_waitcnt(kLgkm0);                  // the patch has been read: this wave's loads may fill it
     SV_SB;
   }
-  // The finished streams keep reading into the free buffers (the loop has no branch for it): every
-  // such load must have landed before the workgroup gives its LDS back.
+  // The finished streams' loads write zeros into the free buffers: every one must have done so before the workgroup gives its LDS back.
   __builtin_amdgcn_s_waitcnt(0);
 #undef SV_MEET
 #undef SV_SB
 }
 
 // ------------------------------------------------------------------------------------------
-// Direct-to-LDS kernel on smaller tiles: (WM * 32 * MI) x (WN * 32 * NI) outputs per workgroup of WM x WN waves, NST LDS
-// stages of one 64-deep slice each.  It serves what the 256x256 kernel cannot fill the chip with (fewer than about one
-// tile per CU) and widths that are no multiple of 256: any multiple of 8 columns -- weight rows past the end re-read the
-// last group of 8, outputs past the end (rows and columns) are dropped by the bounds check of the buffer stores.
+// Direct-to-LDS kernel on smaller tiles: (32 MI) x (32 NI) outputs per workgroup of 2 x 2 waves.  It serves what the 256x256 kernel
+// cannot fill the chip with (fewer than about one tile per CU) and widths that are no multiple of 256: any multiple of 8
+// columns -- weight rows past the end re-read the last group of 8, outputs past the end (rows and columns) are dropped by the bounds
+// check of the buffer stores.
 //
-// What bounds it: LDS.  A 128x128 tile moves 32 KB into LDS (64 B/clk) and 64 KB out of it (about 200 B/clk) per slice
-// of 512 matrix cycles, so a CU is busy with LDS about 1.5 x as long as with MFMAs; the 256x256 tile (0.75 x) stays the
-// better one wherever it fills the chip.  NST: the loads of slice k + NST - 1 are issued when slice k is multiplied.  As many
-// stages as a CU's 160 KB hold for one workgroup (256x128: 3, 128x128: 4, 64x64: 8), since a CU has about one tile where these
-// serve; 64x128 takes 3, and its 72 KB let two workgroups share a CU.  (128x128 with two stages and two workgroups on a CU,
-// each under the other's wait for memory, measured slower than one with four.)
-//
-// The one wait + barrier per slice stands before the last of its four 16-wide k steps, whose fragments are in registers
-// by then: behind it the first fragments of the next slice are asked for, and the step's MFMAs hide their latency.
-template <int WM, int WN, int MI, int NI, int NST, bool DUAL>
+// What bounds it: the operands' way into LDS, 64 bytes a clock and CU, and out of it.  A 128x128 tile moves 32 KB in and 64 KB out per
+// slice of 512 matrix cycles; the 256x256 tile (half of both per multiply-add) stays the better one wherever it fills the chip.  RA
+// and RB: buffers of activations and of weights, as many as one workgroup's 160 KB or two workgroups' 80 KB hold.  The k loop is
+// the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the next step and the loads of a later slice
+// spread over the first three quarters of a step's MFMAs, activations in the one step and weights in the other, one wait and barrier a
+// slice that leaves the youngest loads in flight.  Against eight waves with their loads and reads in groups around the MFMAs of
+// a 16-wide step, us: 1024^3 on 64x64 7.1 -> 6.2; 512 x 4096, K = 4096 on 64x128 24.3 -> 20.5; 4096 x 1024, K = 2816 on 128x128 25.6 -> 23.4;
+// 6144 x 1024, K = 4096 on 256x128 54.3 -> 47.2.
+template <int MI, int NI, int RA, int RB, bool DUAL>
 struct MidCfg {
-  static constexpr int NW = WM * WN, NT = 64 * NW, BM = WM * 32 * MI, BN = WN * 32 * NI, NOUT = DUAL ? BN / 2 : BN;
-  static constexpr int STAGE = (BM + BN) * 128, LDS = NST * STAGE;
-  static constexpr int NA = BM / 8 / NW, NB = BN / 8 / NW, ND = NA + NB;      // 1 KB loads per wave and slice
-  static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && (!DUAL || NI % 2 == 0), "tile shape");
-  static_assert(NW * 32 * NI * 32 * 4 <= LDS, "the epilogue's patches fit the stages");
-  static_assert(ND * (NST - 2) < 64, "the wait count has 6 bits");
+  static constexpr int BM = 32 * MI, BN = 32 * NI, NOUT = DUAL ? BN / 2 : BN;
+  static constexpr int ABUF = BM * 128, WBUF = BN * 128, LDS = RA * ABUF + RB * WBUF;
+  static constexpr int OCC = 2 * LDS <= 160 * 1024 ? 2 : 1;                     // workgroups on a CU
+  // the loads that are younger than slice k + 1's activations and weights when slice k has been read
+  static constexpr int YA = (RA - 2) * (MI + NI), YB = (RB - 1) * MI + (RB - 2) * NI, LEFT = YA < YB ? YA : YB;
+  static_assert(LDS <= 160 * 1024 && RA >= RB && RB >= 2 && LEFT < 64 && (!DUAL || NI % 4 == 0), "tile shape");
 };
 
 //
@@ -899,14 +879,14 @@ struct MidCfg {
 // a.split_ws[run][M][N] and splitk_reduce_kernel adds the runs in order.  SUMMED: the same sum of runs (GemmArgs::runs) in one
 // workgroup, the running total beside the accumulators: bit for bit what the partial products and their reduction give.
 // TAIL: the last round of a product on 256x256 tiles (GemmArgs::tail).
-template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT, bool SUMMED, bool TAIL>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, int tiles_m, int tiles_n, int nsplit) {
+template <int MI, int NI, int RA, int RB, int EPI, bool GROUPED, bool SPLIT, bool SUMMED, bool TAIL>
+__global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OCC)) void gemm_mid_kernel(GemmArgs a, int tiles_m, int tiles_n, int nsplit) {
   constexpr bool DUAL = EPI == EPI_SWIGLU;
   static_assert(!SPLIT || (EPI == EPI_STORE && !GROUPED), "a split run stores bare partial products");
   static_assert(!SUMMED || (!DUAL && !GROUPED && !SPLIT), "one sum of runs per output");
-  using C = MidCfg<WM, WN, MI, NI, NST, DUAL>;
-  constexpr int BM = C::BM, BN = C::BN, STAGE = C::STAGE, NW = C::NW, NA = C::NA, NB = C::NB;
-  constexpr int kGroup = 1024 / BM;                       // row tiles per raster group: 1024 rows, as on the large tile
+  using C = MidCfg<MI, NI, RA, RB, DUAL>;
+  constexpr int BM = C::BM, BN = C::BN, ABUF = C::ABUF, WBUF = C::WBUF, W0 = RA * ABUF;     // weights' buffers from W0
+  constexpr int kGroup = BM >= 256 ? 4 : BM >= 128 ? 8 : 16;          // row tiles per raster group: about 1024 rows
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int M = GROUPED ? *a.m_dev : a.M;
@@ -914,13 +894,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
   // tile assignment as in the 256x256 kernel: ids congruent mod 8 (one XCD) walk a contiguous run of tiles.  As that kernel's last
   // round: its map and its tiles, each in SUB pieces next to each other.
   constexpr int SUBN = 256 / BN, SUB = 256 / BM * SUBN;
-  static_assert(!TAIL || (!SPLIT && !SUMMED), "a tail's tiles are whole");
+  static_assert(!TAIL || (!SPLIT && !SUMMED && 256 % BM == 0), "a tail's tiles are whole");
   int group = kGroup, skip = 0, sub = 0, slot = blockIdx.x >> 3;
   if (TAIL) {
-    int slices = 0;
-    for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
     tiles_m = (M + 255) / 256; tiles_n = a.N / (DUAL ? 128 : 256);
-    const int all = (tiles_m * tiles_n + 7) >> 3, rem = tail_tiles(all, a.tail, slices);
+    const int all = (tiles_m * tiles_n + 7) >> 3, rem = tail_tiles(all, a.tail, a.slices);
     sub = slot % SUB; slot /= SUB;
     if (slot >= rem) return;
     skip = all - rem;
@@ -939,38 +917,36 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
   const int n0 = ((pid % in_group) / gsz) * (TAIL ? SUBN * C::NOUT : C::NOUT) + sub % SUBN * C::NOUT;
   if (TAIL && m0 >= M) return;
 
-  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lhi = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % WM, wn = wave / WM;
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lhi = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
 
-  // ---- the stream of slices: segment dseg, offset dk
-  int dseg = 0, dk = 0, d_K = 0, left;
-  int nsl = 0;
-  for (int s = 0; s < a.nseg; ++s) nsl += a.seg[s].K / BK;
-  left = nsl;
+  // ---- the two streams of slices: segment seg, offset k in it, `left` slices to go; past the last one a stream's loads go through a
+  // descriptor of no bytes (read again, the last slices were up to half of a short product's traffic)
+  int nsl = a.slices, seg0 = 0, k0 = 0;
   if (SPLIT) {                                            // run r takes the slices [r * nsl / nsplit, (r + 1) * nsl / nsplit)
     const int ks = (int)((int64_t)run * nsl / nsplit);
     nsl = (int)((int64_t)(run + 1) * nsl / nsplit) - ks;
-    left = nsl;
-    int k = ks * BK;
-    while (k >= a.seg[dseg].K) { k -= a.seg[dseg].K; ++dseg; }
-    dk = k;
+    k0 = ks * BK;
+    while (k0 >= a.seg[seg0].K) { k0 -= a.seg[seg0].K; ++seg0; }
   }
-  const bf16* pA;
-  const bf16* pB[NB];                                     // first row of the panel; of each group of 8 weight rows
-  unsigned voffA[NA], voffB[NB];
-  auto set_segment = [&]() {
-    const GemmSeg& sg = a.seg[dseg];
-    d_K = sg.K;
+  int a_seg = seg0, a_k = k0, a_K = 0, a_left = nsl, w_seg = seg0, w_k = k0, w_K = 0, w_left = nsl, a_bytes = -1, w_bytes = -1;
+  const bf16 *pA, *pB[NI];                                // first row of the panel; of each group of 8 weight rows
+  unsigned voffA[MI], voffB[NI];
+  auto set_a = [&](const GemmSeg& sg) {
+    a_K = __builtin_amdgcn_readfirstlane(sg.K);
     pA = (const bf16*)sg.A + (int64_t)m0 * sg.lda;
-    const int64_t goff = GROUPED ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int r = (wave + NW * i) * 8 + (lane >> 3), c = (lane & 7) ^ swz(r);
+    for (int i = 0; i < MI; ++i) {
+      const int r = (wave + 4 * i) * 8 + (lane >> 3), c = (lane & 7) ^ swz16(r);
       voffA[i] = (unsigned)((int64_t)min(r, M - 1 - m0) * sg.lda + c * 8) * 2u;
     }
+  };
+  auto set_b = [&](const GemmSeg& sg) {
+    w_K = __builtin_amdgcn_readfirstlane(sg.K);
+    const int64_t goff = GROUPED ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int g = (wave + NW * i) * 8, r = g + (lane >> 3), c = (lane & 7) ^ swz(r);
+    for (int i = 0; i < NI; ++i) {
+      const int g = (wave + 4 * i) * 8, r = g + (lane >> 3), c = (lane & 7) ^ swz16(r);
       const bf16* B = (const bf16*)sg.B + goff;
       int64_t ldb = sg.ldb;
       int row;                                            // the group's first weight row
@@ -991,26 +967,40 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
       voffB[i] = (unsigned)((int64_t)(lane >> 3) * ldb + c * 8) * 2u;
     }
   };
-  auto dma = [&](int stage, int j) {                      // j: the wave's NA activation groups, then its NB weight groups
-    const int i = j < NA ? j : j - NA;
-    char* dst = smem + stage * STAGE + (j < NA ? 0 : BM * 128) + (wave + NW * i) * 1024;
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(j < NA ? pA : pB[j < NA ? 0 : i]), (short)0, -1, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16,
-                                             (int)(j < NA ? voffA[j < NA ? i : 0] : voffB[j < NA ? 0 : i]), dk * 2, 0, 0);
+  auto dma_a = [&](int buf, int i) {                      // 1 KB: the wave's i-th group of 8 rows
+    const __amdgpu_buffer_rsrc_t r = open_rsrc(pA, a_bytes);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i],
+                                             a_k * 2, 0, 0);
   };
-  auto advance = [&]() {                                  // to the next slice; past the last one the stream re-reads it
-    if (--left <= 0) return;
-    dk += BK;
-    if (dk < d_K) return;
-    dk = 0; ++dseg; set_segment();
+  auto dma_b = [&](int buf, int i) {
+    const __amdgpu_buffer_rsrc_t r = open_rsrc(pB[i], w_bytes);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffB[i],
+                                             w_k * 2, 0, 0);
   };
+  auto advance_a = [&]() {
+    if (--a_left <= 0) { a_bytes = 0; return; }
+    a_k += BK;
+    if (a_k < a_K) return;
+    a_k = 0; ++a_seg; set_a(a.seg[a_seg]);
+  };
+  auto advance_b = [&]() {
+    if (--w_left <= 0) { w_bytes = 0; return; }
+    w_k += BK;
+    if (w_k < w_K) return;
+    w_k = 0; ++w_seg; set_b(a.seg[w_seg]);
+  };
+  auto next_a = [](int b) { return b == (RA - 1) * ABUF ? 0 : b + ABUF; };
+  auto next_w = [](int b) { return b == W0 + (RB - 1) * WBUF ? W0 : b + WBUF; };
+  auto last_a = [](int b) { return b == 0 ? (RA - 1) * ABUF : b - ABUF; };
+  auto last_w = [](int b) { return b == W0 ? W0 + (RB - 1) * WBUF : b - WBUF; };
 
-  // ---- the epilogue's places.  Each wave turns its accumulators over 32 rows at a time through an LDS patch of its own and
-  // reads them back so that LPR consecutive lanes hold one row's outputs (4 per lane), RPI rows per instruction.
+  // ---- the epilogue's places.  Each wave turns its accumulators over 16 rows at a time through an LDS patch of its own and
+  // reads them back so that LPR consecutive lanes hold one row's outputs (8 per lane), RPI rows per instruction.
   constexpr bool kHasInputs = EPI == EPI_RESID || EPI == EPI_SWIGLU_BWD || EPI == EPI_GELU_BWD || EPI == EPI_ROPE;
-  constexpr int LPR = DUAL ? NI * 4 : NI * 8, RPI = 64 / LPR, TR = 32 / RPI;
+  constexpr int LPR = DUAL ? NI : 2 * NI, RPI = 64 / LPR, TR = 16 / RPI;
+  static_assert(RPI <= 16, "a pass is no more than a row block");
   const int er = lane / LPR, ec = lane % LPR;
-  const int mw = wm * 32 * MI, n = n0 + wn * (DUAL ? NI * 16 : NI * 32) + ec * 4;    // the lane's first row (+ er) and columns n .. n + 3
+  const int mw = wm * 16 * MI, n = n0 + wn * (DUAL ? NI * 8 : NI * 16) + ec * 8;     // the lane's first row (+ er) and columns n .. n + 7
   const int rows = min(M - m0, BM);
   // rows past M lie past the descriptor's end, columns past N are sent there
   auto desc = [&](const void* base, int64_t ld, int es) {
@@ -1018,24 +1008,31 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
   };
   const unsigned vcol = n < a.N ? (unsigned)n : SPLIT ? 0x20000000u : 0x40000000u;     // byte offset 2^31: past every descriptor's end
   const bool rscaled = kEpiScaled<EPI> && !GROUPED && !SPLIT && a.rscale;
-  EpiIn in[2][TR];
+  EpiIn in_lo[2][TR], in_hi[2][TR];
   float rs[2][TR];
   int rope_p0 = 0, rope_i0 = 0;
   if (EPI == EPI_ROPE) { rope_p0 = (m0 + mw) % a.rope_S; rope_i0 = (n % a.rope_hd) >> 1; }
-  auto load_inputs = [&](int mi, EpiIn (&e)[TR], float (&f)[TR]) {
+  auto ld16 = [&](__amdgpu_buffer_rsrc_t b, unsigned vo, bf16x4& lo, bf16x4& hi) {
+    const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, (int)vo, 0, 0));
+    lo = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+    hi = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+  };
+  auto load_inputs = [&](int mi, EpiIn (&lo)[TR], EpiIn (&hi)[TR], float (&f)[TR]) {
     if (kHasInputs) {
       const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr, 2), bR2 = desc(a.R2, a.ldr, 2);
 #pragma unroll
       for (int t = 0; t < TR; ++t) {
-        const int r = mw + mi * 32 + t * RPI + er;
+        const int r = mw + mi * 16 + t * RPI + er;
         if (EPI == EPI_ROPE) {
-          int p = rope_p0 + mi * 32 + t * RPI + er;
+          int p = rope_p0 + mi * 16 + t * RPI + er;
           if (a.rope_S >= BM) p -= p >= a.rope_S ? a.rope_S : 0; else p %= a.rope_S;
-          e[t].cs = *reinterpret_cast<const f32x4*>(a.rope_cs + ((int64_t)p * (a.rope_hd >> 1) + rope_i0) * 2);
+          const float* cs = a.rope_cs + ((int64_t)p * (a.rope_hd >> 1) + rope_i0) * 2;
+          lo[t].cs = *reinterpret_cast<const f32x4*>(cs);
+          hi[t].cs = *reinterpret_cast<const f32x4*>(cs + 4);
         } else {
           const unsigned vo = ((unsigned)(r * (int)a.ldr) + vcol) * 2u;
-          e[t].r = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(bR, (int)vo, 0, 0));
-          if (EPI == EPI_SWIGLU_BWD) e[t].r2 = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(bR2, (int)vo, 0, 0));
+          ld16(bR, vo, lo[t].r, hi[t].r);
+          if (EPI == EPI_SWIGLU_BWD) ld16(bR2, vo, lo[t].r2, hi[t].r2);
         }
       }
     }
@@ -1044,62 +1041,74 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
       for (int t = 0; t < TR; ++t) f[t] = 1.0f;
       if (rscaled) {
 #pragma unroll
-        for (int t = 0; t < TR; ++t) f[t] = a.rscale[min(m0 + mw + mi * 32 + t * RPI + er, M - 1)];
+        for (int t = 0; t < TR; ++t) f[t] = a.rscale[min(m0 + mw + mi * 16 + t * RPI + er, M - 1)];
       }
     }
   };
 
-  f32x16 acc[NI][MI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < MI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  f32x4 acc[NI][MI];
 
-  // ---- fragment addresses: row 32 b + (lane & 31) of a tile, chunk 2 kk + lhi.  The swizzle sees a 32-row block only by
-  // its parity, which turns chunk 2 kk into 2 (kk ^ 2): one base per k step and operand, block offsets are immediates.
-  const int bx = wm * MI, bw = wn * (DUAL ? NI / 2 : NI);
-  unsigned offX[4], offW[4];
+  // ---- fragment addresses: rows 16 b + (lane & 15) of an operand, chunk 4 s + (lane >> 4); swz16 does not see b
+  unsigned offX[2], offW[2];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    offX[kk] = (unsigned)(bx * 4096 + lds_off(l31, (kk * 2 + lhi) ^ ((bx & 1) << 2)));
-    offW[kk] = (unsigned)(BM * 128 + bw * 4096 + lds_off(l31, (kk * 2 + lhi) ^ ((bw & 1) << 2)));
+  for (int s = 0; s < 2; ++s) {
+    const int chunk = ((s * 4 + lhi) ^ swz16(l15)) << 4;
+    offX[s] = (unsigned)((wm * 16 * MI + l15) * 128 + chunk);
+    offW[s] = (unsigned)((wn * (DUAL ? 8 : 16) * NI + l15) * 128 + chunk);
   }
-  constexpr int kUp = DUAL ? BN / 64 - NI / 2 : 0;         // from the block after the last gate block to the first up block
-  auto read = [&](const char* base, int kk, bf16x8 (&x)[MI], bf16x8 (&w)[NI]) {
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int b = DUAL && ni >= NI / 2 ? ni + kUp : ni;
-      w[ni] = *reinterpret_cast<const bf16x8*>(base + offW[kk ^ ((b & 1) << 1)] + b * 4096);
-    }
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) x[mi] = *reinterpret_cast<const bf16x8*>(base + offX[kk ^ ((mi & 1) << 1)] + mi * 4096);
-  };
+  constexpr int kUp = DUAL ? BN / 32 - NI / 2 : 0;         // from the block after the last gate block to the first up block
+  auto read_x = [&](int buf, int s, int b) { return *reinterpret_cast<const bf16x8*>(smem + buf + offX[s] + b * 2048); };
+  auto read_w = [&](int buf, int s, int b) { return *reinterpret_cast<const bf16x8*>(smem + buf + offW[s] + (DUAL && b >= NI / 2 ? b + kUp : b) * 2048); };
 #define SV_SB __builtin_amdgcn_sched_barrier(0)
-  constexpr int kLgkm0 = 0xc07f;                           // lgkmcnt(0), nothing else
-  constexpr int kLandedCnt = C::ND * (NST - 2);            // loads that may still be in flight when the next slice has landed
-  constexpr int kLanded = 0x0070 | (kLandedCnt & 15) | ((kLandedCnt >> 4) << 14);      // vmcnt(kLandedCnt) lgkmcnt(0)
-  // this wave's wait, then the workgroup's barrier
 #define SV_MEET(imm) do { SV_SB; __builtin_amdgcn_s_waitcnt(imm); asm volatile("s_barrier" ::: "memory"); SV_SB; } while (0)
-  auto mul = [&](bf16x8 (&x)[MI], bf16x8 (&w)[NI]) {
+  constexpr int kLgkm0 = 0xc07f;                           // lgkmcnt(0), nothing else
+  auto step = [&](auto first, auto into_w, auto last, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
+    constexpr bool W = decltype(into_w)::value;
+    constexpr int ND = W ? NI : MI, NMEM = MI + NI + ND, NM = MI * NI, SPAN = NM * 3 / 4;
+    const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
+    auto mul = [&](int f) {
+      const int g = f / MI, j = f % MI, m = g & 1 ? MI - 1 - j : j;       // back and forth, so that neighbours share an operand
+      acc[g][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[g], xc[m], decltype(first)::value ? zero : acc[g][m], 0, 0, 0);
+    };
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int f = 0; f < SPAN; ++f) {
+      mul(f);
+      // the memory instructions [lo, hi) stand behind this MFMA
+      const int lo = (f * NMEM + SPAN - 1) / SPAN, hi = f + 1 == SPAN ? NMEM : ((f + 1) * NMEM + SPAN - 1) / SPAN;
+      if (hi > lo) SV_SB;
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ni], x[mi], acc[ni][mi], 0, 0, 0);
+      for (int i = 0; i < 4; ++i) {
+        const int q = lo + i, d = q * ND / NMEM, r = q - d;
+        if (q >= hi || decltype(last)::value) continue;
+        if ((q + 1) * ND / NMEM > d) { if (W) dma_b(db, d); else dma_a(db, d); }
+        else if (r < MI) xn[r] = read_x(ra, s, r);
+        else wn_[r - MI] = read_w(rw, s, r - MI);
+        SV_SB;
+      }
+    }
+    if (!decltype(last)::value) { if (W) advance_b(); else advance_a(); }  // between MFMAs, as there
+    SV_SB;
+#pragma unroll
+    for (int f = SPAN; f < NM; ++f) mul(f);
   };
 
-  if (!SPLIT) load_inputs(0, in[0], rs[0]);                // older than every slice: in order, so landed when the first has
+  if (!SPLIT) load_inputs(0, in_lo[0], in_hi[0], rs[0]);   // older than every slice: in order, so landed when the first has
   SV_SB;
-  set_segment();
+  set_a(a.seg[SPLIT ? seg0 : 0]);
+  set_b(a.seg[SPLIT ? seg0 : 0]);
 #pragma unroll
-  for (int s = 0; s + 1 < NST; ++s) {
+  for (int s = 0; s + 1 < RA; ++s) {
 #pragma unroll
-    for (int j = 0; j < C::ND; ++j) dma(s, j);
-    advance();
+    for (int j = 0; j < MI; ++j) dma_a(s * ABUF, j);
+    advance_a();
+    if (s + 1 < RB) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) dma_b(W0 + s * WBUF, j);
+      advance_b();
+    }
   }
   bf16x8 x0[MI], w0[NI], x1[MI], w1[NI];
-  f32x16 tot[SUMMED ? NI : 1][SUMMED ? MI : 1];
+  f32x4 tot[SUMMED ? NI : 1][SUMMED ? MI : 1];
   int run_end = nsl, runs = 1, run_i = 0;                  // SUMMED: the run being summed ends before slice run_end
   if (SUMMED) {
     int j = 0, c = n0;
@@ -1107,127 +1116,118 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_mid_kernel(GemmArgs a, i
     runs = a.runs[j];
     run_end = nsl / runs;
   }
-  SV_MEET(kLanded);
-  read(smem, 0, x0, w0);
-  int st = 0;
-  for (int kt = 0; kt < nsl; ++kt) {
-    const char* base = smem + st * STAGE;
-    const int fill = st == 0 ? NST - 1 : st - 1;           // the stage slice kt - 1 has left
-    st = st + 1 == NST ? 0 : st + 1;
+  int ca = 0, cw = W0;                                     // the buffers of the slice being multiplied
+  SV_MEET(meet_wait(C::LEFT));
+#pragma unroll
+  for (int j = 0; j < NI; ++j) dma_b(last_w(cw), j);
+  advance_b();
+#pragma unroll
+  for (int b = 0; b < MI; ++b) x0[b] = read_x(ca, 0, b);
+#pragma unroll
+  for (int b = 0; b < NI; ++b) w0[b] = read_w(cw, 0, b);
+  // SUMMED: the accumulators go to the total and begin again
+  auto end_run = [&](auto summed) {
+    if constexpr (decltype(summed)::value) {
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            tot[ni][mi][r] = run_i == 0 ? acc[ni][mi][r] : tot[ni][mi][r] + acc[ni][mi][r];
+            acc[ni][mi][r] = 0.0f;
+          }
+      ++run_i;
+      run_end = (int)((int64_t)(run_i + 1) * nsl / runs);
+    }
+  };
+  __builtin_amdgcn_s_waitcnt(kLgkm0);
+  SV_SB;
+  step(std::true_type{}, std::false_type{}, std::false_type{}, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+  ca = next_a(ca); cw = next_w(cw);
+  for (int kt = 1; kt < nsl; ++kt) {
+    SV_MEET(meet_wait(C::LEFT));                           // everybody's loads of slice kt have landed, their reads of slice kt - 1 are done
+    step(std::false_type{}, std::true_type{}, std::false_type{}, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+    if (SUMMED && kt == run_end) end_run(std::integral_constant<bool, SUMMED>{});
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
-    read(base, 1, x1, w1);
-    SV_SB;
-#pragma unroll
-    for (int j = 0; j < C::ND; ++j) {                      // the next loads, one behind each MFMA
-      if (j < MI * NI) acc[j / MI][j % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[j / MI], x0[j % MI], acc[j / MI][j % MI], 0, 0, 0);
-      SV_SB;
-      dma(fill, j);
-      SV_SB;
-      if (j + 1 == MI * NI) {
-        __builtin_amdgcn_s_waitcnt(kLgkm0);
-        SV_SB;
-        read(base, 2, x0, w0);
-        SV_SB;
-      }
-      if (j >= MI * NI && j < 2 * MI * NI) {
-        const int i = j - MI * NI;
-        acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[i / MI], x1[i % MI], acc[i / MI][i % MI], 0, 0, 0);
-        SV_SB;
-      }
-    }
-#pragma unroll
-    for (int i = C::ND; i < MI * NI; ++i) acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0[i / MI], x0[i % MI], acc[i / MI][i % MI], 0, 0, 0);
-    if (C::ND < MI * NI) {
-      __builtin_amdgcn_s_waitcnt(kLgkm0);
-      SV_SB;
-      read(base, 2, x0, w0);
-      SV_SB;
-    }
-#pragma unroll
-    for (int i = C::ND > MI * NI ? C::ND - MI * NI : 0; i < MI * NI; ++i)
-      acc[i / MI][i % MI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1[i / MI], x1[i % MI], acc[i / MI][i % MI], 0, 0, 0);
-    advance();
-    __builtin_amdgcn_s_waitcnt(kLgkm0);
-    SV_SB;
-    read(base, 3, x1, w1);
-    SV_SB;
-    mul(x0, w0);
-    SV_SB;
-    SV_MEET(kLanded);                                         // everybody's loads of slice kt + 1 have landed, their reads of slice kt are done
-    read(smem + st * STAGE, 0, x0, w0);                    // past the last slice: a stage nobody needs
-    SV_SB;
-    mul(x1, w1);
-    SV_SB;
-    if constexpr (SUMMED) {
-      if (kt + 1 == run_end) {
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-          for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              tot[ni][mi][r] = run_i == 0 ? acc[ni][mi][r] : tot[ni][mi][r] + acc[ni][mi][r];
-              acc[ni][mi][r] = 0.0f;
-            }
-        ++run_i;
-        run_end = (int)((int64_t)(run_i + 1) * nsl / runs);
-      }
-    }
+    step(std::false_type{}, std::false_type{}, std::false_type{}, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+    ca = next_a(ca); cw = next_w(cw);
   }
-  SV_MEET(0);                                                 // the re-read slices too: the stages become the patches
+  SV_MEET(meet_wait(C::LEFT));
+  step(std::false_type{}, std::true_type{}, std::true_type{}, x1, w1, x0, w0, ca, cw, 0, last_w(cw));     // without reads and loads
+  end_run(std::integral_constant<bool, SUMMED>{});
 
-  // ---- epilogue
-  char* patch = smem + wave * (32 * NI * 128);
+  // ---- epilogue.  A row of a patch: 4 NI chunks of 16 bytes (4 features), those of a lane's 8 columns LPR apart, XOR-swizzled by the row.
+  // The patches lie in the weights' buffer that everybody has read and no load is on its way to.
+  char* patch = smem + last_w(cw) + wave * (NI * 1024);
   const __amdgpu_buffer_rsrc_t bC = SPLIT ? desc(a.split_ws + (int64_t)run * M * a.N, a.N, 4) : desc(a.C, a.ldc, 2);
   const __amdgpu_buffer_rsrc_t bC2 = desc(a.C2, a.ldc, 2), bC3 = desc(a.C3, a.ldc, 2);
+  auto mix = [](int row) { return (row >> (NI == 2 ? 1 : 0)) & (2 * NI - 1); };
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
-    constexpr int kMask = NI * 8 - 1;
-    if (!SPLIT && mi + 1 < MI) load_inputs(mi + 1, in[(mi + 1) & 1], rs[(mi + 1) & 1]);
+    if (!SPLIT && mi + 1 < MI) load_inputs(mi + 1, in_lo[(mi + 1) & 1], in_hi[(mi + 1) & 1], rs[(mi + 1) & 1]);
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        f32x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = SUMMED ? tot[SUMMED ? ni : 0][SUMMED ? mi : 0][q * 4 + i] : acc[ni][mi][q * 4 + i];
-        *reinterpret_cast<f32x4*>(patch + l31 * (NI * 128) + (((ni * 8 + q * 2 + lhi) ^ (l31 & kMask)) << 4)) = v;
-      }
+    for (int ni = 0; ni < NI; ++ni) {
+      const bool up = DUAL && ni >= NI / 2;
+      const int slot = (up ? ni - NI / 2 : ni) * 2 + (lhi >> 1) + (lhi & 1) * LPR + (up ? 2 * NI : 0);
+      *reinterpret_cast<f32x4*>(patch + l15 * (NI * 64) + ((slot ^ mix(l15)) << 4)) = SUMMED ? tot[SUMMED ? ni : 0][SUMMED ? mi : 0] : acc[ni][mi];
+    }
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     __builtin_amdgcn_wave_barrier();
-    f32x4 va[TR], vu[TR];
+    f32x4 lo[TR], hi[TR], ulo[TR], uhi[TR];
 #pragma unroll
     for (int t = 0; t < TR; ++t) {
       const int row = t * RPI + er;
-      va[t] = *reinterpret_cast<const f32x4*>(patch + row * (NI * 128) + ((ec ^ (row & kMask)) << 4));
-      if (DUAL) vu[t] = *reinterpret_cast<const f32x4*>(patch + row * (NI * 128) + (((ec + NI * 4) ^ (row & kMask)) << 4));
+      auto at = [&](int slot) { return *reinterpret_cast<const f32x4*>(patch + row * (NI * 64) + ((slot ^ mix(row)) << 4)); };
+      lo[t] = at(ec); hi[t] = at(LPR + ec);
+      if (DUAL) { ulo[t] = at(2 * NI + ec); uhi[t] = at(2 * NI + LPR + ec); }
     }
 #pragma unroll
     for (int t = 0; t < TR; ++t) {
-      const int r = mw + mi * 32 + t * RPI + er;
+      const int r = mw + mi * 16 + t * RPI + er;
       if (SPLIT) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, va[t]), bC, (int)(((unsigned)(r * a.N) + vcol) * 4u), 0, 0);
+        const int vo = (int)(((unsigned)(r * a.N) + vcol) * 4u);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo[t]), bC, vo, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi[t]), bC, vo + 16, 0, 0);
         continue;
       }
-      float v[4], u[4];
+      const int vo = (int)(((unsigned)(r * (int)a.ldc) + vcol) * 2u);
+      const bool roped = EPI == EPI_ROPE && n < a.rope_cols;
+      const float f = kEpiScaled<EPI> ? rs[mi & 1][t] : 1.0f;
+      bf16x4 o[2][3];
+      auto half = [&](int h, const f32x4& x, const f32x4& y, const EpiIn& e) {
+        float v[4], u[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { v[i] = va[t][i]; u[i] = DUAL ? vu[t][i] : 0.0f; }
-      const unsigned vo = ((unsigned)(r * (int)a.ldc) + vcol) * 2u;
-      epilogue_math4<EPI>(a, EPI == EPI_ROPE && n < a.rope_cols, v, u, in[mi & 1][t], kEpiScaled<EPI> ? rs[mi & 1][t] : 1.0f, [&](int w, bf16x4 p) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, p), w == 0 ? bC : w == 1 ? bC2 : bC3, (int)vo, 0, 0);
-      });
+        for (int i = 0; i < 4; ++i) { v[i] = x[i]; u[i] = DUAL ? y[i] : 0.0f; }
+        epilogue_math4<EPI>(a, roped, v, u, e, f, [&](int w, bf16x4 p) { o[h][w] = p; });
+      };
+      half(0, lo[t], DUAL ? ulo[t] : lo[t], in_lo[mi & 1][t]);
+      half(1, hi[t], DUAL ? uhi[t] : hi[t], in_hi[mi & 1][t]);
+      auto put = [&](const __amdgpu_buffer_rsrc_t& b, int w) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, __builtin_shufflevector(o[0][w], o[1][w], 0, 1, 2, 3, 4, 5, 6, 7)), b, vo, 0, 0);
+      };
+      put(bC, 0);
+      if (EPI == EPI_SWIGLU_BWD || ((EPI == EPI_GELU || EPI == EPI_SWIGLU) && a.C2)) put(bC2, 1);
+      if (EPI == EPI_SWIGLU && a.C3) put(bC3, 2);
     }
     __builtin_amdgcn_wave_barrier();                       // the reads of this block are issued before the next block's writes
   }
+  __builtin_amdgcn_s_waitcnt(0);                           // every load has written its zeros before the workgroup gives its LDS back
 #undef SV_MEET
 #undef SV_SB
 }
 
-template <int WM, int WN, int MI, int NI, int NST, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false, bool TAIL = false>
+inline int k_slices(const GemmArgs& a) {
+  int n = 0;
+  for (int s = 0; s < a.nseg; ++s) n += a.seg[s].K / BK;
+  return n;
+}
+
+template <int MI, int NI, int RA, int RB, int EPI, bool GROUPED, bool SPLIT = false, bool SUMMED = false, bool TAIL = false>
 hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st, int tail_max = 0) {      // tail_max: tiles per XCD a tail has at most
-  using C = MidCfg<WM, WN, MI, NI, NST, EPI == EPI_SWIGLU>;
-  auto kern = gemm_mid_kernel<WM, WN, MI, NI, NST, EPI, GROUPED, SPLIT, SUMMED, TAIL>;
+  using C = MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>;
+  auto kern = gemm_mid_kernel<MI, NI, RA, RB, EPI, GROUPED, SPLIT, SUMMED, TAIL>;
   static bool configured = false;   // per process; the attribute is per function
   if (!configured) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
@@ -1236,7 +1236,9 @@ hipError_t launch_mid(const GemmArgs& a, int nsplit, hipStream_t st, int tail_ma
   }
   const int tiles_m = (a.M + C::BM - 1) / C::BM, tiles_n = (a.N + C::NOUT - 1) / C::NOUT;
   const int64_t per_xcd = TAIL ? (int64_t)tail_max * (256 / C::BM) * (256 / C::BN) : ((int64_t)tiles_m * tiles_n * nsplit + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(C::NT), C::LDS, st, a, tiles_m, tiles_n, nsplit);
+  GemmArgs g = a;
+  g.slices = k_slices(a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(per_xcd * 8)), dim3(256), C::LDS, st, g, tiles_m, tiles_n, nsplit);
   return hipGetLastError();
 }
 
@@ -1254,7 +1256,9 @@ hipError_t launch_dma(const GemmArgs& a, hipStream_t st) {
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
   const int n_cu = std::max(8, cu_count() / 8 * 8);       // one persistent workgroup per CU (all of its LDS)
   const int grid = per_xcd * 8 < n_cu ? per_xcd * 8 : n_cu;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a, tiles_m, tiles_n);
+  GemmArgs g = a;
+  g.slices = k_slices(a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
@@ -1316,15 +1320,21 @@ bool fits_mid(const GemmArgs& a) {        // buffer descriptors over a tile's ro
 bool summed_runs(const GemmArgs& a) { return a.runs[0] > 1 || a.runs[1] > 1 || a.runs[2] > 1; }
 
 // The epilogues that form an activation or its derivative are a fifth to a third of a product's time at K = 1024, and a launch of fewer
-// 256x256 tiles than CUs does them on part of the chip.  192x256 tiles (eight waves, two stages), while they too are one round, give every
-// CU three quarters of a tile.  256x256 -> 192x256, us: GELU 2331 x 3840, K = 960 (150 tiles, 195 of these) 38.1 -> 31.4, its backward
-// 37.4 -> 30.9; 4096 x 2560, K = 1024 39.1 -> 33.1; SwiGLU with its stashes 2331 x 1920, K = 960 30.7 -> 25.6, its backward at 3840
+// 256x256 tiles than CUs does them on part of the chip.  192x256 tiles, while they too are one round, give every
+// CU three quarters of a tile.  256x256 -> 192x256, us: GELU 2331 x 3840, K = 960 (150 tiles, 195 of these) 38.1 -> 31.0, its backward
+// 37.4 -> 31.2; 4096 x 2560, K = 1024 39.1 -> 33.1; SwiGLU with its stashes 2331 x 1920, K = 960 30.7 -> 25.6, its backward at 3840
 // columns 34.9 -> 32.1; 900 x 5120, K = 2048 48.3 -> 43.3; 800 x 6144, K = 3072 68.2 -> 62.6.  With a longer k loop the bare product
 // decides: GELU 768 x 16384, K = 4096 104 -> 112.  (Plain stores and residual sums gain 1 - 9 % and stay where they are: what they run
-// on is what sv_gemm_plan tells.)
-bool narrower_pays(const GemmArgs& a, int slices) {
+// on is what sv_gemm_plan tells.)  Where 256x128 tiles were chosen, whole rounds decide, at what a round of either was measured to take
+// (6.1 us and 0.65 a slice, 6.0 and 0.92).
+bool narrower_pays(const GemmArgs& a, int kind, int slices) {
   if (a.epi != EPI_GELU && a.epi != EPI_GELU_BWD && a.epi != EPI_SWIGLU && a.epi != EPI_SWIGLU_BWD) return false;
-  return !a.tile_group && slices <= 48 && fits_mid(a) && (int64_t)((a.M + 191) / 192) * (a.N / (a.epi == EPI_SWIGLU ? 128 : 256)) <= cu_count();
+  const int64_t nout = a.epi == EPI_SWIGLU ? 128 : 256, cus = cu_count(), tiles = (a.M + 191) / 192 * (a.N / nout);
+  if (a.tile_group || slices > 48 || !fits_mid(a)) return false;
+  if (kind == kTile256) return tiles <= cus;
+  const int64_t tiles128 = (int64_t)((a.M + 255) / 256) * (2 * a.N / nout);
+  return kind == kTile256x128 && a.N % nout == 0 &&
+         (double)((tiles + cus - 1) / cus) * (6.0 + 0.92 * slices) < 0.95 * (double)((tiles128 + cus - 1) / cus) * (6.1 + 0.65 * slices);
 }
 
 // Asked twice for a product that may leave row sums, once to know whether it will (mfma_gemm_emits_rowsq) and once to launch it:
@@ -1332,8 +1342,7 @@ bool narrower_pays(const GemmArgs& a, int slices) {
 Plan plan_gemm(const GemmArgs& a) {
   if (summed_runs(a)) return Plan{kTile128, 1};
   const bool dual = a.epi == EPI_SWIGLU;
-  int slices = 0;
-  for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
+  const int slices = k_slices(a);
   const double cus = cu_count();
   Plan best{-1, 1};
   double best_cost = 0.0;
@@ -1360,7 +1369,7 @@ Plan plan_gemm(const GemmArgs& a) {
       if (best.kind < 0 || cost < best_cost) { best = Plan{k, runs}; best_cost = cost; }
     }
   }
-  if (best.kind == kTile256 && narrower_pays(a, slices)) best.kind = kTile192x256;
+  if (narrower_pays(a, best.kind, slices)) best.kind = kTile192x256;
   return best;
 }
 
@@ -1371,8 +1380,7 @@ template <int EPI, bool GROUPED>
 int tail_pays(const GemmArgs& a) {
   if (a.rowsq || !fits_mid(a)) return 0;                 // row sums come from whole 256 x 256 tiles only
   const int tiles_n = a.N / (EPI == EPI_SWIGLU ? 128 : 256), slots = tile_slots();
-  int slices = 0;
-  for (int s = 0; s < a.nseg; ++s) slices += a.seg[s].K / BK;
+  const int slices = k_slices(a);
   if (!GROUPED) return tail_tiles(((a.M + 255) / 256 * tiles_n + 7) / 8, slots, slices);
   const int most = a.M / 256, pad = std::min(most - 1, a.groups);
   int with = 0, all = 0, left = 0;
@@ -1382,6 +1390,13 @@ int tail_pays(const GemmArgs& a) {
   }
   for (int b = std::max(1, most - pad); b <= most; ++b) left = std::max(left, tail_tiles((b * tiles_n + 7) / 8, slots, slices));
   return 2 * with >= all ? left : 0;
+}
+
+// 128x128 tiles: two workgroups of 80 KB on a CU where there are tiles for them (4096 x 3072, K = 1024 28.0 -> 25.8 us, 8192 x 1024 19.6 ->
+// 17.9), one with twice the buffers where every tile has a CU of its own (4096 x 1024, K = 2816 23.4 us against 26.2).
+bool two_per_cu(const GemmArgs& a, int runs) {
+  const int nout = a.epi == EPI_SWIGLU ? 64 : 128;
+  return (int64_t)((a.M + 127) / 128) * ((a.N + nout - 1) / nout) * runs > cu_count();
 }
 
 // the form that scales rows, where there is one
@@ -1401,22 +1416,22 @@ hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
         g.tail = tile_slots();
         hipError_t e = g.rscale ? launch_dma_nf<EPI, GROUPED>(g, st) : launch_dma<EPI, GROUPED>(g, st);
         if (e != hipSuccess) return e;
-        if (GROUPED || 4 * left <= g.tail) return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED, false, false, true>(g, 1, st, left);
-        if constexpr (!GROUPED) return launch_mid<4, 2, 2, 2, 3, EPI, false, false, false, true>(g, 1, st, left);
+        if (GROUPED || 4 * left <= g.tail) return launch_mid<4, 4, 5, 4, EPI, GROUPED, false, false, true>(g, 1, st, left);
+        if constexpr (!GROUPED) return launch_mid<8, 4, 3, 3, EPI, false, false, false, true>(g, 1, st, left);
       }
       if constexpr (!GROUPED && EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD)
         if (a.rscale || a.rowsq) return launch_dma<EPI, false, true>(a, st);   // the ends of a norm that runs inside the products
       return launch_dma<EPI, GROUPED>(a, st);
     }
-    case kTile256x128: return launch_mid<4, 2, 2, 2, 3, EPI, GROUPED>(a, 1, st);
-    case kTile128: return launch_mid<4, 2, 1, 2, 4, EPI, GROUPED>(a, 1, st);
-    case kTile64x128: return launch_mid<2, 2, 1, 2, 3, EPI, GROUPED>(a, 1, st);
+    case kTile256x128: return launch_mid<8, 4, 3, 3, EPI, GROUPED>(a, 1, st);
+    case kTile128: return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, GROUPED>(a, 1, st) : launch_mid<4, 4, 5, 4, EPI, GROUPED>(a, 1, st);
+    case kTile64x128: return launch_mid<2, 4, 4, 3, EPI, GROUPED>(a, 1, st);
     case kTile192x256:
       if constexpr (!GROUPED && (EPI == EPI_GELU || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD))
-        return launch_mid<2, 4, 3, 2, 2, EPI, false>(a, 1, st);
+        return launch_mid<6, 8, 3, 2, EPI, false>(a, 1, st);
       return hipErrorInvalidValue;
     default:
-      if constexpr (EPI != EPI_SWIGLU) return launch_mid<2, 2, 1, 1, 8, EPI, GROUPED>(a, 1, st);
+      if constexpr (EPI != EPI_SWIGLU) return launch_mid<2, 2, 5, 5, EPI, GROUPED>(a, 1, st);
       return hipErrorInvalidValue;
   }
 }
@@ -1426,10 +1441,10 @@ template <int EPI>
 hipError_t launch_runs(const GemmArgs& a, const Plan& p, hipStream_t st) {
   hipError_t e;
   switch (p.kind) {
-    case kTile256x128: e = launch_mid<4, 2, 2, 2, 3, EPI_STORE, false, true>(a, p.runs, st); break;
-    case kTile128: e = launch_mid<4, 2, 1, 2, 4, EPI_STORE, false, true>(a, p.runs, st); break;
-    case kTile64x128: e = launch_mid<2, 2, 1, 2, 3, EPI_STORE, false, true>(a, p.runs, st); break;
-    case kTile64: e = launch_mid<2, 2, 1, 1, 8, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile256x128: e = launch_mid<8, 4, 3, 3, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile128: e = two_per_cu(a, p.runs) ? launch_mid<4, 4, 3, 2, EPI_STORE, false, true>(a, p.runs, st) : launch_mid<4, 4, 5, 4, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile64x128: e = launch_mid<2, 4, 4, 3, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile64: e = launch_mid<2, 2, 5, 5, EPI_STORE, false, true>(a, p.runs, st); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
@@ -1442,7 +1457,7 @@ template <int EPI>
 hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
   if (a.rowsq && (p.kind != kTile256 || p.runs > 1)) return hipErrorInvalidValue;    // somebody will read them: mfma_gemm_emits_rowsq first
   if (summed_runs(a)) {
-    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE) return launch_mid<4, 2, 1, 2, 4, EPI, false, false, true>(a, 1, st);
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE) return launch_mid<4, 4, 5, 4, EPI, false, false, true>(a, 1, st);
     return hipErrorInvalidValue;
   }
   if constexpr (EPI != EPI_SWIGLU)
@@ -1506,7 +1521,7 @@ bool mfma_gemm_shape(const GemmArgs& a) {
     int tot = 0;
     for (int j = 0; j < a.nbcol; ++j) { if (a.ncol[j] % 8 || !aligned16(a.Bcol[j])) return false; tot += a.ncol[j]; }
     if (a.nbcol > 0 && (tot != a.N || a.epi == EPI_SWIGLU)) return false;
-    if (a.epi == EPI_ROPE && (!a.rope_cs || a.rope_hd % 4 || a.rope_cols % 4 || a.rope_S < 1)) return false;
+    if (a.epi == EPI_ROPE && (!a.rope_cs || a.rope_hd % 8 || a.rope_cols % 8 || a.rope_S < 1)) return false;
   }
   if ((a.tile_group != nullptr) != (a.m_dev != nullptr)) return false;      // the grouped form needs both
   if (a.tile_group && (a.b_is_kn || a.nbcol > 0 || a.group_stride % 8 || a.M % 256)) return false;
