@@ -1108,7 +1108,7 @@ sv_status sv_sw_projection_ema(sv_ctx* c, float* ref_proj, const float* claim_pr
     else ++n;
   }
   if (n == 0) return SV_OK;
-  SV_HIP(c, launch_sw_proj_ema(ref_proj, claim_proj, n_claims, skip, L, T, sw_padded_len(T), beta, (1.0f - beta) / (float)n, (hipStream_t)stream));
+  SV_HIP(c, launch_sw_proj_ema(ref_proj, ref_proj, claim_proj, n_claims, skip, L, T, sw_padded_len(T), beta, (1.0f - beta) / (float)n, (hipStream_t)stream));
   return SV_OK;
 }
 

@@ -430,8 +430,8 @@ __global__ void sw_finalize_kernel(const float* __restrict__ w1, int n_claims, i
 }
 
 // The projection is linear, so the projections of m <- beta m + (1 - beta) mean_clean(x) are the same combination of
-// the projections: pm <- beta pm + w sum_{c not skipped} P_c (index order, fp32), per direction and token.
-__global__ __launch_bounds__(256) void sw_proj_ema_kernel(float* __restrict__ pm, const float* __restrict__ P, int n, uint32_t skip,
+// the projections: out = beta pm + w sum_{c not skipped} P_c (index order, fp32), per direction and token; out may be pm.
+__global__ __launch_bounds__(256) void sw_proj_ema_kernel(float* out, const float* pm, const float* __restrict__ P, int n, uint32_t skip,
                                                           int64_t slot, int64_t T, int64_t Tpad, float beta, float w) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= T) return;
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256) void sw_proj_ema_kernel(float* __restrict__ pm
   float acc = 0.0f;
   for (int c = 0; c < n; ++c)
     if (((skip >> c) & 1u) == 0) acc += P[(int64_t)c * slot + i];
-  pm[i] = beta * pm[i] + w * acc;
+  out[i] = beta * pm[i] + w * acc;
 }
 
 template <typename E, typename E2, int LB>
@@ -517,9 +517,9 @@ hipError_t launch_sw_sort(float* P, int n_seg, int64_t T, int64_t Tpad, const fl
   return hipGetLastError();
 }
 
-hipError_t launch_sw_proj_ema(float* pm, const float* P, int n, uint32_t skip, int L, int64_t T, int64_t Tpad, float beta, float w,
+hipError_t launch_sw_proj_ema(float* out, const float* pm, const float* P, int n, uint32_t skip, int L, int64_t T, int64_t Tpad, float beta, float w,
                               hipStream_t st) {
-  sw_proj_ema_kernel<<<dim3((unsigned)((T + 255) / 256), (unsigned)L), 256, 0, st>>>(pm, P, n, skip, (int64_t)L * Tpad, T, Tpad, beta, w);
+  sw_proj_ema_kernel<<<dim3((unsigned)((T + 255) / 256), (unsigned)L), 256, 0, st>>>(out, pm, P, n, skip, (int64_t)L * Tpad, T, Tpad, beta, w);
   return hipGetLastError();
 }
 
