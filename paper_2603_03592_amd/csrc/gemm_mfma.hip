@@ -1393,7 +1393,8 @@ int tail_pays(const GemmArgs& a) {
 }
 
 // 128x128 tiles: two workgroups of 80 KB on a CU where there are tiles for them (4096 x 3072, K = 1024 28.0 -> 25.8 us, 8192 x 1024 19.6 ->
-// 17.9), one with twice the buffers where every tile has a CU of its own (4096 x 1024, K = 2816 23.4 us against 26.2).
+// 17.9; 8192 x 768 with rotation and settled sums, K = 512 23.0 -> 16.6), one with twice the buffers where every tile has a CU of its own
+// (4096 x 1024, K = 2816 23.4 us against 26.2).
 bool two_per_cu(const GemmArgs& a, int runs) {
   const int nout = a.epi == EPI_SWIGLU ? 64 : 128;
   return (int64_t)((a.M + 127) / 128) * ((a.N + nout - 1) / nout) * runs > cu_count();
@@ -1457,7 +1458,8 @@ template <int EPI>
 hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
   if (a.rowsq && (p.kind != kTile256 || p.runs > 1)) return hipErrorInvalidValue;    // somebody will read them: mfma_gemm_emits_rowsq first
   if (summed_runs(a)) {
-    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE) return launch_mid<4, 4, 5, 4, EPI, false, false, true>(a, 1, st);
+    if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE)
+      return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, false, false, true>(a, 1, st) : launch_mid<4, 4, 5, 4, EPI, false, false, true>(a, 1, st);
     return hipErrorInvalidValue;
   }
   if constexpr (EPI != EPI_SWIGLU)
