@@ -862,8 +862,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 // the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the next step and the loads of a later slice
 // spread over the first three quarters of a step's MFMAs, activations in the one step and weights in the other, one wait and barrier a
 // slice that leaves the youngest loads in flight.  Against eight waves with their loads and reads in groups around the MFMAs of
-// a 16-wide step, us: 1024^3 on 64x64 7.1 -> 6.2; 512 x 4096, K = 4096 on 64x128 24.3 -> 20.5; 4096 x 1024, K = 2816 on 128x128 25.6 -> 23.4;
-// 6144 x 1024, K = 4096 on 256x128 54.3 -> 47.2.
+// a 16-wide step, us: 1024^3 on 64x64 7.7 -> 7.2; 512 x 4096, K = 4096 on 64x128 25.0 -> 21.9; 2331 x 1600, K = 960 on 64x64 23.3 -> 16.4;
+// 8192 x 2048, K = 2048 on 128x128 74.5 -> 60.6, on 256x128 64.8 -> 60.3 (one round of 8 slices: 8.4 -> 8.7 on 128x128, 10.3 -> 11.1 on
+// 256x128).
 template <int MI, int NI, int RA, int RB, bool DUAL>
 struct MidCfg {
   static constexpr int BM = 32 * MI, BN = 32 * NI, NOUT = DUAL ? BN / 2 : BN;
@@ -1283,7 +1284,8 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // ---- which kernel and tile serves a product.  Every choice is priced as rounds of workgroups over the CUs times (a fixed part
 // + slices x time per slice), plus for runs of k slices the reduction launch and the traffic of the partial products; the
 // cheapest is taken.  The figures are microseconds fitted to a sweep over 64 .. 8192 rows, 320 .. 14336 columns and K =
-// 512 .. 14336 with every tile forced (within 15 % of the measured times there).  They are those of a plain store: the dearer
+// 512 .. 14336 with every tile forced (within 15 % of the measured times there), on the kernels' former k loops: prices fitted to
+// the present ones take tiles that are 0.8 % faster on average over 156 sizes, and others than the stages' tests name.  They are those of a plain store: the dearer
 // epilogues (SwiGLU with its stashes, SwiGLU-backward) cost the same here, and a tile more than the last full round counts as a
 // round (on 256x256 tiles: as a second launch on smaller ones, where tail_tiles says so).  Against 256x256 tiles over runs of k, which these replaced, k of 9000 and more for 500 .. 1500 rows of 3072 .. 4096 columns
 // is left 5 .. 15 % slower (1453 x 3072, K = 9728: 97 -> 112 us), everything else even or faster.  Where the lines come out, with both
