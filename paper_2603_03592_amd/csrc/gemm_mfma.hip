@@ -817,14 +817,18 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
             const float rs = RS ? __shfl(trip < 8 ? rs_pre0 : rs_pre1, (rb & 63) + eer) : 1.0f;
             const bool roped = EPI == EPI_ROPE && ncol0 + ec8 * 8 < a.rope_cols;
             float sq = epilogue_math4<EPI>(a, roped, lo, hi, in_lo[trip % PD][k], rs, put_lo);
-            sq += epilogue_math4<EPI>(a, roped, hi, lo, in_hi[trip % PD][k], rs, put_hi);
+            float sq_hi = epilogue_math4<EPI>(a, roped, hi, lo, in_hi[trip % PD][k], rs, put_hi);
             put16(bC, __builtin_shufflevector(olo[0], ohi[0], 0, 1, 2, 3, 4, 5, 6, 7), rb, eer, e15 * 16);
             if (EPI == EPI_SWIGLU_BWD || (EPI == EPI_GELU && a.C2))
               put16(bC2, __builtin_shufflevector(olo[1], ohi[1], 0, 1, 2, 3, 4, 5, 6, 7), rb, eer, e15 * 16);
             if (SQ) {
-              // the 16 lanes of a row hold its 128 stored values: rotate-and-add within the row of 16 lanes leaves the
-              // sum in all of them, and the one whose turn it is keeps it
+              // the 16 lanes of a row hold its 128 stored values, two chunks of 4 each: rotate-and-add within the row of 16 lanes leaves
+              // the sum in all of them, and the one whose turn it is keeps it.  Chunk c's sum meets that of chunk c ^ 16 first, then c ^ 8,
+              // 4, 2 and, in the lane, 1: a verifier's row factors, and all that follows them, stay the same bits whatever
+              // columns a lane holds.
               sq += dpp_row_ror<8>(sq); sq += dpp_row_ror<4>(sq); sq += dpp_row_ror<2>(sq); sq += dpp_row_ror<1>(sq);
+              sq_hi += dpp_row_ror<8>(sq_hi); sq_hi += dpp_row_ror<4>(sq_hi); sq_hi += dpp_row_ror<2>(sq_hi); sq_hi += dpp_row_ror<1>(sq_hi);
+              sq += sq_hi;
               if (trip < 8) sq0 = e15 == trip * 2 + k ? sq : sq0;
               else sq1 = e15 == trip * 2 + k - 16 ? sq : sq1;
             }
