@@ -622,8 +622,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     // In the read-back of the epilogue a lane serves row er of each group of 4 rows, 8 columns from 8 ec.
     // One buffer descriptor per tensor, based at the tile's first row and the wave's first column, up to the last of the M rows: what
     // lies past them is dropped or read as zero, and a ragged tile runs the same code as a full one.  Inside it a lane's
-    // byte offset is (row * ld + column) * 2, of which the lane's part never changes and the row block's part is a scalar:
-    // no 64-bit address arithmetic per access.
+    // byte offset is (row * ld + column) * 2: no 64-bit address arithmetic per access.  All of it is in the vector register: the
+    // bounds test subtracts a scalar offset from the descriptor's size, and a ragged tile's row blocks begin past its end.
     constexpr int PD = kEpiAhead<EPI>;                   // trips the epilogue's global reads run ahead of its stores
     const int er = lhi, ec8 = l15;
     const int ncol0 = n0 + wn * (DUAL ? 64 : 128);
@@ -633,7 +633,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     };
     const __amdgpu_buffer_rsrc_t bC = desc(a.C, a.ldc), bC2 = desc(a.C2, a.ldc), bC3 = desc(a.C3, a.ldc);
     const __amdgpu_buffer_rsrc_t bR = desc(a.R, a.ldr), bR2 = desc(a.R2, a.ldr);
-    // byte offset of row `row` of a group of the wave's 128 rows, `bytes` into it: the lane's part; the group's first row is the scalar part
+    // byte offset of row `row` of the wave's 128 rows, `bytes` into it; a group's first row is added behind it
     auto place = [&](int row, int ld, int bytes) { return (wm * 128 + row) * ld * 2 + bytes; };
     int rope_p0 = 0, rope_v = 0;                         // first row's position; byte offset of the lane's feature pairs in a table row
     if (EPI == EPI_ROPE) {
@@ -641,8 +641,8 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       rope_v = (((ncol0 + ec8 * 8) % a.rope_hd) >> 1) * 8;
     }
     const __amdgpu_buffer_rsrc_t bT = __builtin_amdgcn_make_buffer_rsrc((void*)a.rope_cs, (short)0, -1, 0x00020000);
-    auto ld16 = [&](__amdgpu_buffer_rsrc_t b, int vo, int so, bf16x4& lo, bf16x4& hi) {
-      const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, vo, so, 0));
+    auto ld16 = [&](__amdgpu_buffer_rsrc_t b, int vo, bf16x4& lo, bf16x4& hi) {
+      const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(b, vo, 0, 0));
       lo = __builtin_shufflevector(v, v, 0, 1, 2, 3);
       hi = __builtin_shufflevector(v, v, 4, 5, 6, 7);
     };
@@ -660,9 +660,9 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
           lo[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo, 0, 0));
           hi[k].cs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bT, vo + 16, 0, 0));
         } else if (kHasInputs) {
-          const int vo = place(er, a.ldr, ec8 * 16), so = rb * a.ldr * 2;
-          ld16(bR, vo, so, lo[k].r, hi[k].r);
-          if (EPI == EPI_SWIGLU_BWD) ld16(bR2, vo, so, lo[k].r2, hi[k].r2);
+          const int vo = place(er, a.ldr, ec8 * 16) + rb * a.ldr * 2;
+          ld16(bR, vo, lo[k].r, hi[k].r);
+          if (EPI == EPI_SWIGLU_BWD) ld16(bR2, vo, lo[k].r2, hi[k].r2);
         }
       }
     };
@@ -725,7 +725,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
         return v;
       };
       auto put16 = [&](__amdgpu_buffer_rsrc_t b, bf16x8 v, int rb, int row, int bytes) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, place(row, a.ldc, bytes), rb * a.ldc * 2, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, place(row, a.ldc, bytes) + rb * a.ldc * 2, 0, 0);
       };
       if constexpr (DUAL) {
         // Gate and up of one feature sit in the same lane and register index, so SiLU(g) * u is taken in the accumulator layout
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
           const int r = wm * 128 + e15 * 4 + eer;
           const __amdgpu_buffer_rsrc_t bQ = __builtin_amdgcn_make_buffer_rsrc((void*)(a.rowsq + (int64_t)((n0 >> 7) + wn) * a.rowsq_ld + m0), (short)0, rows * 4, 0x00020000);
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq0), bQ, r * 4, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq1), bQ, r * 4, 256, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, sq1), bQ, (r + 64) * 4, 0, 0);
         }
       }
     }
@@ -983,13 +983,13 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
                                              w_k * 2, 0, 0);
   };
   auto advance_a = [&]() {
-    if (--a_left <= 0) { a_bytes = 0; return; }
+    if (--a_left <= 0) { a_bytes = 0; a_k = 0; return; }
     a_k += BK;
     if (a_k < a_K) return;
     a_k = 0; ++a_seg; set_a(a.seg[a_seg]);
   };
   auto advance_b = [&]() {
-    if (--w_left <= 0) { w_bytes = 0; return; }
+    if (--w_left <= 0) { w_bytes = 0; w_k = 0; return; }
     w_k += BK;
     if (w_k < w_K) return;
     w_k = 0; ++w_seg; set_b(a.seg[w_seg]);
