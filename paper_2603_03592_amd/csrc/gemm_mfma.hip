@@ -1315,8 +1315,7 @@ bool fits_256(const GemmArgs& a) {        // the persistent 256x256 kernel has w
   if (a.N % (a.epi == EPI_SWIGLU ? 128 : 256)) return false;
   for (int j = 0; j < a.nbcol; ++j)
     if (a.ncol[j] % 256) return false;
-  if (256 * a.ldc * 2 >= (int64_t)1 << 31 || 256 * a.ldr * 2 >= (int64_t)1 << 31) return false;   // a tile's outputs by 32-bit byte offsets
-  return !(a.epi == EPI_SWIGLU && a.ldc % 8);            // its epilogue stores 16 bytes per lane
+  return 256 * a.ldc * 2 < (int64_t)1 << 31 && 256 * a.ldr * 2 < (int64_t)1 << 31;      // a tile's outputs by 32-bit byte offsets
 }
 
 bool fits_mid(const GemmArgs& a) {        // buffer descriptors over a tile's rows keep below 2^31 bytes
@@ -1543,6 +1542,8 @@ bool mfma_gemm_shape(const GemmArgs& a) {
   if ((a.epi == EPI_RESID || a.epi == EPI_SWIGLU_BWD || a.epi == EPI_GELU_BWD) && !a.R) return false;
   if (a.epi == EPI_SWIGLU_BWD && (!a.R2 || !a.C2)) return false;
   if (a.N < 8 || a.N % (a.b_is_kn ? 128 : 8)) return false;
+  // Row strides are multiples of 4 values: the epilogues' accesses of 16 bytes then stand on 8-byte boundaries, and buffer accesses of any
+  // width need whole dwords only.
   if (a.ldc % 4 || !aligned16(a.C)) return false;
   if ((a.C2 && !aligned16(a.C2)) || (a.C3 && !aligned16(a.C3))) return false;
   if ((a.R || a.R2) && (a.ldr % 4 || !aligned16(a.R) || (a.R2 && !aligned16(a.R2)))) return false;
