@@ -1374,7 +1374,7 @@ Plan plan_gemm(const GemmArgs& a) {
       if (best.kind < 0 || cost < best_cost) { best = Plan{k, runs}; best_cost = cost; }
     }
   }
-  if (narrower_pays(a, best.kind, slices)) best.kind = kTile192x256;
+  if (best.runs == 1 && narrower_pays(a, best.kind, slices)) best.kind = kTile192x256;      // 192x256 tiles have no form over runs of k
   return best;
 }
 

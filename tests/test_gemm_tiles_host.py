@@ -1,4 +1,5 @@
 """Which tiles a block's products run on is decided on the host: what the device tests of those tiles count on, and what the kernels do."""
+import numpy as np
 import pytest
 
 import paper_2603_03592_amd as sv
@@ -30,6 +31,18 @@ def test_the_stages_of_the_narrower_tile_take_it(M, mlp, ffn):
     """test_gpu_gemm_narrower.py: 512 columns."""
     assert sv.sv_gemm_tiles(M, ffn, 512, mlp, 0, SCRATCH)[0] == 6
     assert sv.sv_gemm_tiles(M, 6144, 512, mlp + "_bwd", 0, SCRATCH)[0] == 6
+
+
+def test_the_narrower_tile_is_never_planned_over_runs_of_k():
+    """It has no form that leaves partial products."""
+    rng, six = np.random.default_rng(0), 0
+    for _ in range(20000):
+        M, N, K = int(2 ** rng.uniform(5, 16)), 256 * int(2 ** rng.uniform(0, 7)), 64 * int(rng.integers(1, 49))
+        for epilogue in ("gelu", "gelu_bwd", "swiglu", "swiglu_bwd"):
+            tile, runs, _ = sv.sv_gemm_tiles(M, N, K, epilogue, 0, 1 << 40)
+            six += tile == 6
+            assert tile != 6 or runs == 1, (M, N, K, epilogue)
+    assert six > 1000
 
 
 @pytest.mark.parametrize("epilogue", ["store", "swiglu", "swiglu_bwd"])
