@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import paper_2603_03592_amd as sv
-from test_gpu_gemm_same_bits import MIXTURES, STAGES, mixture_plan, stage_plan
+from test_gpu_gemm_same_bits import MIXTURES, STAGES, mixture_plan, stage_plan, stage_products
 
 SCRATCH = 8 * 160 * 128 * 128
 
@@ -17,6 +17,13 @@ def test_stages_run_on_what_their_device_test_names(case):
     for name, (tile, tail) in c.aims.items():
         assert whole[name][0] == tile and tail(whole[name][2]), (name, whole[name])
         assert piece[name][0] != tile or (whole[name][2] > 0 and piece[name][2] == 0), (name, whole[name], piece[name])
+
+
+@pytest.mark.parametrize("case", [c for c in STAGES if "_rounds" in c])
+def test_stages_of_several_rounds_take_them(case):
+    for name, (N, K, e) in stage_products(STAGES[case]).items():
+        M = STAGES[case].batch * STAGES[case].seq
+        assert (M + 255) // 256 * (N // (128 if e == "swiglu" else 256)) > 256, name
 
 
 @pytest.mark.parametrize("case", list(MIXTURES))

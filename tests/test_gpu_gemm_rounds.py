@@ -1,6 +1,7 @@
-"""Products of more tiles than a round of the compute units takes: the stream of slices that runs on from tile to tile (as short as one
-slice a tile), two workgroups of 128x128 tiles on a compute unit, and activations on 192x256 tiles in two rounds.  Every tile
-adds up an element in the same order, so all give the same bits; against fp32 the bound is the rounding to bf16 and K steps of fp32."""
+"""Products of more tiles than a round of the compute units takes: their last round in a second launch or in the persistent kernel, whose
+stream of slices then runs on from tile to tile (as short as one slice a tile), two workgroups of 128x128 tiles on a compute unit, and activations
+on 192x256 tiles in two rounds.  Every tile adds up an element in the same order, so all give the same bits; against fp32 the bound
+is the rounding to bf16 and K steps of fp32."""
 import ctypes
 
 import pytest
@@ -31,7 +32,7 @@ def _operands(M, N, K):
     return tuple(torch.randn((r, K), generator=gen, device="cuda").bfloat16() for r in (M, N))
 
 
-# 17 x 18 tiles of 256x256 (the last of them with 1, 64 or all rows); 33 and more x 36 of 128x128
+# 17 x 18 tiles of 256x256 (the last of them with 1, 64 or all rows), the second round in a launch of its own; 33 and more x 36 of 128x128
 @pytest.mark.parametrize("M", [4097, 4160, 4352])
 @pytest.mark.parametrize("K", [64, 128, 192, 320])
 def test_tiles_agree_beyond_a_round(M, K):
@@ -43,6 +44,39 @@ def test_tiles_agree_beyond_a_round(M, K):
     assert ((want.float() - ref).abs() <= bound).all()
     for tile in (1, 2, 3, 4):
         assert torch.equal(_product(A, B, tile), want), tile
+
+
+# 24 x 18 tiles, 54 per XCD: 22 of its 32 workgroups run a second one (the last row of tiles with 1, 64 or all rows); 39 x 18: 24 a third
+@pytest.mark.parametrize("M", [5889, 5952, 6144, 9984])
+@pytest.mark.parametrize("K", [64, 128, 192, 320])
+def test_a_workgroup_runs_on_to_its_next_tile(M, K):
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are chosen for 256 compute units")
+    assert sv.sv_gemm_tiles(M, 4608, K, "store")[2] == 0 and (M + 255) // 256 * 18 > 256
+    A, B = _operands(M, 4608, K)
+    want = _product(A, B, 2)
+    for _ in range(3):
+        assert torch.equal(_product(A, B, 1), want)
+
+
+@pytest.mark.parametrize("mlp", ["swiglu", "gelu"])
+def test_forward_without_stashes_runs_on_to_the_next_tile(mlp):
+    """Without gate, up or the input of the activation to keep, a tile's epilogue makes the fewest stores."""
+    import torch
+
+    import stage_inputs as si
+    from gpu_util import dev_weights
+    from test_gpu_gemm_same_bits import STAGES
+    c = STAGES[mlp + "_rounds"]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    h = torch.randn((c.batch, c.seq, c.d), generator=gen, device="cuda").bfloat16()
+    ver = sv.Verifier(c.desc, c.batch * c.seq, c.seq)
+    wc = ver.pack_weights(wd := dev_weights(si.make_weights(c.desc, 7), "bf16"))
+    run = lambda x: ver.verify_forward(wc, x, x, want_h_hat=True)["h_hat"].clone()
+    whole = run(h)
+    assert torch.isfinite(whole).all() and torch.equal(whole, torch.cat([run(x[None].contiguous()) for x in h]))
+    ver.close()
 
 
 @pytest.mark.parametrize("M,N,K,runs", [(4099, 1152, 512, 3), (4099, 1152, 576, 8), (4099, 896, 512, 3)])

@@ -27,6 +27,9 @@ class Case:
         return si.StageDesc(1, self.d, self.d // 64, self.d // 64, self.ffn, mlp=self.mlp, norm="rms", rope=self.rope)
 
 
+# the kinds of products that take more rounds of 256x256 tiles than one without leaving any to a second launch, so that a workgroup goes on from a
+# tile to the next with its stores on their way
+_rounds = {n: (1, lambda t: t == 0) for n in ("qkv", "o", "up", "down", "dact", "dn2", "do", "dn1")}
 _some, _half, _any = (lambda t: 0 < t <= 8), (lambda t: t > 8), (lambda t: True)
 _quarter = {n: (1, _some) for n in ("qkv", "o", "up", "down", "dact", "dn2", "do", "dn1")}
 STAGES = {
@@ -38,6 +41,9 @@ STAGES = {
     "swiglu_bwd_half": Case("swiglu", 2048, 2048, 7, 1500, 1, {n: (1, _half) for n in ("dact", "o", "down")}),
     "row_factors": Case("swiglu", 1024, 1536, 11, 1500, 1, {"qkv": (1, _some), "up": (1, _some)}, fuse=True),
     "row_factors_gelu": Case("gelu", 1280, 1024, 12, 1500, 1, {"qkv": (1, _some), "up": (1, _some)}, fuse=True),
+    "gelu_rounds": Case("gelu", 1024, 1024, 18, 1500, 1, _rounds),
+    "swiglu_rounds": Case("swiglu", 1024, 1024, 18, 1500, 1, _rounds),
+    "swiglu_rounds_no_rope": Case("swiglu", 1024, 1024, 18, 1500, 1, _rounds, rope=False),
     "narrower_gelu": Case("gelu", 1536, 1024, 9, 1229, 1, {"up": (6, _any), "dact": (6, _any)}),
     "narrower_gelu_ragged": Case("gelu", 768, 3840, 3, 777, 1, {"up": (6, _any), "dact": (6, _any)}),
     "narrower_swiglu": Case("swiglu", 512, 1536, 5, 777, 1, {"up": (6, _any)}),
@@ -66,12 +72,15 @@ class Mixture:
 MIXTURES = {"top2": Mixture(256, 256, 8, 2, 35, 1024, 6), "top1": Mixture(256, 256, 4, 1, 66, 1024, 12)}
 
 
+def stage_products(c):
+    D, F, two = c.d, c.ffn, 2 if c.mlp == "swiglu" else 1
+    return {"qkv": (3 * D, D, "rope" if c.rope else "store"), "o": (D, D, "residual"), "up": (F, D, c.mlp), "down": (D, F, "residual"),
+            "dact": (F, D, c.mlp + "_bwd"), "dn2": (D, two * F, "store"), "do": (D, D, "store"), "dn1": (D, 3 * D, "store")}
+
+
 def stage_plan(c, batch):
-    M, D, F, ws = batch * c.seq, c.d, c.ffn, min(8 * 160 * 128 * 128, 8 * c.batch * c.seq * max(c.d, c.ffn))
-    two = 2 if c.mlp == "swiglu" else 1
-    products = {"qkv": (3 * D, D, "rope" if c.rope else "store"), "o": (D, D, "residual"), "up": (F, D, c.mlp), "down": (D, F, "residual"),
-                "dact": (F, D, c.mlp + "_bwd"), "dn2": (D, two * F, "store"), "do": (D, D, "store"), "dn1": (D, 3 * D, "store")}
-    return {n: sv.sv_gemm_tiles(M, N, K, e, 0, ws) for n, (N, K, e) in products.items()}
+    M, ws = batch * c.seq, min(8 * 160 * 128 * 128, 8 * c.batch * c.seq * max(c.d, c.ffn))
+    return {n: sv.sv_gemm_tiles(M, N, K, e, 0, ws) for n, (N, K, e) in stage_products(c).items()}
 
 
 def mixture_plan(c, batch):
