@@ -420,12 +420,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int nspl
 // are in registers and the loads of the slices behind it are on their way, so a tile begins without a wait.  A tile's first MFMAs
 // take zero for their accumulators, no instruction clears them.
 //
-// GROUPED: the grouped form (per-row-block weight group, row count from device memory) as its own instantiation, so
-// that the dense form's code -- in particular its waits, which scalar loads in the tile-change path would disturb
-// (they share a counter with the LDS reads) -- is unaffected by it.
-//
-// NF: the forms that stand at the two ends of an RMSNorm run inside the products (their own instantiations, for the same
-// reason): the kinds that can follow a norm multiply every row by GemmArgs::rscale, EPI_RESID also writes GemmArgs::rowsq.
+// A wave has its SIMD to itself and issues an instruction in about 4 cycles, so three fit behind two 16-cycle MFMAs and every further one
+// delays the next.  Most slices are therefore run by a loop that only counts and adds to offsets; what a stream has to do at a segment's
+// or a tile's end stands in the slices at which that happens.  With the walk through those conditions in every step a slice took 2456
+// cycles, so 2282, of which 2048 are MFMAs.  Where every CU has a tile the clock follows the power and gives a part of that back: 8192 x 4096,
+// K = 14336 659 -> 618 us, 8192 x 2048, K = 2048 51.4 -> 50.3; with fewer tiles 6144 x 1536, K = 2048 44.2 -> 41.4 (42.5 on
+// v_mfma_f32_32x32x16_bf16), 6144 x 1024, K = 4096 80.5 -> 75.0 (74.6).
+
 // the stores a full tile's epilogue makes last of all (at least: 6 bits of a wait count hold no more than 63 with the eight loads)
 template <int EPI> constexpr int kEpiStores = EPI == EPI_SWIGLU ? 16 : EPI == EPI_SWIGLU_BWD ? 55 : 32;
 constexpr int meet_wait(int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14); }       // vmcnt(vm) lgkmcnt(0)
@@ -435,12 +436,21 @@ constexpr int meet_wait(int vm) { return 0x0070 | (vm & 15) | ((vm >> 4) << 14);
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t open_rsrc(const void* base, int bytes = -1) {
   const uint64_t v = (uint64_t)base;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, bytes, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-struct Stream { int vb, m0, n0, seg, k, K; bool ok; };
+// called where a branch is not expected, lambdas stay calls, and the registers they set go to memory
+#define SV_INLINE __attribute__((always_inline))
+
+struct Stream { int vb, m0, n0, seg, k, left; };
 __device__ __forceinline__ int swz16(int row) { return (row >> 1) & 7; }
 
+// GROUPED: the grouped form (per-row-block weight group, row count from device memory) as its own instantiation, so
+// that the dense form's code -- in particular its waits, which scalar loads in the tile-change path would disturb
+// (they share a counter with the LDS reads) -- is unaffected by it.
+//
+// NF: the forms that stand at the two ends of an RMSNorm run inside the products (their own instantiations, for the same
+// reason): the kinds that can follow a norm multiply every row by GemmArgs::rscale, EPI_RESID also writes GemmArgs::rowsq.
 template <int EPI, bool GROUPED, bool NF = false>
 __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tiles_m, int tiles_n) {
   constexpr bool DUAL = EPI == EPI_SWIGLU;
@@ -461,7 +471,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   const int per_xcd = (nblk + 7) >> 3;
   const int nslices = a.slices;
   const int own = a.tail ? per_xcd - tail_tiles(per_xcd, a.tail, nslices) : per_xcd;     // tiles per XCD of this launch
-  auto tile_of = [&](int vb, int& m0, int& n0) -> bool {
+  auto tile_of = [&](int vb, int& m0, int& n0) SV_INLINE -> bool {
     if (vb >= own * 8) return false;
     const int pid = (vb & 7) * per_xcd + (vb >> 3);
     if (pid >= nblk) return false;
@@ -477,31 +487,31 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
 
   // ---- the two streams of slices across this workgroup's tiles.  State: virtual block vb (tile m0, n0), segment seg, offset k in
-  // it; K is the segment's length, kept in a register (a per-slice kernel-argument load would share its wait counter with the
+  // it, `left` slices to its end, in registers (a per-slice kernel-argument load would share its wait counter with the
   // LDS reads).  A finished stream's loads go on (the loop has no branch for it) through a descriptor of no bytes, which costs no memory.
-  Stream sa{(int)blockIdx.x, 0, 0, 0, 0, 0, false};
-  sa.ok = tile_of(sa.vb, sa.m0, sa.n0);
-  if (!sa.ok) return;
+  Stream sa{(int)blockIdx.x, 0, 0, 0, 0, 0};
+  if (!tile_of(sa.vb, sa.m0, sa.n0)) return;
   Stream sb = sa;
-  __amdgpu_buffer_rsrc_t rA, rB, rB2;     // buffer descriptors of the panels the streams read: base = first row, no bound
+  const bf16 *pA, *pB, *pB2;              // first rows of the panels the streams read; their descriptors, without a bound, are made at each step
+  int a_bytes = -1, b_bytes = -1;
   unsigned voffA[8], voffB[8];
   // (the lane's number is opaque here: the offsets of a product of one segment would otherwise be kept twice)
-  auto set_a = [&](const GemmSeg& sg) {
+  auto set_a = [&](const GemmSeg& sg) SV_INLINE {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    sa.K = __builtin_amdgcn_readfirstlane(sg.K);
+    sa.left = __builtin_amdgcn_readfirstlane(sg.K) / BK;
     const unsigned lda2 = (unsigned)sg.lda * 2u;             // panels_fit: a panel's offsets have 32 bits
-    rA = open_rsrc((const bf16*)sg.A + (int64_t)sa.m0 * sg.lda);
+    pA = (const bf16*)sg.A + (int64_t)sa.m0 * sg.lda;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = (wave + 4 * i) * 8 + (ln >> 3), c = (ln & 7) ^ swz16(r);
       voffA[i] = (unsigned)min(r, M - 1 - sa.m0) * lda2 + c * 16u;      // ragged row tail: re-read the last row
     }
   };
-  auto set_b = [&](const GemmSeg& sg) {
+  auto set_b = [&](const GemmSeg& sg) SV_INLINE {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    sb.K = __builtin_amdgcn_readfirstlane(sg.K);
+    sb.left = __builtin_amdgcn_readfirstlane(sg.K) / BK;
     const unsigned ldb2 = (unsigned)sg.ldb * 2u, ldu2 = DUAL ? (unsigned)a.ldb2 * 2u : 0u;
     const int64_t goff = GROUPED ? (int64_t)a.tile_group[sb.m0 >> 8] * a.group_stride : 0;
     const bf16* B;
@@ -512,35 +522,42 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     } else {
       B = (const bf16*)sg.B + goff + (int64_t)sb.n0 * sg.ldb;
     }
-    rB = open_rsrc(B);
-    rB2 = DUAL ? open_rsrc((const bf16*)a.B2 + goff + (int64_t)sb.n0 * a.ldb2) : rB;
+    pB = B;
+    pB2 = DUAL ? (const bf16*)a.B2 + goff + (int64_t)sb.n0 * a.ldb2 : B;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int r = (wave + 4 * i) * 8 + (ln >> 3), c = (ln & 7) ^ swz16(r);
       voffB[i] = (unsigned)(DUAL ? r & 127 : r) * (DUAL && i >= 4 ? ldu2 : ldb2) + c * 16u;
     }
   };
-  auto advance = [&](Stream& s, auto&& set, auto&& close) {   // to the next slice
-    if (!s.ok) return;
+  // to the next slice, at a segment's or a tile's end with all that brings; a finished stream ends at every slice
+  auto advance = [&](Stream& s, auto&& set, auto&& close) SV_INLINE {
     s.k += BK;
-    if (s.k < s.K) return;
-    s.k = 0;
-    if (s.seg + 1 < a.nseg) { ++s.seg; set(a.seg[s.seg]); return; }
-    s.seg = 0;
-    s.vb += gridDim.x;
-    s.ok = tile_of(s.vb, s.m0, s.n0);
-    if (s.ok) set(a.seg[0]); else close();
+    s.left = __builtin_amdgcn_readfirstlane(s.left - 1);
+    if (__builtin_expect(s.left == 0, 0)) {
+      s.k = 0;
+      if (s.seg + 1 < a.nseg) { ++s.seg; set(a.seg[s.seg]); return; }
+      s.seg = 0;
+      s.vb += gridDim.x;
+      if (tile_of(s.vb, s.m0, s.n0)) { set(a.seg[0]); return; }
+      s.seg = a.nseg - 1; s.vb = own * 8; s.left = 1;
+      close();
+    }
   };
-  auto close_a = [&]() { rA = open_rsrc(a.seg[0].A, 0); };
-  auto close_b = [&]() { rB = open_rsrc(a.seg[0].B, 0); rB2 = rB; };
-  auto dma_a = [&](int buf, int i) {                          // 1 KB: the wave's i-th group of 8 rows
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i],
-                                             sa.k * 2, 0, 0);
+  auto close_a = [&]() SV_INLINE { a_bytes = 0; };
+  auto close_b = [&]() SV_INLINE { b_bytes = 0; };
+  // 1 KB: the wave's i-th group of 8 rows
+  auto dma_a = [&](__amdgpu_buffer_rsrc_t r, int k, int buf, int i) SV_INLINE {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i], k, 0, 0);
   };
-  auto dma_b = [&](int buf, int i) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(DUAL && i >= 4 ? rB2 : rB, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16,
-                                             (int)voffB[i], sb.k * 2, 0, 0);
+  auto dma_b = [&](__amdgpu_buffer_rsrc_t r, __amdgpu_buffer_rsrc_t r2, int k, int buf, int i) SV_INLINE {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(DUAL && i >= 4 ? r2 : r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16,
+                                             (int)voffB[i], k, 0, 0);
   };
+  // what the steps' loads go through: the streams' panels (SwiGLU's weights lie in two) and their slices' byte offsets
+#define SV_PANELS                                                                                                  \
+  const __amdgpu_buffer_rsrc_t rA = open_rsrc(pA, a_bytes), rB = open_rsrc(pB, b_bytes), rB2 = open_rsrc(pB2, b_bytes); \
+  int ka = __builtin_amdgcn_readfirstlane(sa.k * 2), kb = __builtin_amdgcn_readfirstlane(sb.k * 2)
   auto behind = [](int buf) { return buf == 2 * BUF ? 0 : buf + BUF; };      // the next of the activations' buffers
 
   // ---- fragment addresses: rows 16 b + (lane & 15) of an operand, chunk 4 s + (lane >> 4); swz16 does not see b
@@ -559,8 +576,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   f32x4 acc[NI][MI];
 #define SV_SB __builtin_amdgcn_sched_barrier(0)
   // One step of 32 k: MFMAs on (xc, wc), on zero accumulators if `first`; the fragments of step s of the slice in buffers ra, rw
-  // are read into (xn, wn_), and the eight loads of a stream's next slice are issued (into_w: weights) into buffer db.
-  auto step = [&](auto first, auto into_w, auto reads, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
+  // are read into (xn, wn_), and the eight loads of a stream's next slice are issued (into_w: weights) through d and d2, at offset k, into
+  // buffer db; `ends`: the stream goes on by itself (advance).
+  auto step = [&](auto first, auto into_w, auto reads, auto ends, __amdgpu_buffer_rsrc_t d, __amdgpu_buffer_rsrc_t d2, int k, bf16x8 (&xc)[MI],
+                  bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
     const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
     auto two = [&](int q) {
       const int g = q >> 2;
@@ -575,12 +594,12 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     for (int q = 0; q < 24; ++q) {                            // two MFMAs, then one memory instruction
       two(q);
       const int r = q - q / 3;
-      if (q % 3 == 2) { if (decltype(into_w)::value) dma_b(db, q / 3); else dma_a(db, q / 3); }
+      if (q % 3 == 2) { if (decltype(into_w)::value) dma_b(d, d2, k, db, q / 3); else dma_a(d, k, db, q / 3); }
       else if (decltype(reads)::value) { if (r < 8) xn[r] = read_x(ra, s, r); else wn_[r - 8] = read_w(rw, s, r - 8); }
       SV_SB;
     }
     // between MFMAs: behind the last of them its scalar chain would idle the matrix pipe
-    if (decltype(into_w)::value) advance(sb, set_b, close_b); else advance(sa, set_a, close_a);
+    if (decltype(ends)::value) { if (decltype(into_w)::value) advance(sb, set_b, close_b); else advance(sa, set_a, close_a); }
     SV_SB;
 #pragma unroll
     for (int q = 24; q < 32; ++q) two(q);
@@ -597,18 +616,24 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   constexpr int kOther = WBUF ^ (WBUF + BUF);
   set_a(a.seg[0]);
   set_b(a.seg[0]);
+  auto load_a = [&](int buf) SV_INLINE {
+    SV_PANELS;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) dma_a(0, j);
+    for (int j = 0; j < 8; ++j) dma_a(rA, ka, buf, j);
+  };
+  auto load_b = [&](int buf) SV_INLINE {
+    SV_PANELS;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) dma_b(WBUF, j);
+    for (int j = 0; j < 8; ++j) dma_b(rB, rB2, kb, buf, j);
+  };
+  load_a(0);
+  load_b(WBUF);
   advance(sa, set_a, close_a);
   advance(sb, set_b, close_b);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) dma_a(BUF, j);
+  load_a(BUF);
   advance(sa, set_a, close_a);
   SV_MEET(meet_wait(8));
-#pragma unroll
-  for (int j = 0; j < 8; ++j) dma_b(cw ^ kOther, j);
+  load_b(cw ^ kOther);
   advance(sb, set_b, close_b);
   if (!kHasInputs) {
 #pragma unroll
@@ -681,17 +706,40 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
     }
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
-    step(Yes{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+    {
+      SV_PANELS;
+      step(Yes{}, No{}, Yes{}, Yes{}, rA, rA, ka, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+    }
     ca = behind(ca); cw ^= kOther;
-    for (int kt = 1; kt < nslices; ++kt) {
+    if (nslices > 1) {
       // the tile's second slice was asked for before the last tile's results were stored: those may still be on their way
-      if (kt == 1 && stored) SV_MEET(meet_wait(8 + kEpiStores<EPI>));
-      else SV_MEET(meet_wait(8));
-      step(No{}, Yes{}, Yes{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
-      __builtin_amdgcn_s_waitcnt(kLgkm0);
       SV_SB;
-      step(No{}, No{}, Yes{}, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
-      ca = behind(ca); cw ^= kOther;
+      __builtin_amdgcn_s_waitcnt(meet_wait(8 + kEpiStores<EPI>));
+      if (!stored) __builtin_amdgcn_s_waitcnt(meet_wait(8));
+      SV_MEET(meet_wait(63));
+      for (int kt = 1;;) {
+        // the slices before one at which a stream's segment or the tile ends
+        SV_PANELS;
+        const int n = __builtin_amdgcn_readfirstlane(min(min(sa.left, sb.left), nslices - kt) - 1);
+        for (int i = 0; i < n; ++i) {
+          step(No{}, Yes{}, Yes{}, No{}, rB, rB2, kb, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+          __builtin_amdgcn_s_waitcnt(kLgkm0);
+          SV_SB;
+          step(No{}, No{}, Yes{}, No{}, rA, rA, ka, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+          ca = behind(ca); cw ^= kOther;
+          ka += BK * 2; kb += BK * 2;
+          SV_MEET(meet_wait(8));
+        }
+        kt += n;
+        sa.left -= n; sb.left -= n; sa.k += n * BK; sb.k += n * BK;
+        step(No{}, Yes{}, Yes{}, Yes{}, rB, rB2, kb, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+        __builtin_amdgcn_s_waitcnt(kLgkm0);
+        SV_SB;
+        step(No{}, No{}, Yes{}, Yes{}, rA, rA, ka, x0, w0, x1, w1, ca, cw, 1, behind(behind(ca)));
+        ca = behind(ca); cw ^= kOther;
+        if (++kt == nslices) break;
+        SV_MEET(meet_wait(8));
+      }
     }
     SV_SB;
     if (kHasInputs) {                                    // the epilogue's first inputs: their round trip hides behind the last step's products
@@ -699,7 +747,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
       for (int t = 0; t < PD; ++t) load_inputs(t, er, in_lo[t], in_hi[t]);
     }
     SV_MEET(meet_wait(8 + (kHasInputs ? PD * (EPI == EPI_SWIGLU_BWD || EPI == EPI_ROPE ? 4 : 2) : 0)));
-    step(No{}, Yes{}, std::integral_constant<bool, !kHasInputs>{}, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+    {
+      SV_PANELS;
+      step(No{}, Yes{}, std::integral_constant<bool, !kHasInputs>{}, Yes{}, rB, rB2, kb, x1, w1, x0, w0, ca, cw, 0, cw ^ kOther);
+    }
     SV_SB;
     stored = true;
 
@@ -934,11 +985,11 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     k0 = ks * BK;
     while (k0 >= a.seg[seg0].K) { k0 -= a.seg[seg0].K; ++seg0; }
   }
-  int a_seg = seg0, a_k = k0, a_K = 0, a_left = nsl, w_seg = seg0, w_k = k0, w_K = 0, w_left = nsl, a_bytes = -1, w_bytes = -1;
+  int a_seg = seg0, a_k = k0, a_dk = BK, a_turn = 0, a_left = nsl, w_seg = seg0, w_k = k0, w_dk = BK, w_turn = 0, w_left = nsl, a_bytes = -1, w_bytes = -1;
   const bf16 *pA, *pB[NI];                                // first row of the panel; of each group of 8 weight rows
   unsigned voffA[MI], voffB[NI];
-  auto set_a = [&](const GemmSeg& sg) {
-    a_K = __builtin_amdgcn_readfirstlane(sg.K);
+  auto set_a = [&](const GemmSeg& sg) SV_INLINE {
+    a_turn = min((__builtin_amdgcn_readfirstlane(sg.K) - a_k) / BK, a_left);
     pA = (const bf16*)sg.A + (int64_t)m0 * sg.lda;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -946,8 +997,8 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
       voffA[i] = (unsigned)((int64_t)min(r, M - 1 - m0) * sg.lda + c * 8) * 2u;
     }
   };
-  auto set_b = [&](const GemmSeg& sg) {
-    w_K = __builtin_amdgcn_readfirstlane(sg.K);
+  auto set_b = [&](const GemmSeg& sg) SV_INLINE {
+    w_turn = min((__builtin_amdgcn_readfirstlane(sg.K) - w_k) / BK, w_left);
     const int64_t goff = GROUPED ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -982,17 +1033,22 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffB[i],
                                              w_k * 2, 0, 0);
   };
-  auto advance_a = [&]() {
-    if (--a_left <= 0) { a_bytes = 0; a_k = 0; return; }
-    a_k += BK;
-    if (a_k < a_K) return;
-    a_k = 0; ++a_seg; set_a(a.seg[a_seg]);
+  // as in the 256x256 kernel: a countdown to the segment's or the stream's end, and nothing else in the loop's way
+  auto advance_a = [&]() SV_INLINE {
+    a_k += a_dk;
+    --a_left;
+    if (__builtin_expect(--a_turn == 0, 0)) {
+      a_k = 0;
+      if (a_left == 0) { a_bytes = 0; a_dk = 0; } else { ++a_seg; set_a(a.seg[a_seg]); }
+    }
   };
-  auto advance_b = [&]() {
-    if (--w_left <= 0) { w_bytes = 0; w_k = 0; return; }
-    w_k += BK;
-    if (w_k < w_K) return;
-    w_k = 0; ++w_seg; set_b(a.seg[w_seg]);
+  auto advance_b = [&]() SV_INLINE {
+    w_k += w_dk;
+    --w_left;
+    if (__builtin_expect(--w_turn == 0, 0)) {
+      w_k = 0;
+      if (w_left == 0) { w_bytes = 0; w_dk = 0; } else { ++w_seg; set_b(a.seg[w_seg]); }
+    }
   };
   auto next_a = [](int b) { return b == (RA - 1) * ABUF ? 0 : b + ABUF; };
   auto next_w = [](int b) { return b == W0 + (RB - 1) * WBUF ? W0 : b + WBUF; };
