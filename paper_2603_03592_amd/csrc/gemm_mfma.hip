@@ -903,6 +903,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
   __builtin_amdgcn_s_waitcnt(0);
 #undef SV_MEET
 #undef SV_SB
+#undef SV_PANELS
 }
 
 // ------------------------------------------------------------------------------------------
@@ -911,23 +912,27 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 // columns -- weight rows past the end re-read the last group of 8, outputs past the end (rows and columns) are dropped by the bounds
 // check of the buffer stores.
 //
-// What bounds it: the operands' way into LDS, 64 bytes a clock and CU, and out of it.  A 128x128 tile moves 32 KB in and 64 KB out per
-// slice of 512 matrix cycles; the 256x256 tile (half of both per multiply-add) stays the better one wherever it fills the chip.  RA
-// and RB: buffers of activations and of weights, as many as one workgroup's 160 KB or two workgroups' 80 KB hold.  The k loop is
-// the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the next step and the loads of a later slice
-// spread over the first three quarters of a step's MFMAs, activations in the one step and weights in the other, one wait and barrier a
-// slice that leaves the youngest loads in flight.  Against eight waves with their loads and reads in groups around the MFMAs of
-// a 16-wide step, us: 1024^3 on 64x64 7.7 -> 7.2; 512 x 4096, K = 4096 on 64x128 25.0 -> 21.9; 2331 x 1600, K = 960 on 64x64 23.3 -> 16.4;
-// 8192 x 2048, K = 2048 on 128x128 74.5 -> 60.6, on 256x128 64.8 -> 60.3 (one round of 8 slices: 8.4 -> 8.7 on 128x128, 10.3 -> 11.1 on
-// 256x128).
+// What bounds it: on 128x128 and 256x128 tiles the operands' way into LDS, about 40 bytes a clock and CU where all CUs load (750 and 1290
+// cycles a slice of 512 and 1024 matrix cycles; the 256x256 tile, with half the loads of the one per multiply-add, stays better wherever it fills
+// the chip); on smaller ones instructions: a wave has a SIMD to itself, or half of one, and behind each of its few MFMAs stand a load with
+// its LDS address or a fragment read.  RA and RB: buffers of activations and of weights, as many as one workgroup's 160 KB or two
+// workgroups' 80 KB hold.  The k loop is the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the
+// next step and the loads of a later slice spread over the first three quarters of a step's MFMAs, activations in the one step and
+// weights in the other, one wait and barrier a slice that leaves the youngest loads in flight; the slices at which a segment or a run ends
+// stand apart from the others, and so do the last RA - 1, which load nothing.  Before they did, us (and on eight waves with loads and reads
+// in groups around the MFMAs of a 16-wide step): 1024^3 on 64x64 6.7 -> 6.3 (7.0); 512 x 4096, K = 4096 on 64x128 24.4 -> 22.0 (26.4);
+// 1536 x 1536, K = 2048 on 128x128 16.4 -> 15.7 (16.4); 2048 x 4096, K = 4096 on 256x128 58 -> 58 (62).
 template <int MI, int NI, int RA, int RB, bool DUAL>
 struct MidCfg {
   static constexpr int BM = 32 * MI, BN = 32 * NI, NOUT = DUAL ? BN / 2 : BN;
   static constexpr int ABUF = BM * 128, WBUF = BN * 128, LDS = RA * ABUF + RB * WBUF;
   static constexpr int OCC = 2 * LDS <= 160 * 1024 ? 2 : 1;                     // workgroups on a CU
-  // the loads that are younger than slice k + 1's activations and weights when slice k has been read
-  static constexpr int YA = (RA - 2) * (MI + NI), YB = (RB - 1) * MI + (RB - 2) * NI, LEFT = YA < YB ? YA : YB;
-  static_assert(LDS <= 160 * 1024 && RA >= RB && RB >= 2 && LEFT < 64 && (!DUAL || NI % 4 == 0), "tile shape");
+  // The loads that may be in flight when a slice with `j` more behind it is to be complete: those of the slices behind it, of which the
+  // activations are RA - 2 ahead and the weights RB - 2.  (All of them are younger than that slice's, as long as the activations'
+  // ring is at most one longer.)
+  static constexpr int left(int j) { return (j < RA - 2 ? j : RA - 2) * MI + (j < RB - 2 ? j : RB - 2) * NI; }
+  static constexpr int LEFT = left(RA);
+  static_assert(LDS <= 160 * 1024 && RA >= RB && RA <= RB + 1 && RB >= 2 && LEFT < 64 && (!DUAL || NI % 4 == 0), "tile shape");
 };
 
 //
@@ -940,6 +945,7 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   constexpr bool DUAL = EPI == EPI_SWIGLU;
   static_assert(!SPLIT || (EPI == EPI_STORE && !GROUPED), "a split run stores bare partial products");
   static_assert(!SUMMED || (!DUAL && !GROUPED && !SPLIT), "one sum of runs per output");
+  static_assert(NI <= 4 || (EPI != EPI_STORE && EPI != EPI_ROPE), "a panel for each group of weight rows");
   using C = MidCfg<MI, NI, RA, RB, DUAL>;
   constexpr int BM = C::BM, BN = C::BN, ABUF = C::ABUF, WBUF = C::WBUF, W0 = RA * ABUF;     // weights' buffers from W0
   constexpr int kGroup = BM >= 256 ? 4 : BM >= 128 ? 8 : 16;          // row tiles per raster group: about 1024 rows
@@ -976,8 +982,7 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, lhi = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
 
-  // ---- the two streams of slices: segment seg, offset k in it, `left` slices to go; past the last one a stream's loads go through a
-  // descriptor of no bytes (read again, the last slices were up to half of a short product's traffic)
+  // ---- the two streams of slices: segment seg, offset k in it, `turn` slices to its end
   int nsl = a.slices, seg0 = 0, k0 = 0;
   if (SPLIT) {                                            // run r takes the slices [r * nsl / nsplit, (r + 1) * nsl / nsplit)
     const int ks = (int)((int64_t)run * nsl / nsplit);
@@ -985,11 +990,16 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     k0 = ks * BK;
     while (k0 >= a.seg[seg0].K) { k0 -= a.seg[seg0].K; ++seg0; }
   }
-  int a_seg = seg0, a_k = k0, a_dk = BK, a_turn = 0, a_left = nsl, w_seg = seg0, w_k = k0, w_dk = BK, w_turn = 0, w_left = nsl, a_bytes = -1, w_bytes = -1;
-  const bf16 *pA, *pB[NI];                                // first row of the panel; of each group of 8 weight rows
+  int a_seg = seg0, a_k = k0, a_turn = 0, w_seg = seg0, w_k = k0, w_turn = 0;
+  // The weights' panels: the tile's columns lie in one matrix, or in gate and up, but for products over column blocks of several matrices,
+  // where every group of 8 rows has a panel of its own.
+  constexpr bool OWN = EPI == EPI_STORE || EPI == EPI_ROPE;
+  constexpr int NP = OWN ? NI : DUAL ? 2 : 1;
+  auto panel = [](int i) SV_INLINE { return OWN ? i : DUAL ? i / (NI / 2) : 0; };
+  const bf16 *pA, *pB[NP];                                // first rows of the panels
   unsigned voffA[MI], voffB[NI];
   auto set_a = [&](const GemmSeg& sg) SV_INLINE {
-    a_turn = min((__builtin_amdgcn_readfirstlane(sg.K) - a_k) / BK, a_left);
+    a_turn = (__builtin_amdgcn_readfirstlane(sg.K) - a_k) / BK;
     pA = (const bf16*)sg.A + (int64_t)m0 * sg.lda;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -998,57 +1008,57 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     }
   };
   auto set_b = [&](const GemmSeg& sg) SV_INLINE {
-    w_turn = min((__builtin_amdgcn_readfirstlane(sg.K) - w_k) / BK, w_left);
-    const int64_t goff = GROUPED ? (int64_t)a.tile_group[m0 >> 8] * a.group_stride : 0;
+    w_turn = (__builtin_amdgcn_readfirstlane(sg.K) - w_k) / BK;
+    const int64_t goff = GROUPED ? (int64_t)__builtin_amdgcn_readfirstlane(a.tile_group[m0 >> 8]) * a.group_stride : 0;
+    const bf16* B0 = (const bf16*)sg.B + goff;
+    if (!OWN) pB[0] = B0 + (int64_t)n0 * sg.ldb;
+    if (DUAL) pB[NP - 1] = (const bf16*)a.B2 + goff + (int64_t)n0 * a.ldb2;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int g = (wave + 4 * i) * 8, r = g + (lane >> 3), c = (lane & 7) ^ swz16(r);
-      const bf16* B = (const bf16*)sg.B + goff;
-      int64_t ldb = sg.ldb;
-      int row;                                            // the group's first weight row
-      if (DUAL) {
-        const bool up = g >= BN / 2;
-        if (up) { B = (const bf16*)a.B2 + goff; ldb = a.ldb2; }
-        row = min(n0 + (up ? g - BN / 2 : g), a.N - 8);
-      } else {
-        row = min(n0 + g, a.N - 8);
-        if ((EPI == EPI_STORE || EPI == EPI_ROPE) && a.nbcol > 0) {
+      const int64_t ldb = DUAL && panel(i) ? a.ldb2 : sg.ldb;
+      int row = min(n0 + g - (DUAL ? panel(i) * (BN / 2) : 0), a.N - 8);      // the group's first weight row
+      if (OWN) {
+        const bf16* B = B0;
+        if (a.nbcol > 0) {
           const int o1 = a.ncol[0], o2 = o1 + a.ncol[1];
           if (a.nbcol > 2 && row >= o2) { B = (const bf16*)a.Bcol[2]; row -= o2; }
           else if (a.nbcol > 1 && row >= o1) { B = (const bf16*)a.Bcol[1]; row -= o1; }
           else B = (const bf16*)a.Bcol[0];
         }
+        pB[panel(i)] = B + (int64_t)row * ldb;
+        row = 0;
+      } else {
+        row -= n0;
       }
-      pB[i] = B + (int64_t)row * ldb;
-      voffB[i] = (unsigned)((int64_t)(lane >> 3) * ldb + c * 8) * 2u;
+      voffB[i] = (unsigned)((int64_t)(row + (lane >> 3)) * ldb + c * 8) * 2u;
     }
   };
-  auto dma_a = [&](int buf, int i) {                      // 1 KB: the wave's i-th group of 8 rows
-    const __amdgpu_buffer_rsrc_t r = open_rsrc(pA, a_bytes);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i],
-                                             a_k * 2, 0, 0);
-  };
-  auto dma_b = [&](int buf, int i) {
-    const __amdgpu_buffer_rsrc_t r = open_rsrc(pB[i], w_bytes);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffB[i],
-                                             w_k * 2, 0, 0);
-  };
-  // as in the 256x256 kernel: a countdown to the segment's or the stream's end, and nothing else in the loop's way
+  // to the next slice, at a segment's end with all that brings (behind the last one there is none)
   auto advance_a = [&]() SV_INLINE {
-    a_k += a_dk;
-    --a_left;
-    if (__builtin_expect(--a_turn == 0, 0)) {
-      a_k = 0;
-      if (a_left == 0) { a_bytes = 0; a_dk = 0; } else { ++a_seg; set_a(a.seg[a_seg]); }
-    }
+    a_k += BK;
+    if (__builtin_expect(--a_turn == 0 && a_seg + 1 < a.nseg, 0)) { a_k = 0; ++a_seg; set_a(a.seg[a_seg]); }
   };
   auto advance_b = [&]() SV_INLINE {
-    w_k += w_dk;
-    --w_left;
-    if (__builtin_expect(--w_turn == 0, 0)) {
-      w_k = 0;
-      if (w_left == 0) { w_bytes = 0; w_dk = 0; } else { ++w_seg; set_b(a.seg[w_seg]); }
-    }
+    w_k += BK;
+    if (__builtin_expect(--w_turn == 0 && w_seg + 1 < a.nseg, 0)) { w_k = 0; ++w_seg; set_b(a.seg[w_seg]); }
+  };
+  // what the steps' loads go through: the activations' panel, the groups of 8 weight rows, the slices' byte offsets
+#define SV_PANELS                                                                                                                         \
+  const __amdgpu_buffer_rsrc_t rA = open_rsrc(pA), rB0 = open_rsrc(pB[0]), rB1 = open_rsrc(pB[NP > 1 ? 1 : 0]), \
+                               rB2 = open_rsrc(pB[NP > 2 ? 2 : 0]), rB3 = open_rsrc(pB[NP > 2 ? 3 : 0]);                \
+  int ka = __builtin_amdgcn_readfirstlane(a_k * 2), kb = __builtin_amdgcn_readfirstlane(w_k * 2)
+#define SV_PANEL_ARGS rA, rB0, rB1, rB2, rB3
+#define SV_PANEL_PARAMS                                                                                                                   \
+  __amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB0, __amdgpu_buffer_rsrc_t rB1, __amdgpu_buffer_rsrc_t rB2, __amdgpu_buffer_rsrc_t rB3
+  // 1 KB: the wave's i-th group of 8 rows
+  auto dma_a = [&](SV_PANEL_PARAMS, int k, int buf, int i) SV_INLINE {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffA[i], k, 0, 0);
+  };
+  auto dma_b = [&](SV_PANEL_PARAMS, int k, int buf, int i) SV_INLINE {
+    const int j = panel(i);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(j == 0 ? rB0 : j == 1 ? rB1 : j == 2 ? rB2 : rB3,
+                                             (__attribute__((address_space(3))) void*)(smem + buf + (wave + 4 * i) * 1024), 16, (int)voffB[i], k, 0, 0);
   };
   auto next_a = [](int b) { return b == (RA - 1) * ABUF ? 0 : b + ABUF; };
   auto next_w = [](int b) { return b == W0 + (RB - 1) * WBUF ? W0 : b + WBUF; };
@@ -1123,7 +1133,8 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
 #define SV_SB __builtin_amdgcn_sched_barrier(0)
 #define SV_MEET(imm) do { SV_SB; __builtin_amdgcn_s_waitcnt(imm); asm volatile("s_barrier" ::: "memory"); SV_SB; } while (0)
   constexpr int kLgkm0 = 0xc07f;                           // lgkmcnt(0), nothing else
-  auto step = [&](auto first, auto into_w, auto last, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI], bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
+  auto step = [&](auto first, auto into_w, auto reads, auto loads, auto ends, SV_PANEL_PARAMS, int k, bf16x8 (&xc)[MI], bf16x8 (&wc)[NI], bf16x8 (&xn)[MI],
+                  bf16x8 (&wn_)[NI], int ra, int rw, int s, int db) {
     constexpr bool W = decltype(into_w)::value;
     constexpr int ND = W ? NI : MI, NMEM = MI + NI + ND, NM = MI * NI, SPAN = NM * 3 / 4;
     const f32x4 zero{0.0f, 0.0f, 0.0f, 0.0f};
@@ -1140,14 +1151,15 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int q = lo + i, d = q * ND / NMEM, r = q - d;
-        if (q >= hi || decltype(last)::value) continue;
-        if ((q + 1) * ND / NMEM > d) { if (W) dma_b(db, d); else dma_a(db, d); }
+        const bool load = (q + 1) * ND / NMEM > d;
+        if (q >= hi || !(load ? decltype(loads)::value : decltype(reads)::value)) continue;
+        if (load) { if (W) dma_b(SV_PANEL_ARGS, k, db, d); else dma_a(SV_PANEL_ARGS, k, db, d); }
         else if (r < MI) xn[r] = read_x(ra, s, r);
         else wn_[r - MI] = read_w(rw, s, r - MI);
         SV_SB;
       }
     }
-    if (!decltype(last)::value) { if (W) advance_b(); else advance_a(); }  // between MFMAs, as there
+    if (decltype(ends)::value) { if (W) advance_b(); else advance_a(); }   // between MFMAs, as there
     SV_SB;
 #pragma unroll
     for (int f = SPAN; f < NM; ++f) mul(f);
@@ -1157,14 +1169,17 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   SV_SB;
   set_a(a.seg[SPLIT ? seg0 : 0]);
   set_b(a.seg[SPLIT ? seg0 : 0]);
+  // Slices past the last are not loaded (from memory or as zeros, they were up to half of a short product's way into LDS).
 #pragma unroll
   for (int s = 0; s + 1 < RA; ++s) {
+    if (s > 0 && s >= nsl) continue;
+    SV_PANELS;
 #pragma unroll
-    for (int j = 0; j < MI; ++j) dma_a(s * ABUF, j);
+    for (int j = 0; j < MI; ++j) dma_a(SV_PANEL_ARGS, ka, s * ABUF, j);
     advance_a();
     if (s + 1 < RB) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j) dma_b(W0 + s * WBUF, j);
+      for (int j = 0; j < NI; ++j) dma_b(SV_PANEL_ARGS, kb, W0 + s * WBUF, j);
       advance_b();
     }
   }
@@ -1178,16 +1193,29 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     run_end = nsl / runs;
   }
   int ca = 0, cw = W0;                                     // the buffers of the slice being multiplied
-  SV_MEET(meet_wait(C::LEFT));
+  // this wave's wait for a slice with j more behind it, then the workgroup's barrier: everybody's loads of that slice have landed, their
+  // reads of the one before are done
+  auto meet = [&](int j) SV_INLINE {
+    SV_SB;
+    if (j >= RA - 2) __builtin_amdgcn_s_waitcnt(meet_wait(C::LEFT));
+    if (j == 0) __builtin_amdgcn_s_waitcnt(meet_wait(C::left(0)));
+    if (RA > 3 && j == 1) __builtin_amdgcn_s_waitcnt(meet_wait(C::left(1)));
+    if (RA > 4 && j == 2) __builtin_amdgcn_s_waitcnt(meet_wait(C::left(2)));
+    SV_MEET(meet_wait(63));
+  };
+  meet(nsl - 1);
+  if (nsl >= RB) {
+    SV_PANELS;
 #pragma unroll
-  for (int j = 0; j < NI; ++j) dma_b(last_w(cw), j);
-  advance_b();
+    for (int j = 0; j < NI; ++j) dma_b(SV_PANEL_ARGS, kb, last_w(cw), j);
+    advance_b();
+  }
 #pragma unroll
   for (int b = 0; b < MI; ++b) x0[b] = read_x(ca, 0, b);
 #pragma unroll
   for (int b = 0; b < NI; ++b) w0[b] = read_w(cw, 0, b);
   // SUMMED: the accumulators go to the total and begin again
-  auto end_run = [&](auto summed) {
+  auto end_run = [&](auto summed) SV_INLINE {
     if constexpr (decltype(summed)::value) {
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
@@ -1202,21 +1230,71 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
       run_end = (int)((int64_t)(run_i + 1) * nsl / runs);
     }
   };
+  using Yes = std::true_type;
+  using No = std::false_type;
   __builtin_amdgcn_s_waitcnt(kLgkm0);
   SV_SB;
-  step(std::true_type{}, std::false_type{}, std::false_type{}, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+  if (nsl >= RA) {
+    SV_PANELS;
+    step(Yes{}, No{}, Yes{}, Yes{}, Yes{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+  } else {
+    SV_PANELS;
+    step(Yes{}, No{}, Yes{}, No{}, No{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+  }
   ca = next_a(ca); cw = next_w(cw);
-  for (int kt = 1; kt < nsl; ++kt) {
-    SV_MEET(meet_wait(C::LEFT));                           // everybody's loads of slice kt have landed, their reads of slice kt - 1 are done
-    step(std::false_type{}, std::true_type{}, std::false_type{}, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+  meet(nsl - 2);
+  int kt = 1;
+  while (kt <= nsl - RA) {
+    // the slices before one at which a stream's segment or a run ends: as in the 256x256 kernel
+    SV_PANELS;
+    int n = min(min(a_turn, w_turn) - 1, nsl - RA - kt + 1);
+    if (SUMMED && run_end >= kt) n = min(n, run_end - kt);
+    n = __builtin_amdgcn_readfirstlane(n);
+    for (int i = 0; i < n; ++i) {
+      step(No{}, Yes{}, Yes{}, Yes{}, No{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+      __builtin_amdgcn_s_waitcnt(kLgkm0);
+      SV_SB;
+      step(No{}, No{}, Yes{}, Yes{}, No{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+      ca = next_a(ca); cw = next_w(cw);
+      ka += BK * 2; kb += BK * 2;
+      SV_MEET(meet_wait(C::LEFT));
+    }
+    kt += n;
+    a_turn -= n; a_k += n * BK;
+    w_turn -= n; w_k += n * BK;
+    if (kt > nsl - RA) break;
+    step(No{}, Yes{}, Yes{}, Yes{}, Yes{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
     if (SUMMED && kt == run_end) end_run(std::integral_constant<bool, SUMMED>{});
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
-    step(std::false_type{}, std::false_type{}, std::false_type{}, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+    step(No{}, No{}, Yes{}, Yes{}, Yes{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
     ca = next_a(ca); cw = next_w(cw);
+    ++kt;
+    SV_MEET(meet_wait(C::LEFT));
   }
-  SV_MEET(meet_wait(C::LEFT));
-  step(std::false_type{}, std::true_type{}, std::true_type{}, x1, w1, x0, w0, ca, cw, 0, last_w(cw));     // without reads and loads
+  // the last slices, with j more behind each: their activations are on their way, and so are their weights but for one slice's where the
+  // activations' ring is the longer
+  auto ending = [&](auto jc) SV_INLINE {
+    constexpr int j = decltype(jc)::value;
+    if (nsl < j + 2) return;
+    SV_PANELS;
+    step(No{}, Yes{}, Yes{}, std::integral_constant<bool, (j >= RB - 1)>{}, No{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+    if (SUMMED && nsl - 1 - j == run_end) end_run(std::integral_constant<bool, SUMMED>{});
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    SV_SB;
+    step(No{}, No{}, Yes{}, No{}, No{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
+    ca = next_a(ca); cw = next_w(cw);
+    SV_MEET(meet_wait(C::left(j > 0 ? j - 1 : 0)));
+  };
+  if constexpr (RA > 4) ending(std::integral_constant<int, 3>{});
+  if constexpr (RA > 3) ending(std::integral_constant<int, 2>{});
+  ending(std::integral_constant<int, 1>{});
+  ending(std::integral_constant<int, 0>{});
+  static_assert(RA >= 3 && RA <= 5, "the last slices");
+  {
+    SV_PANELS;
+    step(No{}, Yes{}, No{}, No{}, No{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+  }
   end_run(std::integral_constant<bool, SUMMED>{});
 
   // ---- epilogue.  A row of a patch: 4 NI chunks of 16 bytes (4 features), those of a lane's 8 columns LPR apart, XOR-swizzled by the row.
@@ -1274,9 +1352,11 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     }
     __builtin_amdgcn_wave_barrier();                       // the reads of this block are issued before the next block's writes
   }
-  __builtin_amdgcn_s_waitcnt(0);                           // every load has written its zeros before the workgroup gives its LDS back
 #undef SV_MEET
 #undef SV_SB
+#undef SV_PANELS
+#undef SV_PANEL_ARGS
+#undef SV_PANEL_PARAMS
 }
 
 inline int k_slices(const GemmArgs& a) {
