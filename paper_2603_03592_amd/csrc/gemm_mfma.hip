@@ -915,10 +915,10 @@ __global__ __launch_bounds__(256) void gemm_mfma_dma_kernel(GemmArgs a, int tile
 // What bounds it: on 128x128 and 256x128 tiles the operands' way into LDS, about 40 bytes a clock and CU where all CUs load (750 and 1290
 // cycles a slice of 512 and 1024 matrix cycles; the 256x256 tile, with half the loads of the one per multiply-add, stays better wherever it fills
 // the chip); on smaller ones instructions: a wave has a SIMD to itself, or half of one, and behind each of its few MFMAs stand a load with
-// its LDS address or a fragment read.  RA and RB: buffers of activations and of weights, as many as one workgroup's 160 KB or two
-// workgroups' 80 KB hold.  The k loop is the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the
+// its LDS address or a fragment read.  RA and RB: buffers of activations and of weights, within one workgroup's 160 KB or two
+// workgroups' 80 KB.  The k loop is the 256x256 kernel's: two steps of 32 k a slice on 16x16x32 MFMAs, the fragment reads of the
 // next step and the loads of a later slice spread over the first three quarters of a step's MFMAs, activations in the one step and
-// weights in the other, one wait and barrier a slice that leaves the youngest loads in flight; the slices at which a segment or a run ends
+// weights in the other, one wait and barrier a slice that leaves the youngest loads in flight; the slices at which a segment ends
 // stand apart from the others, and so do the last RA - 1, which load nothing.  Before they did, us (and on eight waves with loads and reads
 // in groups around the MFMAs of a 16-wide step): 1024^3 on 64x64 6.7 -> 6.3 (7.0); 512 x 4096, K = 4096 on 64x128 24.4 -> 22.0 (26.4);
 // 1536 x 1536, K = 2048 on 128x128 16.4 -> 15.7 (16.4); 2048 x 4096, K = 4096 on 256x128 58 -> 58 (62).
@@ -1079,8 +1079,11 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   };
   const unsigned vcol = n < a.N ? (unsigned)n : SPLIT ? 0x20000000u : 0x40000000u;     // byte offset 2^31: past every descriptor's end
   const bool rscaled = kEpiScaled<EPI> && !GROUPED && !SPLIT && a.rscale;
+  // Plain and SwiGLU results are formed in the accumulators' layout, where a lane's values of a row block are of one row, and turned over in bf16.
+  // (GELU, with so much arithmetic in front of the LDS writes: 30.9 -> 32.7 us for 2331 x 3840, K = 960 on 192x256.)
+  constexpr bool kPacked = (EPI == EPI_STORE && !SPLIT) || EPI == EPI_SWIGLU;
   EpiIn in_lo[2][TR], in_hi[2][TR];
-  float rs[2][TR];
+  float rs[2][TR], rs_row[kPacked ? MI : 1];
   int rope_p0 = 0, rope_i0 = 0;
   if (EPI == EPI_ROPE) { rope_p0 = (m0 + mw) % a.rope_S; rope_i0 = (n % a.rope_hd) >> 1; }
   auto ld16 = [&](__amdgpu_buffer_rsrc_t b, unsigned vo, bf16x4& lo, bf16x4& hi) {
@@ -1107,7 +1110,7 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
         }
       }
     }
-    if (kEpiScaled<EPI>) {
+    if (kEpiScaled<EPI> && !kPacked) {
 #pragma unroll
       for (int t = 0; t < TR; ++t) f[t] = 1.0f;
       if (rscaled) {
@@ -1165,7 +1168,14 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     for (int f = SPAN; f < NM; ++f) mul(f);
   };
 
-  if (!SPLIT) load_inputs(0, in_lo[0], in_hi[0], rs[0]);   // older than every slice: in order, so landed when the first has
+  if (kPacked) {
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) rs_row[mi] = 1.0f;
+    if (rscaled) {
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) rs_row[mi] = a.rscale[min(m0 + mw + mi * 16 + l15, M - 1)];
+    }
+  } else if (!SPLIT) load_inputs(0, in_lo[0], in_hi[0], rs[0]);      // older than every slice: in order, so landed when the first has
   SV_SB;
   set_a(a.seg[SPLIT ? seg0 : 0]);
   set_b(a.seg[SPLIT ? seg0 : 0]);
@@ -1245,13 +1255,13 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   meet(nsl - 2);
   int kt = 1;
   while (kt <= nsl - RA) {
-    // the slices before one at which a stream's segment or a run ends: as in the 256x256 kernel
+    // the slices before one at which a stream's segment ends: as in the 256x256 kernel
     SV_PANELS;
     int n = min(min(a_turn, w_turn) - 1, nsl - RA - kt + 1);
-    if (SUMMED && run_end >= kt) n = min(n, run_end - kt);
     n = __builtin_amdgcn_readfirstlane(n);
     for (int i = 0; i < n; ++i) {
       step(No{}, Yes{}, Yes{}, Yes{}, No{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
+      if (SUMMED && __builtin_expect(kt + i == run_end, 0)) end_run(std::integral_constant<bool, SUMMED>{});
       __builtin_amdgcn_s_waitcnt(kLgkm0);
       SV_SB;
       step(No{}, No{}, Yes{}, Yes{}, No{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
@@ -1264,7 +1274,7 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     w_turn -= n; w_k += n * BK;
     if (kt > nsl - RA) break;
     step(No{}, Yes{}, Yes{}, Yes{}, Yes{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
-    if (SUMMED && kt == run_end) end_run(std::integral_constant<bool, SUMMED>{});
+    if (SUMMED && __builtin_expect(kt == run_end, 0)) end_run(std::integral_constant<bool, SUMMED>{});
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
     step(No{}, No{}, Yes{}, Yes{}, Yes{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
@@ -1279,7 +1289,7 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
     if (nsl < j + 2) return;
     SV_PANELS;
     step(No{}, Yes{}, Yes{}, std::integral_constant<bool, (j >= RB - 1)>{}, No{}, SV_PANEL_ARGS, kb, x1, w1, x0, w0, ca, cw, 0, last_w(cw));
-    if (SUMMED && nsl - 1 - j == run_end) end_run(std::integral_constant<bool, SUMMED>{});
+    if (SUMMED && __builtin_expect(nsl - 1 - j == run_end, 0)) end_run(std::integral_constant<bool, SUMMED>{});
     __builtin_amdgcn_s_waitcnt(kLgkm0);
     SV_SB;
     step(No{}, No{}, Yes{}, No{}, No{}, SV_PANEL_ARGS, ka, x0, w0, x1, w1, ca, cw, 1, last_a(ca));
@@ -1297,60 +1307,109 @@ __global__ __launch_bounds__(256, (MidCfg<MI, NI, RA, RB, EPI == EPI_SWIGLU>::OC
   }
   end_run(std::integral_constant<bool, SUMMED>{});
 
-  // ---- epilogue.  A row of a patch: 4 NI chunks of 16 bytes (4 features), those of a lane's 8 columns LPR apart, XOR-swizzled by the row.
-  // The patches lie in the weights' buffer that everybody has read and no load is on its way to.
+  // ---- epilogue.  The patches lie in the weights' buffer that everybody has read and no load is on its way to.  A wave's LDS accesses are
+  // served in their order: block mi + 1 is on its way into the patch and out of it while block mi's results are formed or stored, with no
+  // wait between its writes and reads.
   char* patch = smem + last_w(cw) + wave * (NI * 1024);
   const __amdgpu_buffer_rsrc_t bC = SPLIT ? desc(a.split_ws + (int64_t)run * M * a.N, a.N, 4) : desc(a.C, a.ldc, 2);
   const __amdgpu_buffer_rsrc_t bC2 = desc(a.C2, a.ldc, 2), bC3 = desc(a.C3, a.ldc, 2);
-  auto mix = [](int row) { return (row >> (NI == 2 ? 1 : 0)) & (2 * NI - 1); };
+  const bool keeps2 = EPI == EPI_SWIGLU_BWD || ((EPI == EPI_GELU || EPI == EPI_SWIGLU) && a.C2), keeps3 = EPI == EPI_SWIGLU && a.C3;
+  if constexpr (kPacked) {
+    // A row of a patch: LPR chunks of 16 bytes (8 features), XOR-swizzled by the row; a patch for each output.  Half of the LDS traffic of fp32
+    // patches: 3000 x 1536 on 256x128, K = 512 10.8 -> 10.3 us.
+    constexpr int PB = 16 * LPR * 16;
+    static_assert((DUAL ? 3 : 1) * PB <= NI * 1024, "the patches lie in the wave's part of the buffer");
+    auto mix = [](int row) { return LPR == 16 ? row : LPR == 8 ? row >> 1 : row >> 2; };
+    bf16x8 out[2][TR][3];
+    auto turn_over = [&](int mi) SV_INLINE {
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    if (!SPLIT && mi + 1 < MI) load_inputs(mi + 1, in_lo[(mi + 1) & 1], in_hi[(mi + 1) & 1], rs[(mi + 1) & 1]);
+      for (int ni = 0; ni < (DUAL ? NI / 2 : NI); ++ni) {
+        float v[4], u[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          v[i] = SUMMED ? tot[SUMMED ? ni : 0][SUMMED ? mi : 0][i] : acc[ni][mi][i];
+          u[i] = DUAL ? acc[DUAL ? ni + NI / 2 : ni][mi][i] : 0.0f;
+        }
+        char* const at = patch + l15 * (LPR * 16) + (((ni * 2 + (lhi >> 1)) ^ mix(l15)) << 4) + (lhi & 1) * 8;
+        epilogue_math4<EPI>(a, false, v, u, EpiIn{}, rs_row[mi], [&](int w, bf16x4 x) { *reinterpret_cast<bf16x4*>(at + w * PB) = x; });
+      }
+      SV_SB;
+#pragma unroll
+      for (int t = 0; t < TR; ++t) {
+        const char* const at = patch + (t * RPI + er) * (LPR * 16) + ((ec ^ mix(t * RPI + er)) << 4);
+        out[mi & 1][t][0] = *reinterpret_cast<const bf16x8*>(at);
+        if (keeps2) out[mi & 1][t][1] = *reinterpret_cast<const bf16x8*>(at + PB);
+        if (keeps3) out[mi & 1][t][2] = *reinterpret_cast<const bf16x8*>(at + 2 * PB);
+      }
+      SV_SB;
+    };
+    turn_over(0);
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+      if (mi + 1 < MI) turn_over(mi + 1);
+#pragma unroll
+      for (int t = 0; t < TR; ++t) {
+        const int vo = (int)(((unsigned)((mw + mi * 16 + t * RPI + er) * (int)a.ldc) + vcol) * 2u);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[mi & 1][t][0]), bC, vo, 0, 0);
+        if (keeps2) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[mi & 1][t][1]), bC2, vo, 0, 0);
+        if (keeps3) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, out[mi & 1][t][2]), bC3, vo, 0, 0);
+      }
+      SV_SB;
+    }
+    return;
+  }
+  // With inputs, and for partial products, in fp32.  A row of a patch: 4 NI chunks of 16 bytes (4 features), those of a lane's 8 columns LPR
+  // apart, XOR-swizzled by the row.
+  auto mix = [](int row) { return (row >> (NI == 2 ? 1 : 0)) & (2 * NI - 1); };
+  f32x4 lo[2][TR], hi[2][TR];
+  auto turn_over = [&](int mi) SV_INLINE {
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
-      const bool up = DUAL && ni >= NI / 2;
-      const int slot = (up ? ni - NI / 2 : ni) * 2 + (lhi >> 1) + (lhi & 1) * LPR + (up ? 2 * NI : 0);
+      const int slot = ni * 2 + (lhi >> 1) + (lhi & 1) * LPR;
       *reinterpret_cast<f32x4*>(patch + l15 * (NI * 64) + ((slot ^ mix(l15)) << 4)) = SUMMED ? tot[SUMMED ? ni : 0][SUMMED ? mi : 0] : acc[ni][mi];
     }
-    __builtin_amdgcn_s_waitcnt(kLgkm0);
-    __builtin_amdgcn_wave_barrier();
-    f32x4 lo[TR], hi[TR], ulo[TR], uhi[TR];
+    SV_SB;
 #pragma unroll
     for (int t = 0; t < TR; ++t) {
       const int row = t * RPI + er;
       auto at = [&](int slot) { return *reinterpret_cast<const f32x4*>(patch + row * (NI * 64) + ((slot ^ mix(row)) << 4)); };
-      lo[t] = at(ec); hi[t] = at(LPR + ec);
-      if (DUAL) { ulo[t] = at(2 * NI + ec); uhi[t] = at(2 * NI + LPR + ec); }
+      lo[mi & 1][t] = at(ec); hi[mi & 1][t] = at(LPR + ec);
     }
+    SV_SB;
+  };
+  turn_over(0);
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    if (!SPLIT && mi + 1 < MI) load_inputs(mi + 1, in_lo[(mi + 1) & 1], in_hi[(mi + 1) & 1], rs[(mi + 1) & 1]);
+    if (mi + 1 < MI) turn_over(mi + 1);
 #pragma unroll
     for (int t = 0; t < TR; ++t) {
       const int r = mw + mi * 16 + t * RPI + er;
       if (SPLIT) {
         const int vo = (int)(((unsigned)(r * a.N) + vcol) * 4u);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo[t]), bC, vo, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi[t]), bC, vo + 16, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo[mi & 1][t]), bC, vo, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi[mi & 1][t]), bC, vo + 16, 0, 0);
         continue;
       }
       const int vo = (int)(((unsigned)(r * (int)a.ldc) + vcol) * 2u);
       const bool roped = EPI == EPI_ROPE && n < a.rope_cols;
       const float f = kEpiScaled<EPI> ? rs[mi & 1][t] : 1.0f;
       bf16x4 o[2][3];
-      auto half = [&](int h, const f32x4& x, const f32x4& y, const EpiIn& e) {
+      auto half = [&](int h, const f32x4& x, const EpiIn& e) {
         float v[4], u[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { v[i] = x[i]; u[i] = DUAL ? y[i] : 0.0f; }
+        for (int i = 0; i < 4; ++i) { v[i] = x[i]; u[i] = 0.0f; }
         epilogue_math4<EPI>(a, roped, v, u, e, f, [&](int w, bf16x4 p) { o[h][w] = p; });
       };
-      half(0, lo[t], DUAL ? ulo[t] : lo[t], in_lo[mi & 1][t]);
-      half(1, hi[t], DUAL ? uhi[t] : hi[t], in_hi[mi & 1][t]);
+      half(0, lo[mi & 1][t], in_lo[mi & 1][t]);
+      half(1, hi[mi & 1][t], in_hi[mi & 1][t]);
       auto put = [&](const __amdgpu_buffer_rsrc_t& b, int w) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, __builtin_shufflevector(o[0][w], o[1][w], 0, 1, 2, 3, 4, 5, 6, 7)), b, vo, 0, 0);
       };
       put(bC, 0);
-      if (EPI == EPI_SWIGLU_BWD || ((EPI == EPI_GELU || EPI == EPI_SWIGLU) && a.C2)) put(bC2, 1);
-      if (EPI == EPI_SWIGLU && a.C3) put(bC3, 2);
+      if (keeps2) put(bC2, 1);
     }
-    __builtin_amdgcn_wave_barrier();                       // the reads of this block are issued before the next block's writes
+    SV_SB;
   }
 #undef SV_MEET
 #undef SV_SB
@@ -1534,8 +1593,8 @@ int tail_pays(const GemmArgs& a) {
 }
 
 // 128x128 tiles: two workgroups of 80 KB on a CU where there are tiles for them (4096 x 3072, K = 1024 28.0 -> 25.8 us, 8192 x 1024 19.6 ->
-// 17.9; 8192 x 768 with rotation and settled sums, K = 512 23.0 -> 16.6), one with twice the buffers where every tile has a CU of its own
-// (4096 x 1024, K = 2816 23.4 us against 26.2).
+// 17.9; 8192 x 768 with rotation and settled sums, K = 512 23.0 -> 16.6), one with four buffers of each operand where every tile has a CU
+// of its own (2304 x 960, K = 960 from memory 13.3 us against 15.2; with five and four of them, 16 KB more to fill before the first MFMA, 13.6).
 bool two_per_cu(const GemmArgs& a, int runs) {
   const int nout = a.epi == EPI_SWIGLU ? 64 : 128;
   return (int64_t)((a.M + 127) / 128) * ((a.N + nout - 1) / nout) * runs > cu_count();
@@ -1558,7 +1617,7 @@ hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
         g.tail = tile_slots();
         hipError_t e = g.rscale ? launch_dma_nf<EPI, GROUPED>(g, st) : launch_dma<EPI, GROUPED>(g, st);
         if (e != hipSuccess) return e;
-        if (GROUPED || 4 * left <= g.tail) return launch_mid<4, 4, 5, 4, EPI, GROUPED, false, false, true>(g, 1, st, left);
+        if (GROUPED || 4 * left <= g.tail) return launch_mid<4, 4, 4, 4, EPI, GROUPED, false, false, true>(g, 1, st, left);
         if constexpr (!GROUPED) return launch_mid<8, 4, 3, 3, EPI, false, false, false, true>(g, 1, st, left);
       }
       if constexpr (!GROUPED && EPI != EPI_SWIGLU_BWD && EPI != EPI_GELU_BWD)
@@ -1566,7 +1625,7 @@ hipError_t launch_tile(const GemmArgs& a, int kind, hipStream_t st) {
       return launch_dma<EPI, GROUPED>(a, st);
     }
     case kTile256x128: return launch_mid<8, 4, 3, 3, EPI, GROUPED>(a, 1, st);
-    case kTile128: return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, GROUPED>(a, 1, st) : launch_mid<4, 4, 5, 4, EPI, GROUPED>(a, 1, st);
+    case kTile128: return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, GROUPED>(a, 1, st) : launch_mid<4, 4, 4, 4, EPI, GROUPED>(a, 1, st);
     case kTile64x128: return launch_mid<2, 4, 4, 3, EPI, GROUPED>(a, 1, st);
     case kTile192x256:
       if constexpr (!GROUPED && (EPI == EPI_GELU || EPI == EPI_GELU_BWD || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD))
@@ -1584,7 +1643,7 @@ hipError_t launch_runs(const GemmArgs& a, const Plan& p, hipStream_t st) {
   hipError_t e;
   switch (p.kind) {
     case kTile256x128: e = launch_mid<8, 4, 3, 3, EPI_STORE, false, true>(a, p.runs, st); break;
-    case kTile128: e = two_per_cu(a, p.runs) ? launch_mid<4, 4, 3, 2, EPI_STORE, false, true>(a, p.runs, st) : launch_mid<4, 4, 5, 4, EPI_STORE, false, true>(a, p.runs, st); break;
+    case kTile128: e = two_per_cu(a, p.runs) ? launch_mid<4, 4, 3, 2, EPI_STORE, false, true>(a, p.runs, st) : launch_mid<4, 4, 4, 4, EPI_STORE, false, true>(a, p.runs, st); break;
     case kTile64x128: e = launch_mid<2, 4, 4, 3, EPI_STORE, false, true>(a, p.runs, st); break;
     case kTile64: e = launch_mid<2, 2, 5, 5, EPI_STORE, false, true>(a, p.runs, st); break;
     default: return hipErrorInvalidValue;
@@ -1600,7 +1659,7 @@ hipError_t launch_plan(const GemmArgs& a, const Plan& p, hipStream_t st) {
   if (a.rowsq && (p.kind != kTile256 || p.runs > 1)) return hipErrorInvalidValue;    // somebody will read them: mfma_gemm_emits_rowsq first
   if (summed_runs(a)) {
     if constexpr (EPI == EPI_STORE || EPI == EPI_RESID || EPI == EPI_ROPE)
-      return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, false, false, true>(a, 1, st) : launch_mid<4, 4, 5, 4, EPI, false, false, true>(a, 1, st);
+      return two_per_cu(a, 1) ? launch_mid<4, 4, 3, 2, EPI, false, false, true>(a, 1, st) : launch_mid<4, 4, 4, 4, EPI, false, false, true>(a, 1, st);
     return hipErrorInvalidValue;
   }
   if constexpr (EPI != EPI_SWIGLU)
