@@ -353,7 +353,7 @@ sv_status sv_replace_with_ema(sv_ctx *ctx, void *signals, int64_t stride, int32_
  * stage 0 .. n_stages-1, sv_sentinel_backward for stage n_stages-1 .. 0.  A forward / backward call
  *   1. computes Gamma [n_workers, n_metrics] of the workers' signals against the EMA (whole-signal
  *      form of every enabled statistic, columns in the order rel-L2, L1, z-scored L2, sign flips, SW),
- *   2. waits for the stream and runs the policy (warm-up: every value enters the history; else: workers
+ *   2. waits for those checks and runs the policy (warm-up: every value enters the history; else: workers
  *      of a pipe tainted at an earlier stage of this iteration are not examined (forward), workers of a
  *      pipe tainted at a later stage are tainted without examination (backward)),
  *   3. backward only: overwrites the gradient of every worker tainted at this stage in this iteration
@@ -367,9 +367,10 @@ sv_status sv_replace_with_ema(sv_ctx *ctx, void *signals, int64_t stride, int32_
  * Device memory the object holds: two EMAs [T, D] float per stage, and -- with at most 32 workers -- one more
  * [T, D] float (where one pass does the checks and updates the EMA, what the EMA was before, until the verdicts
  * stand; else the sum over the signals that the score pass leaves: sv_score_and_sum) and, with SV_M_SW and
- * sv_sw_row_len(T) <= 16384, the projections of the EMAs and of the current signals
- * ((2 n_stages + n_workers) [n_dirs, sv_sw_row_len(T)] floats: sv_sw_against_projection) and the EMAs' sorted
- * (2 n_stages times as many).                                                                        */
+ * sv_sw_row_len(T) <= 16384, the projections of the EMAs and of the current signals and a spare
+ * ((2 n_stages + n_workers + 1) [n_dirs, sv_sw_row_len(T)] floats: sv_sw_against_projection) and the EMAs' sorted
+ * (2 n_stages times as many).  On return the EMA's update, and the replacement of gradients, may still be queued on
+ * the stream.                                                                                        */
 typedef struct {
   int32_t n_stages, n_workers;
   int64_t T;

@@ -3,8 +3,9 @@
 // worker's signal against the stage's EMA, the gradient replacement, the EMA update over the clean set --
 // goes through the library's own entry points (the checks of a call through one pass over the signals, check_signals, where
 // the shape allows it) on the caller's stream; the decisions in between are the
-// host-side policy (sv_policy_*).  Each forward / backward call therefore waits once for the stream: the
-// few scalars per worker have to reach the host before the policy can decide who enters the EMA.
+// host-side policy (sv_policy_*).  Each forward / backward call therefore waits once for its checks: the
+// few scalars per worker have to reach the host before the policy can decide who enters the EMA.  (For the stream, or, where work that
+// is likely to stand is queued behind the checks already, for an event between the two.)
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -39,11 +40,11 @@ struct sv_sentinel {
   std::vector<float*> ps[2];
   std::vector<uint8_t> sorted_ok[2];
   float* pm_next = nullptr;
-  hipEvent_t checked = nullptr;            // the checks of the call under way have run
+  hipEvent_t checked = nullptr;            // the checks of the call under way have run; releases to the system: the host reads what they wrote
   float* cproj = nullptr;                  // [d, n_dirs, Tpad]: the current signals' projections
   int64_t n_calls = 0, n_from_sum = 0, n_from_signals = 0, n_sw_carried = 0;
-  // pinned host memory; the statistics' last kernels write their few scalars straight into the first two, and the call waits for the
-  // stream before it reads them (as copies they were two launches more in every call's chain)
+  // pinned host memory; the statistics' last kernels write their few scalars straight into the first two, and the call waits for
+  // the checks before it reads them (as copies they were two launches more in every call's chain)
   sv_result* res_host = nullptr;
   float* sw_host = nullptr;
   uint8_t* mask_host = nullptr;
@@ -87,7 +88,7 @@ struct CallEma {
   }
 };
 
-// Gamma [d, n_metrics] of the d signals against the reference point ema.m, on the host (waits for the stream).
+// Gamma [d, n_metrics] of the d signals against the reference point ema.m, on the host (waits for the checks).
 // `skip` [d]: the signals known to be excluded from the EMA before they are scored.  Where the score pass can do it,
 // it also leaves the sum over the others in sum_dev, or updates the EMA with it (*summed = true), which saves the EMA update its own
 // pass over the signals whenever the verdicts exclude nobody else.
@@ -243,7 +244,7 @@ sv_status sv_sentinel_create(sv_ctx* ctx, const sv_sentinel_cfg* cfg, sv_sentine
         if (ok) { s->ps[kind].push_back(q); s->sorted_ok[kind].push_back(0); }
       }
     if (ok && (hipMalloc(&s->pm_next, p_bytes) != hipSuccess || hipMemset(s->pm_next, 0, p_bytes) != hipSuccess ||
-               hipEventCreateWithFlags(&s->checked, hipEventDisableTiming) != hipSuccess)) {       // optional: without it behind the verdicts
+               hipEventCreateWithFlags(&s->checked, hipEventDisableTiming | hipEventReleaseToSystem) != hipSuccess)) {       // optional: without it behind the verdicts
       if (s->pm_next) (void)hipFree(s->pm_next);
       s->pm_next = nullptr;
       (void)hipGetLastError();
