@@ -1496,12 +1496,13 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // ---- which kernel and tile serves a product.  Every choice is priced as rounds of workgroups over the CUs times (a fixed part
 // + slices x time per slice), plus for runs of k slices the reduction launch and the traffic of the partial products; the
 // cheapest is taken.  The figures are microseconds fitted to a sweep over 64 .. 8192 rows, 320 .. 14336 columns and K =
-// 512 .. 14336 with every tile forced (within 15 % of the measured times there), on the kernels' former k loops: prices fitted to
-// the present ones take tiles that are 0.8 % faster on average over 156 sizes, and others than the stages' tests name.  They are those of a plain store: the dearer
+// 512 .. 14336 with every tile forced, within 15 % of what the kernels took before their present k loops, one workgroup of 128x128
+// a CU.  They stand for the lines between the tiles, which the tests name, and no longer for times: prices fitted later to kernels on
+// these loops took tiles that were 0.8 % faster on average over 156 sizes.  They are those of a plain store: the dearer
 // epilogues (SwiGLU with its stashes, SwiGLU-backward) cost the same here, and a tile more than the last full round counts as a
 // round (on 256x256 tiles: as a second launch on smaller ones, where tail_tiles says so).  Against 256x256 tiles over runs of k, which these replaced, k of 9000 and more for 500 .. 1500 rows of 3072 .. 4096 columns
-// is left 5 .. 15 % slower (1453 x 3072, K = 9728: 97 -> 112 us), everything else even or faster.  Where the lines come out, with both
-// sides as measured on that sweep: 4096 x 1024, K = 1024 (256 tiles of 128 x 128) 13.4 us against 19 on 256 x 128 and 33 on
+// was left 5 .. 15 % slower (1453 x 3072, K = 9728: 97 -> 112 us), everything else even or faster.  Where the lines come out, with both
+// sides as they were measured on that sweep: 4096 x 1024, K = 1024 (256 tiles of 128 x 128) 13.4 us against 19 on 256 x 128 and 33 on
 // 256 x 256 over runs; 8192 x 1024, K = 8192 (256 tiles of 256 x 128) 113 us against 121 and 124; 8192 x 2048, K = 2048
 // (256 tiles of 256 x 256) 59 us against 64 on 256 x 128; 512 x 4096, K = 14336 (256 x 128 over 4 runs) 63 us against 85 whole;
 // 1024^3 (256 tiles of 64 x 64) 7.0 us against 8.1 on 64 x 128 and 9.6 on 128 x 128.
@@ -1538,8 +1539,8 @@ bool summed_runs(const GemmArgs& a) { return a.runs[0] > 1 || a.runs[1] > 1 || a
 // 37.4 -> 31.2; 4096 x 2560, K = 1024 39.1 -> 33.1; SwiGLU with its stashes 2331 x 1920, K = 960 30.7 -> 25.6, its backward at 3840
 // columns 34.9 -> 32.1; 900 x 5120, K = 2048 48.3 -> 43.3; 800 x 6144, K = 3072 68.2 -> 62.6.  With a longer k loop the bare product
 // decides: GELU 768 x 16384, K = 4096 104 -> 112.  (Plain stores and residual sums gain 1 - 9 % and stay where they are: what they run
-// on is what sv_gemm_plan tells.)  Where 256x128 tiles were chosen, whole rounds decide, at what a round of either was measured to take
-// (6.1 us and 0.65 a slice, 6.0 and 0.92).
+// on is what sv_gemm_plan tells.)  Where 256x128 tiles were chosen, whole rounds decide, at what a round of either took on kernels with four waves'
+// k loop (6.1 us and 0.65 a slice, 6.0 and 0.92; the plan's own price of 256x128 is of the form before).
 bool narrower_pays(const GemmArgs& a, int kind, int slices) {
   if (a.epi != EPI_GELU && a.epi != EPI_GELU_BWD && a.epi != EPI_SWIGLU && a.epi != EPI_SWIGLU_BWD) return false;
   const int64_t nout = a.epi == EPI_SWIGLU ? 128 : 256, cus = cu_count(), tiles = (a.M + 191) / 192 * (a.N / nout);
